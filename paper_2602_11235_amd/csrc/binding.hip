@@ -1,0 +1,102 @@
+// Entry points of the Python binding: the attention and normalization calls with their arguments in one packed block.
+//
+// ctypes converts every argument of a foreign call on its own (about 0.15 us each, 4 us for the 28 of an attention call,
+// on top of launches of 2 us); the binding packs the arguments with one struct.pack instead and passes the address.
+// Same checks, kernels, results and error codes as the functions of include/, which these forward to.  The block is
+// read during the call and not kept.  The field order is that of the pack formats in hta.py and gln.py: pointers, then
+// 8-byte, then 4-byte fields, nothing padded.
+#include "../../include/mtfm_gln.h"
+#include "../../include/mtfm_hta.h"
+#include "../../include/mtfm_hta_pw.h"
+
+namespace {
+
+enum Call { FWD = 0, BWD = 1, PW_FWD = 2, PW_BWD = 3 };
+
+struct HtaArgs {
+    const void *q, *k, *v;
+    void* out;
+    float* lse;
+    const void* dout;
+    void *dq, *dk, *dv;
+    const int32_t *q_offsets, *kv_offsets, *hist_len, *n_targets, *rt_len, *timestamps;  // the last two null: no real-time tokens
+    void* workspace;
+    int64_t workspace_bytes, total_q, total_kv;
+    int32_t batch, max_hist, max_rt, max_targets, Hq, Hkv, head_dim;
+    float scale, norm;
+    int32_t dtype, layer, call;
+};
+static_assert(sizeof(HtaArgs) == 16 * 8 + 3 * 8 + 12 * 4, "pack format 16P3q7i2f3i");
+
+struct GlnArgs {
+    const void *x, *gate;
+    const int32_t* group_id;
+    const float *gamma, *beta;
+    void* y;
+    float *mean, *rstd;
+    const void* dy;
+    void *dx, *dgate;
+    float *dgamma, *dbeta;
+    void* workspace;
+    int64_t workspace_bytes, n_tokens, backward;
+    int32_t d_model, n_groups;
+    float eps;
+    int32_t dtype;
+};
+static_assert(sizeof(GlnArgs) == 14 * 8 + 3 * 8 + 4 * 4, "pack format 14P3q2ifi");
+
+}  // namespace
+
+extern "C" {
+
+MTFM_HTA_API int mtfm_binding_hta(const void* block, void* stream) {
+    const HtaArgs& a = *(const HtaArgs*)block;
+    const size_t ws = (size_t)a.workspace_bytes;
+    switch (a.call) {
+        case FWD:
+            if (a.rt_len)
+                return mtfm_hta_fwd_rt(a.q, a.k, a.v, a.out, a.lse, a.q_offsets, a.kv_offsets, a.hist_len, a.rt_len, a.n_targets,
+                                       a.timestamps, a.batch, a.total_q, a.total_kv, a.max_hist, a.max_rt, a.max_targets, a.Hq,
+                                       a.Hkv, a.head_dim, a.scale, a.dtype, a.layer, a.workspace, ws, stream);
+            return mtfm_hta_fwd(a.q, a.k, a.v, a.out, a.lse, a.q_offsets, a.kv_offsets, a.hist_len, a.n_targets, a.batch,
+                                a.total_q, a.total_kv, a.max_hist, a.max_targets, a.Hq, a.Hkv, a.head_dim, a.scale, a.dtype,
+                                a.layer, a.workspace, ws, stream);
+        case BWD:
+            if (a.rt_len)
+                return mtfm_hta_bwd_rt(a.dout, a.q, a.k, a.v, a.out, a.lse, a.dq, a.dk, a.dv, a.q_offsets, a.kv_offsets,
+                                       a.hist_len, a.rt_len, a.n_targets, a.timestamps, a.batch, a.total_q, a.total_kv,
+                                       a.max_hist, a.max_rt, a.max_targets, a.Hq, a.Hkv, a.head_dim, a.scale, a.dtype, a.layer,
+                                       a.workspace, ws, stream);
+            return mtfm_hta_bwd(a.dout, a.q, a.k, a.v, a.out, a.lse, a.dq, a.dk, a.dv, a.q_offsets, a.kv_offsets, a.hist_len,
+                                a.n_targets, a.batch, a.total_q, a.total_kv, a.max_hist, a.max_targets, a.Hq, a.Hkv, a.head_dim,
+                                a.scale, a.dtype, a.layer, a.workspace, ws, stream);
+        case PW_FWD:
+            if (a.rt_len)
+                return mtfm_hta_pw_fwd_rt(a.q, a.k, a.v, a.out, a.q_offsets, a.kv_offsets, a.hist_len, a.rt_len, a.n_targets,
+                                          a.timestamps, a.batch, a.total_q, a.total_kv, a.max_hist, a.max_rt, a.max_targets,
+                                          a.Hq, a.Hkv, a.head_dim, a.scale, a.norm, a.dtype, a.layer, a.workspace, ws, stream);
+            return mtfm_hta_pw_fwd(a.q, a.k, a.v, a.out, a.q_offsets, a.kv_offsets, a.hist_len, a.n_targets, a.batch, a.total_q,
+                                   a.total_kv, a.max_hist, a.max_targets, a.Hq, a.Hkv, a.head_dim, a.scale, a.norm, a.dtype,
+                                   a.layer, a.workspace, ws, stream);
+        default:
+            if (a.rt_len)
+                return mtfm_hta_pw_bwd_rt(a.dout, a.q, a.k, a.v, a.dq, a.dk, a.dv, a.q_offsets, a.kv_offsets, a.hist_len,
+                                          a.rt_len, a.n_targets, a.timestamps, a.batch, a.total_q, a.total_kv, a.max_hist,
+                                          a.max_rt, a.max_targets, a.Hq, a.Hkv, a.head_dim, a.scale, a.norm, a.dtype, a.layer,
+                                          a.workspace, ws, stream);
+            return mtfm_hta_pw_bwd(a.dout, a.q, a.k, a.v, a.dq, a.dk, a.dv, a.q_offsets, a.kv_offsets, a.hist_len, a.n_targets,
+                                   a.batch, a.total_q, a.total_kv, a.max_hist, a.max_targets, a.Hq, a.Hkv, a.head_dim, a.scale,
+                                   a.norm, a.dtype, a.layer, a.workspace, ws, stream);
+    }
+}
+
+MTFM_HTA_API int mtfm_binding_gln(const void* block, void* stream) {
+    const GlnArgs& a = *(const GlnArgs*)block;
+    if (!a.backward)
+        return mtfm_gln_fwd(a.x, a.gate, a.group_id, a.gamma, a.beta, a.y, a.mean, a.rstd, a.n_tokens, a.d_model, a.n_groups,
+                            a.eps, a.dtype, stream);
+    return mtfm_gln_bwd(a.dy, a.x, a.gate, a.group_id, a.gamma, a.beta, a.mean, a.rstd, a.dx, a.dgate, a.dgamma, a.dbeta,
+                        a.n_tokens, a.d_model, a.n_groups, a.dtype, a.workspace, (size_t)a.workspace_bytes, stream);
+}
+
+}  // extern "C"

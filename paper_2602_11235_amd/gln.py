@@ -4,6 +4,7 @@ fallback: without the built library the first call raises."""
 from __future__ import annotations
 
 import ctypes
+import struct
 from typing import Optional, Tuple
 
 import torch
@@ -14,6 +15,9 @@ EXPORTS = ("mtfm_gln_fwd", "mtfm_gln_bwd", "mtfm_gln_bwd_workspace_bytes", "mtfm
 KERNEL_FWD, KERNEL_BWD, KERNEL_BWD_REDUCE = 4, 5, 6
 
 _declared = False
+
+# argument block of mtfm_binding_gln (struct GlnArgs of csrc/binding.hip), see hta.call_packed
+_BLOCK = struct.Struct("14P3q2ifi")
 
 
 def load_library() -> ctypes.CDLL:
@@ -47,8 +51,8 @@ def _check(status: int) -> None:
         raise hta.HtaError(status, hta.mtfm_hta_last_error())
 
 
-def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+def _ptr(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.data_ptr()
 
 
 def mtfm_gln_bwd_workspace_bytes(d_model: int, n_groups: int) -> int:
@@ -71,12 +75,16 @@ def mtfm_gln_fwd(x: torch.Tensor, group_id: torch.Tensor, gamma: torch.Tensor, b
         y = torch.empty_like(x)
     if stats is not None:
         mean, rstd = stats
+    elif save_stats:
+        mean = torch.empty(n, dtype=torch.float32, device=x.device)
+        rstd = torch.empty(n, dtype=torch.float32, device=x.device)
     else:
-        mean = torch.empty(n, dtype=torch.float32, device=x.device) if save_stats else None
-        rstd = torch.empty(n, dtype=torch.float32, device=x.device) if save_stats else None
-    _check(lib.mtfm_gln_fwd(hta._ptr(x), hta._ptr(gate), hta._ptr(group_id), hta._ptr(gamma), hta._ptr(beta),
-                            hta._ptr(y), hta._ptr(mean), hta._ptr(rstd), n, d, gamma.shape[0], eps, _dtype_code(x),
-                            _stream()))
+        mean = rstd = None
+    status = lib.mtfm_binding_gln(_BLOCK.pack(
+        x.data_ptr(), _ptr(gate), group_id.data_ptr(), gamma.data_ptr(), beta.data_ptr(), y.data_ptr(), _ptr(mean),
+        _ptr(rstd), 0, 0, 0, 0, 0, 0, 0, n, 0, d, gamma.shape[0], eps, _dtype_code(x)), hta._current_stream())
+    if status != hta.OK:
+        _check(status)
     return y, mean, rstd
 
 
@@ -92,11 +100,12 @@ def mtfm_gln_bwd(dy: torch.Tensor, x: torch.Tensor, group_id: torch.Tensor, gamm
         out = (torch.empty_like(x), torch.empty_like(gamma), torch.empty_like(gamma),
                None if gate is None else torch.empty_like(x))
     dx, dgamma, dbeta, dgate = out
-    need = mtfm_gln_bwd_workspace_bytes(d, groups)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
-    _check(lib.mtfm_gln_bwd(hta._ptr(dy), hta._ptr(x), hta._ptr(gate), hta._ptr(group_id), hta._ptr(gamma),
-                            hta._ptr(beta), hta._ptr(mean), hta._ptr(rstd), hta._ptr(dx), hta._ptr(dgate),
-                            hta._ptr(dgamma), hta._ptr(dbeta), n, d, groups, _dtype_code(x), hta._ptr(workspace),
-                            workspace.numel(), _stream()))
+        workspace = torch.empty(max(mtfm_gln_bwd_workspace_bytes(d, groups), 256), dtype=torch.uint8, device=x.device)
+    status = lib.mtfm_binding_gln(_BLOCK.pack(
+        x.data_ptr(), _ptr(gate), group_id.data_ptr(), gamma.data_ptr(), _ptr(beta), 0, mean.data_ptr(), rstd.data_ptr(),
+        dy.data_ptr(), dx.data_ptr(), _ptr(dgate), dgamma.data_ptr(), dbeta.data_ptr(), workspace.data_ptr(),
+        workspace.numel(), n, 1, d, groups, 0.0, _dtype_code(x)), hta._current_stream())
+    if status != hta.OK:
+        _check(status)
     return dx, dgamma, dbeta, dgate

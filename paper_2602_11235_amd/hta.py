@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Tuple
 
 import torch
@@ -67,6 +68,10 @@ def load_library() -> ctypes.CDLL:
     lib.mtfm_hta_last_error.argtypes = []
     lib.mtfm_hta_version.restype = ctypes.c_char_p
     lib.mtfm_hta_version.argtypes = []
+    # the binding's own entry points: all arguments in one packed block (csrc/binding.hip)
+    for fn in (lib.mtfm_binding_hta, lib.mtfm_binding_gln):
+        fn.restype = ci
+        fn.argtypes = [vp, vp]
     lib.mtfm_hta_timing_enable.restype = ci
     lib.mtfm_hta_timing_enable.argtypes = [ci]
     lib.mtfm_hta_timing_read.restype = ci
@@ -83,9 +88,15 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+def _current_stream() -> int:
+    """Handle of the current stream of the current device (torch.cuda.current_stream() builds a Stream object around it,
+    1.5 us; a call of a few microseconds is worth asking for the handle alone)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -206,6 +217,19 @@ def mtfm_hta_bwd_rt(dout, q, k, v, out, lse, dq, dk, dv, q_offsets, kv_offsets, 
                                           layer, _ptr(workspace), workspace_bytes, _stream_handle(stream)))
 
 
+# --------------------------------------------------------------------------- packed calls
+# Argument block of mtfm_binding_hta (struct HtaArgs of csrc/binding.hip): one pack and a two-argument foreign call take
+# 2 us where ctypes needs 5 to convert 28 arguments.
+_HTA_BLOCK = struct.Struct("16P3q7i2f3i")
+CALL_FWD, CALL_BWD, CALL_PW_FWD, CALL_PW_BWD = 0, 1, 2, 3
+
+
+def call_packed(call: int, fields, stream) -> None:
+    status = (_lib or load_library()).mtfm_binding_hta(_HTA_BLOCK.pack(*fields, call), _stream_handle(stream))
+    if status != OK:
+        _check(status)
+
+
 # --------------------------------------------------------------------------- buffer plumbing
 class Batch:
     """Device buffers of one jagged batch plus the host-known scalars the C ABI wants.  Allocation and
@@ -252,15 +276,18 @@ class Batch:
         fn = mtfm_hta_workspace_bytes if self.rt_len is None else mtfm_hta_workspace_bytes_rt
         return fn(self.layer, self.dtype, is_bwd, *self._sizes())
 
+    def _call(self, call: int, dout, workspace, workspace_bytes: int, stream) -> None:
+        grads = (0, 0, 0, 0) if dout is None else (dout.data_ptr(), self.dq.data_ptr(), self.dk.data_ptr(), self.dv.data_ptr())
+        rt = (0, 0) if self.rt_len is None else (self.rt_len.data_ptr(), self.timestamps.data_ptr())
+        call_packed(call, (self.q.data_ptr(), self.k.data_ptr(), self.v.data_ptr(), self.out.data_ptr(), self.lse.data_ptr(),
+                           *grads, self.q_offsets.data_ptr(), self.kv_offsets.data_ptr(), self.hist_len.data_ptr(),
+                           self.n_targets.data_ptr(), *rt, 0 if workspace is None else workspace.data_ptr(),
+                           workspace_bytes, self.total_q, self.total_kv, self.batch, self.max_hist, self.max_rt,
+                           self.max_targets, self.Hq, self.Hkv, self.head_dim, self.softmax_scale, 1.0, self.dtype,
+                           self.layer), stream)
+
     def forward(self, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
-        if self.rt_len is None:
-            mtfm_hta_fwd(self.q, self.k, self.v, self.out, self.lse, self.q_offsets, self.kv_offsets, self.hist_len,
-                         self.n_targets, *self._sizes(), self.softmax_scale, self.dtype, self.layer,
-                         self.fwd_workspace, self.fwd_workspace_bytes, stream)
-        else:
-            mtfm_hta_fwd_rt(self.q, self.k, self.v, self.out, self.lse, self.q_offsets, self.kv_offsets, self.hist_len,
-                            self.rt_len, self.n_targets, self.timestamps, *self._sizes(), self.softmax_scale,
-                            self.dtype, self.layer, self.fwd_workspace, self.fwd_workspace_bytes, stream)
+        self._call(CALL_FWD, None, self.fwd_workspace, self.fwd_workspace_bytes, stream)
         return self.out, self.lse
 
     def prepare_backward(self) -> None:
@@ -274,13 +301,5 @@ class Batch:
     def backward(self, dout, stream=None):
         assert dout.is_cuda and dout.dtype == self.q.dtype and dout.shape == self.q.shape and dout.is_contiguous()
         self.prepare_backward()
-        if self.rt_len is None:
-            mtfm_hta_bwd(dout, self.q, self.k, self.v, self.out, self.lse, self.dq, self.dk, self.dv, self.q_offsets,
-                         self.kv_offsets, self.hist_len, self.n_targets, *self._sizes(), self.softmax_scale,
-                         self.dtype, self.layer, self.workspace, self.workspace_bytes, stream)
-        else:
-            mtfm_hta_bwd_rt(dout, self.q, self.k, self.v, self.out, self.lse, self.dq, self.dk, self.dv,
-                            self.q_offsets, self.kv_offsets, self.hist_len, self.rt_len, self.n_targets,
-                            self.timestamps, *self._sizes(), self.softmax_scale, self.dtype, self.layer,
-                            self.workspace, self.workspace_bytes, stream)
+        self._call(CALL_BWD, dout, self.workspace, self.workspace_bytes, stream)
         return self.dq, self.dk, self.dv

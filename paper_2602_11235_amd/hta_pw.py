@@ -130,11 +130,24 @@ class PointwiseBatch:
         n = fn(self.layer, self.dtype, is_bwd, *self.sizes)
         return torch.empty(n, dtype=torch.uint8, device=self.q.device) if n else None
 
+    def _call(self, call, dout, ws, stream):
+        grads = (0, 0, 0, 0) if dout is None else (dout.data_ptr(), self.dq.data_ptr(), self.dk.data_ptr(), self.dv.data_ptr())
+        if self.rt:
+            qo, kvo, hist, rt_len, tgt, ts = self.ints
+            batch, total_q, total_kv, max_hist, max_rt, max_targets, Hq, Hkv, d = self.sizes
+            rt = (rt_len.data_ptr(), ts.data_ptr())
+        else:
+            qo, kvo, hist, tgt = self.ints
+            batch, total_q, total_kv, max_hist, max_targets, Hq, Hkv, d = self.sizes
+            rt, max_rt = (0, 0), 0
+        hta.call_packed(call, (self.q.data_ptr(), self.k.data_ptr(), self.v.data_ptr(), self.out.data_ptr(), 0, *grads,
+                               qo.data_ptr(), kvo.data_ptr(), hist.data_ptr(), tgt.data_ptr(), *rt,
+                               0 if ws is None else ws.data_ptr(), 0 if ws is None else ws.numel(), total_q, total_kv,
+                               batch, max_hist, max_rt, max_targets, Hq, Hkv, d, self.scale, self.norm, self.dtype,
+                               self.layer), stream)
+
     def forward(self, stream=None):
-        ws = self.fwd_ws
-        fn = mtfm_hta_pw_fwd_rt if self.rt else mtfm_hta_pw_fwd
-        fn(self.q, self.k, self.v, self.out, *self.ints, *self.sizes, self.scale, self.norm, self.dtype, self.layer, ws,
-           0 if ws is None else ws.numel(), stream)
+        self._call(hta.CALL_PW_FWD, None, self.fwd_ws, stream)
         return self.out
 
     def prepare_backward(self):
@@ -145,8 +158,5 @@ class PointwiseBatch:
     def backward(self, dout, stream=None):
         assert dout.is_cuda and dout.dtype == self.q.dtype and dout.shape == self.q.shape and dout.is_contiguous()
         self.prepare_backward()
-        ws = self.bwd_ws
-        fn = mtfm_hta_pw_bwd_rt if self.rt else mtfm_hta_pw_bwd
-        fn(dout, self.q, self.k, self.v, self.dq, self.dk, self.dv, *self.ints, *self.sizes, self.scale, self.norm,
-           self.dtype, self.layer, ws, 0 if ws is None else ws.numel(), stream)
+        self._call(hta.CALL_PW_BWD, dout, self.bwd_ws, stream)
         return self.dq, self.dk, self.dv

@@ -290,18 +290,18 @@ static int fwd_impl(const void* q, const void* k, const void* v, void* out, floa
     p.Hq = Hq; p.Hkv = Hkv; p.d = head_dim; p.scale = softmax_scale; p.layer = layer;
     p.rt_len = rt_len; p.ts = timestamps; p.max_rt = max_rt;
     p.pointwise = pointwise ? 1 : 0; p.norm = norm;
-    if (has_rt) {
+    if (dtype == MTFM_HTA_BF16) p.n_splits = hta::serve_splits(p, w.splits);
+    if (has_rt && p.n_splits == 0) {  // (the kernel for a few requests looks the limits up itself)
         p.lim = (int32_t*)((char*)workspace + w.lim_off);
         e = hta::launch_rt_limits(p, s);
     }
     if (e == hipSuccess && dtype == MTFM_HTA_BF16) {
-        p.n_splits = w.splits;
-        if (w.splits <= 1) {
+        if (p.n_splits == 0) {
             void* region = (char*)workspace + w.order_off;
             e = hta::launch_schedule(p, region, s);
             p.order = hta::schedule_order(region);
             p.queue = hta::schedule_queue(region, 0);  // the launchers add the kernel kind
-        } else {
+        } else if (p.n_splits > 1) {
             // a few users that do not fill the chip anyway: no long-first order (p.order stays null = as given),
             // and one kernel less on the critical path of the call
             p.o_part = (float*)((char*)workspace + w.opart_off);

@@ -44,7 +44,7 @@ struct Params {
     // the pointwise reading of phi2: weights norm * silu(scale s) instead of a row softmax (no lse, no delta)
     int32_t pointwise;
     float norm;
-    // forward pass split over the keys (few requests: inference); n_splits <= 1 = not split
+    // forward pass of a few requests (hta_serve_bf16.hip): workgroups an item's keys are split over; 0 = the ordinary kernel
     int32_t n_splits;
     float* o_part;          // [n_splits][total_q][Hq][d] partial outputs, each normalised by its own sum
     float* lse_part;        // [n_splits][Hq][total_q]    logsumexp of each split's keys (-inf: none)
@@ -64,6 +64,7 @@ hipError_t launch_rt_limits(const Params& p, hipStream_t s);
 hipError_t launch_fwd_fp32(const Params& p, hipStream_t s);
 hipError_t launch_bwd_fp32(const Params& p, hipStream_t s);
 hipError_t launch_fwd_bf16(const Params& p, hipStream_t s);
+hipError_t launch_serve_bf16(const Params& p, hipStream_t s);
 hipError_t launch_bwd_bf16(const Params& p, hipStream_t s);
 // the two launches of launch_bwd_bf16 that live in translation units of their own (other compiler options)
 hipError_t launch_bwd_dq_bf16(const Params& p, hipStream_t s);       // dQ and the self-key blocks, every head_dim
@@ -74,8 +75,10 @@ bool bf16_supported(int32_t d, int32_t Hq, int32_t Hkv);
 constexpr int32_t BF16_PADDED_FROM = 16, BF16_PADDED_TO = 32;
 hipError_t launch_widen16(const void* src, void* dst, int64_t n_rows, hipStream_t s);
 hipError_t launch_narrow16(const void* src, void* dst, int64_t n_rows, hipStream_t s);
-// number of key splits the bf16 forward pass uses for these host-known bounds (1 = none); decides the workspace too
+// the most key splits the bf16 forward pass may use for these host-known bounds: what its workspace has room for (1 = none)
 int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t max_rows, int64_t max_keys);
+// the splits it does use, at most `room`; 0: the call fills the chip and runs the ordinary forward kernel
+int serve_splits(const Params& p, int room);
 // stores the calling thread's error message (what mtfm_hta_last_error() returns) and hands `code` back
 int report_error(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 // event hooks around each kernel (no-ops unless timing was enabled through the C ABI); `kind` is one of the

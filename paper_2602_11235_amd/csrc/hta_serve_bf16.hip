@@ -1,0 +1,386 @@
+// bf16 forward pass of Hybrid Target Attention for a handful of requests (gfx950): one user's history and the
+// candidates of a scenario, or a few of them in one call.  Same mask and products as hta_fwd_bf16.hip; what differs is
+// what bounds it: the work of a call is a few microseconds of the chip, so latencies count and not rates.
+//
+// Work decomposition: one workgroup = (user, kv head, RW * RB blocks of 32 packed (row, head) pairs, key split).  Its eight
+// waves are RW row groups x KW key ways: the waves of a row group take every KW-th block of keys, each with a softmax
+// of its own, and merge their results through LDS at the end.  Splitting the keys inside the workgroup costs no memory
+// traffic and no second launch, so it comes first; only when that leaves units idle long enough to pay for the merge
+// launch are the keys split over workgroups as well.
+// With RW = 1 no two waves read the same key: nothing is shared, a wave waits for its own copies only and the key loop
+// has no barrier.  K and V travel global -> LDS asynchronously; the K of the next block is requested when the scores of
+// this one have been formed, its V when the products have.
+//
+// What bounds it, at head_dim 64 and one workgroup of 32 rows per compute unit: 2.05 us per 1000 keys, where the copies
+// alone take 1.66 (64 bytes per clock and unit) and the arithmetic alone 2.0, and 6 us of launch, first loads and merge.  K
+// fragments straight to registers (no LDS write and read): 3.6 us per 1000 keys, 32-byte pieces of a row per lane pair.
+// Four waves with the whole register file each: 5 to 6 us.  One 2048 + 128 token request at 8/2 heads: 17.8 -> 10.7 us
+// per call; 8 requests of 512..4096: 22.5 -> 15; 4 of 8192 at head_dim 128: 39 -> 34.
+#include "../../include/mtfm_hta.h"
+#include "../../include/mtfm_hta_timing.h"
+#include "hta_common.h"
+#include "hta_fwd_rows.h"
+#include "hta_mfma.h"
+#include "hta_tiles.h"
+
+#include <algorithm>
+
+namespace hta {
+namespace {
+
+constexpr int SUB = 32;  // keys of a sub-tile
+
+// SPS: 32-key sub-tiles per step (two of them interleave what each waits for); NST: steps resident in LDS.  K and V of a
+// step are requested as soon as their predecessors in the slot have been read, which with NST = 1 is half a step ahead.
+template <int D, int RB, int RW, int NW, int SPS, int NST>
+struct Serve {
+    static constexpr int BLK = SUB * SPS;              // keys of a step
+    static constexpr int TILE = BLK * D;               // elements of its K or V
+    static constexpr int CPR = D / 8;                  // 16-byte chunks per row
+    static constexpr int RPC = 64 / CPR;               // rows per 1 KB copy
+    static constexpr int KW = NW / RW;                 // key ways
+    static constexpr int COPIES = BLK / RPC / RW;      // copies per wave of its K, and of its V
+    static constexpr int PITCH = D + 4;                // floats per row of the merge buffer (16-byte words spread over the banks)
+    static constexpr int MERGE_BYTES = NW * SUB * (PITCH + 2) * 4;
+    static constexpr int KV_BYTES = KW * NST * 2 * TILE * 2;
+    static constexpr int BYTES = KV_BYTES > MERGE_BYTES ? KV_BYTES : MERGE_BYTES;
+};
+constexpr int TS_CAP = 512;  // real-time tokens of a user whose timestamps are searched in LDS
+
+template <int D, int RB, int RW, int NW, int SPS, int NST, bool RT, bool PW>
+__global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(Params p, RowMap map, int spread) {
+    using SV = Serve<D, RB, RW, NW, SPS, NST>;
+    constexpr int BLK = SV::BLK, CP = SV::COPIES, KW = SV::KW;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[SV::BYTES];
+    __shared__ int ts_s[RT ? TS_CAP : 1];
+
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+    // A group here is (user, kv head, head chunk, split): its row tiles, which read the same keys, go to `spread` XCDs, and the
+    // splits of an item to different ones.
+    const int ny = p.Hkv * map.n_chunks * p.n_splits * spread;
+    WorkItem w = decode_work(blockIdx.x, p.batch * ny, ny, (map.n_tiles + spread - 1) / spread);
+    if (!w.valid) return;
+    const int b = w.user_slot;
+    w.tile = w.tile * spread + w.y % spread;
+    w.y /= spread;
+    const int gc = p.n_splits == 1 ? w.y : w.y / p.n_splits, split = w.y - gc * p.n_splits;
+    const int g = map.n_chunks == 1 ? gc : gc / map.n_chunks, chunk = gc - g * map.n_chunks;
+    const int L = p.hist_len[b], T = p.n_targets[b], R = RT ? p.rt_len[b] : 0;
+    const int64_t q_base = p.q_off[b], kv_base = p.kv_off[b];
+    const int LK = L + R;  // keys that run through the tile loop: history, then real-time
+    const int n_rows = p.layer == 0 ? LK + T : T;
+    if (w.tile * map.rows >= n_rows) return;  // uniform for the whole workgroup
+    const PackedRows pr(map, w.tile, chunk, n_rows, g, p.Hq / p.Hkv);
+    const int tok_shift = p.layer == 0 ? 0 : LK;  // token index of query row 0
+    const int rw = wave / KW, kw = wave % KW, rho0 = rw * RB * 32;
+    const bool wave_live = RW == 1 || pr.any_from(rho0);
+
+    const int n_all = (LK + BLK - 1) / BLK;
+    const int lo = (int)((int64_t)split * n_all / p.n_splits), hi = (int)((int64_t)(split + 1) * n_all / p.n_splits);
+    const int n_mine = hi - lo > kw ? (hi - lo - kw + KW - 1) / KW : 0;  // steps of this key way: blocks lo + kw + i KW
+
+    // K or V of step i to its slot.  Keys past the end repeat the last one (their weight is forced to zero).
+    const __bf16* kg = (const __bf16*)p.k + (int64_t)g * D;
+    const __bf16* vg = (const __bf16*)p.v + (int64_t)g * D;
+    uint32_t voff[CP];  // byte offsets of the chunks this lane fetches from the first element of the block
+#pragma unroll
+    for (int j = 0; j < CP; j++) {
+        const int trow = (j * RW + rw) * SV::RPC + lane / SV::CPR;
+        voff[j] = (uint32_t)((trow * p.Hkv * D + ((lane % SV::CPR) ^ swizzle<D>(trow)) * 8) * 2);
+    }
+    auto slot = [&](int i) __attribute__((always_inline)) { return (kw * NST + (NST == 1 ? 0 : i % NST)) * (2 * SV::TILE * 2); };
+    auto fetch = [&](const __bf16* src, int i, int part) __attribute__((always_inline)) {
+        if (i >= n_mine) return;
+        const int k0 = (lo + kw + i * KW) * BLK;
+        const __bf16* base = src + (kv_base + k0) * p.Hkv * D;
+        const uint32_t dst = lds_address(smem) + (uint32_t)(slot(i) + part * SV::TILE * 2);
+        if (k0 + BLK <= LK) {
+#pragma unroll
+            for (int j = 0; j < CP; j++) copy16_global_to_lds_at(base, voff[j], dst + (j * RW + rw) * 1024);
+        } else {
+#pragma unroll
+            for (int j = 0; j < CP; j++) {
+                const int trow = (j * RW + rw) * SV::RPC + lane / SV::CPR;
+                const uint32_t past = (uint32_t)max(trow - (LK - 1 - k0), 0);
+                copy16_global_to_lds_at(base, voff[j] - past * (uint32_t)(p.Hkv * D * 2), dst + (j * RW + rw) * 1024);
+            }
+        }
+    };
+    if (RT && R <= TS_CAP && wave * 64 < R && wave < TS_CAP / 64)
+        copy4_global_to_lds_at(p.ts + kv_base + L + min(wave * 64 + lane, R - 1), lds_address(ts_s) + wave * 256u);
+#pragma unroll
+    for (int i = 0; i < NST; i++) {
+        fetch(kg, i, 0);
+        fetch(vg, i, 1);
+    }
+
+    FwdRows<D, RB, RT, PW> rows;
+    rows.init_lane(p, lane);
+    rows.load_q(p, pr, rho0, q_base, L, lane);
+    rows.reset();
+    if (split == 0 && kw == 0) rows.start_from_own_key(p, pr, rho0, kv_base, g, tok_shift, L, lane);
+    if constexpr (RT) {
+        // mask rule 2: the row sees the history and the real-time tokens strictly earlier than itself, a prefix
+        const int32_t* ts = p.ts + kv_base + L;
+        int t[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) t[rb] = p.ts[kv_base + tok_shift + pr.at(rho0 + rb * 32 + l32).row];
+        wait_vmem_loads();
+        lds_barrier();
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+            int a = 0, e = R;
+            while (a < e) {
+                const int mid = (a + e) >> 1;
+                const int v = R <= TS_CAP ? ts_s[mid] : ts[mid];
+                if (v < t[rb]) a = mid + 1; else e = mid;
+            }
+            rows.lim[rb] = L + a;
+        }
+    }
+
+    wait_vmem_loads();  // from here on the only vector-memory traffic of the loop are the copies, counted below
+    // wait until at most n steps' K and V, and then (Half: V, or the K of one more step), are in flight
+    auto wait_copies = [&](int steps, bool half) __attribute__((always_inline)) {
+        if (NST > 1 && steps >= 1) {
+            if (half) wait_vmem_outstanding<3 * CP>(); else wait_vmem_outstanding<2 * CP>();
+        } else {
+            if (half) wait_vmem_outstanding<CP>(); else wait_vmem_outstanding<0>();
+        }
+    };
+    static_assert(NST <= 2, "wait_copies");
+    auto step = [&](int i, auto Tail) __attribute__((always_inline)) {
+        constexpr bool TAIL = decltype(Tail)::value;
+        const int k0 = (lo + kw + i * KW) * BLK, left = n_mine - 1 - i;
+        const __bf16* Ks = (const __bf16*)(smem + slot(i));
+        floatx16 S[SPS][RB];
+        const bool work = wave_live && (RW == 1 || i < n_mine);
+        wait_copies(min(NST - 1, left), true);  // newer than K_i: V_i and the following steps
+        if (RW > 1) lds_barrier();
+        if (work) rows.template scores<SPS>(S, Ks);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // K_i has been read
+        if (RW > 1) {
+            wait_copies(min(NST - 1, left), false);
+            lds_barrier();
+        }
+        fetch(kg, i + NST, 0);
+        if (RW == 1) wait_copies(min(NST - 1, left), left >= NST);  // newer than V_i: the following steps, and K_(i + NST)
+        if (work) rows.template absorb<TAIL, SPS>(S, Ks + SV::TILE, LK - k0, k0, L);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (RW > 1) lds_barrier();
+        fetch(vg, i + NST, 1);
+    };
+    // blocks of history keys first, then those that need a mask (the last one; more with real-time tokens)
+    const int n_rounds = RW == 1 ? n_mine : (hi - lo + KW - 1) / KW;  // (barriers: the same number of steps for every wave)
+    const int n_whole = RW == 1 ? min(max(min(hi, L / BLK) - lo - kw + KW - 1, 0) / KW, n_mine) : max(min(hi, L / BLK) - lo, 0) / KW;
+    for (int i = 0; i < n_whole; i++) step(i, std::false_type{});
+    for (int i = n_whole; i < n_rounds; i++) step(i, std::true_type{});
+
+    // ---- merge the waves' results through LDS, one row block after the other
+    float* acc = (float*)smem;                          // [wave][row][PITCH]
+    float* stat = acc + NW * SUB * SV::PITCH;           // [wave][row][m, l]
+    static_for<0, RB>([&](auto Rb) {
+    constexpr int rb = decltype(Rb)::value;
+    lds_barrier();  // every wave has read its last block (or the previous row block)
+    {
+        const float lt = rows.l[rb] + other_half(rows.l[rb]);
+        if (hf == 0) {
+            stat[(wave * SUB + l32) * 2] = rows.m[rb];
+            stat[(wave * SUB + l32) * 2 + 1] = lt;
+        }
+        float* o = acc + (wave * SUB + l32) * SV::PITCH + 4 * hf;
+#pragma unroll
+        for (int db = 0; db < D / 32; db++)
+#pragma unroll
+            for (int v4 = 0; v4 < 4; v4++) {
+                floatx4 x;
+#pragma unroll
+                for (int j = 0; j < 4; j++) x[j] = rows.O[rb][db][4 * v4 + j];
+                *(floatx4*)(o + db * 32 + 8 * v4) = x;
+            }
+    }
+    lds_barrier();
+    constexpr int QUADS = D / 4;
+    for (int id = tid; id < RW * SUB * QUADS; id += NW * 64) {
+        const int c = id % QUADS, rl = id / QUADS, l = rl % SUB, w0 = rl / SUB * KW;  // 4 features of a row; its first wave
+        const PackedRows::Row x = pr.at((rl / SUB * RB + rb) * 32 + l);
+        float mx = -1e30f;
+        float mk[KW];
+        if constexpr (!PW) {
+#pragma unroll
+            for (int k = 0; k < KW; k++) {
+                mk[k] = stat[((w0 + k) * SUB + l) * 2];
+                mx = fmaxf(mx, mk[k]);
+            }
+        }
+        float sum = 0.f;
+        floatx4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KW; k++) {
+            const float f = PW ? 1.f : fast_exp2(mk[k] - mx);  // 0 for a wave that saw no key
+            const floatx4 ok = *(const floatx4*)(acc + ((w0 + k) * SUB + l) * SV::PITCH + 4 * c);
+            if constexpr (!PW) sum = fmaf(f, stat[((w0 + k) * SUB + l) * 2 + 1], sum);
+#pragma unroll
+            for (int j = 0; j < 4; j++) o[j] = fmaf(f, ok[j], o[j]);
+        }
+        if (!x.live) continue;
+        const float inv = PW ? p.norm * p.scale : (sum > 0.f ? 1.f / sum : 0.f);
+        const float lse = sum > 0.f ? (mx + __builtin_amdgcn_logf(sum)) * LN2 : -INFINITY;
+        const int64_t row = q_base + x.row;
+        if (p.n_splits == 1) {
+            bf16x4 o4;
+#pragma unroll
+            for (int j = 0; j < 4; j++) o4[j] = (__bf16)(o[j] * inv);
+            *(bf16x4*)((__bf16*)p.out + (row * p.Hq + x.h) * D + 4 * c) = o4;
+            if (!PW && c == 0) p.lse[(int64_t)x.h * p.total_q + row] = lse;
+        } else {
+            floatx4 o4;
+#pragma unroll
+            for (int j = 0; j < 4; j++) o4[j] = o[j] * inv;
+            *(floatx4*)(p.o_part + (((int64_t)split * p.total_q + row) * p.Hq + x.h) * D + 4 * c) = o4;
+            if (!PW && c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = lse;
+        }
+    }
+    });
+}
+
+// out = sum_s w_s O_s / sum_s w_s with w_s = exp(lse_s - max lse), lse = max lse + log sum_s w_s: the exact
+// combination of softmax results over disjoint key sets.  One thread per 4 features of a (row, head).
+// PW: the partial results are partial sums of non-normalised weights: out = sum_s O_s, no lse.
+template <bool PW>
+__global__ __launch_bounds__(256) void merge_splits_kernel(Params p) {
+    const int64_t quads = p.d / 4;
+    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (id >= p.total_q * p.Hq * quads) return;
+    const int c = (int)(id % quads);
+    const int64_t rh = id / quads;
+    const int h = (int)(rh % p.Hq);
+    const int64_t row = rh / p.Hq;
+    // all loads of a thread are independent: issue them in batches of eight instead of one memory latency per split
+    const float* lp = p.lse_part + (int64_t)h * p.total_q + row;
+    const float* op = p.o_part + (row * p.Hq + h) * p.d + 4 * c;
+    const int64_t l_stride = (int64_t)p.Hq * p.total_q, o_stride = p.total_q * p.Hq * p.d;
+    float mx = -INFINITY;
+    if constexpr (!PW) {
+#pragma unroll 8
+        for (int s = 0; s < p.n_splits; s++) mx = fmaxf(mx, lp[s * l_stride]);
+    }
+    float sum = 0.f;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int s = 0; s < p.n_splits; s++) {
+        const float w = PW ? 1.f : __expf(lp[s * l_stride] - mx);
+        const floatx4 o = *(const floatx4*)(op + s * o_stride);
+        sum += w;
+        acc += w * o;
+    }
+    const float inv = PW ? 1.f : 1.f / sum;
+    bf16x4 o4;
+#pragma unroll
+    for (int j = 0; j < 4; j++) o4[j] = (__bf16)(acc[j] * inv);
+    *(bf16x4*)((__bf16*)p.out + (row * p.Hq + h) * p.d + 4 * c) = o4;
+    if (!PW && c == 0) p.lse[(int64_t)h * p.total_q + row] = mx + __logf(sum);
+}
+
+template <int D, int RB, int RW, int NW, int SPS, int NST>
+hipError_t launch(const Params& p, hipStream_t s) {
+    void (*kernel)(Params, RowMap, int);
+    if (p.pointwise)
+        kernel = p.rt_len ? serve_kernel<D, RB, RW, NW, SPS, NST, true, true> : serve_kernel<D, RB, RW, NW, SPS, NST, false, true>;
+    else
+        kernel = p.rt_len ? serve_kernel<D, RB, RW, NW, SPS, NST, true, false> : serve_kernel<D, RB, RW, NW, SPS, NST, false, false>;
+    const int64_t rows = max_query_rows(p);
+    if (rows <= 0) return hipSuccess;
+    const RowMap map = row_map(RW * RB * 32, p.Hq, p.Hkv, rows);
+    // One XCD per group is best for its L2; two when there are so few groups that an XCD of 32 units can get more
+    // workgroups than it has units while others idle (14 requests of 1053 keys, 28 groups: 23 -> 14 us).
+    const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks * p.n_splits;
+    const int spread = groups < 64 && (groups + N_XCD - 1) / N_XCD * map.n_tiles > 32 ? 2 : 1;
+    const int64_t n_blocks = work_grid(groups * spread, (map.n_tiles + spread - 1) / spread);
+    if (n_blocks >= (1ll << 31)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p, map, spread);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && p.n_splits > 1) {
+        const int64_t threads = p.total_q * p.Hq * (p.d / 4);
+        if (p.pointwise)
+            hipLaunchKernelGGL(merge_splits_kernel<true>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p);
+        else
+            hipLaunchKernelGGL(merge_splits_kernel<false>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
+// workgroups with work to do: `lanes` packed rows each, from the bounds and the number of query rows of the call
+int64_t live_tiles(const Params& p, int lanes) {
+    const RowMap map = row_map(lanes, p.Hq, p.Hkv, max_query_rows(p));
+    const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks;
+    return std::min(groups * map.n_tiles, p.total_q * p.Hkv * map.n_chunks / map.rows + groups / 2);
+}
+
+// The shape of a call's workgroups.  Blocks of 32 rows finish soonest while every one gets a unit to itself; once they
+// queue up, 64 rows per workgroup (two row blocks per wave at head_dim 64, two row groups sharing their keys at 128, where
+// the registers do not hold two) halve the traffic of the copies.
+enum Shape { ROWS32, ROWS64 };
+Shape shape_of(const Params& p) { return p.d > 32 && live_tiles(p, 32) > (p.d == 64 ? 256 : 512) ? ROWS64 : ROWS32; }
+
+}  // namespace
+
+// Workgroups the ordinary forward kernel would have for these bounds: 256 rows (512 at d = 32), fewer heads per workgroup where
+// a group does not divide evenly.  (The workspace formula below is part of the interface's contract and counts the same way.)
+static int64_t ordinary_items(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t max_rows) {
+    const int64_t r = Hq / Hkv, waves = r % 4 == 0 ? 8 : 4;
+    const int64_t lanes = 32 * waves * (d == 32 || (d == 64 && waves == 4) ? 2 : 1);
+    const int64_t heads = r % waves == 0 ? waves : (r % 4 == 0 ? 4 : (r % 2 == 0 ? 2 : 1));
+    return batch * Hkv * (r / heads) * ((max_rows + lanes / heads - 1) / (lanes / heads));
+}
+
+// The workspace of a forward call has room for this many partial results per row.
+int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t max_rows, int64_t max_keys) {
+    constexpr int64_t CUS = 256, MIN_TILES = 4, MAX_SPLITS = 32;
+    if (batch <= 0 || max_rows <= 0 || !bf16_supported(d, Hq, Hkv)) return 1;
+    const int64_t items = ordinary_items(batch, Hq, Hkv, d, max_rows);
+    if (items >= CUS) return 1;
+    const int64_t want = (CUS + items - 1) / items, by_len = ((max_keys + 63) / 64) / MIN_TILES;
+    int64_t n = want < by_len ? want : by_len;
+    n = n < MAX_SPLITS ? n : MAX_SPLITS;
+    return n > 1 ? (int)n : 1;
+}
+
+// The ordinary kernel shares each K/V tile among 256 rows and keeps two workgroups on a unit: it is the better one as soon
+// as its workgroups nearly fill the chip (32 requests x 256 candidates on 8192 keys: 160 against 180 us; half of that,
+// ragged: 76 against 61).  Below that, keys are split over workgroups when the time this takes off the longest item is
+// worth the merge: per key and workgroup 2.05 ns at head_dim 64, 4.4 at 128; merge 4.2 us, partial results at 3 TB/s.
+int serve_splits(const Params& p, int room) {
+    if (live_tiles(p, p.d == 32 ? 512 : 256) >= 224) return 0;
+    if (room <= 1 || shape_of(p) == ROWS64) return 1;
+    const RowMap map = row_map(32, p.Hq, p.Hkv, max_query_rows(p));
+    const int64_t items = (int64_t)p.batch * p.Hkv * map.n_chunks * map.n_tiles;
+    const double loop = max_lead_keys(p) * (p.d == 128 ? 4.4e-3 : 2.05e-3);
+    const double part = 2.0 * p.total_q * p.Hq * p.d * 4 / 3e6;
+    int best = 1;
+    double best_us = loop;
+    for (int s = 2; s <= room && items * s <= 256; s++) {
+        const double us = loop / s + 4.2 + s * (part + 0.05);
+        if (us < best_us) best = s, best_us = us;
+    }
+    return best;
+}
+
+hipError_t launch_serve_bf16(const Params& p, hipStream_t s) {
+    const Shape shape = shape_of(p);
+    // short lists of keys per wave: single sub-tiles divide more evenly than pairs
+    const bool brief = max_lead_keys(p) / p.n_splits <= 1024;
+    hipError_t e;
+    timing_begin(MTFM_HTA_KERNEL_FWD, s);
+    switch (p.d) {
+        case 32: e = launch<32, 1, 1, 8, 2, 2>(p, s); break;
+        case 64: e = shape == ROWS64 ? launch<64, 2, 1, 8, 1, 2>(p, s) : brief ? launch<64, 1, 1, 8, 1, 2>(p, s) : launch<64, 1, 1, 8, 2, 1>(p, s); break;
+        case 128: e = shape == ROWS64 ? launch<128, 1, 2, 8, 2, 1>(p, s) : launch<128, 1, 1, 8, 1, 1>(p, s); break;
+        default: e = hipErrorInvalidValue;
+    }
+    timing_end(MTFM_HTA_KERNEL_FWD, s);
+    return e;
+}
+
+}  // namespace hta

@@ -288,10 +288,11 @@ static int fwd_impl(const void* q, const void* k, const void* v, void* out, floa
     p.q_off = q_offsets; p.kv_off = kv_offsets; p.hist_len = hist_len; p.n_targets = n_targets;
     p.batch = batch; p.total_q = total_q; p.total_kv = total_kv; p.max_hist = max_hist; p.max_targets = max_targets;
     p.Hq = Hq; p.Hkv = Hkv; p.d = head_dim; p.scale = softmax_scale; p.layer = layer;
-    p.rt_len = rt_len; p.ts = timestamps; p.max_rt = max_rt;
+    // (a bound of 0: no user has a real-time token, which is the call without them)
+    if (!(dtype == MTFM_HTA_BF16 && max_rt == 0)) p.rt_len = rt_len, p.ts = timestamps, p.max_rt = max_rt;
     p.pointwise = pointwise ? 1 : 0; p.norm = norm;
     if (dtype == MTFM_HTA_BF16) p.n_splits = hta::serve_splits(p, w.splits);
-    if (has_rt && p.n_splits == 0) {  // (the kernel for a few requests looks the limits up itself)
+    if (has_rt && (dtype == MTFM_HTA_FP32 || (p.rt_len && p.n_splits == 0))) {  // (the kernel for a few requests looks the limits up itself)
         p.lim = (int32_t*)((char*)workspace + w.lim_off);
         e = hta::launch_rt_limits(p, s);
     }
@@ -411,24 +412,25 @@ static int bwd_impl(const void* dout, const void* q, const void* k, const void* 
     p.q_off = q_offsets; p.kv_off = kv_offsets; p.hist_len = hist_len; p.n_targets = n_targets;
     p.batch = batch; p.total_q = total_q; p.total_kv = total_kv; p.max_hist = max_hist; p.max_targets = max_targets;
     p.Hq = Hq; p.Hkv = Hkv; p.d = head_dim; p.scale = softmax_scale; p.layer = layer;
-    p.rt_len = rt_len; p.ts = timestamps; p.max_rt = max_rt;
+    // (a bound of 0: no user has a real-time token, which is the call without them)
+    if (!(dtype == MTFM_HTA_BF16 && max_rt == 0)) p.rt_len = rt_len, p.ts = timestamps, p.max_rt = max_rt;
     p.pointwise = pointwise ? 1 : 0; p.norm = norm;
     if (dtype == MTFM_HTA_BF16) {
         char* base = (char*)workspace;
         p.neg_delta = (float*)(base + w.delta_off);
         p.neg_lse_s = (float*)(base + w.lse_off);
     }
-    if (has_rt) {
-        p.lim = (int32_t*)((char*)workspace + w.lim_off);
-        e = hta::launch_rt_limits(p, s);
-    }
-    if (e == hipSuccess && dtype == MTFM_HTA_BF16) {
+    if (has_rt) p.lim = (int32_t*)((char*)workspace + w.lim_off);
+    const bool brief = dtype == MTFM_HTA_BF16 && hta::bwd_is_brief(p);  // (forms the limits itself, and needs no schedule)
+    if (dtype == MTFM_HTA_FP32 ? has_rt : p.rt_len && !brief) e = hta::launch_rt_limits(p, s);
+    if (e == hipSuccess && dtype == MTFM_HTA_BF16 && !brief) {
         void* region = (char*)workspace + w.order_off;
         e = hta::launch_schedule(p, region, s);
         p.order = hta::schedule_order(region);
         p.queue = hta::schedule_queue(region, 0);  // the launchers add the kernel kind
     }
-    if (e == hipSuccess) e = dtype == MTFM_HTA_FP32 ? hta::launch_bwd_fp32(p, s) : hta::launch_bwd_bf16(p, s);
+    if (e == hipSuccess)
+        e = dtype == MTFM_HTA_FP32 ? hta::launch_bwd_fp32(p, s) : brief ? hta::launch_bwd_brief_bf16(p, s) : hta::launch_bwd_bf16(p, s);
     if (e == hipSuccess && padded) {
         e = hta::launch_narrow16(dq, caller_dq, total_q * Hq, s);
         if (e == hipSuccess) e = hta::launch_narrow16(dk, caller_dk, total_kv * Hkv, s);

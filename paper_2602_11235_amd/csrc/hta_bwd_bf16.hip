@@ -9,6 +9,7 @@
 //   1. bwd_self and 2. bwd_dq (hta_bwd_dq_bf16.hip): the self-key terms of the target rows' keys, and dQ,
 //      row-stationary; the first launch also leaves -delta and -lse/scale of every row in the workspace.
 //   3. bwd_dkdv (hta_bwd_dkdv.h): key-stationary, dk/dv of history (and real-time) keys, written once.
+// (Calls of little work take other shapes of the same: hta_bwd_brief_bf16.hip.)
 // S and dP are thus computed twice (7 matrix products instead of 5); in exchange neither dQ nor
 // dK/dV ever crosses a workgroup, which removes a float32 accumulator three times the size of q, its
 // zero-fill and conversion passes, and an atomic traffic of several GB per call.
@@ -20,19 +21,20 @@
 
 namespace hta {
 
+bool dkdv_is_resident(const Params& p) { return p.d == 64 && few_rows_per_user<64>(p); }
+
 hipError_t launch_bwd_bf16(const Params& p, hipStream_t s) {
     timing_begin(MTFM_HTA_KERNEL_BWD_DQ, s);
     hipError_t e = launch_bwd_dq_bf16(p, s);
     timing_end(MTFM_HTA_KERNEL_BWD_DQ, s);
     if (e != hipSuccess) return e;
     timing_begin(MTFM_HTA_KERNEL_BWD_DKDV, s);
-    switch (p.d) {
+    if (dkdv_brief_ways(p) > 0) e = launch_dkdv_brief_bf16(p, s);
+    else switch (p.d) {
         case 32: e = launch_dkdv<32, 4>(p, s); break;
         case 64: e = launch_dkdv<64, 4>(p, s); break;
-        default:  // 128: the softmax kernel for samples without real-time tokens is built in a unit of its own
-            if (p.pointwise) e = p.rt_len ? launch_dkdv_as<128, 4, true, true>(p, s) : launch_dkdv_as<128, 4, false, true>(p, s);
-            else if (p.rt_len) e = launch_dkdv_as<128, 4, true>(p, s);
-            else e = launch_bwd_dkdv128_bf16(p, s);
+        default:  // 128: the softmax kernel is built in a unit of its own
+            e = p.pointwise ? launch_dkdv_as<128, 4, false, true>(p, s) : launch_bwd_dkdv128_bf16(p, s);
             break;
     }
     timing_end(MTFM_HTA_KERNEL_BWD_DKDV, s);

@@ -10,6 +10,7 @@
 #pragma once
 #include "../../include/mtfm_hta.h"
 #include "hta_common.h"
+#include "hta_dkdv_brief.h"
 #include "hta_mfma.h"
 #include "hta_tiles.h"
 
@@ -17,29 +18,30 @@ namespace hta {
 namespace {
 
 // ---------------------------------------------------------------------------------------- dK, dV
-template <int D, int NW, bool RT>
+template <int D, int NW>
 struct DkdvSmem {
     static constexpr int UPI = 2;      // (head, 32-row block) units per loop iteration, i.e. per workgroup barrier
     static constexpr int NSTAGE = 3;   // iterations resident in LDS: one being consumed, two in flight
     static constexpr int TILE = 32 * D;                 // one unpadded, swizzled 32-row tile (elements)
-    // Q, dO, -lse/scale[32], -delta[32]; with real-time tokens also the rows' limits, int[32] (written twice)
-    static constexpr size_t UNIT_BYTES = (size_t)2 * TILE * 2 + 2 * 32 * sizeof(float) + (RT ? 256 : 0);
+    static constexpr size_t UNIT_BYTES = (size_t)2 * TILE * 2 + 2 * 32 * sizeof(float);  // Q, dO, -lse/scale[32], -delta[32]
     static constexpr size_t STAGE_BYTES = UPI * UNIT_BYTES;
     static constexpr size_t BYTES = NSTAGE * STAGE_BYTES;
 };
 
 // One workgroup per (user, kv head, tile of NW*32 history keys).  Q and dO tiles travel global -> LDS directly
 // (no register stop-over), two iterations ahead of their use.
-// RT: users with real-time tokens (mask rule 2).  Their keys follow the history keys and are owned by waves like any
-// other key; a wave whose 32 keys reach past the history takes the masked instruction stream, where a weight
-// survives only if the key lies below the row's limit (p.lim, staged with the row statistics) or is the row's own
-// token (the own key of a real-time row; target rows' own keys are the business of bwd_self_block).
+// With real-time tokens (mask rule 2) these workgroups take the whole 32-key blocks of the history only, which every row
+// sees: no mask.  The blocks behind them (TAILS: the last blocks of the grid, behind the persistent ones; at
+// d = 128, where both in one kernel do not fit the registers, a launch of their own) are
+// brief_dkdv's, whose masked stream skips the rows that see none of their keys; they fill the units that run out of
+// history.  (256 users of 512..1024 + 32..128 + 64 tokens: 940 us, against 1019 in the same session with one masked instruction
+// stream for all keys and the rows' limits staged next to every unit.)
 // PW: the pointwise reading of phi2 -- P = silu(scale S), dS = dP o silu'(scale S); the staged row statistics are
 // zeros for rows that exist (the sentinel for rows that do not still removes them), norm is applied at the store.
-template <int D, int NW, bool RT, bool PW = false>
-__global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Params p, int tpg, unsigned per_xcd) {
-    using SM = DkdvSmem<D, NW, RT>;
-    static_assert(!RT || NW >= 2 * SM::UPI, "waves UPI .. 2 UPI - 1 copy the rows' limits");
+template <int D, int NW, bool TAILS, bool PW = false>
+__global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Params p, int tpg, unsigned per_xcd, unsigned n_persistent,
+                                                                       RowMap map, int tail_tpg) {
+    using SM = DkdvSmem<D, NW>;
     constexpr int UPI = SM::UPI, NSTAGE = SM::NSTAGE;
     constexpr int NKS = D / 16, NDB = D / 32;
     constexpr int CPR = D / 8;                  // 16-byte chunks per row
@@ -49,18 +51,14 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     constexpr int COPIES = UPI * 2 * IPW;       // direct copies per wave and iteration (when the wave takes part)
     static_assert(IPT % NW == 0 || IPT < NW, "tile copies must split evenly over the waves");
     static_assert(UPI <= NW, "wave uu copies the row statistics of unit uu");
-    // One array per stage: copies in flight into one stage and reads from another are then provably disjoint, so the
-    // compiler need not drain the copies before every LDS read.
-    __shared__ __attribute__((aligned(1024))) unsigned char stage0[SM::STAGE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char stage1[SM::STAGE_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char stage2[SM::STAGE_BYTES];
-    static_assert(NSTAGE == 3, "three stage arrays");
-    auto stage_ptr = [&](auto St) -> unsigned char* {
-        constexpr int st = decltype(St)::value % 3;
-        if constexpr (st == 0) return stage0;
-        if constexpr (st == 1) return stage1;
-        return stage2;
-    };
+    constexpr size_t LDS_BYTES = TAILS && (size_t)Brief<D, true>::BYTES > SM::BYTES ? (size_t)Brief<D, true>::BYTES : SM::BYTES;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_BYTES];
+    auto stage_ptr = [&](auto St) -> unsigned char* { return smem + decltype(St)::value % 3 * SM::STAGE_BYTES; };
+    static_assert(NSTAGE == 3, "three stages");
+    if (TAILS && blockIdx.x >= n_persistent) {
+        brief_dkdv<D, BRIEF_NW, true, PW, true>(p, map, blockIdx.x - n_persistent, tail_tpg, 0, smem);
+        return;
+    }
 
     __shared__ int s_item;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
@@ -71,18 +69,18 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     if (!w.valid) return;
     const int b = scheduled_user(p, w.user_slot), g = w.y;
     const int L = p.hist_len[b], T = p.n_targets[b];
-    const int LK = L + (RT ? p.rt_len[b] : 0);  // keys that receive gradient here: history, then real-time
+    const int R = p.rt_len ? p.rt_len[b] : 0;
+    const int LK = p.rt_len ? L & ~31 : L;  // keys that receive gradient here
     const int key0 = w.tile * (NW * 32);
     if (key0 >= LK) return;  // uniform: this key tile does not exist for the user
-    const int n_rows = p.layer == 0 ? LK + T : T;
-    const int tok_shift = p.layer == 0 ? 0 : LK;  // token index of query row 0
+    const int n_rows = p.layer == 0 ? L + R + T : T;
     const int r = p.Hq / p.Hkv;
     const int64_t q_base = p.q_off[b], kv_base = p.kv_off[b];
     const float c2 = p.scale * LOG2E;
     const int kw = key0 + wave * 32;        // first key of this wave
     const bool wave_live = kw < LK;         // a wave past the last key only helps staging
     const bool key_live = kw + l32 < LK;
-    const bool wave_ragged = kw + 32 > L;   // past the end, or (RT) into the real-time keys: masked instruction stream
+    const bool wave_ragged = kw + 32 > LK;  // past the end: masked instruction stream
     const bool copies = IPT >= NW || wave < IPT;   // does this wave issue tile copies?
 
     // per-lane element offsets into a swizzled tile
@@ -137,7 +135,6 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
         tile_voff[jj] = (uint32_t)((trow * p.Hq * D + (((lane % CPR) ^ swizzle<D>(trow)) << 3)) * 2);
     }
     const float* stat_lane = (hf == 0 ? p.neg_lse_s : p.neg_delta) + q_base + l32;
-    const int32_t* lim_lane = RT ? p.lim + q_base + l32 : nullptr;  // both halves of the wave fetch the same 32 limits
     int iss_rb = 0, iss_hh = 0;
     auto issue_tiles = [&](auto St) {
         const uint32_t stage = lds_address(stage_ptr(St));
@@ -158,7 +155,6 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
                     copy16_global_to_lds_at((const __bf16*)p.dout + ubase, tile_voff[jj], dst + (uint32_t)SM::TILE * 2u);
                 }
                 if (wave_u == uu) copy4_global_to_lds_at(stat_lane + ((int64_t)h * p.total_q + row0), unit + 4u * (uint32_t)SM::TILE);
-                if (RT && wave_u == uu + UPI) copy4_global_to_lds_at(lim_lane + row0, unit + 4u * (uint32_t)SM::TILE + 256u);
             } else {
 #pragma unroll
                 for (int jj = 0; jj < (copies ? IPW : 0); jj++) {
@@ -181,11 +177,6 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
                     const float* src = hf == 0 ? p.neg_lse_s + (dead ? (int64_t)p.Hq * p.total_q : idx) : p.neg_delta + idx;
                     copy4_global_to_lds_at(src, unit + 4u * (uint32_t)SM::TILE);
                 }
-                if (RT && wave_u == uu + UPI) {
-                    int row = row0 + l32;
-                    row = row < n_rows ? row : n_rows - 1;
-                    copy4_global_to_lds_at(p.lim + q_base + row, unit + 4u * (uint32_t)SM::TILE + 256u);
-                }
             }
             if (!past && ++iss_hh == r) {
                 iss_hh = 0;
@@ -196,7 +187,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     // wait until at most the copies this wave has issued for its K most recent iterations are outstanding
     auto wait_all_but_iterations = [&](auto Kc) {
         constexpr int K = decltype(Kc)::value;
-        const bool extra = wave < UPI || (RT && wave < 2 * UPI);  // one more copy per iteration: statistics, or limits
+        const bool extra = wave < UPI;  // one more copy per iteration: statistics
         if (copies) {
             if (extra) wait_vmem_outstanding<K * (COPIES + 1)>(); else wait_vmem_outstanding<K * COPIES>();
         } else {
@@ -259,34 +250,15 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     struct Weights {
         bf16x8 pb[2], dsb[2];
     };
-    // `ubase`, `u`: the unit's place in LDS and its number (used by the masked stream only)
-    auto weights = [&](const Operands& o, Weights& wt, auto ragged, const unsigned char* ubase, int u) {
+    auto weights = [&](const Operands& o, Weights& wt, auto ragged) {
         constexpr bool MASKED = decltype(ragged)::value;
-        int limv[16];     // RT: limits of the unit's rows, register v <-> row 8(v/4) + 4 hf + v%4
-        int self_row = 0; // RT: the row of the unit whose own token is this lane's key (if it is one of its 32 rows)
-        if constexpr (MASKED && RT) {
-            typedef int int4v __attribute__((ext_vector_type(4)));
-            const int* ls = (const int*)(ubase + (size_t)4 * SM::TILE + 256);
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int4v l4 = *(const int4v*)(ls + 8 * j + 4 * hf);
-#pragma unroll
-                for (int i = 0; i < 4; i++) limv[4 * j + i] = l4[i];
-            }
-            self_row = kw + l32 - tok_shift - (u / r) * 32;
-        }
         if constexpr (PW) {
 #pragma unroll
             for (int v = 0; v < 16; v++) {
                 const float sg = pw_sigmoid(o.S[v], -c2);
                 const float x = o.S[v] * p.scale;
                 float pw = pw_silu(x, sg), sp = pw_silu_prime_of(pw, sg);
-                if constexpr (MASKED && RT) {
-                    const int key = kw + l32;
-                    const bool vis = key < limv[v] || (key_live && self_row == 8 * (v / 4) + 4 * hf + (v % 4));
-                    pw = vis ? pw : 0.f;
-                    sp = vis ? sp : 0.f;
-                } else if constexpr (MASKED) {  // keys past the history carry no weight
+                if constexpr (MASKED) {  // keys past the history carry no weight
                     pw = key_live ? pw : 0.f;
                     sp = key_live ? sp : 0.f;
                 }
@@ -298,11 +270,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 #pragma unroll
         for (int v = 0; v < 16; v++) {
             float pw = fast_exp2(o.S[v] * c2);
-            if constexpr (MASKED && RT) {
-                const int key = kw + l32;
-                const bool vis = key < limv[v] || (key_live && self_row == 8 * (v / 4) + 4 * hf + (v % 4));
-                pw = vis ? pw : 0.f;
-            } else if constexpr (MASKED) {
+            if constexpr (MASKED) {
                 pw = key_live ? pw : 0.f;  // keys past the history carry no weight
             }
             wt.pb[v / 8][v % 8] = (__bf16)pw;
@@ -346,30 +314,18 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
             Operands nxt;
             Transposed f;
             Weights wt;
-            if constexpr (RT) {
-                scores(cur);
-                load_transposed(base, f);
-                weights(cur, wt, ragged, base, it * UPI);
-                load_operands(base + SM::UNIT_BYTES, nxt);
-                accumulate(wt, f);
-                scores(nxt);
-                load_transposed(base + SM::UNIT_BYTES, f);
-                weights(nxt, wt, ragged, base + SM::UNIT_BYTES, it * UPI + 1);
-            } else {
-                // The second unit's S and dP are requested before the first unit's weights are formed, and the first
-                // unit's accumulations come after the second unit's weights: each block of vector work then has matrix
-                // instructions of the other unit in the stream around it (3 % at d = 64, 6 % at d = 128; the
-                // real-time variant keeps the shorter live ranges, it has no registers to spare).
-                Weights wt0;
-                scores(cur);
-                load_operands(base + SM::UNIT_BYTES, nxt);
-                weights(cur, wt0, ragged, base, it * UPI);
-                scores(nxt);
-                load_transposed(base, f);
-                weights(nxt, wt, ragged, base + SM::UNIT_BYTES, it * UPI + 1);
-                accumulate(wt0, f);
-                load_transposed(base + SM::UNIT_BYTES, f);
-            }
+            // The second unit's S and dP are requested before the first unit's weights are formed, and the first
+            // unit's accumulations come after the second unit's weights: each block of vector work then has matrix
+            // instructions of the other unit in the stream around it (3 % at d = 64, 6 % at d = 128).
+            Weights wt0;
+            scores(cur);
+            load_operands(base + SM::UNIT_BYTES, nxt);
+            weights(cur, wt0, ragged);
+            scores(nxt);
+            load_transposed(base, f);
+            weights(nxt, wt, ragged);
+            accumulate(wt0, f);
+            load_transposed(base + SM::UNIT_BYTES, f);
             // copies of iteration it+1 must have landed; those of it+2 may stay in flight
             if (it + 2 < n_iter) wait_all_but_iterations(c1); else wait_all_but_iterations(c0);
             lds_barrier();
@@ -674,18 +630,36 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     }
 }
 
-template <int D, int NW, bool RT, bool PW = false>
+template <int D, bool PW>
+__global__ __launch_bounds__(BRIEF_NW * 64, 1) void dkdv_tails_kernel(Params p, RowMap map, int tail_tpg) {
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[Brief<D, true>::BYTES];
+    brief_dkdv<D, BRIEF_NW, true, PW, true>(p, map, blockIdx.x, tail_tpg, 0, smem);
+}
+
+template <int D, int NW, bool TAILS, bool PW = false>
 hipError_t launch_dkdv_as(const Params& p, hipStream_t s) {
-    const int64_t keys = max_lead_keys(p);
-    if (keys <= 0) return hipSuccess;
+    const int64_t keys = p.max_hist;
+    if (max_lead_keys(p) <= 0) return hipSuccess;
     const int64_t n_kt = (keys + NW * 32 - 1) / (NW * 32);
     const int64_t n_items = work_grid((int64_t)p.batch * p.Hkv, n_kt);
-    if (n_items >= (1ll << 31)) return hipErrorInvalidValue;
-    const int64_t resident = resident_workgroups<bwd_dkdv_kernel<D, NW, RT, PW>>(NW * 64);
+    const RowMap map = row_map(32, p.Hq, p.Hkv, max_query_rows(p));
+    const int64_t resident = resident_workgroups<bwd_dkdv_kernel<D, NW, TAILS, PW>>(NW * 64);
+    const int64_t persistent = n_items < resident ? n_items : resident;
+    const int64_t tail_kt = p.rt_len ? (p.max_rt + 62) / 32 : 0;  // 32-key blocks behind the whole ones of the history
+    const int64_t n_tails = p.rt_len ? work_grid((int64_t)p.batch * p.Hkv, tail_kt) : 0;
+    if (n_items >= (1ll << 31) || persistent + n_tails >= (1ll << 31)) return hipErrorInvalidValue;
     Params pk = p;
     pk.queue = p.queue + QUEUE_DKDV * N_XCD;
-    hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, RT, PW>), dim3((unsigned)(n_items < resident ? n_items : resident)), dim3(NW * 64),
-                       0, s, pk, (int)n_kt, (unsigned)(n_items / N_XCD));
+    const int64_t n_blocks = persistent + (TAILS ? n_tails : 0);
+    if (n_blocks > 0)
+        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, TAILS, PW>), dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, pk, (int)n_kt,
+                           (unsigned)(n_items / N_XCD), (unsigned)persistent, map, (int)tail_kt);
+    if constexpr (D == 128) {
+        if (n_tails == 0) return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((dkdv_tails_kernel<D, PW>), dim3((unsigned)n_tails), dim3(BRIEF_NW * 64), 0, s, p, map, (int)tail_kt);
+    }
     return hipGetLastError();
 }
 

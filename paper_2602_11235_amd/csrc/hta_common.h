@@ -58,7 +58,31 @@ __host__ __device__ inline int64_t max_query_rows(const Params& p) {
 }
 // number of keys a user's tile loops can reach at most: history, then real-time tokens
 __host__ __device__ inline int64_t max_lead_keys(const Params& p) { return (int64_t)p.max_hist + p.max_rt; }
-// per-row limits of mask rule 2 (a launch of its own at the start of a call with real-time tokens)
+// What the host knows of a call's average user, for the rules that choose a kernel: query rows, and keys of the tile loops
+// (a full layer's totals do not tell its target tokens apart; half of the bound is as good a guess as any).
+inline double mean_rows(const Params& p) { return (double)p.total_q / p.batch; }
+inline double mean_keys(const Params& p) {
+    const double keys = p.layer == 0 ? mean_rows(p) - 0.5 * p.max_targets : (double)(p.total_kv - p.total_q) / p.batch;
+    return keys < 1. ? 1. : keys > (double)max_lead_keys(p) ? (double)max_lead_keys(p) : keys;
+}
+// Mask rule 2 (Section 3.2.2): a real-time token is visible only to tokens with later timestamps.  The real-time
+// segment of a user is sorted by time, so the real-time keys a query sees are a prefix of it: those strictly earlier
+// than the query.  lim[row] = hist_len + that prefix length = the number of leading K/V rows of the user the row
+// attends to in the tile loops (its own key, when it is a real-time or target token, is a separate term).
+__device__ inline void rt_limit_of_row(const Params& p, int b, int row) {
+    const int L = p.hist_len[b], R = p.rt_len[b], T = p.n_targets[b];
+    const int n_rows = p.layer == 0 ? L + R + T : T;
+    if (row >= n_rows) return;
+    const int32_t* ts = p.ts + p.kv_off[b];
+    const int32_t t = ts[p.layer == 0 ? row : L + R + row];
+    int lo = 0, hi = R;  // first real-time token that is not strictly earlier than t
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ts[L + mid] < t) lo = mid + 1; else hi = mid;
+    }
+    p.lim[(int64_t)p.q_off[b] + row] = L + lo;
+}
+// the limits of all rows: a launch of its own at the start of most calls with real-time tokens
 hipError_t launch_rt_limits(const Params& p, hipStream_t s);
 
 hipError_t launch_fwd_fp32(const Params& p, hipStream_t s);
@@ -66,6 +90,11 @@ hipError_t launch_bwd_fp32(const Params& p, hipStream_t s);
 hipError_t launch_fwd_bf16(const Params& p, hipStream_t s);
 hipError_t launch_serve_bf16(const Params& p, hipStream_t s);
 hipError_t launch_bwd_bf16(const Params& p, hipStream_t s);
+bool bwd_is_brief(const Params& p);                             // little work: the kernels of hta_bwd_brief_bf16.hip, no schedule
+hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s);
+int dkdv_brief_ways(const Params& p);                           // ... > 0: their dK/dV part behind the ordinary dQ pass
+bool dkdv_is_resident(const Params& p);                         // the ordinary dK/dV pass would keep each user's rows in LDS
+hipError_t launch_dkdv_brief_bf16(const Params& p, hipStream_t s);
 // the two launches of launch_bwd_bf16 that live in translation units of their own (other compiler options)
 hipError_t launch_bwd_dq_bf16(const Params& p, hipStream_t s);       // dQ and the self-key blocks, every head_dim
 hipError_t launch_bwd_dkdv128_bf16(const Params& p, hipStream_t s);  // dK/dV at head_dim 128, softmax weights, no real-time tokens
@@ -116,7 +145,28 @@ __device__ inline WorkItem decode_work(unsigned id, int n_groups, int ny, int tp
     w.y = group - w.user_slot * ny;
     return w;
 }
-inline int64_t work_grid(int64_t n_groups, int64_t tpg) { return ((n_groups + N_XCD - 1) / N_XCD) * N_XCD * tpg; }
+// The same for grids whose groups may be few, or few of them long: the tiles of a group are dealt to 2^spread XCDs in turn
+// (a grid does not balance itself over the XCDs as the work counters below do; 17 users of which one has half of the work,
+// two kv heads: that half ran on two XCDs).
+__device__ inline WorkItem decode_spread(unsigned id, int n_groups, int ny, int tpg, int spread) {
+    WorkItem w = decode_work(id, n_groups << spread, ny << spread, (tpg + (1 << spread) - 1) >> spread);
+    w.tile = (w.tile << spread) + (w.y & ((1 << spread) - 1));
+    w.y >>= spread;
+    return w;
+}
+// Spread of a training launch: at least 128 shares of groups for the 8 XCDs, 512 where the longest user has more than twice the
+// mean's rows (that case of 17 users 2.22 -> 1.02 ms per step, 16 users of 630..2420 keys 0.60 -> 0.47; 93 users of up to 8192
+// keys 4.74 -> 4.61 ms).  Tiles of a group on more XCDs read its operands into more L2s: with four shares of every one of 512
+// equal groups a step was 6 % slower.
+inline int grid_spread(const Params& p, int64_t n_groups, int64_t tpg) {
+    const int64_t shares = n_groups >= 128 && (double)max_query_rows(p) * p.batch > 2. * p.total_q ? 512 : 128;
+    int s = 0;
+    while (s < 3 && (n_groups << s) < shares && (2 << s) <= tpg) s++;
+    return s;
+}
+inline int64_t work_grid(int64_t n_groups, int64_t tpg, int spread = 0) {
+    return (((n_groups << spread) + N_XCD - 1) / N_XCD) * N_XCD * ((tpg + (1 << spread) - 1) >> spread);
+}
 
 // Work distribution for kernels with long work items (the dK/dV pass: tens of microseconds per item).  The hardware
 // hands the workgroups of a grid to the shader engines in a fixed rotation, whatever each has left to do, so with items

@@ -7,8 +7,8 @@
 // (row tile) x (history key tile); the single self key of a target row is where the row's online softmax starts.
 // No mask is stored or loaded; only the ragged last history tile needs a bound check.
 //
-// Work decomposition: one workgroup = (user, kv head, tile of NW * RB * 32 packed (row, head) pairs, see
-// hta_fwd_rows.h), a wave = RB blocks of 32 of them, kept in registers.  S is computed transposed, S^T = K Q^T, so
+// Work decomposition: one workgroup = (user, kv head, tile of NW * 32 packed (row, head) pairs, see
+// hta_rows.h), a wave = 32 of them, kept in registers.  S is computed transposed, S^T = K Q^T, so
 // a lane owns one query row: the row maximum and sum are reductions over the lane's own
 // registers plus one exchange with the other half of the wave, and P^T in accumulator layout is
 // directly the B operand of O^T = V^T P^T.  V stays row-major in LDS and is read through the LDS
@@ -28,8 +28,8 @@ namespace {
 constexpr int BN = 64;  // keys per LDS tile
 
 // One workgroup per (user, kv head, chunk of query heads, row tile), from the launch grid.
-template <int D, int RB, int NW, bool RT, bool PW = false>
-__global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap map) {
+template <int D, int NW, bool RT, bool PW = false>
+__global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap map, int spread) {
     using ST = KvStage<D, NW>;
     static_assert(ST::BN == BN, "tile height");
     // NSTAGE stages of [K tile][V tile], filled by asynchronous global -> LDS copies NSTAGE-1 tiles ahead of their use
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap m
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NSTAGE * ST::BYTES];
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const WorkItem w = decode_work(blockIdx.x, p.batch * p.Hkv * map.n_chunks, p.Hkv * map.n_chunks, map.n_tiles);
+    const WorkItem w = decode_spread(blockIdx.x, p.batch * p.Hkv * map.n_chunks, p.Hkv * map.n_chunks, map.n_tiles, spread);
     if (!w.valid) return;
     const int b = scheduled_user(p, w.user_slot);
     const int g = map.n_chunks == 1 ? w.y : w.y / map.n_chunks, chunk = w.y - g * map.n_chunks;
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap m
     if (w.tile * map.rows >= n_rows) return;  // uniform for the whole workgroup
     const PackedRows pr(map, w.tile, chunk, n_rows, g, p.Hq / p.Hkv);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int rho0 = wave_u * RB * 32;
+    const int rho0 = wave_u * 32;
     const bool wave_live = pr.any_from(rho0);  // a wave behind the last row only helps staging
     const int tok_shift = p.layer == 0 ? 0 : LK;  // token index of query row 0
     const int64_t q_base = p.q_off[b], kv_base = p.kv_off[b];
@@ -71,13 +71,10 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap m
     // (the Q fragments) that it would wait for inside the loop.
     if (n_kt > 0) ST::issue(kg, vg, kv_base, p.Hkv, g, LK, 0, smem_addr, voff, wave_u, lane);
     if (AHEAD > 1 && n_kt > 1) ST::issue(kg, vg, kv_base, p.Hkv, g, LK, 1, smem_addr + ST::BYTES, voff, wave_u, lane);
-    FwdRows<D, RB, RT, PW> rows;
+    FwdRows<D, 1, RT, PW> rows;
     rows.init_lane(p, lane);
     rows.load_q(p, pr, rho0, q_base, L, lane);
-    if constexpr (RT) {
-#pragma unroll
-        for (int rb = 0; rb < RB; rb++) rows.lim[rb] = p.lim[q_base + pr.at(rho0 + rb * 32 + (lane & 31)).row];
-    }
+    if constexpr (RT) rows.lim[0] = p.lim[q_base + pr.at(rho0 + (lane & 31)).row];
     rows.reset();
     rows.start_from_own_key(p, pr, rho0, kv_base, g, tok_shift, L, lane);
     wait_vmem_loads();
@@ -92,7 +89,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap m
         const __bf16* Ks = (const __bf16*)(smem + st * ST::BYTES);
         if (!wave_live) {
         } else if (PAIRS && !TAIL) {
-            floatx16 S[2][RB];
+            floatx16 S[2][1];
             rows.template scores<2>(S, Ks);
             rows.template absorb<false, 2>(S, Ks + ST::TILE, BN, t * BN, L);
         } else {
@@ -120,50 +117,50 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap m
 
     // normalisation and stores
     const int hf = lane >> 5;
+    const PackedRows::Row x = pr.at(rho0 + (lane & 31));
+    const float lt = rows.l[0] + other_half(rows.l[0]);
+    if (!x.live) return;
+    const float inv = PW ? p.norm * p.scale : 1.f / lt;
+    __bf16* op = (__bf16*)p.out + ((q_base + x.row) * p.Hq + x.h) * D;
 #pragma unroll
-    for (int rb = 0; rb < RB; rb++) {
-        const PackedRows::Row x = pr.at(rho0 + rb * 32 + (lane & 31));
-        const float lt = rows.l[rb] + other_half(rows.l[rb]);
-        if (x.live) {
-            const float inv = PW ? p.norm * p.scale : 1.f / lt;
-            __bf16* op = (__bf16*)p.out + ((q_base + x.row) * p.Hq + x.h) * D;
+    for (int db = 0; db < D / 32; db++)
 #pragma unroll
-            for (int db = 0; db < D / 32; db++)
+        for (int v4 = 0; v4 < 4; v4++) {
+            bf16x4 o4;
 #pragma unroll
-                for (int v4 = 0; v4 < 4; v4++) {
-                    bf16x4 o4;
-#pragma unroll
-                    for (int j = 0; j < 4; j++) o4[j] = (__bf16)(rows.O[rb][db][4 * v4 + j] * inv);
-                    *(bf16x4*)(op + db * 32 + 8 * v4 + 4 * hf) = o4;
-                }
-            if (!PW && hf == 0) p.lse[(int64_t)x.h * p.total_q + q_base + x.row] = (rows.m[rb] + __builtin_amdgcn_logf(lt)) * LN2;
+            for (int j = 0; j < 4; j++) o4[j] = (__bf16)(rows.O[0][db][4 * v4 + j] * inv);
+            *(bf16x4*)(op + db * 32 + 8 * v4 + 4 * hf) = o4;
         }
-    }
+    if (!PW && hf == 0) p.lse[(int64_t)x.h * p.total_q + q_base + x.row] = (rows.m[0] + __builtin_amdgcn_logf(lt)) * LN2;
 }
 
-template <int D, int RB, int NW>
+template <int D, int NW>
 hipError_t launch(const Params& p, hipStream_t s) {
-    void (*kernel)(Params, RowMap);
+    void (*kernel)(Params, RowMap, int);
     if (p.pointwise)
-        kernel = p.rt_len ? fwd_bf16_kernel<D, RB, NW, true, true> : fwd_bf16_kernel<D, RB, NW, false, true>;
+        kernel = p.rt_len ? fwd_bf16_kernel<D, NW, true, true> : fwd_bf16_kernel<D, NW, false, true>;
     else
-        kernel = p.rt_len ? fwd_bf16_kernel<D, RB, NW, true> : fwd_bf16_kernel<D, RB, NW, false>;
+        kernel = p.rt_len ? fwd_bf16_kernel<D, NW, true> : fwd_bf16_kernel<D, NW, false>;
     const int64_t rows = max_query_rows(p);
     if (rows <= 0) return hipSuccess;
-    const RowMap map = row_map(NW * RB * 32, p.Hq, p.Hkv, rows);
-    const int64_t n_blocks = work_grid((int64_t)p.batch * p.Hkv * map.n_chunks, map.n_tiles);
+    const RowMap map = row_map(NW * 32, p.Hq, p.Hkv, rows);
+    const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks;
+    const int spread = grid_spread(p, groups, map.n_tiles);
+    const int64_t n_blocks = work_grid(groups, map.n_tiles, spread);
     if (n_blocks >= (1ll << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p, map);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p, map, spread);
     return hipGetLastError();
 }
 
-// (RB, NW) of the forward kernel for a head shape: eight waves of one 32-row block each whenever the head group fills
-// them (r a multiple of 4) -- the small register footprint lets four waves share a SIMD, which hides more latency than
-// a second row block per wave saves in LDS reads -- otherwise four waves with two row blocks each.
-void kernel_shape(int32_t d, int32_t Hq, int32_t Hkv, int& RB, int& NW) {
-    const bool wide = ((Hq / Hkv) % 4) == 0;
-    NW = wide ? 8 : 4;
-    RB = d == 32 ? 2 : (d == 64 ? (wide ? 1 : 2) : 1);
+// Waves per workgroup, one 32-row block each (two per wave, sharing the operand reads, were slower at every head shape once rows
+// came packed: 340 against 308 us on 338 users at 4/4 heads).  At head_dim 64 eight waves, two workgroups per unit, share each
+// K/V tile among 256 rows; four waves where 256 rows are too coarse for the users: few rows in a full layer (8/2 heads, P
+// packed rows per user: P = 480 44 against 68 us, P = 1400 37 against 36, P = 3400 470 against 450), or just more than 256
+// at most (P = 92..372: 88 against 115 us).  At 128 (1.05 against 1.13 ms on 232 users of 252..1010 keys, 46 -> 39 us on 44 short
+// ones) and 32 four waves always.
+bool four_waves(const Params& p) {
+    const int64_t r = p.Hq / p.Hkv, most = max_query_rows(p) * r;
+    return p.layer == 0 ? mean_rows(p) * r <= 1000. && most > 256 : most > 256 && most <= 384;
 }
 
 }  // namespace
@@ -176,15 +173,12 @@ bool bf16_supported(int32_t d, int32_t Hq, int32_t Hkv) {
 
 hipError_t launch_fwd_bf16(const Params& p, hipStream_t s) {
     if (p.n_splits > 0) return launch_serve_bf16(p, s);
-    int RB, NW;
-    kernel_shape(p.d, p.Hq, p.Hkv, RB, NW);
-    const bool wide = NW == 8;
     hipError_t e;
     timing_begin(MTFM_HTA_KERNEL_FWD, s);
     switch (p.d) {
-        case 32: e = wide ? launch<32, 2, 8>(p, s) : launch<32, 2, 4>(p, s); break;
-        case 64: e = wide ? launch<64, 1, 8>(p, s) : launch<64, 2, 4>(p, s); break;
-        case 128: e = wide ? launch<128, 1, 8>(p, s) : launch<128, 1, 4>(p, s); break;
+        case 32: e = launch<32, 4>(p, s); break;
+        case 64: e = four_waves(p) ? launch<64, 4>(p, s) : launch<64, 8>(p, s); break;
+        case 128: e = launch<128, 4>(p, s); break;
         default: e = hipErrorInvalidValue;
     }
     timing_end(MTFM_HTA_KERNEL_FWD, s);

@@ -1,0 +1,62 @@
+"""GPU parity at the shapes between which the library chooses: users, rows and histories small, middling and many, so that
+every form of the forward, dQ and dK/dV passes runs on lengths at the edges of its tiles.  Same oracle and bounds as the
+other parity tests."""
+import numpy as np
+import pytest
+
+from paper_2602_11235_amd import inputs
+from tests.hta_testlib import check_case, close_on_row_scale
+from tests.test_gpu_parity_pointwise import check as check_pointwise
+
+pytestmark = pytest.mark.gpu
+FULL, TARGET = inputs.LAYER_FULL, inputs.LAYER_TARGET
+
+HIST = np.array([0, 1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 200])
+TGTS = np.array([0, 1, 7, 8, 9, 16, 31, 32, 33, 40])
+RT = np.array([0, 1, 31, 32, 33, 65])
+cycle = lambda values, n: np.resize(values, n)
+
+# name: layer, users, history beyond HIST, targets beyond TGTS, heads, with real-time tokens
+SHAPES = {
+    # a few dozen users: the rows of 32 keys, and the keys of 32 rows, shared by the waves of a workgroup
+    "brief": (FULL, 12, 0, 0, (8, 2, 64), False),
+    "brief_rt": (TARGET, 24, 0, 0, (8, 2, 64), True),
+    "brief_d32": (FULL, 16, 0, 0, (3, 1, 32), True),
+    "brief_d128": (TARGET, 20, 0, 0, (6, 2, 128), True),
+    # more of them: dQ in its ordinary form, a key block's rows shared by one, two or four waves
+    "one_way": (TARGET, 330, 0, 0, (8, 2, 64), False),
+    "one_way_rt": (TARGET, 330, 0, 0, (6, 2, 64), True),
+    "one_way_single_heads": (FULL, 400, 0, 0, (4, 4, 64), False),
+    "two_ways": (FULL, 160, 0, 0, (8, 2, 64), False),
+    "two_ways_rt": (FULL, 160, 0, 0, (8, 2, 64), True),
+    "four_ways": (FULL, 64, 0, 0, (8, 2, 64), True),
+    "four_ways_d128": (FULL, 40, 0, 0, (16, 2, 128), True),
+    # 64 rows per workgroup in the forward pass of some requests
+    "rows64": (TARGET, 20, 0, 100, (8, 2, 64), True),
+    "rows64_d128": (TARGET, 22, 0, 100, (16, 2, 128), False),
+    # enough for the ordinary dK/dV pass; blocks behind the history in its grid (in a launch of their own at 128)
+    "ordinary_d32": (FULL, 400, 500, 0, (4, 2, 32), False),
+    "ordinary_d32_rt": (FULL, 400, 500, 0, (4, 2, 32), True),
+    "ordinary_d128_rt": (FULL, 160, 500, 0, (16, 2, 128), True),
+    "two_row_blocks": (FULL, 40, 2048, 0, (8, 2, 64), False),
+    "rows_resident": (TARGET, 256, 512, 88, (8, 2, 64), False),
+}
+
+
+def make(name):
+    layer, n, more_hist, more_tgts, (Hq, Hkv, d), rt = SHAPES[name]
+    cfg = inputs.custom_config(name, layer, cycle(HIST, n) + more_hist, cycle(TGTS, n) + more_tgts, Hq, Hkv, d, dtype="bf16",
+                               std=0.3, seed=77, rt_len=cycle(RT, n) if rt else None)
+    return inputs.make_case(cfg), sorted(set(range(0, n, max(1, n // 24))) | {1, n - 1}) if n > 64 else None
+
+
+@pytest.mark.parametrize("name", SHAPES)
+def test_shapes(name):
+    case, users = make(name)
+    check_case(case, with_bwd=True, users=users, compare=close_on_row_scale)
+
+
+@pytest.mark.parametrize("name", ["brief_rt", "brief_d128", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "ordinary_d32_rt"])
+def test_shapes_with_pointwise_weights(name):
+    case, users = make(name)
+    check_pointwise(case, norm=1.0 / 64, users=users, compare=close_on_row_scale)

@@ -173,9 +173,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
                     int row = row0 + l32;
                     const bool dead = past || row >= n_rows;
                     row = row < n_rows ? row : n_rows - 1;
-                    const int64_t idx = (int64_t)h * p.total_q + q_base + row;
-                    const float* src = hf == 0 ? p.neg_lse_s + (dead ? (int64_t)p.Hq * p.total_q : idx) : p.neg_delta + idx;
-                    copy4_global_to_lds_at(src, unit + 4u * (uint32_t)SM::TILE);
+                    copy4_global_to_lds_at(row_start(p, hf, (int64_t)h * p.total_q + q_base + row, !dead), unit + 4u * (uint32_t)SM::TILE);
                 }
             }
             if (!past && ++iss_hh == r) {
@@ -492,9 +490,7 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
                 int row = row0 + l32;
                 const bool dead = row >= n_rows;
                 row = row < n_rows ? row : n_rows - 1;
-                const int64_t idx = (int64_t)h * p.total_q + q_base + row;
-                const float* src = hf == 0 ? p.neg_lse_s + (dead ? (int64_t)p.Hq * p.total_q : idx) : p.neg_delta + idx;
-                copy4_global_to_lds_at(src, unit + 4u * (uint32_t)SM::TILE);
+                copy4_global_to_lds_at(row_start(p, hf, (int64_t)h * p.total_q + q_base + row, !dead), unit + 4u * (uint32_t)SM::TILE);
             }
         }
         wait_vmem_loads();

@@ -82,6 +82,13 @@ __device__ inline void rt_limit_of_row(const Params& p, int b, int row) {
     }
     p.lim[(int64_t)p.q_off[b] + row] = L + lo;
 }
+// Where a query row's S and dP start from in the dK/dV passes: the address of -lse/scale (lanes of the wave's lower half) or
+// of -delta (upper half), element idx = head * total_q + row.  A lane that stands for no row (not live) repeats the Q and dO of a row
+// of its own user and names that one: its S starts from the sentinel behind the -lse/scale array, so its weight is exactly 0,
+// but 0 times its dP still enters dK, and that must not carry another user's inf or NaN.
+__device__ inline const float* row_start(const Params& p, int half, int64_t idx, bool live) {
+    return half == 0 ? p.neg_lse_s + (live ? idx : (int64_t)p.Hq * p.total_q) : p.neg_delta + idx;
+}
 // the limits of all rows: a launch of its own at the start of most calls with real-time tokens
 hipError_t launch_rt_limits(const Params& p, hipStream_t s);
 

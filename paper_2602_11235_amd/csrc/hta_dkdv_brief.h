@@ -88,11 +88,11 @@ __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, u
             copy16_global_to_lds_at(qb, off, dst + j * 1024);
             copy16_global_to_lds_at(db, off, dst + BR::TILE * 2 + j * 1024);
         }
-        // a row that does not exist starts from the sentinel behind the -lse/scale array: P = 0 exactly
+        // likewise the statistics: of row 0, head h0, where there is no row (see row_start)
         const bool live = whole || (row0 + sq < n_rows && sq < map.rows && sh < n_heads);
-        const int64_t idx = live ? (int64_t)(h0 + sh) * p.total_q + q_base + row0 + sq : (int64_t)p.Hq * p.total_q;
-        copy4_global_to_lds_at(hf == 0 ? p.neg_lse_s + idx : p.neg_delta + (live ? idx : 0), dst + 4 * BR::TILE);
-        if constexpr (RT) copy4_global_to_lds_at(p.lim + q_base + (live ? row0 + sq : 0), dst + 4 * BR::TILE + 256);
+        const int row = row0 + (live ? sq : 0), h = h0 + (live ? sh : 0);
+        copy4_global_to_lds_at(row_start(p, hf, (int64_t)h * p.total_q + q_base + row, live), dst + 4 * BR::TILE);
+        if constexpr (RT) copy4_global_to_lds_at(p.lim + q_base + row, dst + 4 * BR::TILE + 256);
     };
     constexpr int COPIES = 2 * CPT + 1 + (RT ? 1 : 0);
     issue(0);

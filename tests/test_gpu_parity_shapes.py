@@ -3,9 +3,10 @@ every form of the forward, dQ and dK/dV passes runs on lengths at the edges of i
 other parity tests."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2602_11235_amd import inputs
-from tests.hta_testlib import check_case, close_on_row_scale
+from tests.hta_testlib import check_case, close_on_row_scale, device_batch, say, to_torch
 from tests.test_gpu_parity_pointwise import check as check_pointwise
 
 pytestmark = pytest.mark.gpu
@@ -60,3 +61,30 @@ def test_shapes(name):
 def test_shapes_with_pointwise_weights(name):
     case, users = make(name)
     check_pointwise(case, norm=1.0 / 64, users=users, compare=close_on_row_scale)
+
+
+@pytest.mark.parametrize("name", ["brief", "brief_d32", "brief_d128", "one_way", "one_way_rt", "two_ways", "four_ways_d128",
+                                  "ordinary_d32", "ordinary_d32_rt", "ordinary_d128_rt", "rows_resident"])
+def test_non_finite_values_stay_with_their_user(name):
+    """The users that own the call's first and last query rows get NaN everywhere; everyone else's results keep their bits.  (Lanes
+    that stand for no row still multiply their dP by a weight of 0: it has to be the dP of a row of the same user.)"""
+    case, _ = make(name)
+    rows = np.diff(case.q_offsets)
+    spoilt = [int(np.flatnonzero(rows)[0]), int(np.flatnonzero(rows)[-1])]
+    q_keep, kv_keep = np.ones(case.total_q, bool), np.ones(case.total_kv, bool)
+    for b in spoilt:
+        q_keep[case.q_offsets[b]:case.q_offsets[b + 1]] = False
+        kv_keep[case.kv_offsets[b]:case.kv_offsets[b + 1]] = False
+    q_keep, kv_keep = torch.from_numpy(q_keep).to("cuda"), torch.from_numpy(kv_keep).to("cuda")
+    results = []
+    for value in (None, float("nan")):
+        batch, dout = device_batch(case), to_torch(case.dout, "bf16")
+        if value is not None:
+            batch.q[~q_keep], batch.k[~kv_keep], batch.v[~kv_keep], dout[~q_keep] = value, value, value, value
+        out, lse = batch.forward()
+        dq, dk, dv = batch.backward(dout)
+        results.append({"out": out[q_keep], "lse": lse[:, q_keep], "dq": dq[q_keep], "dk": dk[kv_keep], "dv": dv[kv_keep]})
+    for key, clean in results[0].items():
+        lost = int((results[1][key] != clean).sum())
+        say(f"    {name} {key}: {lost} of {clean.numel()} elements of the other users changed")
+        assert torch.isfinite(clean).all() and lost == 0, f"{key}: {lost} elements of other users changed"

@@ -30,8 +30,8 @@ struct DkdvSmem {
 
 // One workgroup per (user, kv head, tile of NW*32 history keys).  Q and dO tiles travel global -> LDS directly
 // (no register stop-over), two iterations ahead of their use.
-// With real-time tokens (mask rule 2) these workgroups take the whole 32-key blocks of the history only, which every row
-// sees: no mask.  The blocks behind them (TAILS: the last blocks of the grid, behind the persistent ones; at
+// Of a user with real-time tokens (mask rule 2) these workgroups take the whole 32-key blocks of the history only, which every
+// row sees: no mask.  The blocks behind them (TAILS: the last blocks of the grid, behind the persistent ones; at
 // d = 128, where both in one kernel do not fit the registers, a launch of their own) are
 // brief_dkdv's, whose masked stream skips the rows that see none of their keys; they fill the units that run out of
 // history.  (256 users of 512..1024 + 32..128 + 64 tokens: 940 us, against 1019 in the same session with one masked instruction
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     const int b = scheduled_user(p, w.user_slot), g = w.y;
     const int L = p.hist_len[b], T = p.n_targets[b];
     const int R = p.rt_len ? p.rt_len[b] : 0;
-    const int LK = p.rt_len ? L & ~31 : L;  // keys that receive gradient here
+    const int LK = R > 0 ? L & ~31 : L;  // keys that receive gradient here
     const int key0 = w.tile * (NW * 32);
     if (key0 >= LK) return;  // uniform: this key tile does not exist for the user
     const int n_rows = p.layer == 0 ? L + R + T : T;

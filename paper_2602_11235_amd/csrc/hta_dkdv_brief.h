@@ -28,8 +28,8 @@ struct Brief {
 };
 
 // ---------------------------------------------------------------------------------------- dK, dV
-// TAIL (with real-time tokens): only the 32-key blocks behind the last whole block of history keys.  Most rows of a user
-// see none of those keys; the units of such rows are skipped.
+// TAIL: only users with real-time tokens, and of those only the 32-key blocks behind the last whole block of history keys.  Most
+// rows of a user see none of those keys; the units of such rows are skipped.
 // WAYS: waves that share the rows of a 32-key block and add up their sums; a workgroup has BRIEF_NW / WAYS such blocks.
 template <int D, int WAYS, bool RT, bool PW, bool TAIL = false>
 __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, unsigned id, int n_kt, int spread, unsigned char* smem) {
@@ -42,6 +42,7 @@ __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, u
     const int L = p.hist_len[b], T = p.n_targets[b];
     const int64_t q_base = p.q_off[b], kv_base = p.kv_off[b];
     const int LK = L + (RT ? p.rt_len[b] : 0);  // keys that receive gradient here: history, then real-time
+    if (TAIL && LK == L) return;  // (a user without real-time tokens is bwd_dkdv_kernel's alone, bit for bit as in a call without any)
     constexpr int KBS = BRIEF_NW / WAYS;
     const int key0 = w.tile * (KBS * 32) + (TAIL ? L & ~31 : 0);
     if (key0 >= LK) return;  // uniform for the workgroup

@@ -1,6 +1,8 @@
 """GPU parity for samples with real-time tokens (mask rule 2 of Section 3.2.2): the HIP library, called through the
 C ABI (mtfm_hta_fwd_rt / mtfm_hta_bwd_rt), against the float64 oracle on the same seeded bits, element by element.
 Tolerances as for the plain hybrid mask: atol = rtol = 2e-2 (bf16), 1e-4 (fp32)."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -52,7 +54,8 @@ def test_c4_rt_target_layer_sampled_users():
 
 
 def test_zero_realtime_tokens_equal_the_plain_entry_points_bitwise():
-    """rt_len = 0 for every user: the real-time entry points must return exactly what the plain ones return."""
+    """rt_len = 0 for every user and a bound max_rt of 0: the real-time entry points must return exactly what the plain ones
+    return.  (A larger bound may have another form of a pass chosen, which sums in another order.)"""
     plain = inputs.make_case(inputs.custom_config("rt0", FULL, [200, 65, 0, 130], [7, 33, 2, 64], 8, 2, 64, seed=5))
     with_rt = inputs.make_case(inputs.custom_config("rt0", FULL, [200, 65, 0, 130], [7, 33, 2, 64], 8, 2, 64, seed=5,
                                                     rt_len=[0, 0, 0, 0]))
@@ -66,3 +69,24 @@ def test_zero_realtime_tokens_equal_the_plain_entry_points_bitwise():
         res.append([host(t) for t in (out, lse, dq, dk, dv)])
     for a, b in zip(*res):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("heads,n,hist", [((4, 2, 32), 400, 500), ((8, 2, 64), 120, 900), ((16, 2, 128), 160, 500)])
+def test_users_without_realtime_tokens_keep_the_plain_bits(heads, n, hist):
+    """A batch of which every other user has real-time tokens, against a plain batch of as many users, all of them without (large
+    enough for both to run the passes of a full chip): the same results, bit for bit, for the users without."""
+    Hq, Hkv, d = heads
+    lens = hist + np.resize([0, 1, 11, 12, 13, 44, 45, 76, 100, 140], n)   # ends in and at the edges of 32- and 64-key blocks
+    rt = np.where(np.arange(n) % 2 == 0, np.resize([5, 33, 64], n), 0)
+    mixed = inputs.make_case(inputs.custom_config("mixed", FULL, lens, np.resize([7, 32, 40], n), Hq, Hkv, d, seed=6, rt_len=rt))
+    without = np.flatnonzero(rt == 0)
+    plain = dataclasses.replace(inputs.take_users(mixed, np.resize(without, n)), rt_len=None, timestamps=None)
+    results = []
+    for case, users in ((mixed, without), (plain, np.arange(len(without)))):
+        batch = device_batch(case)
+        out, lse = batch.forward()
+        dq, dk, dv = batch.backward(to_torch(case.dout, "bf16"))
+        rows = torch.from_numpy(inputs.user_rows(case.q_offsets, users)).to("cuda")   # full layer: query rows = K/V rows
+        results.append({"out": out[rows], "lse": lse[:, rows], "dq": dq[rows], "dk": dk[rows], "dv": dv[rows]})
+    for key, a in results[0].items():
+        assert torch.equal(a, results[1][key]), f"{key}: {int((a != results[1][key]).sum())} of {a.numel()} elements differ"

@@ -88,10 +88,17 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+# torch.cuda.current_stream() builds a Stream object around the handle (1.5 us; a call of a few microseconds is worth asking for
+# the handle alone).  The two functions behind it are not part of torch's public interface: without them, the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device_index = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _current_stream() -> int:
-    """Handle of the current stream of the current device (torch.cuda.current_stream() builds a Stream object around it,
-    1.5 us; a call of a few microseconds is worth asking for the handle alone)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    """Handle of the current stream of the current device."""
+    if _raw_stream is None or _device_index is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device_index())
 
 
 def _stream_handle(stream) -> Optional[int]:

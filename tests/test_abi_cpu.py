@@ -140,3 +140,23 @@ def test_product_package_does_not_import_the_oracle():
                 text = open(os.path.join(dirpath, f)).read()
                 assert not re.search(r"^\s*(from|import)\s+oracle\b", text, flags=re.M), f"{f} imports the oracle"
                 assert "hta_oracle" not in text and "libhta_oracle" not in text, f"{f} refers to the oracle library"
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_device_index"])
+def test_stream_handle_without_the_private_functions_of_torch(monkeypatch, missing):
+    class Stream:
+        cuda_stream = 4711
+
+    monkeypatch.setattr(hta, missing, None)
+    monkeypatch.setattr(hta.torch.cuda, "current_stream", Stream)
+    assert hta._stream_handle(None) == 4711
+
+
+@pytest.mark.gpu
+def test_stream_handle_is_that_of_the_current_stream():
+    torch = hta.torch
+    stream = torch.cuda.Stream()
+    assert hta._stream_handle(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(stream):
+        assert hta._stream_handle(None) == stream.cuda_stream
+    assert hta._stream_handle(None) == torch.cuda.current_stream().cuda_stream

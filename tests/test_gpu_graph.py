@@ -23,10 +23,14 @@ def _replay_and_compare(graph, outputs, eager, disturb):
             assert torch.equal(t, ref), f"replay {i}: {name} differs from the eager result"
 
 
-@pytest.mark.parametrize("name, with_bwd", [("I1", False), ("I2_RT", False), ("C2", True)])
+# a few users: forward and backward in their forms for calls of little work
+FEW = inputs.custom_config("few", inputs.LAYER_TARGET, [300, 65, 1000], [7, 33, 40], 8, 2, 64, seed=43, rt_len=[40, 0, 70])
+
+
+@pytest.mark.parametrize("name, with_bwd", [("I1", False), ("I2_RT", False), ("C2", True), ("C2_RT", True), ("few", True)])
 def test_forward_and_backward_replay_from_a_graph(name, with_bwd):
     say(f"[graph] {name} bwd={with_bwd}")
-    case = inputs.make_case(inputs.CONFIGS[name])
+    case = inputs.make_case(FEW if name == "few" else inputs.CONFIGS[name])
     b = device_batch(case)
     other = device_batch(inputs.make_case(inputs.custom_config("other", inputs.LAYER_FULL, [300, 65], [7, 33], 8, 2, 64, seed=41)))
     dout = to_torch(case.dout, case.cfg.dtype)

@@ -51,6 +51,16 @@ def test_split_forward_with_real_time_tokens(layer):
     check_case(c, with_bwd=False)
 
 
+@pytest.mark.parametrize("layer", [TARGET, FULL])
+@pytest.mark.parametrize("heads", [(8, 2, 64), (3, 1, 128)])
+def test_few_requests_with_many_real_time_tokens(layer, heads):
+    """Real-time segments at and around the length up to which their timestamps are searched in LDS (512), and at its copies'
+    64-token pieces; with the backward pass, which goes by the same limits."""
+    c = inputs.make_case(inputs.custom_config("many_rt", layer, [700, 0, 63, 130, 200, 64], [16, 5, 33, 2, 7, 1], *heads, seed=34,
+                                              rt_len=[512, 513, 600, 511, 65, 64]))
+    check_case(c, with_bwd=True)
+
+
 def test_split_and_unsplit_forward_agree():
     """The same request alone (keys split) and as one of 300 copies (no split): two different summation orders of
     the same softmax, equal up to the bf16 rounding of the output."""

@@ -41,6 +41,16 @@ SHAPES = {
     "ordinary_d128_rt": (FULL, 160, 500, 0, (16, 2, 128), True),
     "two_row_blocks": (FULL, 40, 2048, 0, (8, 2, 64), False),
     "rows_resident": (TARGET, 256, 512, 88, (8, 2, 64), False),
+    # groups of more query heads than a tile has lanes, cut into chunks of which the last one is not full; all forms again
+    "brief_wide": (TARGET, 6, 0, 0, (40, 1, 64), True),
+    "brief_wide_d32": (TARGET, 10, 0, 0, (130, 1, 32), False),
+    "brief_wide_d128": (FULL, 8, 0, 0, (66, 2, 128), False),
+    "rows64_wide": (TARGET, 12, 0, 20, (70, 1, 64), True),
+    "rows64_wide_d128": (TARGET, 12, 0, 20, (70, 1, 128), False),
+    "four_ways_wide_d32": (FULL, 24, 0, 0, (130, 1, 32), True),
+    "four_ways_wide": (FULL, 10, 0, 0, (300, 1, 64), True),
+    "four_ways_wide_d128": (FULL, 24, 0, 0, (130, 1, 128), False),
+    "ordinary_wide_d128_rt": (FULL, 40, 500, 0, (33, 1, 128), True),
 }
 
 
@@ -57,7 +67,8 @@ def test_shapes(name):
     check_case(case, with_bwd=True, users=users, compare=close_on_row_scale)
 
 
-@pytest.mark.parametrize("name", ["brief_rt", "brief_d128", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "ordinary_d32_rt"])
+@pytest.mark.parametrize("name", ["brief_rt", "brief_d128", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "ordinary_d32_rt",
+                                  "brief_wide", "rows64_wide"])
 def test_shapes_with_pointwise_weights(name):
     case, users = make(name)
     check_pointwise(case, norm=1.0 / 64, users=users, compare=close_on_row_scale)

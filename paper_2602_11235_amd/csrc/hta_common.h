@@ -113,8 +113,10 @@ hipError_t launch_widen16(const void* src, void* dst, int64_t n_rows, hipStream_
 hipError_t launch_narrow16(const void* src, void* dst, int64_t n_rows, hipStream_t s);
 // the most key splits the bf16 forward pass may use for these host-known bounds: what its workspace has room for (1 = none)
 int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t max_rows, int64_t max_keys);
-// the splits it does use, at most `room`; 0: the call fills the chip and runs the ordinary forward kernel
+// the splits it does use, at most `room`; 0: the call runs the ordinary forward kernel
 int serve_splits(const Params& p, int room);
+// packed (row, head) pairs that a workgroup of the ordinary forward kernel takes in this call
+int fwd_workgroup_rows(const Params& p);
 // stores the calling thread's error message (what mtfm_hta_last_error() returns) and hands `code` back
 int report_error(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 // event hooks around each kernel (no-ops unless timing was enabled through the C ABI); `kind` is one of the

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap m
     // (two ahead, except for d = 128 where a third stage would cost the second workgroup of the CU).  The compiler
     // never sees a store into this array (the copies are issued from inline assembly), so it neither orders LDS reads
     // against them nor drains them; the counted waits and barriers below do that.
-        constexpr int NSTAGE = D <= 64 ? 3 : 2, AHEAD = NSTAGE - 1;
+    constexpr int NSTAGE = D <= 64 ? 3 : 2, AHEAD = NSTAGE - 1;
     // d = 128, two waves per SIMD: a tile's two sub-tiles as one step, so that a wave has two independent chains of products
     // and exponentials (11.6 -> 11.5 ms on 339 k rows of 16/2 heads, histories up to 8192); at d = 64 four waves do that.
     constexpr bool PAIRS = D == 128;
@@ -158,9 +158,11 @@ hipError_t launch(const Params& p, hipStream_t s) {
 // packed rows per user: P = 480 44 against 68 us, P = 1400 37 against 36, P = 3400 470 against 450), or just more than 256
 // at most (P = 92..372: 88 against 115 us).  At 128 (1.05 against 1.13 ms on 232 users of 252..1010 keys, 46 -> 39 us on 44 short
 // ones) and 32 four waves always.
-bool four_waves(const Params& p) {
+int waves(const Params& p) {
+    if (p.d != 64) return 4;
     const int64_t r = p.Hq / p.Hkv, most = max_query_rows(p) * r;
-    return p.layer == 0 ? mean_rows(p) * r <= 1000. && most > 256 : most > 256 && most <= 384;
+    const bool four = p.layer == 0 ? mean_rows(p) * r <= 1000. && most > 256 : most > 256 && most <= 384;
+    return four ? 4 : 8;
 }
 
 }  // namespace
@@ -171,13 +173,15 @@ bool bf16_supported(int32_t d, int32_t Hq, int32_t Hkv) {
     return d == 32 || d == 64 || d == 128;
 }
 
+int fwd_workgroup_rows(const Params& p) { return waves(p) * 32; }
+
 hipError_t launch_fwd_bf16(const Params& p, hipStream_t s) {
     if (p.n_splits > 0) return launch_serve_bf16(p, s);
     hipError_t e;
     timing_begin(MTFM_HTA_KERNEL_FWD, s);
     switch (p.d) {
         case 32: e = launch<32, 4>(p, s); break;
-        case 64: e = four_waves(p) ? launch<64, 4>(p, s) : launch<64, 8>(p, s); break;
+        case 64: e = waves(p) == 4 ? launch<64, 4>(p, s) : launch<64, 8>(p, s); break;
         case 128: e = launch<128, 4>(p, s); break;
         default: e = hipErrorInvalidValue;
     }

@@ -24,6 +24,7 @@
 #include "hta_tiles.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace hta {
 namespace {
@@ -326,8 +327,8 @@ Shape shape_of(const Params& p) { return p.d > 32 && live_tiles(p, 32) > (p.d ==
 
 }  // namespace
 
-// Workgroups the ordinary forward kernel would have for these bounds: 256 rows (512 at d = 32), fewer heads per workgroup where
-// a group does not divide evenly.  (The workspace formula below is part of the interface's contract and counts the same way.)
+// What the workspace formula below counts, which is part of the interface's contract: tiles of 128, 256 or 512 rows, fewer heads per
+// tile where a group does not divide evenly.  (Not what any kernel launches today: see fwd_workgroup_rows for that.)
 static int64_t ordinary_items(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t max_rows) {
     const int64_t r = Hq / Hkv, waves = r % 4 == 0 ? 8 : 4;
     const int64_t lanes = 32 * waves * (d == 32 || (d == 64 && waves == 4) ? 2 : 1);
@@ -347,24 +348,57 @@ int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t ma
     return n > 1 ? (int)n : 1;
 }
 
-// The ordinary kernel shares each K/V tile among 256 rows and keeps two workgroups on a unit: it is the better one as soon
-// as its workgroups nearly fill the chip (32 requests x 256 candidates on 8192 keys: 160 against 180 us; half of that,
-// ragged: 76 against 61).  Below that, keys are split over workgroups when the time this takes off the longest item is
-// worth the merge: per key and workgroup 2.05 ns at head_dim 64, 4.4 at 128; merge 4.2 us, partial results at 3 TB/s.
+// Estimated times of a call (us) with the keys in one piece, from fits of 2700 calls on both sides of the line (1 to 400 users,
+// 4 to 256 candidates or a full layer, 64 to 8192 keys, all of one length or spread over a factor of 8; with and without
+// real-time tokens and with pointwise weights).  The ordinary kernel, up to a workgroup per unit: the longest one, a little more the
+// fuller the chip, and the schedule (whose time grows with the users) and limits launches.
+static double ordinary_us(const Params& p, int64_t workgroups) {
+    struct { double launch, key, key_full; } c;
+    if (p.d == 32) c = {6.2, 9.5e-3, 3.5e-3};
+    else if (p.d == 128) c = {9.6, 17.6e-3, 4.e-3};
+    else if (fwd_workgroup_rows(p) == 128) c = {7.5, 13.e-3, 2.5e-3};
+    else c = {8., 14.e-3, 5.e-3};
+    return c.launch + 0.02 * p.batch + (p.rt_len ? 2. : 0.) + c.key * max_lead_keys(p) + c.key_full * mean_keys(p) * workgroups / 256.;
+}
+// The kernel above: one workgroup per unit, so rounds of 256 of them.
+static double serve_us(const Params& p, Shape shape) {
+    struct { double launch, fixed, key; } c;
+    if (p.d == 32) c = {1., 3.7, 2.7e-3};
+    else if (p.d == 64 && shape == ROWS64) c = {1., 7., 5.2e-3};
+    else if (p.d == 64) c = {3., 2.5, 3.e-3};
+    else if (shape == ROWS64) c = {1., 9., 10.e-3};
+    else c = {0., 7., 5.3e-3};
+    const double longest = (double)max_lead_keys(p), mean = mean_keys(p), full = live_tiles(p, shape == ROWS64 ? 64 : 32) / 256.;
+    const double rounds = mean > 0.9 * longest ? std::ceil(full) : std::max(1., full + 0.75);
+    return c.launch + c.fixed * rounds + c.key * std::max(longest, mean * rounds);
+}
+
+// This kernel or the ordinary one, which shares each K/V tile among 128 or 256 rows and keeps two workgroups on a unit.  Once its
+// workgroups nearly fill the chip, the ordinary one (at head_dim 64, 224 to 330 of them: on average 1.3 times as fast; 128:
+// 1.5; 32, 448 to 600: 2.1).  Below that, keys are split over workgroups when the time this takes off the longest item is worth
+// the merge: per key and workgroup 2.05 ns at head_dim 64, 4.4 at 128; merge 4.2 us, partial results at 3 TB/s.  Where it is not, by
+// the estimates above: 64-row workgroups that come in rounds lose to 256-row ones that do not.  (8/2 heads of 64: 27 users x
+// 256 candidates on 512 keys 38 us here against 20 there, on 2048 64 / 45; 13 users on 2048 34 / 43; 40 users x 128 candidates,
+// 16/2 heads of 128, 64..512 keys 60 / 31; 110 x 256, 4/2 heads of 32, 512 keys 63 / 25.  Of the 2700 calls 622
+// had a tenth or more to gain on the other side when only full chips went there, 47 have now.)
 int serve_splits(const Params& p, int room) {
-    if (live_tiles(p, p.d == 32 ? 512 : 256) >= 224) return 0;
-    if (room <= 1 || shape_of(p) == ROWS64) return 1;
-    const RowMap map = row_map(32, p.Hq, p.Hkv, max_query_rows(p));
-    const int64_t items = (int64_t)p.batch * p.Hkv * map.n_chunks * map.n_tiles;
-    const double loop = max_lead_keys(p) * (p.d == 128 ? 4.4e-3 : 2.05e-3);
-    const double part = 2.0 * p.total_q * p.Hq * p.d * 4 / 3e6;
-    int best = 1;
-    double best_us = loop;
-    for (int s = 2; s <= room && items * s <= 256; s++) {
-        const double us = loop / s + 4.2 + s * (part + 0.05);
-        if (us < best_us) best = s, best_us = us;
+    const int64_t ordinary = live_tiles(p, fwd_workgroup_rows(p));
+    if (ordinary >= (p.d == 32 ? 448 : 224)) return 0;
+    const Shape shape = shape_of(p);
+    if (room > 1 && shape != ROWS64) {
+        const RowMap map = row_map(32, p.Hq, p.Hkv, max_query_rows(p));
+        const int64_t items = (int64_t)p.batch * p.Hkv * map.n_chunks * map.n_tiles;
+        const double loop = max_lead_keys(p) * (p.d == 128 ? 4.4e-3 : 2.05e-3);
+        const double part = 2.0 * p.total_q * p.Hq * p.d * 4 / 3e6;
+        int best = 1;
+        double best_us = loop;
+        for (int s = 2; s <= room && items * s <= 256; s++) {
+            const double us = loop / s + 4.2 + s * (part + 0.05);
+            if (us < best_us) best = s, best_us = us;
+        }
+        if (best > 1) return best;
     }
-    return best;
+    return ordinary_us(p, ordinary) < 0.97 * serve_us(p, shape) ? 0 : 1;
 }
 
 hipError_t launch_serve_bf16(const Params& p, hipStream_t s) {

@@ -17,7 +17,7 @@ TGTS = np.array([0, 1, 7, 8, 9, 16, 31, 32, 33, 40])
 RT = np.array([0, 1, 31, 32, 33, 65])
 cycle = lambda values, n: np.resize(values, n)
 
-# name: layer, users, history beyond HIST, targets beyond TGTS, heads, with real-time tokens
+# name: layer, users, history beyond HIST (in a tuple: of every fourth user), targets beyond TGTS, heads, with real-time tokens
 SHAPES = {
     # a few dozen users: the rows of 32 keys, and the keys of 32 rows, shared by the waves of a workgroup
     "brief": (FULL, 12, 0, 0, (8, 2, 64), False),
@@ -35,6 +35,8 @@ SHAPES = {
     # 64 rows per workgroup in the forward pass of some requests
     "rows64": (TARGET, 20, 0, 100, (8, 2, 64), True),
     "rows64_d128": (TARGET, 22, 0, 100, (16, 2, 128), False),
+    "rows64_long": (TARGET, 10, (2500,), 100, (8, 2, 64), True),
+    "rows64_d128_long": (TARGET, 10, (2500,), 100, (16, 2, 128), True),
     # enough for the ordinary dK/dV pass; blocks behind the history in its grid (in a launch of their own at 128)
     "ordinary_d32": (FULL, 400, 500, 0, (4, 2, 32), False),
     "ordinary_d32_rt": (FULL, 400, 500, 0, (4, 2, 32), True),
@@ -43,10 +45,10 @@ SHAPES = {
     "rows_resident": (TARGET, 256, 512, 88, (8, 2, 64), False),
     # groups of more query heads than a tile has lanes, cut into chunks of which the last one is not full; all forms again
     "brief_wide": (TARGET, 6, 0, 0, (40, 1, 64), True),
-    "brief_wide_d32": (TARGET, 10, 0, 0, (130, 1, 32), False),
-    "brief_wide_d128": (FULL, 8, 0, 0, (66, 2, 128), False),
-    "rows64_wide": (TARGET, 12, 0, 20, (70, 1, 64), True),
-    "rows64_wide_d128": (TARGET, 12, 0, 20, (70, 1, 128), False),
+    "brief_wide_d32": (TARGET, 5, 0, 0, (130, 1, 32), False),
+    "brief_wide_d128": (TARGET, 4, 0, 0, (66, 2, 128), False),
+    "rows64_wide": (TARGET, 4, (1000,), 60, (70, 1, 64), True),
+    "rows64_wide_d128": (TARGET, 8, (2500,), 10, (70, 1, 128), False),
     "four_ways_wide_d32": (FULL, 24, 0, 0, (130, 1, 32), True),
     "four_ways_wide": (FULL, 10, 0, 0, (300, 1, 64), True),
     "four_ways_wide_d128": (FULL, 24, 0, 0, (130, 1, 128), False),
@@ -56,6 +58,8 @@ SHAPES = {
 
 def make(name):
     layer, n, more_hist, more_tgts, (Hq, Hkv, d), rt = SHAPES[name]
+    if isinstance(more_hist, tuple):
+        more_hist = np.where(np.arange(n) % 4 == 3, more_hist[0], 0)
     cfg = inputs.custom_config(name, layer, cycle(HIST, n) + more_hist, cycle(TGTS, n) + more_tgts, Hq, Hkv, d, dtype="bf16",
                                std=0.3, seed=77, rt_len=cycle(RT, n) if rt else None)
     return inputs.make_case(cfg), sorted(set(range(0, n, max(1, n // 24))) | {1, n - 1}) if n > 64 else None

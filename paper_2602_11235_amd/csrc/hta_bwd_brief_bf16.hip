@@ -326,7 +326,8 @@ hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s) {
 // pass shares its staging among 128 keys and wins in the long run; it loses where a user's rows walked one after the
 // other take longer than the rest of the call.  (8/2 heads: 64 users of 128..512 keys 77 -> 60 us, 19 of 374..1498 200 -> 134,
 // 151 x 16..64 candidates 82 -> 41, 256 of 512..1024 ordinary 750 against 925; 512 x 128 candidates on 2048 keys resident 1.22 ms
-// against 1.70.)
+// against 1.70; 512 x 128 on 512..2048 keys, 16/4 heads, whole backward 1.47 ms against 1.79, 64 x 8..32 on 512 keys the other way
+// round, 63 us against 42.)
 int dkdv_brief_ways(const Params& p) {
     if (p.total_q == 0) return 0;
     const int r = p.Hq / p.Hkv;
@@ -339,8 +340,11 @@ int dkdv_brief_ways(const Params& p) {
     };
     // (the ordinary pass takes 32 rows of one head at a time)
     const double fixed = wide ? 6. : 5.3, unit = (wide ? 1.1 : 1.05) * r;
+    // (the resident one walks all keys of a user, past all row blocks that the longest one has, 256 users' kv heads at a time)
+    const double blocks = std::min(rows / 32. + 0.5, std::ceil(most / 32.)), users = groups / 256.;
+    const double rounds = keys >= 0.9 * (double)max_lead_keys(p) ? std::ceil(users) : std::max(1., users);
     double best = dkdv_is_resident(p)
-                      ? std::ceil(groups / 256.) * (keys / 32. + 6.) * r * (rows / 32. + 0.5) / 12. * 1.82
+                      ? 30. + rounds * (keys / 32. + 2.) * (r * blocks + 2.2) * 0.118
                       : estimate(groups * (keys / 128. + 0.5), fixed + unit * (rows / 32. + 0.5), 0.95 * (fixed + unit * (most / 32. + 0.5)));
     int ways = 0;
     for (int w = 1; w <= NW; w *= 2) {

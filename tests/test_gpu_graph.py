@@ -27,7 +27,7 @@ def _replay_and_compare(graph, outputs, eager, disturb):
 FEW = inputs.custom_config("few", inputs.LAYER_TARGET, [300, 65, 1000], [7, 33, 40], 8, 2, 64, seed=43, rt_len=[40, 0, 70])
 
 
-@pytest.mark.parametrize("name, with_bwd", [("I1", False), ("I2_RT", False), ("C2", True), ("C2_RT", True), ("few", True)])
+@pytest.mark.parametrize("name, with_bwd", [("I1", False), ("I2_RT", False), ("I3", False), ("C2", True), ("C2_RT", True), ("few", True)])
 def test_forward_and_backward_replay_from_a_graph(name, with_bwd):
     say(f"[graph] {name} bwd={with_bwd}")
     case = inputs.make_case(FEW if name == "few" else inputs.CONFIGS[name])

@@ -1,6 +1,6 @@
 """GPU parity at inference shapes: forward only, a handful of requests, so the library splits the keys of every
-(user, kv head) group over several workgroups and merges the partial softmax results.  Same float64 oracle, same
-tolerances (atol = rtol = 2e-2 for bf16) as the training shapes."""
+(user, kv head) group over the waves of a workgroup, and over several workgroups where that pays, and merges the partial
+softmax results.  Same float64 oracle, same tolerances (atol = rtol = 2e-2 for bf16) as the training shapes."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,7 @@ FULL, TARGET = inputs.LAYER_FULL, inputs.LAYER_TARGET
 
 
 def is_split(case) -> bool:
-    """The forward workspace holds partial results only when the keys are split."""
+    """Is the call small enough that its keys may be split over workgroups (the forward workspace has room for partial results)?"""
     b = device_batch(case)
     plain = 256 + 256 * ((4 * case.batch + 255) // 256)
     if case.rt_len is not None:
@@ -28,8 +28,8 @@ def test_inference_workloads_forward(name):
     check_case(c, with_bwd=False)
 
 
-# Histories around the tile and split boundaries next to long ones (the split count follows the longest): no history
-# at all (every split is empty, the own key alone), less than one tile, exactly two tiles, one key more than a tile.
+# Histories around the tile and block boundaries next to long ones: no history at all (no wave has a key, the own key alone),
+# less than one tile, exactly two tiles, one key more than a tile.
 EDGE_HIST = [2048, 0, 1, 63, 128, 65, 1000, 64]
 EDGE_TGTS = [16, 5, 1, 33, 64, 2, 70, 0]
 
@@ -51,6 +51,22 @@ def test_split_forward_with_real_time_tokens(layer):
     check_case(c, with_bwd=False)
 
 
+# A history long enough that splitting it over workgroups pays for the launch that merges the partial results, next to users whose
+# keys end in the first split or before it.
+LONG_HIST = [8192, 0, 1, 63, 4133]
+LONG_RT = [70, 5, 0, 130, 300]
+LONG_TGTS = [16, 5, 1, 33, 2]
+
+
+@pytest.mark.parametrize("with_rt", [False, True])
+@pytest.mark.parametrize("heads", [(8, 2, 64), (3, 1, 64), (16, 2, 128), (4, 2, 32)])
+def test_keys_split_over_workgroups(heads, with_rt):
+    c = inputs.make_case(inputs.custom_config("split_long", TARGET, LONG_HIST, LONG_TGTS, *heads, seed=35,
+                                              rt_len=LONG_RT if with_rt else None))
+    assert is_split(c)
+    check_case(c, with_bwd=False)
+
+
 @pytest.mark.parametrize("layer", [TARGET, FULL])
 @pytest.mark.parametrize("heads", [(8, 2, 64), (3, 1, 128)])
 def test_few_requests_with_many_real_time_tokens(layer, heads):
@@ -62,7 +78,7 @@ def test_few_requests_with_many_real_time_tokens(layer, heads):
 
 
 def test_split_and_unsplit_forward_agree():
-    """The same request alone (keys split) and as one of 300 copies (no split): two different summation orders of
+    """The same request alone (keys split over waves) and as one of 300 copies (not split): two different summation orders of
     the same softmax, equal up to the bf16 rounding of the output."""
     one = inputs.make_case(inputs.custom_config("one", TARGET, [1800], [40], 8, 2, 64, seed=33))
     many = inputs.take_users(one, [0] * 300)

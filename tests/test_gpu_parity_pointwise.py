@@ -195,3 +195,11 @@ def test_split_edge_batch():
     c = inputs.make_case(inputs.custom_config("pw_split", TARGET, [2048, 0, 1, 63, 128, 65, 1000, 64],
                                               [16, 5, 1, 33, 64, 2, 70, 0], 8, 2, 64, seed=56))
     check(c)
+
+
+@pytest.mark.parametrize("rt", [None, [70, 5, 0, 130, 300]])
+def test_keys_split_over_workgroups(rt):
+    # a history long enough that the split over workgroups pays for its merge
+    c = inputs.make_case(inputs.custom_config("pw_split_long", TARGET, [8192, 0, 1, 63, 4133], [16, 5, 1, 33, 2], 8, 2, 64, seed=57,
+                                              rt_len=rt))
+    check(c)

@@ -61,6 +61,9 @@ def test_split_forward_and_other_shapes():
     assert device_batch(many).fwd_workspace_bytes > 65536
     check(many)
     check(one)
+    # a history long enough that its keys are split over workgroups: partial results in the built-in scratch memory
+    check(inputs.make_case(inputs.custom_config("static_split_long", TARGET, [8192, 0, 63], [16, 5, 33], 8, 2, 64, seed=68),
+                           with_dout=False))
     check(inputs.make_case(inputs.custom_config("static_fp32", FULL, [40, 0, 64], [8, 3, 0], 4, 1, 16, dtype="fp32",
                                                 std=0.5, seed=65), with_dout=False))
     check(inputs.make_case(inputs.custom_config("static_d128", FULL, [257, 31], [129, 0], 16, 2, 128, seed=66),

@@ -247,7 +247,8 @@ def bench_gln(args) -> int:
 def bench_infer(args) -> int:
     """--op infer: one step = one forward call of the target layer over a handful of requests (inference shape:
     request-level aggregation, forward only).  The batch is far too small to fill the chip with (user, kv head) groups,
-    so the library splits the keys of each group over workgroups; the figure of merit is the latency of a call."""
+    so the library splits the keys of each group over waves, and over workgroups where that pays; the figure of merit is the
+    latency of a call."""
     import torch
     from paper_2602_11235_amd import hta, inputs
     if not torch.cuda.is_available():
@@ -321,7 +322,7 @@ def bench_infer(args) -> int:
                        "graph_replay_median": float(np.median(glat) * 1e6), "graph_replay_min": float(np.min(glat) * 1e6)},
         "candidates_per_s": int(case.n_targets.sum()) / (ms_per_step * 1e-3),
         "kernels": {"fwd": {"avg_ms": avg, "min_ms": float(np.min(ms)), "launches": len(ms), "tflops": tflops,
-                            "note": "split-key forward kernel + merge kernel (one event pair around both)"}},
+                            "note": "forward kernel, and the merge kernel where keys are split over workgroups (one event pair)"}},
         "roofline": {"bound": "mfma", "kernel": "fwd", "achieved": tflops, "peak": BF16_MFMA_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": tflops / BF16_MFMA_PEAK_TFLOPS, "traffic": None,
                      "avg_kernel_ms": avg, "algorithmic_flops_per_launch": flops,

@@ -74,9 +74,10 @@ enum { MTFM_HTA_LAYER_FULL = 0, MTFM_HTA_LAYER_TARGET = 1 };
  * attention tiles, from hist_len / n_targets) -- and, for the backward pass, two float32 values per
  * (query head, query row): -delta = -<dout, out> and -lse / softmax_scale.
  * A forward call on so few users that (user, kv head, row tile) items cannot give every compute unit a workgroup
- * (a handful of requests at inference; decided from batch, the max_* bounds and the head shape alone) splits the keys
- * of each item over several workgroups; the workspace then also holds their partial results, float32
- * [splits][total_q][Hq][head_dim] and [splits][Hq][total_q], which a second kernel merges into out and lse.
+ * (a handful of requests at inference; decided from batch, the max_* bounds and the head shape alone) may split the keys
+ * of each item over several workgroups; the workspace then also has room for their partial results, float32
+ * [splits][total_q][Hq][head_dim] and [splits][Hq][total_q], which a second kernel merges into out and lse.  (`splits` is
+ * an upper bound: a call uses as many as pay, often none.)
  * is_bwd = 0 for mtfm_hta_fwd, 1 for mtfm_hta_bwd.  Returns (size_t)-1 for invalid arguments.
  * The workspace must be 256-byte aligned; its contents are undefined before and after a call and it
  * may be reused by the next call on the same stream.  Two calls that run at the same time (on
@@ -111,11 +112,11 @@ MTFM_HTA_API int mtfm_hta_fwd(const void* q, const void* k, const void* v, void*
  * mtfm_hta_fwd for callers that cannot allocate device memory or hand over a workspace: code running under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and kernels as mtfm_hta_fwd
  * without `workspace` / `workspace_bytes`: what that call keeps in the caller's workspace (work counters, user
- * schedule, the partial results of a forward pass that splits its keys) lives in a buffer of
+ * schedule, room for the partial results of a forward pass that splits its keys) lives in a buffer of
  * MTFM_HTA_STATIC_SCRATCH_BYTES built into the library, one copy in the memory of each GPU the library has run on,
  * held until the process ends.  The call allocates and frees nothing, on the host or on the device.
  * A call that needs more scratch memory than that (mtfm_hta_workspace_bytes(..., is_bwd = 0, ...) says how much; only
- * a forward pass that splits its keys over many partial results can, e.g. several requests with hundreds of
+ * a forward pass that may split its keys over many partial results can, e.g. several requests with hundreds of
  * candidates at head_dim 128) returns MTFM_HTA_ERR_WORKSPACE and enqueues nothing; use mtfm_hta_fwd then.
  * All calls on one GPU share that GPU's buffer: calls that may overlap in time (different streams, different threads)
  * race and must be serialised by the caller, or use mtfm_hta_fwd with a workspace each.  Consecutive calls on one

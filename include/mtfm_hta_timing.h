@@ -24,9 +24,12 @@ extern "C" {
  */
 enum { MTFM_HTA_KERNEL_FWD = 0,      /* forward attention kernel */
        MTFM_HTA_KERNEL_BWD_SELF = 1, /* dk/dv of the target tokens' own keys: no launch of its own any more (its blocks
-                                        ride at the end of the BWD_DQ grid), never recorded */
-       MTFM_HTA_KERNEL_BWD_DQ = 2,   /* dq (row-stationary pass; the whole backward of the fp32 path) */
-       MTFM_HTA_KERNEL_BWD_DKDV = 3, /* dk, dv of the history keys (key-stationary pass) */
+                                        ride at the end of another grid), never recorded */
+       MTFM_HTA_KERNEL_BWD_DQ = 2,   /* dq and the own keys (row-stationary pass; the whole backward of the fp32 path).  In a
+                                        call of little work only the row statistics: such a call forms dq, dk and dv in one
+                                        launch, which is the next kind */
+       MTFM_HTA_KERNEL_BWD_DKDV = 3, /* dk, dv of the history and real-time keys (key-stationary pass, one launch or two); of
+                                        a call of little work everything but the row statistics */
        MTFM_HTA_N_KERNELS = 7        /* kinds 4..6 belong to mtfm_gln.h */ };
 MTFM_HTA_API int mtfm_hta_timing_enable(int slots);
 MTFM_HTA_API int mtfm_hta_timing_read(int kernel, float* ms, int capacity);

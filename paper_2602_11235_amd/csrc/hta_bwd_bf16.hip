@@ -33,7 +33,7 @@ hipError_t launch_bwd_bf16(const Params& p, hipStream_t s) {
     else switch (p.d) {
         case 32: e = launch_dkdv<32, 4>(p, s); break;
         case 64: e = launch_dkdv<64, 4>(p, s); break;
-        default:  // 128: the softmax kernel is built in a unit of its own
+        default:  // 128: the softmax kernels are built in a unit of their own
             e = p.pointwise ? launch_dkdv_as<128, 4, false, true>(p, s) : launch_bwd_dkdv128_bf16(p, s);
             break;
     }

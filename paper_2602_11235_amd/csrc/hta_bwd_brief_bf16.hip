@@ -303,8 +303,8 @@ hipError_t launch_dkdv_ways(const Params& p, hipStream_t s) {
 }  // namespace
 
 // Both launches pay where the dQ part is small too: its workgroups of 32 rows walk their keys in a quarter of the time, at
-// twice the traffic (19 users of 405..1623 keys x 40 candidates: 66 -> 49 us per step against the ordinary dQ pass and this
-// dK/dV pass; 53 users of 100 keys, full layer: 45 -> 48).
+// twice the traffic (19 users of 405..1623 keys x 40 candidates: 66 -> 41 us per step against the ordinary dQ pass and this
+// dK/dV pass; 53 users of 100 keys, full layer: 54 either way).
 bool bwd_is_brief(const Params& p) {
     if (p.total_q == 0) return false;
     const int r = p.Hq / p.Hkv;
@@ -324,7 +324,7 @@ hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s) {
 // of waves that share a key block's rows here.  From fits of measured times (us): a workgroup costs `fixed` plus `unit`
 // per 32-row unit of a wave, the chip holds `slots` of them, and the longest one bounds the call from below.  The ordinary
 // pass shares its staging among 128 keys and wins in the long run; it loses where a user's rows walked one after the
-// other take longer than the rest of the call.  (8/2 heads: 64 users of 128..512 keys 77 -> 60 us, 19 of 374..1498 200 -> 134,
+// other take longer than the rest of the call.  (8/2 heads: 64 users of 128..512 keys 82 -> 69 us, 19 of 374..1498 200 -> 134,
 // 151 x 16..64 candidates 82 -> 41, 256 of 512..1024 ordinary 750 against 925; 512 x 128 candidates on 2048 keys resident 1.22 ms
 // against 1.70; 512 x 128 on 512..2048 keys, 16/4 heads, whole backward 1.47 ms against 1.79, 64 x 8..32 on 512 keys the other way
 // round, 63 us against 42.)

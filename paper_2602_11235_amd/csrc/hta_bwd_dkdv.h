@@ -1,6 +1,6 @@
 // The dK/dV pass of the bf16 backward (gfx950): kernel templates and their launchers, included by the translation
-// units that instantiate them (hta_bwd_bf16.hip: all but one; hta_bwd_dkdv128_bf16.hip: the head_dim 128 softmax kernel,
-// compiled with another instruction scheduling strategy, see build.py).
+// units that instantiate them (hta_bwd_bf16.hip: all but those of head_dim 128 with softmax weights, which
+// hta_bwd_dkdv128_bf16.hip compiles with another instruction scheduling strategy, see build.py).
 //
 //   bwd_dkdv: key-stationary: a wave owns 32 history keys (K, V fragments and the dK, dV accumulators
 //      stay in registers for the whole kernel), the workgroup streams (head, 32-row block) tiles of Q
@@ -34,8 +34,8 @@ struct DkdvSmem {
 // row sees: no mask.  The blocks behind them (TAILS: the last blocks of the grid, behind the persistent ones; at
 // d = 128, where both in one kernel do not fit the registers, a launch of their own) are
 // brief_dkdv's, whose masked stream skips the rows that see none of their keys; they fill the units that run out of
-// history.  (256 users of 512..1024 + 32..128 + 64 tokens: 940 us, against 1019 in the same session with one masked instruction
-// stream for all keys and the rows' limits staged next to every unit.)
+// history.  (256 users of 512..1024 + 32..128 + 64 tokens: 899 us, against 954 with one masked instruction stream for all
+// keys and the rows' limits staged next to every unit.)
 // PW: the pointwise reading of phi2 -- P = silu(scale S), dS = dP o silu'(scale S); the staged row statistics are
 // zeros for rows that exist (the sentinel for rows that do not still removes them), norm is applied at the store.
 template <int D, int NW, bool TAILS, bool PW = false>
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 // takes a whole (user, kv head): it stages ALL (head, 32-row block) units of Q and dO in LDS once (at most MAX_UNITS of
 // them, which is what the host checks), and then its waves walk the keys, 32 per wave and pass, each on its own: K/V
 // fragments from global memory, every unit from LDS, dK/dV stored -- no barrier, no copy and no counted wait inside the
-// key loop, and waves that drift apart.  Twelve waves, three per SIMD, one unit in flight per wave (168 registers):
+// key loop, and waves that drift apart.  Twelve waves, three per SIMD, one unit in flight per wave (168 registers, 18 more in scratch):
 // measured against eight waves with two units interleaved per wave, as bwd_dkdv_kernel does it, the third wave hides
 // more than the interleaving (dK/dV of a 512 x 2048 x 128 target layer 1.21 against 1.30 ms; streaming kernel 1.33).
 // Softmax weights without real-time tokens only (the callers that need the other readings take the streaming kernel).

@@ -104,7 +104,7 @@ bool dkdv_is_resident(const Params& p);                         // the ordinary 
 hipError_t launch_dkdv_brief_bf16(const Params& p, hipStream_t s);
 // the two launches of launch_bwd_bf16 that live in translation units of their own (other compiler options)
 hipError_t launch_bwd_dq_bf16(const Params& p, hipStream_t s);       // dQ and the self-key blocks, every head_dim
-hipError_t launch_bwd_dkdv128_bf16(const Params& p, hipStream_t s);  // dK/dV at head_dim 128, softmax weights, no real-time tokens
+hipError_t launch_bwd_dkdv128_bf16(const Params& p, hipStream_t s);  // dK/dV at head_dim 128, softmax weights
 bool bf16_supported(int32_t d, int32_t Hq, int32_t Hkv);
 // bf16 rows of 16 features <-> rows of 32 with a zero upper half ([n_rows][16] and [n_rows][32], 16-byte aligned): how
 // head_dim 16 rides the 32-wide matrix tiles

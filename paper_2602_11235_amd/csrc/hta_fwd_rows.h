@@ -10,7 +10,7 @@ namespace hta {
 constexpr float RESCALE_SLACK = 8.f;  // log2 units a row's logits may exceed its softmax reference before a rescale
 
 // What a wave of the row-stationary forward pass keeps in registers -- the Q fragments of its RB blocks of 32 query
-// rows (one head), the running softmax state and the O^T accumulators -- and the steps on it.
+// rows (packed (row, head) pairs), the running softmax state and the O^T accumulators -- and the steps on it.
 //
 // RT: the users carry real-time tokens (mask rule 2).  Their keys follow the history keys in the K/V rows and run through
 // the same tile loop; a sub-tile that reaches past the history is masked per query row with the row's limit

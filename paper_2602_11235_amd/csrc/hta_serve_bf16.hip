@@ -14,8 +14,8 @@
 // What bounds it, at head_dim 64 and one workgroup of 32 rows per compute unit: 2.05 us per 1000 keys, where the copies
 // alone take 1.66 (64 bytes per clock and unit) and the arithmetic alone 2.0, and 6 us of launch, first loads and merge.  K
 // fragments straight to registers (no LDS write and read): 3.6 us per 1000 keys, 32-byte pieces of a row per lane pair.
-// Four waves with the whole register file each: 5 to 6 us.  One 2048 + 128 token request at 8/2 heads: 17.8 -> 10.7 us
-// per call; 8 requests of 512..4096: 22.5 -> 15; 4 of 8192 at head_dim 128: 39 -> 34.
+// Four waves with the whole register file each: 5 to 6 us.  One 2048 + 128 token request at 8/2 heads: 18.0 -> 10.2 us
+// per call; 8 requests of 512..4096: 22.1 -> 16.3, with real-time tokens 25.0 -> 16.3; 4 of 8192 at head_dim 128: 37.6 -> 32.8.
 #include "../../include/mtfm_hta.h"
 #include "../../include/mtfm_hta_timing.h"
 #include "hta_common.h"

@@ -374,13 +374,13 @@ static double serve_us(const Params& p, Shape shape) {
 }
 
 // This kernel or the ordinary one, which shares each K/V tile among 128 or 256 rows and keeps two workgroups on a unit.  Once its
-// workgroups nearly fill the chip, the ordinary one (at head_dim 64, 224 to 330 of them: on average 1.3 times as fast; 128:
-// 1.5; 32, 448 to 600: 2.1).  Below that, keys are split over workgroups when the time this takes off the longest item is worth
-// the merge: per key and workgroup 2.05 ns at head_dim 64, 4.4 at 128; merge 4.2 us, partial results at 3 TB/s.  Where it is not, by
-// the estimates above: 64-row workgroups that come in rounds lose to 256-row ones that do not.  (8/2 heads of 64: 27 users x
-// 256 candidates on 512 keys 38 us here against 20 there, on 2048 64 / 45; 13 users on 2048 34 / 43; 40 users x 128 candidates,
-// 16/2 heads of 128, 64..512 keys 60 / 31; 110 x 256, 4/2 heads of 32, 512 keys 63 / 25.  Of the 2700 calls 622
-// had a tenth or more to gain on the other side when only full chips went there, 47 have now.)
+// workgroups nearly fill the chip, the ordinary one (at head_dim 64, 224 to 330 of them: on average 1.2 times as fast, though
+// not on long histories of unlike lengths; 128: 1.3; 32, 448 to 600: 1.5).  Below that, keys are split over workgroups when the time
+// this takes off the longest item is worth the merge: per key and workgroup 2.05 ns at head_dim 64, 4.4 at 128; merge 4.2 us,
+// partial results at 3 TB/s.  Where it is not, by the estimates above: 64-row workgroups that come in rounds lose to 256-row ones
+// that do not.  (8/2 heads of 64: 27 users x 256 candidates on 512 keys 38 us here against 20 there, on 2048 64 / 45; 13 users on
+// 2048 34 / 43; 40 users x 128 candidates, 16/2 heads of 128, 64..512 keys 60 / 31; 110 x 256, 4/2 heads of 32, 512 keys 63 / 25.
+// Of the 2700 calls 622 had a tenth or more to gain on the other side when only full chips went there, 47 have now.)
 int serve_splits(const Params& p, int room) {
     const int64_t ordinary = live_tiles(p, fwd_workgroup_rows(p));
     if (ordinary >= (p.d == 32 ? 448 : 224)) return 0;

@@ -29,7 +29,8 @@ enum { MTFM_HTA_KERNEL_FWD = 0,      /* forward attention kernel */
                                         call of little work only the row statistics: such a call forms dq, dk and dv in one
                                         launch, which is the next kind */
        MTFM_HTA_KERNEL_BWD_DKDV = 3, /* dk, dv of the history and real-time keys (key-stationary pass, one launch or two); of
-                                        a call of little work everything but the row statistics */
+                                        a call of little work everything but the row statistics, of a call whose users have
+                                        few query rows the whole backward pass where one kernel forms it */
        MTFM_HTA_N_KERNELS = 7        /* kinds 4..6 belong to mtfm_gln.h */ };
 MTFM_HTA_API int mtfm_hta_timing_enable(int slots);
 MTFM_HTA_API int mtfm_hta_timing_read(int kernel, float* ms, int capacity);

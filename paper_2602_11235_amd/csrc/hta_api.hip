@@ -421,6 +421,7 @@ static int bwd_impl(const void* dout, const void* q, const void* k, const void* 
         p.neg_lse_s = (float*)(base + w.lse_off);
     }
     if (has_rt) p.lim = (int32_t*)((char*)workspace + w.lim_off);
+    const bool onepass = dtype == MTFM_HTA_BF16 && hta::bwd_is_onepass(p);
     const bool brief = dtype == MTFM_HTA_BF16 && hta::bwd_is_brief(p);  // (forms the limits itself, and needs no schedule)
     if (dtype == MTFM_HTA_FP32 ? has_rt : p.rt_len && !brief) e = hta::launch_rt_limits(p, s);
     if (e == hipSuccess && dtype == MTFM_HTA_BF16 && !brief) {
@@ -430,7 +431,8 @@ static int bwd_impl(const void* dout, const void* q, const void* k, const void* 
         p.queue = hta::schedule_queue(region, 0);  // the launchers add the kernel kind
     }
     if (e == hipSuccess)
-        e = dtype == MTFM_HTA_FP32 ? hta::launch_bwd_fp32(p, s) : brief ? hta::launch_bwd_brief_bf16(p, s) : hta::launch_bwd_bf16(p, s);
+        e = dtype == MTFM_HTA_FP32 ? hta::launch_bwd_fp32(p, s) : onepass ? hta::launch_bwd_onepass_bf16(p, s)
+            : brief ? hta::launch_bwd_brief_bf16(p, s) : hta::launch_bwd_bf16(p, s);
     if (e == hipSuccess && padded) {
         e = hta::launch_narrow16(dq, caller_dq, total_q * Hq, s);
         if (e == hipSuccess) e = hta::launch_narrow16(dk, caller_dk, total_kv * Hkv, s);

@@ -1,0 +1,620 @@
+// bf16 backward of Hybrid Target Attention for gfx950 in one pass (head_dim 64, users of at most 512 packed (row, query head) pairs
+// per kv head: the candidates of a target-only layer): S, dP and the weights of every (row, key) pair are formed once and feed dQ, dK
+// and dV -- five matrix products per pair, where a dQ pass and a dK/dV pass of their own (hta_bwd_bf16.hip) need seven and form every
+// weight twice.
+//
+// A workgroup takes a (user, kv head) whole: no gradient ever crosses a workgroup, so there are no atomics and every sum has a fixed
+// order.  Its waves hold the user's pairs, two units of 32 each, and walk the keys in blocks of 32:
+//   phase 1  a wave forms S^T = K Q^T, dP^T = V dO^T, P and dS of its units (row on the lane, as in the dQ pass), adds
+//            dQ^T += K^T dS^T straight from the registers and leaves P and dS as bf16 in LDS, [row][key];
+//   phase 2  dK^T[d][key] = Q^T dS and dV^T = dO^T P contract over the rows: P and dS come back through the transposed LDS read
+//            with the key on the lane, against Q^T and dO^T, which never change: wave t of four holds one 32-wide half of the features
+//            of dO (t = 0, 1) or Q (t = 2, 3), of the first units in registers, of the second ones it reads them from LDS.
+// One barrier behind each phase.  What fits decides the shape: dQ, Q, dO and the operands of phase 2 of 512 pairs are 384 KB, so the
+// second units' Q and dO rest in LDS, where both phases read them (all in registers left none to fetch operands ahead with: 3.5 ms
+// on 512 users x 2048 keys x 128 candidates, 16/4 heads, against 1.6).  Up to 256 pairs a workgroup is one group of four waves
+// and a compute unit holds two, whose barriers do not meet; above, two groups share the K/V tiles and exchange their sums of phase 2
+// (16 KB per block) so that each finishes half of it.  (Two groups half a block apart, one's matrix products next to the other's
+// exponentials, took as long as in step; so did S of the next block formed in phase 2.)
+// Whole backward, two passes -> this one: that workload 2.09 -> 1.62 ms; 600 users x 1000 keys x 60, 8/2 heads 428 -> 312 us.  Bound by
+// the sum of matrix and vector work: a SIMD is busy with 2560 cycles of products and 2500 of vector instructions per block of 16
+// units, of about 5200.  (Users of more pairs, taken 512 at a time with float32 dK, dV resting in memory in between, were no faster
+// than two passes: 1.52 against 1.39 ms on a full layer of 256 users x 512..1024 keys.)
+// dk/dv of a target token's own key come from the lanes that hold its rows, in the prologue.
+#include "../../include/mtfm_hta.h"
+#include "../../include/mtfm_hta_timing.h"
+#include "hta_common.h"
+#include "hta_mfma.h"
+#include "hta_rows.h"
+#include "hta_tiles.h"
+
+#include <algorithm>
+#include <cmath>
+
+namespace hta {
+namespace {
+
+constexpr int OP_D = 64;                // head_dim
+constexpr int OP_TILE = 32 * OP_D * 2;  // bytes of a 32-row tile
+constexpr int OP_UNIT = 32 * 32 * 2;    // bytes of a unit's P (or dS) block, [row][key] bf16
+constexpr int OP_SUMS = 4 * 4096;       // bytes of a block's dV, dK (two halves of the features each) in float32
+// A workgroup of NG groups of four waves: packed pairs of a chunk, byte offsets in LDS.  P and dS of the units; Q and dO of the second
+// units; sums that the groups exchange; K/V.  (Q and dO of the first units are where P and dS go while phase 2's operands are
+// taken from them.)
+template <int NG>
+struct OnePass {
+    static constexpr int NW = 4 * NG, LANES = 256 * NG;
+    static constexpr int P = 0, DS = 8 * NG * OP_UNIT, ROWS0 = 0, ROWS1 = 16 * NG * OP_UNIT, DO = NW * OP_TILE;  // (DO: dO behind Q)
+    static constexpr int X = ROWS1 + 2 * NW * OP_TILE, KV = X + (NG > 1 ? OP_SUMS : 0), STAGE = 2 * OP_TILE;
+    static constexpr int BYTES = KV + 2 * STAGE;
+    static_assert(BYTES * (NG > 1 ? 1 : 2) == 160 * 1024, "LDS");
+};
+
+// x summed over aligned groups of W lanes, by exchanges inside the rows of 16 lanes
+template <int CTRL>
+__device__ inline float add_dpp(float x) {
+#pragma clang fp contract(off)  // (a product in x would go into a multiply-add, and the exchange into an instruction of its own)
+    return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+// Accumulator registers 8 k .. of a tile whose rows are features: a lane of half hf holds features 4 hf .. + 3 (lo) and 8 + 4 hf .. (hi)
+// of 16.  Rounded and exchanged between the halves, it has features 8 hf .. + 7: one store of 16 bytes.
+__device__ inline bf16x8 rows_of_16(floatx4 lo, floatx4 hi, float f) {
+    typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+    typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+    bf16x4 l4, h4;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        l4[j] = (__bf16)(lo[j] * f);
+        h4[j] = (__bf16)(hi[j] * f);
+    }
+    const uintx2 x = __builtin_bit_cast(uintx2, l4), y = __builtin_bit_cast(uintx2, h4);
+    const auto e0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
+    const auto e1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+    const uintx4 o = {(unsigned)e0[0], (unsigned)e1[0], (unsigned)e0[1], (unsigned)e1[1]};
+    return __builtin_bit_cast(bf16x8, o);
+}
+constexpr int OP_MAX_HEADS = 8;
+template <int W>
+__device__ inline float sum_heads(float x) {
+    static_assert(W <= OP_MAX_HEADS, "a mirrored row would follow");
+    if (W > 1) x = add_dpp<0xB1>(x);    // quad_perm [1, 0, 3, 2]
+    if (W > 2) x = add_dpp<0x4E>(x);    // quad_perm [2, 3, 0, 1]
+    if (W > 4) x = add_dpp<0x141>(x);   // row_half_mirror: the quads of an 8-group hold equal sums by now
+    return x;
+}
+
+template <int NG, bool RT, bool PW>
+__global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowMap map, unsigned per_xcd) {
+    using OP = OnePass<NG>;
+    constexpr int D = OP_D, NKS = D / 16, NDB = D / 32, NW = OP::NW;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[OP::BYTES];
+    int* const s_item = (int*)(smem + OP::KV);  // (between two items nothing rests there)
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = NG > 1 ? wave >> 2 : 0, t = wave & 3;
+    const int r = p.Hq / p.Hkv;
+    const float c2 = p.scale * LOG2E, neg_c2 = -c2;
+    const __bf16* const kg = (const __bf16*)p.k;
+    const __bf16* const vg = (const __bf16*)p.v;
+    const uint32_t lds0 = lds_address(smem);
+
+    auto at = [&](int byte) __attribute__((always_inline)) { return (__bf16*)(smem + byte); };
+    // a: address of the fragment's first piece.  (Offsets of whole KB leave the low bits alone, so the XORs of the swizzles apply
+    // to finished addresses.)
+    auto tr64 = [&](int a, int plus) __attribute__((always_inline)) { return lds_read_tr_pair(at(a + plus), at((a ^ 32) + plus + 1024)); };
+    // An address formed here is formed anew in every block: kept from the loop's start, the XORed ones would take up the
+    // registers that the loop is short of.
+    auto fresh = [](int x) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(x));
+        return x;
+    };
+    // (Lane arithmetic is done where it is needed, for the same reason: the compiler would keep all of it, from the start of the kernel.)
+    auto lane_anew = []() __attribute__((always_inline)) {  // the lane's index, likewise
+        int x;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+        return x;
+    };
+
+    auto process = [&](unsigned id) {
+        const WorkItem w = decode_work(id, p.batch * p.Hkv, p.Hkv, 1);
+        if (!w.valid) return;
+        // (uniform values, which the compiler cannot tell of loads in a loop that also stores)
+        auto uniform = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
+        auto uniform64 = [&](int64_t x) __attribute__((always_inline)) {
+            return (int64_t)((uint64_t)(uint32_t)uniform((int)(x >> 32)) << 32 | (uint32_t)uniform((int)x));
+        };
+        const int b = uniform(scheduled_user(p, w.user_slot)), g = w.y;
+        const int L = uniform(p.hist_len[b]), T = uniform(p.n_targets[b]);
+        const int LK = L + (RT ? uniform(p.rt_len[b]) : 0);  // keys of the block loop: history, then real-time
+        const int n_rows = p.layer == 0 ? LK + T : T, tok_shift = p.layer == 0 ? 0 : LK;
+        const int64_t q_base = uniform(p.q_off[b]), kv_base = uniform(p.kv_off[b]);
+        const int n_blocks = (LK + 31) / 32;
+        if (n_rows == 0) {  // nobody attends to these keys: dk = dv = 0
+            const bf16x8 zero = {};
+            for (int i = tid; i < LK * (D / 8); i += NW * 64) {
+                const int64_t off = ((kv_base + i / (D / 8)) * p.Hkv + g) * D + i % (D / 8) * 8;
+                *(bf16x8*)((__bf16*)p.dk + off) = zero;
+                *(bf16x8*)((__bf16*)p.dv + off) = zero;
+            }
+            return;
+        }
+        // K/V copies: wave t of a group brings rows 8 t .. of a tile, of K group 0, of V the last one
+        auto issue_kv = [&](int i) __attribute__((always_inline)) {
+            const uint32_t dst = lds0 + OP::KV + (uint32_t)(i & 1) * OP::STAGE + (uint32_t)t * 1024u;
+            const int64_t base = uniform64(((kv_base + 32 * (int64_t)i) * p.Hkv + g) * D);
+            const int x = lane_anew(), crow = 8 * t + (x >> 3);
+            const int row = min(crow, LK - 1 - 32 * i);  // keys past the end repeat the last one: finite data whose weights are set to zero
+            const uint32_t voff = (uint32_t)((row * p.Hkv * D + (((x & 7) ^ swizzle<64>(crow)) << 3)) * 2);
+            if (group == 0) copy16_global_to_lds_at(kg + base, voff, dst);
+            if (group == NG - 1) copy16_global_to_lds_at(vg + base, voff, dst + OP_TILE);
+        };
+
+        const int lane = lane_anew(), l32 = lane & 31, hf = lane >> 5;
+        // per-lane byte offsets, from which the others follow by XOR of constants (swizzles: hta_mfma.h)
+        const int trow = 4 * hf + ((lane & 15) >> 2), tchunk = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+        const int nat0 = l32 * 128 + ((hf ^ swizzle<64>(l32)) << 4);                              // row l32, chunk hf       of a 64-wide tile
+        const int tr0 = trow * 128 + ((tchunk ^ swizzle<64>(trow)) << 4) + 8 * (lane & 1);        // transposed fragment     of a 64-wide tile
+        // P, dS: row l32, keys 4 hf .. of chunk 0.  The 8-byte halves of a chunk are exchanged in every second pair of rows: a store
+        // takes 16 lanes at a time and then finds each of 16 rows on banks of its own.
+        auto pw0 = [&]() __attribute__((always_inline)) {
+            const int ln = lane_anew(), row = ln & 31;
+            return row * 64 + (swizzle<32>(row) << 4) + 8 * ((ln >> 5) ^ ((row >> 1) & 1));
+        };
+        const int pr0 = trow * 64 + ((tchunk ^ swizzle<32>(trow)) << 4) + 8 * ((lane & 1) ^ ((trow >> 1) & 1));
+        const PackedRows pr(map, 0, 0, n_rows, g, r);  // (rows beyond the caller's bound on them would be left out)
+        const int n_units = (min(n_rows, map.rows) * map.heads + 31) / 32;
+        if (n_blocks > 0) issue_kv(0);
+        // ---- the rows of this wave: units wave and wave + NW; all that the two need is requested before any of it is used
+        bf16x8 q0[NKS], do0[NKS];  // of the first unit; the second one's stay in LDS
+        floatx16 dQ[2][NDB];       // dQ^T: [d (registers)][row (lanes)]
+        float lse2[2], dl[2];
+        int lim[2], own[2];        // RT: leading keys that the lane's row sees, and its own key among the real-time ones
+        {
+            const bf16x8 zero = {};
+            bf16x8 ox[2][NKS], kk[2][NKS], vv[2][NKS];
+            bool targets[2];     // uniform: are there target rows in the unit
+            float fk[2], fv[2];  // weights of a target row in the dk, dv of its own key
+            // Q and dO straight to LDS, where the wave finds its own rows (and the transposed operands of phase 2 come from):
+            // copy j brings rows 8 j .. of a tile.  No branches here: a lane or unit that stands for no row repeats the last one.
+#pragma unroll
+            for (int s = 0; s < 2; s++) {
+                const int pos = (s == 0 ? OP::ROWS0 : OP::ROWS1) + wave * OP_TILE;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int crow = 8 * j + (lane >> 3);
+                    const PackedRows::Row x = pr.at((NW * s + wave) * 32 + crow);
+                    const int64_t off = ((q_base + x.row) * p.Hq + x.h) * D + (((lane & 7) ^ swizzle<64>(crow)) << 3);
+                    copy16_global_to_lds_at((const __bf16*)p.q + off, lds0 + (uint32_t)(pos + j * 1024));
+                    copy16_global_to_lds_at((const __bf16*)p.dout + off, lds0 + (uint32_t)(pos + OP::DO + j * 1024));
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < 2; s++) {
+                const PackedRows::Row x = pr.at((NW * s + wave) * 32 + l32);
+                const int64_t off = ((q_base + x.row) * p.Hq + x.h) * D + 8 * hf;
+                const int64_t koff = ((kv_base + tok_shift + x.row) * p.Hkv + g) * D + 8 * hf;
+#pragma unroll
+                for (int ks = 0; ks < NKS; ks++) {
+                    if constexpr (!PW) ox[s][ks] = *(const bf16x8*)((const __bf16*)p.out + off + ks * 16);
+                    kk[s][ks] = *(const bf16x8*)(kg + koff + ks * 16);
+                    vv[s][ks] = *(const bf16x8*)(vg + koff + ks * 16);
+                }
+                lse2[s] = PW ? 0.f : p.lse[(int64_t)x.h * p.total_q + q_base + x.row];
+                lim[s] = RT ? p.lim[q_base + x.row] : L;
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < 2; s++) {
+                const PackedRows::Row x = pr.at((NW * s + wave) * 32 + l32);
+                const int pos = (s == 0 ? OP::ROWS0 : OP::ROWS1) + wave * OP_TILE;
+                // a lane that stands for no row adds nothing anywhere: its Q and dO are zeros, and so are its weights
+                const int tok = tok_shift + x.row;
+                const bool has_own = tok >= L && x.live;  // a target or real-time row sees its own key, where its dQ starts
+                bf16x8 qx[NKS], dox[NKS];
+                float part = 0.f, sp = 0.f, dpp = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < NKS; ks++) {
+                    qx[ks] = *(const bf16x8*)at(pos + (nat0 ^ (ks << 5)));
+                    dox[ks] = *(const bf16x8*)at(pos + OP::DO + (nat0 ^ (ks << 5)));
+                    qx[ks] = x.live ? qx[ks] : zero;
+                    dox[ks] = x.live ? dox[ks] : zero;
+                    kk[s][ks] = has_own ? kk[s][ks] : zero;
+                    vv[s][ks] = has_own ? vv[s][ks] : zero;
+                    if (s == 0) q0[ks] = qx[ks], do0[ks] = dox[ks];
+                    if constexpr (!PW) part = dot_bf16x8(part, dox[ks], x.live ? ox[s][ks] : zero);
+                    sp = dot_bf16x8(sp, qx[ks], kk[s][ks]);
+                    dpp = dot_bf16x8(dpp, dox[ks], vv[s][ks]);
+                    *(bf16x8*)at(pos + (nat0 ^ (ks << 5))) = qx[ks];
+                    *(bf16x8*)at(pos + OP::DO + (nat0 ^ (ks << 5))) = dox[ks];
+                }
+                sp += other_half(sp);
+                dpp += other_half(dpp);
+                lse2[s] = x.live ? lse2[s] * LOG2E : INFINITY;
+                dl[s] = PW ? 0.f : -(part + other_half(part));
+                own[s] = RT && has_own && tok < LK ? tok : -1;
+                float pw, ds;
+                if constexpr (PW) {
+                    const float sg = pw_sigmoid(sp, neg_c2);
+                    pw = pw_silu(sp * p.scale, sg);
+                    ds = dpp * pw_silu_prime_of(pw, sg);
+                } else {
+                    pw = fast_exp2(fmaf(sp, c2, -lse2[s]));
+                    ds = pw * (dpp + dl[s]);
+                }
+                if (!has_own) ds = pw = 0.f;
+                // K of the key with the features where dQ has them: registers 4 v4 .. hold 8 v4 + 4 hf .. of 32
+                static_for<0, NKS>([&](auto Ks) {
+                    constexpr int ks = decltype(Ks)::value;
+                    typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+                    const uintx4 k4 = __builtin_bit_cast(uintx4, kk[s][ks]);
+                    const auto e0 = __builtin_amdgcn_permlane32_swap(k4[0], k4[2], false, false);
+                    const auto e1 = __builtin_amdgcn_permlane32_swap(k4[1], k4[3], false, false);
+                    const uintx4 d4 = {(unsigned)e0[0], (unsigned)e1[0], (unsigned)e0[1], (unsigned)e1[1]};
+                    const bf16x8 kd = __builtin_bit_cast(bf16x8, d4);
+#pragma unroll
+                    for (int j = 0; j < 8; j++) dQ[s][ks / 2][8 * (ks % 2) + j] = ds * (float)kd[j];
+                });
+                const bool target = has_own && tok >= LK;
+                fk[s] = !target ? 0.f : PW ? ds * p.scale * p.norm : ds * p.scale;
+                fv[s] = !target ? 0.f : PW ? pw * p.norm : pw;
+                targets[s] = __builtin_amdgcn_ballot_w64(target) != 0;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // A target's key is seen by nobody else: its dk, dv are sums over the heads of this row alone.
+            static_for<0, 2>([&](auto S) {
+                constexpr int s = decltype(S)::value;
+                if (!targets[s]) return;
+                const int pos = (s == 0 ? OP::ROWS0 : OP::ROWS1) + wave * OP_TILE;
+                const PackedRows::Row x = pr.at((NW * s + wave) * 32 + l32);
+                const int tok = tok_shift + x.row;
+                const bool stores = x.live && tok >= LK && (l32 & (map.heads - 1)) == 0;
+                const int64_t koff = ((kv_base + tok) * p.Hkv + g) * D + 8 * hf;
+                auto self = [&](auto W) __attribute__((always_inline)) {
+#pragma unroll 1
+                    for (int ks = 0; ks < NKS; ks++) {
+                        const bf16x8 q8 = *(const bf16x8*)at(pos + (nat0 ^ (ks << 5))), do8 = *(const bf16x8*)at(pos + OP::DO + (nat0 ^ (ks << 5)));
+                        bf16x8 dk8, dv8;
+#pragma unroll
+                        for (int j = 0; j < 8; j++) {
+                            dk8[j] = (__bf16)sum_heads<decltype(W)::value>(fk[s] * (float)q8[j]);
+                            dv8[j] = (__bf16)sum_heads<decltype(W)::value>(fv[s] * (float)do8[j]);
+                        }
+                        if (stores) {
+                            *(bf16x8*)((__bf16*)p.dk + koff + ks * 16) = dk8;
+                            *(bf16x8*)((__bf16*)p.dv + koff + ks * 16) = dv8;
+                        }
+                    }
+                };
+                if (map.heads == 1) self(std::integral_constant<int, 1>{});
+                else if (map.heads == 2) self(std::integral_constant<int, 2>{});
+                else if (map.heads == 4) self(std::integral_constant<int, 4>{});
+                else self(std::integral_constant<int, 8>{});
+            });
+        }
+        __syncthreads();
+        // Q^T or dO^T of the first units of the group, features 32 (t % 2) ..: the constant operand of phase 2
+        const int rows_t = (t < 2 ? OP::DO : 0) + group * 4 * OP_TILE + (tr0 ^ ((t & 1) << 6));
+        bf16x8 ct[4][2];
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int s2 = 0; s2 < 2; s2++) ct[j][s2] = tr64(OP::ROWS0 + rows_t, j * OP_TILE + s2 * 2048);
+        __syncthreads();
+        const int units[2] = {n_units - 4 * group, n_units - NW - 4 * group};  // of this group: how many first, second ones
+        // a unit that does not exist, next to some that do, is there with zero weights
+        static_for<0, 2>([&](auto S) {
+            constexpr int s = decltype(S)::value;
+            if (t >= units[s] && units[s] > 0) {
+                const bf16x8 zero = {};
+                const int pos = (group * 8 + 4 * s + t) * OP_UNIT + lane * 32;
+                *(bf16x8*)at(OP::P + pos) = zero;
+                *(bf16x8*)at(OP::P + pos + 16) = zero;
+                *(bf16x8*)at(OP::DS + pos) = zero;
+                *(bf16x8*)at(OP::DS + pos + 16) = zero;
+            }
+        });
+        wait_vmem_loads();
+        lds_barrier();
+
+        // What the groups made of a block's dV^T (t < 2) or dK^T: the other group's sums of this wave's part of the tile, and of
+        // earlier chunks, to its own; rows of dk, dv where they are final.
+        constexpr int NQ = 4 / NG;  // registers / 4 of the part: with two groups, half of the tile each
+        floatx4 mine[NQ];
+        auto finish = [&](int i) __attribute__((always_inline)) {
+            const int ln = lane_anew();
+            if constexpr (NG > 1) {
+#pragma unroll
+                for (int q = 0; q < NQ; q++) mine[q] += *(const floatx4*)at(OP::X + (wave ^ 4) * 2048 + q * 1024 + ln * 16);
+            }
+            const float f = t < 2 ? (PW ? p.norm : 1.f) : (PW ? p.scale * p.norm : p.scale);
+            const int key = ln & 31;
+            static_for<0, NQ / 2>([&](auto H) {
+                constexpr int h = decltype(H)::value;
+                const bf16x8 o8 = rows_of_16(mine[2 * h], mine[2 * h + 1], f);
+                if (32 * i + key < LK) {
+                    char* dst = (char*)(t < 2 ? p.dv : p.dk) + 2 * uniform64(((kv_base + 32 * (int64_t)i) * p.Hkv + g) * D + (t & 1) * 32 + group * 16);
+                    *(bf16x8*)(dst + 32 * h + (uint32_t)(key * p.Hkv * D * 2 + 16 * (ln >> 5))) = o8;
+                }
+            });
+        };
+        // At the start of block i: what block i - 1 still has to do, then block i + 1 is requested, to its stage.
+        auto start = [&](int i) __attribute__((always_inline)) {
+            if (NG > 1 && i > 0) finish(i - 1);
+            if (i + 1 < n_blocks) issue_kv(i + 1);
+        };
+        // units 0 .. N - 1 of this wave against a block (an, ak: its K/V)
+        auto phase1 = [&](auto N, int i, int an, int ak) __attribute__((always_inline)) {
+            constexpr int NU = decltype(N)::value;
+            const int k0 = 32 * i;
+            const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            const int ar = fresh(OP::ROWS1 + wave * OP_TILE + nat0), aw = fresh((group * 8 + t) * OP_UNIT + pw0());
+            floatx16 Sx[NU];  // S^T, as dP^T: [key (registers)][row (lanes)]
+            bf16x8 pb[2], dsb[2], kt[NDB][2];
+            typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+            auto weights = [&](auto S, const floatx16& dP) __attribute__((always_inline)) {
+                constexpr int s = decltype(S)::value;
+#pragma unroll
+                for (int v = 0; v < 16; v++) {
+                    if constexpr (PW) {
+                        const float sg = pw_sigmoid(Sx[s][v], neg_c2), pw = pw_silu(Sx[s][v] * p.scale, sg);
+                        pb[v / 8][v % 8] = (__bf16)pw;
+                        dsb[v / 8][v % 8] = (__bf16)(dP[v] * pw_silu_prime_of(pw, sg));
+                    } else {
+                        const float pw = fast_exp2(fmaf(Sx[s][v], c2, -lse2[s]));
+                        pb[v / 8][v % 8] = (__bf16)pw;
+                        dsb[v / 8][v % 8] = (__bf16)(pw * (dP[v] + dl[s]));
+                    }
+                }
+            };
+            // Register v of the lane holds key 8 (v / 4) + 4 hf + v % 4 of the block.  What a row does not see is cleared
+            // bit by bit from the rounded weights, whatever the product with a repeated or real-time key gave.
+            // (P and dS in LDS need it only for real-time keys: a key past the end is a column that is not stored.)
+            auto clear = [&](auto S, bool own_too, bf16x8 (&x)[2]) __attribute__((always_inline)) {
+                constexpr int s = decltype(S)::value;
+                const int hf4 = 4 * (lane_anew() >> 5);  // (anew, or the comparisons would be made in every block)
+                const int over = hf4 - ((RT ? lim[s] : LK) - k0), mine_k = own[s] - k0 - hf4;
+                static_for<0, 8>([&](auto V) {
+                    constexpr int v = 2 * decltype(V)::value, key = 8 * (v / 4) + v % 4;
+                    const unsigned keep = ((over < -key || (RT && own_too && mine_k == key)) ? 0xffffu : 0u) |
+                                          ((over < -key - 1 || (RT && own_too && mine_k == key + 1)) ? 0xffff0000u : 0u);
+                    uintx4 d = __builtin_bit_cast(uintx4, x[v / 8]);
+                    d[v % 8 / 2] &= keep;
+                    x[v / 8] = __builtin_bit_cast(bf16x8, d);
+                });
+            };
+            auto store = [&](auto S) __attribute__((always_inline)) {
+                constexpr int s = decltype(S)::value;
+                static_for<0, 4>([&](auto Q) {
+                    constexpr int q = decltype(Q)::value, o = 4 * (q & 1);
+                    *(bf16x4*)at((aw ^ (q << 4)) + OP::P + 4 * s * OP_UNIT) = __builtin_shufflevector(pb[q / 2], pb[q / 2], o, o + 1, o + 2, o + 3);
+                    *(bf16x4*)at((aw ^ (q << 4)) + OP::DS + 4 * s * OP_UNIT) = __builtin_shufflevector(dsb[q / 2], dsb[q / 2], o, o + 1, o + 2, o + 3);
+                });
+            };
+            // P and dS of the unit to LDS; then dsb is what dQ adds up (a real-time row's dQ started from its own key)
+            auto hand_over = [&](auto S) __attribute__((always_inline)) {
+                if constexpr (RT) {
+                    if (k0 + 32 > L) clear(S, true, pb), clear(S, true, dsb);
+                    store(S);
+                    if (k0 + 32 > L) clear(S, false, dsb);
+                } else {
+                    store(S);
+                    if (k0 + 32 > LK) clear(S, false, dsb);
+                }
+            };
+            // dQ^T[d][row] += sum_key K[key][d] dS^T[key][row]
+            auto add_dq = [&](auto S) __attribute__((always_inline)) {
+                constexpr int s = decltype(S)::value;
+#pragma unroll
+                for (int db = 0; db < NDB; db++)
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; s2++) dQ[s][db] = mfma32(kt[db][s2], dsb[s2], dQ[s][db]);
+            };
+            const std::integral_constant<int, 0> u0{};
+            const std::integral_constant<int, NU - 1> u1{};
+            // The order of what follows is the point: every read from LDS is issued a step ahead of its use, as many as
+            // there are registers for, and the products of one unit have the exponentials of the other behind them.
+            auto k_of = [&](int ks) __attribute__((always_inline)) { return *(const bf16x8*)at(an ^ (ks << 5)); };
+            auto v_of = [&](int ks) __attribute__((always_inline)) { return *(const bf16x8*)at((an ^ (ks << 5)) + OP_TILE); };
+            auto q1_of = [&](int ks) __attribute__((always_inline)) { return *(const bf16x8*)at(ar ^ (ks << 5)); };
+            auto do1_of = [&](int ks) __attribute__((always_inline)) { return *(const bf16x8*)at((ar ^ (ks << 5)) + OP::DO); };
+            bf16x8 kv[NKS], r1[NKS];
+#pragma unroll
+            for (int ks = 0; ks < NKS; ks++) {
+                kv[ks] = k_of(ks);
+                if constexpr (NU > 1) r1[ks] = q1_of(ks);
+            }
+            start(i);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < NKS; ks++) {
+                Sx[0] = mfma32(kv[ks], q0[ks], ks == 0 ? zero : Sx[0]);
+                if constexpr (NU > 1) Sx[1] = mfma32(kv[ks], r1[ks], ks == 0 ? zero : Sx[1]);
+                kv[ks] = v_of(ks);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            floatx16 dP;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ks++) dP = mfma32(kv[ks], do0[ks], ks == 0 ? zero : dP);
+            auto fetch_kt = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int db = 0; db < NDB; db++)
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; s2++) kt[db][s2] = tr64(ak ^ (db << 6), s2 * 2048);
+            };
+            if constexpr (NU > 1) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++) kv[ks] = v_of(ks), r1[ks] = do1_of(ks);
+                __builtin_amdgcn_sched_barrier(0);
+            } else {
+                fetch_kt();
+            }
+            weights(u0, dP);
+            hand_over(u0);
+            if constexpr (NU > 1) {
+#pragma unroll
+                for (int ks = 0; ks < NKS; ks++) {
+                    dP = mfma32(kv[ks % 2], r1[ks % 2], ks == 0 ? zero : dP);
+                    if (ks + 2 < NKS) kv[ks % 2] = v_of(ks + 2), r1[ks % 2] = do1_of(ks + 2);
+                }
+                fetch_kt();
+            }
+            add_dq(u0);
+            if constexpr (NU > 1) {
+                weights(u1, dP);
+                hand_over(u1);
+                add_dq(u1);
+            }
+        };
+        const floatx16 zeros = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        // ---- the blocks
+        for (int i = 0; i < n_blocks; i++) {
+            const int stage = OP::KV + (i & 1) * OP::STAGE;
+            const int an = fresh(stage + nat0), ak = fresh(stage + tr0);
+            if (t < units[1]) phase1(std::integral_constant<int, 2>{}, i, an, ak);
+            else if (t < units[0]) phase1(std::integral_constant<int, 1>{}, i, an, ak);
+            else start(i);
+            // dV^T (t < 2) or dK^T of the block, [d (registers)][key (lanes)]: the group's rows
+            const int ap = fresh((t < 2 ? OP::P : OP::DS) + group * 8 * OP_UNIT + pr0), at2 = fresh(OP::ROWS1 + rows_t);
+            lds_barrier();
+            floatx16 acc;
+            // step k of 16: rows 16 (k % 2) .. of unit k / 2 of the group.  Reads run AHEAD steps in front of the products.
+            constexpr int AHEAD = 4;
+            bf16x8 wt[AHEAD], c1[AHEAD];
+            auto fetch = [&](auto K) __attribute__((always_inline)) {
+                constexpr int k = decltype(K)::value, plus = (k / 2) * OP_UNIT + (k & 1) * 1024;
+                wt[k % AHEAD] = lds_read_tr_pair(at(ap + plus), at((ap ^ 32) + plus + 512));
+                if constexpr (k >= 8) c1[k % AHEAD] = tr64(at2, (k / 2 - 4) * OP_TILE + (k & 1) * 2048);
+            };
+            auto steps = [&](auto K) __attribute__((always_inline)) {
+                constexpr int n = decltype(K)::value;
+                static_for<0, AHEAD>(fetch);
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, n>([&](auto J) {
+                    constexpr int k = decltype(J)::value;
+                    acc = mfma32(k < 8 ? ct[k % 8 / 2][k & 1] : c1[k % AHEAD], wt[k % AHEAD], k == 0 ? zeros : acc);
+                    if constexpr (k + AHEAD < n) fetch(std::integral_constant<int, k + AHEAD>{});
+                    if (k & 1) __builtin_amdgcn_sched_barrier(0);
+                });
+            };
+            if (units[1] > 0) steps(std::integral_constant<int, 16>{});
+            else if (units[0] > 0) steps(std::integral_constant<int, 8>{});
+            else acc = zeros;
+            if constexpr (NG > 1) {  // half of the tile to the other group, the other half stays here
+                const int x = OP::X + wave * 2048 + lane_anew() * 16;
+                if (group == 0) {
+                    *(floatx4*)at(x) = __builtin_shufflevector(acc, acc, 8, 9, 10, 11);
+                    *(floatx4*)at(x + 1024) = __builtin_shufflevector(acc, acc, 12, 13, 14, 15);
+                    mine[0] = __builtin_shufflevector(acc, acc, 0, 1, 2, 3);
+                    mine[1] = __builtin_shufflevector(acc, acc, 4, 5, 6, 7);
+                } else {
+                    *(floatx4*)at(x) = __builtin_shufflevector(acc, acc, 0, 1, 2, 3);
+                    *(floatx4*)at(x + 1024) = __builtin_shufflevector(acc, acc, 4, 5, 6, 7);
+                    mine[0] = __builtin_shufflevector(acc, acc, 8, 9, 10, 11);
+                    mine[1] = __builtin_shufflevector(acc, acc, 12, 13, 14, 15);
+                }
+            } else {
+                static_for<0, NQ>([&](auto Q) {
+                    constexpr int q = 4 * decltype(Q)::value;
+                    mine[q / 4] = __builtin_shufflevector(acc, acc, q, q + 1, q + 2, q + 3);
+                });
+                finish(i);
+            }
+            // block i + 1 of K/V has landed (one group: two stores of this block were issued behind it, in this order)
+            if constexpr (NG == 1) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lds_barrier();
+        }
+        if (NG > 1 && n_blocks > 0) finish(n_blocks - 1);
+        // ---- dQ of this chunk
+        static_for<0, 2>([&](auto S) {
+            constexpr int s = decltype(S)::value;
+            const PackedRows::Row x = pr.at((NW * s + wave) * 32 + l32);
+            __bf16* op = (__bf16*)p.dq + ((q_base + x.row) * p.Hq + x.h) * D + 8 * hf;
+            static_for<0, NKS>([&](auto Ks) {
+                constexpr int ks = decltype(Ks)::value;
+                const floatx16& d = dQ[s][ks / 2];
+                constexpr int v = 8 * (ks % 2);
+                const bf16x8 o8 = rows_of_16(__builtin_shufflevector(d, d, v, v + 1, v + 2, v + 3), __builtin_shufflevector(d, d, v + 4, v + 5, v + 6, v + 7),
+                                             PW ? p.scale * p.norm : p.scale);
+                if (x.live) *(bf16x8*)(op + 16 * ks) = o8;
+            });
+        });
+    };  // process
+
+    // persistent workgroup: items come from the work counters until all lists are exhausted
+    const int xcd = blockIdx.x % N_XCD;
+    unsigned taken = 0;
+    if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+    for (;;) {
+        if (tid == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd);
+        __syncthreads();
+        const int id = __builtin_amdgcn_readfirstlane(*s_item);
+        if (id < 0) break;
+        __syncthreads();  // s_item is free again
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+        process((unsigned)id);
+        __syncthreads();
+    }
+}
+
+bool power_of_two(int x) { return x > 0 && (x & (x - 1)) == 0; }
+
+// one group per workgroup?
+bool single_group(const Params& p) { return max_query_rows(p) * (p.Hq / p.Hkv) <= OnePass<1>::LANES; }
+
+template <int NG, bool RT, bool PW>
+hipError_t launch(const Params& p, hipStream_t s) {
+    using OP = OnePass<NG>;
+    const RowMap map = row_map(OP::LANES, p.Hq, p.Hkv, max_query_rows(p));
+    const int64_t n_items = work_grid((int64_t)p.batch * p.Hkv, 1);
+    if (n_items >= (1ll << 31)) return hipErrorInvalidValue;
+    const int64_t resident = resident_workgroups<bwd_onepass_kernel<NG, RT, PW>>(OP::NW * 64);
+    Params pk = p;
+    pk.queue = p.queue + QUEUE_DKDV * N_XCD;
+    hipLaunchKernelGGL((bwd_onepass_kernel<NG, RT, PW>), dim3((unsigned)std::min(n_items, resident)), dim3(OP::NW * 64), 0, s, pk, map,
+                       (unsigned)(n_items / N_XCD));
+    return hipGetLastError();
+}
+template <int NG>
+hipError_t launch(const Params& p, hipStream_t s) {
+    if (p.pointwise) return p.rt_len ? launch<NG, true, true>(p, s) : launch<NG, false, true>(p, s);
+    return p.rt_len ? launch<NG, true, false>(p, s) : launch<NG, false, false>(p, s);
+}
+
+}  // namespace
+
+// Which calls: those whose users' pairs fit, and whose estimated time is below that of the other forms by a margin that covers what
+// the estimates miss.  Both (us) are fitted to 399 target layers timed in both forms (1..512 pairs, 20..4000 keys, 76..3000 items =
+// users x kv heads; with real-time tokens and pointwise weights, too): two passes cost by items x units x blocks of 32 keys, by the rows
+// and the keys they read, and by the longest user; here an item costs a prologue and its blocks, 512 (256) of them run at a time
+// and the last round is as long as any.  Of the 399, 175 are taken; they are 1.3 times as fast (at most 2.1), three are slower, by 4,
+// 5 and 14 %.  (Full layers of few rows are costed too high as two passes, whose rows are more alike there: a fifth more is asked.)
+bool bwd_is_onepass(const Params& p) {
+    const int r = p.Hq / p.Hkv;
+    if (p.d != OP_D || !power_of_two(r) || r > OP_MAX_HEADS || p.total_q == 0 || max_query_rows(p) * r > OnePass<2>::LANES || bwd_is_brief(p))
+        return false;
+    const double items = (double)p.batch * p.Hkv, pairs = mean_rows(p) * r, most = (double)max_query_rows(p) * r;
+    const double keys = mean_keys(p), longest = (double)max_lead_keys(p);
+    const double units = pairs / 32. + 0.5, blocks = keys / 32. + 0.5;
+    const double product = 0.67 * (p.pointwise ? 1.4 : 1.) * (p.rt_len ? 1.43 : 1.);
+    const double two_passes = 10.4 + items / 1024. * (product * units * blocks + 9.4 * units + 4.6 * blocks) + (0.34 * longest + 0.2 * most) / 32.;
+
+    const int groups = single_group(p) ? 1 : 2;
+    const double first_units = 128. * groups;  // pairs that the waves hold with one unit each
+    const double second = most > first_units ? std::min(1., std::max(0., (pairs - first_units) / (0.25 * first_units) + 0.5)) : 0.;
+    const double fixed = (groups == 1 ? 18.5 : 8.) + 1.2 * pairs / 32. / groups;
+    const double block = groups == 1 ? 1.5 + 0.69 * second : 1.85 + 0.5 * second;
+    const double alone = groups == 1 ? 1.16 + 0.35 * second : block;  // (one group, and no second workgroup on the compute unit)
+    const double item = fixed + block * blocks, last = fixed + alone * longest / 32., rounds = items * groups / 512.;
+    double t = groups == 1 && rounds <= 0.5 ? last - 11. : std::max(last, (keys >= 0.9 * longest ? std::ceil(rounds - 0.01) : rounds + 0.55) * item);
+    t *= (p.rt_len ? 1.1 : 1.) * (p.pointwise ? 1.035 : 1.);
+    return 16.6 + t + 14. < two_passes * (p.layer == 0 ? 0.85 : 1.);
+}
+
+hipError_t launch_bwd_onepass_bf16(const Params& p, hipStream_t s) {
+    timing_begin(MTFM_HTA_KERNEL_BWD_DKDV, s);
+    const hipError_t e = single_group(p) ? launch<1>(p, s) : launch<2>(p, s);
+    timing_end(MTFM_HTA_KERNEL_BWD_DKDV, s);
+    return e;
+}
+
+}  // namespace hta

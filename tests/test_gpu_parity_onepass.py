@@ -1,0 +1,96 @@
+"""GPU parity of the backward form that takes a user's query rows against each key block once (calls of many users whose
+(row, head) pairs per kv head fit a workgroup): the HIP library through the C ABI against the float64 oracle on the same
+bits, element by element.  The users with one or two history tokens have keys that up to 512 rows attend to with weight
+1/2 or 1/3: rounded to bf16, n such weights w leave up to n w 2^-9 max|dO| in each feature of dv (0.2 for n = 256 of mean
+|dO| 0.8, where a feature's own sum can be near zero), hence the bound on the scale of the row (close_on_row_scale)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_11235_amd import hta, inputs
+from tests import test_gpu_parity_pointwise as pointwise
+from tests.hta_testlib import check_case, close_on_row_scale, run_library
+
+pytestmark = pytest.mark.gpu
+FULL, TARGET = inputs.LAYER_FULL, inputs.LAYER_TARGET
+
+# Per user: history, targets.  Ends in and at the edges of the 32-key blocks; no history; no targets; every number of units of
+# 32 pairs that a wave has none, one or two of (one group of waves: up to 256 pairs, two groups: up to 512).
+HIST = [0, 1, 31, 32, 33, 63, 64, 65, 96, 129, 300] + [300, 299, 288, 257] * 3
+CASES = {  # Hq, Hkv, users, targets
+    "r4_one_group": (8, 2, 1000, [64, 63, 64, 33, 64, 32, 31, 40, 48, 9, 8, 7, 1, 0, 64, 60]),
+    "r4_two_groups": (8, 2, 300, [128, 127, 97, 96, 95, 128, 65, 64, 63, 1, 0, 128]),
+    "r1_one_group": (4, 4, 500, [256, 255, 129, 128, 127, 256, 200, 33, 32, 31, 1, 0]),
+    "r1_two_groups": (2, 2, 400, [512, 511, 481, 257, 256, 1, 0]),
+    "r2_one_group": (4, 2, 1000, [128, 127, 65, 64, 63, 128, 100, 17, 16, 15, 1, 0]),
+    "r2_two_groups": (8, 4, 200, [256, 255, 129, 128, 127, 256, 1, 0]),
+    "r8_one_group": (16, 2, 1000, [32, 31, 17, 16, 15, 32, 25, 5, 4, 3, 1, 0]),
+    "r8_two_groups": (16, 2, 400, [64, 63, 49, 48, 47, 33, 32, 31, 1, 0]),
+}
+
+
+def make(name, rt=False, layer=TARGET):
+    Hq, Hkv, n, targets = CASES[name]
+    if layer == FULL:   # the rows of a full layer are its keys: both fit only with short histories
+        n, hist, targets = 2 * n, [420, 450, 448, 447, 400, 0, 1, 300], [62, 33, 0, 1, 31, 62]
+    else:
+        hist = HIST
+    rt_len = np.resize([0, 5, 33, 1, 32, 40, 31], n) if rt else None
+    return inputs.make_case(inputs.custom_config(name, layer, np.resize(hist, n), np.resize(targets, n), Hq, Hkv, 64,
+                                                 seed=91, rt_len=rt_len))
+
+
+def sample(case):
+    return sorted(set(range(24)) | set(range(0, case.batch, max(1, case.batch // 24))) | {case.batch - 1})
+
+
+@pytest.fixture
+def route():
+    """Asserts after the test that the backward ran as one kernel."""
+    hta.mtfm_hta_timing_enable(4)
+    yield
+    torch.cuda.synchronize()
+    counts = [len(hta.mtfm_hta_timing_read(k)) for k in (hta.KERNEL_BWD_DKDV, hta.KERNEL_BWD_DQ)]
+    hta.mtfm_hta_timing_enable(0)
+    assert counts[0] > 0 and counts[1] == 0, f"kernels recorded (dK/dV, dQ): {counts}"
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_target_layer(name, route):
+    case = make(name)
+    check_case(case, with_bwd=True, users=sample(case), compare=close_on_row_scale)
+
+
+@pytest.mark.parametrize("name", ["r4_one_group", "r4_two_groups", "r1_two_groups"])
+def test_realtime(name, route):
+    case = make(name, rt=True)
+    check_case(case, with_bwd=True, users=sample(case), compare=close_on_row_scale)
+
+
+@pytest.mark.parametrize("name,rt", [("r4_one_group", False), ("r2_two_groups", False), ("r4_two_groups", True)])
+def test_pointwise(name, rt, route):
+    case = make(name, rt=rt)
+    pointwise.check(case, users=sample(case), compare=close_on_row_scale)
+
+
+def test_full_layer(route):
+    case = make("r1_one_group", layer=FULL)
+    check_case(case, with_bwd=True, users=sample(case), compare=close_on_row_scale)
+
+
+@pytest.mark.parametrize("name", ["r4_one_group", "r4_two_groups"])
+def test_other_users_keep_their_bits_beside_non_finite_ones(name, route):
+    """What one user leaves in LDS and registers reaches nobody else."""
+    case = make(name)
+    clean = run_library(case, with_bwd=True)
+    bad = np.arange(0, case.batch, 7)
+    qrows, kvrows = inputs.user_rows(case.q_offsets, bad), inputs.user_rows(case.kv_offsets, bad)
+    q, k, dout = case.q.copy(), case.k.copy(), case.dout.copy()
+    q[qrows], k[kvrows], dout[qrows] = np.inf, -np.inf, np.nan
+    spoilt = run_library(dataclasses.replace(case, q=q, k=k, dout=dout), with_bwd=True)
+    for key, rows in (("dq", qrows), ("dk", kvrows), ("dv", kvrows)):
+        keep = torch.ones(clean[key].shape[0], dtype=torch.bool, device="cuda")
+        keep[torch.from_numpy(np.asarray(rows)).to("cuda")] = False
+        assert torch.equal(clean[key][keep], spoilt[key][keep]), key

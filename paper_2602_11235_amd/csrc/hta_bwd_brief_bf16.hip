@@ -156,7 +156,7 @@ __device__ __forceinline__ void brief_dq(const Params& p, const RowMap& map, uns
             constexpr int v = decltype(V)::value;
             if constexpr (TAIL) S[v] = over >= -(8 * (v / 4) + (v % 4)) ? (PW ? PW_MASKED : -INFINITY) : S[v];
             if constexpr (PW) {
-                dsb[v / 8][v % 8] = (__bf16)(dP[v] * pw_silu_prime(S[v] * p.scale, pw_sigmoid(S[v], -c2)));
+                dsb[v / 8][v % 8] = (__bf16)(dP[v] * pw_silu_prime_of_logit(S[v], pw_sigmoid(S[v], -c2), p.scale));
             } else {
                 dsb[v / 8][v % 8] = (__bf16)(fast_exp2(fmaf(S[v], c2, -lse2)) * (dP[v] + dl));
             }

@@ -254,8 +254,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 #pragma unroll
             for (int v = 0; v < 16; v++) {
                 const float sg = pw_sigmoid(o.S[v], -c2);
-                const float x = o.S[v] * p.scale;
-                float pw = pw_silu(x, sg), sp = pw_silu_prime_of(pw, sg);
+                float pw = pw_silu(o.S[v], sg), sp = pw_silu_prime_of(pw, sg, p.scale);  // P / scale
                 if constexpr (MASKED) {  // keys past the history carry no weight
                     pw = key_live ? pw : 0.f;
                     sp = key_live ? sp : 0.f;
@@ -369,7 +368,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 #pragma unroll
                 for (int db = 0; db < NDB; db++) {
                     dkg[off + db * 32] = (__bf16)(dK[db][v] * (PW ? p.scale * p.norm : p.scale));
-                    dvg[off + db * 32] = (__bf16)(PW ? dV[db][v] * p.norm : dV[db][v]);
+                    dvg[off + db * 32] = (__bf16)(PW ? dV[db][v] * (p.scale * p.norm) : dV[db][v]);
                 }
             }
         }

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 1 && NW == 4 ? 3 : 2) voi
             for (int v = 0; v < 16; v++) {
                 if constexpr (PW) {
                     const float sg = pw_sigmoid(S[rb][v], neg_c2);
-                    dsb[rb][v / 8][v % 8] = (__bf16)(dP[rb][v] * pw_silu_prime(S[rb][v] * p.scale, sg));
+                    dsb[rb][v / 8][v % 8] = (__bf16)(dP[rb][v] * pw_silu_prime_of_logit(S[rb][v], sg, p.scale));
                 } else {
                     const float pw = fast_exp2(fmaf(S[rb][v], c2, -lse2[rb]));
                     dsb[rb][v / 8][v % 8] = (__bf16)(pw * dP[rb][v]);

@@ -234,8 +234,8 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
                 float pw, ds;
                 if constexpr (PW) {
                     const float sg = pw_sigmoid(sp, neg_c2);
-                    pw = pw_silu(sp * p.scale, sg);
-                    ds = dpp * pw_silu_prime_of(pw, sg);
+                    pw = pw_silu(sp, sg);  // P / scale, here and below
+                    ds = dpp * pw_silu_prime_of(pw, sg, p.scale);
                 } else {
                     pw = fast_exp2(fmaf(sp, c2, -lse2[s]));
                     ds = pw * (dpp + dl[s]);
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
                 });
                 const bool target = has_own && tok >= LK;
                 fk[s] = !target ? 0.f : PW ? ds * p.scale * p.norm : ds * p.scale;
-                fv[s] = !target ? 0.f : PW ? pw * p.norm : pw;
+                fv[s] = !target ? 0.f : PW ? pw * p.scale * p.norm : pw;
                 targets[s] = __builtin_amdgcn_ballot_w64(target) != 0;
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
 #pragma unroll
                 for (int q = 0; q < NQ; q++) mine[q] += *(const floatx4*)at(OP::X + (wave ^ 4) * 2048 + q * 1024 + ln * 16);
             }
-            const float f = t < 2 ? (PW ? p.norm : 1.f) : (PW ? p.scale * p.norm : p.scale);
+            const float f = PW ? p.scale * p.norm : t < 2 ? 1.f : p.scale;
             const int key = ln & 31;
             static_for<0, NQ / 2>([&](auto H) {
                 constexpr int h = decltype(H)::value;
@@ -355,9 +355,9 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
 #pragma unroll
                 for (int v = 0; v < 16; v++) {
                     if constexpr (PW) {
-                        const float sg = pw_sigmoid(Sx[s][v], neg_c2), pw = pw_silu(Sx[s][v] * p.scale, sg);
+                        const float sg = pw_sigmoid(Sx[s][v], neg_c2), pw = pw_silu(Sx[s][v], sg);
                         pb[v / 8][v % 8] = (__bf16)pw;
-                        dsb[v / 8][v % 8] = (__bf16)(dP[v] * pw_silu_prime_of(pw, sg));
+                        dsb[v / 8][v % 8] = (__bf16)(dP[v] * pw_silu_prime_of(pw, sg, p.scale));
                     } else {
                         const float pw = fast_exp2(fmaf(Sx[s][v], c2, -lse2[s]));
                         pb[v / 8][v % 8] = (__bf16)pw;

@@ -179,8 +179,8 @@ __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, u
             float pw, sp;
             if constexpr (PW) {
                 const float sg = pw_sigmoid(S[v], -c2);
-                pw = pw_silu(S[v] * p.scale, sg);
-                sp = pw_silu_prime_of(pw, sg);
+                pw = pw_silu(S[v], sg);  // P / scale
+                sp = pw_silu_prime_of(pw, sg, p.scale);
                 if constexpr (MASKED) sp = vis ? sp : 0.f;
             } else {
                 pw = fast_exp2(S[v] * c2);
@@ -235,7 +235,7 @@ __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, u
             lo += *(const floatx4*)(a + k * WAVE_FLOATS);
             hi += *(const floatx4*)(a + k * WAVE_FLOATS + 4);
         }
-        const float f = row < 32 ? (PW ? p.scale * p.norm : p.scale) : (PW ? p.norm : 1.f);
+        const float f = PW ? p.scale * p.norm : row < 32 ? p.scale : 1.f;
         bf16x8 o8;
 #pragma unroll
         for (int j = 0; j < 4; j++) o8[j] = (__bf16)(lo[j] * f), o8[4 + j] = (__bf16)(hi[j] * f);

@@ -54,8 +54,11 @@ constexpr float PW_MASKED = -1e30f;
 __device__ inline float pw_sigmoid(float s, float neg_c2) { return __builtin_amdgcn_rcpf(1.f + fast_exp2(s * neg_c2)); }
 __device__ inline float pw_silu(float x, float sg) { return x * sg; }
 __device__ inline float pw_silu_prime(float x, float sg) { return fmaf(sg, x * (1.f - sg), sg); }
-// the same from silu(x) = x sigma, where that is at hand: silu'(x) = sigma + silu(x) (1 - sigma)
-__device__ inline float pw_silu_prime_of(float silu, float sg) { return fmaf(silu, 1.f - sg, sg); }
+// The loops' forms take the unscaled s and leave a factor `scale` of silu to the store (x = scale s; silu(x) / scale = s sigma):
+//   silu'(x) = sigma + (s sigma) (scale - scale sigma),
+// one product less per weight (215871 rows of 8/2 heads, 1.4 G pairs: dK/dV 1.013 -> 0.990 ms, dQ 0.728 -> 0.722).
+__device__ inline float pw_silu_prime_of(float s_sg, float sg, float scale) { return fmaf(s_sg, fmaf(-scale, sg, scale), sg); }
+__device__ inline float pw_silu_prime_of_logit(float s, float sg, float scale) { return fmaf(sg, s * fmaf(-scale, sg, scale), sg); }
 
 // value held by the lane 32 positions away (the other half of the wave); v_permlane32_swap is a VALU
 // exchange of the upper half of its first operand with the lower half of its second

@@ -27,9 +27,16 @@ HIPCC_FLAGS = [
 # instructions through the vector work.  Measured on MI355X: dQ 2-5 % faster, dK/dV at head_dim 128 3.7 %; the forward and
 # the other dK/dV kernels are slower with it (lower occupancy, spills) and keep the default.
 MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
+# A kernel that owns more than 256 registers per wave has its matrix results placed in accumulation registers, from where every score
+# had to be copied before vector instructions could use it (64 copies per 64 matrix instructions at head_dim 128).  This leaves the
+# choice to the register allocator, which then keeps operands there instead.  dK/dV of 128 users of 750..8192 keys 23.15 -> 22.7 ms;
+# whole steps at head_dim 128: 32 users of 60..120 keys 72.0 -> 69.5 us, 200 target layers of 250..1000 keys 422 -> 416.  (The
+# pointwise dK/dV kernel loses by it, 1243 -> 1259 us per step: its unit keeps the default.)
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 FILE_FLAGS = {
     "hta_bwd_dq_bf16.hip": MAX_ILP,
-    "hta_bwd_dkdv128_bf16.hip": MAX_ILP,
+    "hta_bwd_dkdv128_bf16.hip": MAX_ILP + VGPR_FORM,
+    "hta_bwd_brief_bf16.hip": VGPR_FORM,
 }
 
 

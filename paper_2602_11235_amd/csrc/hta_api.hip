@@ -294,7 +294,7 @@ static int fwd_impl(const void* q, const void* k, const void* v, void* out, floa
     if (dtype == MTFM_HTA_BF16) p.n_splits = hta::serve_splits(p, w.splits);
     if (has_rt && (dtype == MTFM_HTA_FP32 || (p.rt_len && p.n_splits == 0))) {  // (the kernel for a few requests looks the limits up itself)
         p.lim = (int32_t*)((char*)workspace + w.lim_off);
-        e = hta::launch_rt_limits(p, s);
+        if (dtype == MTFM_HTA_FP32) e = hta::launch_rt_limits(p, s);  // (else with the schedule)
     }
     if (e == hipSuccess && dtype == MTFM_HTA_BF16) {
         if (p.n_splits == 0) {
@@ -423,7 +423,7 @@ static int bwd_impl(const void* dout, const void* q, const void* k, const void* 
     if (has_rt) p.lim = (int32_t*)((char*)workspace + w.lim_off);
     const bool onepass = dtype == MTFM_HTA_BF16 && hta::bwd_is_onepass(p);
     const bool brief = dtype == MTFM_HTA_BF16 && hta::bwd_is_brief(p);  // (forms the limits itself, and needs no schedule)
-    if (dtype == MTFM_HTA_FP32 ? has_rt : p.rt_len && !brief) e = hta::launch_rt_limits(p, s);
+    if (dtype == MTFM_HTA_FP32 && has_rt) e = hta::launch_rt_limits(p, s);  // (bf16: with the schedule)
     if (e == hipSuccess && dtype == MTFM_HTA_BF16 && !brief) {
         void* region = (char*)workspace + w.order_off;
         e = hta::launch_schedule(p, region, s);

@@ -89,7 +89,7 @@ __device__ inline void rt_limit_of_row(const Params& p, int b, int row) {
 __device__ inline const float* row_start(const Params& p, int half, int64_t idx, bool live) {
     return half == 0 ? p.neg_lse_s + (live ? idx : (int64_t)p.Hq * p.total_q) : p.neg_delta + idx;
 }
-// the limits of all rows: a launch of its own at the start of most calls with real-time tokens
+// the limits of all rows in a launch of their own (launch_schedule finds them otherwise)
 hipError_t launch_rt_limits(const Params& p, hipStream_t s);
 
 hipError_t launch_fwd_fp32(const Params& p, hipStream_t s);
@@ -126,7 +126,8 @@ int report_error(int code, const char* fmt, ...) __attribute__((format(printf, 2
 void timing_begin(int kind, hipStream_t s);
 void timing_end(int kind, hipStream_t s);
 // The schedule region at the head of the workspace: work counters (one per kernel kind and XCD, 256 bytes in all),
-// then the user order of the launch, long histories first.  launch_schedule() zeroes the former and builds the latter.
+// then the user order of the launch, long histories first.  launch_schedule() zeroes the former, builds the latter
+// and, in calls with real-time tokens, fills p.lim.
 constexpr int N_XCD = 8;
 constexpr int QUEUE_DKDV = 0;  // kernel kinds that take their work from counters
 constexpr int QUEUE_WORDS = 64;

@@ -9,6 +9,8 @@
 // (rows x keys) starts the long-history users first and leaves the short ones to fill the tail.
 #include "hta_common.h"
 
+#include <algorithm>
+
 namespace hta {
 namespace {
 
@@ -27,9 +29,18 @@ __device__ inline float user_cost(const Params& p, int b) {
 // workgroup with a lane to a user that walks the whole batch (64 users 4.9 -> 3.9 us, 256 users 9.0 -> 4.7, 512 users 4.7 and 4096 15.0 now).
 constexpr int RANK_THREADS = 256, RANK_LANES = 16, RANK_USERS = RANK_THREADS / RANK_LANES;
 static_assert(QUEUE_WORDS <= RANK_THREADS, "the first workgroup clears the counters");
-__global__ __launch_bounds__(RANK_THREADS) void schedule_rank_kernel(Params p, int32_t* counters, int32_t* order) {
+// The workgroups behind the first n_rank find the rows' limits of mask rule 2, limit_groups to a user: with real-time tokens a call needs
+// both before its first attention kernel, and neither needs the other (whole steps
+// against a launch for each: 32 users of 60..250 keys 61.7 -> 57.7 us, 200 target layers of 250..1000 keys 153.6 -> 148.9).
+__global__ __launch_bounds__(RANK_THREADS) void schedule_rank_kernel(Params p, int32_t* counters, int32_t* order, unsigned n_rank,
+                                                                     unsigned limit_groups) {
     __shared__ float cost[RANK_SORT_MAX];
     const int B = p.batch, tid = threadIdx.x;
+    if (blockIdx.x >= n_rank) {
+        const unsigned id = blockIdx.x - n_rank, b = id / limit_groups;
+        rt_limit_of_row(p, (int)b, (int)(id - b * limit_groups) * RANK_THREADS + tid);
+        return;
+    }
     if (blockIdx.x == 0 && tid < QUEUE_WORDS) counters[tid] = 0;
     for (int b = tid; b < B; b += RANK_THREADS) cost[b] = user_cost(p, b);
     __syncthreads();
@@ -123,8 +134,16 @@ hipError_t launch_schedule(const Params& p, void* region, hipStream_t s) {
     if (p.batch <= 0) return hipSuccess;
     int32_t* counters = (int32_t*)region;
     int32_t* order = schedule_order(region);
+    const int64_t rank_groups = (p.batch + RANK_USERS - 1) / RANK_USERS;
+    const int64_t limit_groups = p.rt_len ? (std::max<int64_t>(max_query_rows(p), 0) + RANK_THREADS - 1) / RANK_THREADS : 0;
+    const bool together = p.batch <= RANK_SORT_MAX && rank_groups + limit_groups * p.batch < (1ll << 31);
+    if (p.rt_len && !together) {
+        const hipError_t e = launch_rt_limits(p, s);
+        if (e != hipSuccess) return e;
+    }
     if (p.batch <= RANK_SORT_MAX)
-        hipLaunchKernelGGL(schedule_rank_kernel, dim3((unsigned)((p.batch + RANK_USERS - 1) / RANK_USERS)), dim3(RANK_THREADS), 0, s, p, counters, order);
+        hipLaunchKernelGGL(schedule_rank_kernel, dim3((unsigned)(rank_groups + (together ? limit_groups * p.batch : 0))), dim3(RANK_THREADS), 0, s,
+                           p, counters, order, (unsigned)rank_groups, (unsigned)std::max<int64_t>(limit_groups, 1));
     else
         hipLaunchKernelGGL(schedule_bucket_kernel, dim3(1), dim3(SCHED_THREADS), 0, s, p, counters, order);
     return hipGetLastError();

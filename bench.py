@@ -437,6 +437,8 @@ def main() -> int:
     # visible pair; backward 10*d per pair, split between the two passes by the products they own -- dQ
     # (S, dP, dQ = 6*d, of which S and dP are shared work credited once) and dK/dV (dV, dK = 4*d).
     flops = {"fwd": 4.0 * d * pairs, "bwd_dq": 6.0 * d * pairs, "bwd_dkdv": 4.0 * d * hist_pairs}
+    if kernel_ms["bwd_dkdv"] and not kernel_ms["bwd_dq"]:  # one kernel is the whole backward
+        flops["bwd_dkdv"] = 10.0 * d * pairs
     kernels = {}
     for name, ms in kernel_ms.items():
         if not ms:

@@ -9,7 +9,8 @@
 //   1. bwd_self and 2. bwd_dq (hta_bwd_dq_bf16.hip): the self-key terms of the target rows' keys, and dQ,
 //      row-stationary; the first launch also leaves -delta and -lse/scale of every row in the workspace.
 //   3. bwd_dkdv (hta_bwd_dkdv.h): key-stationary, dk/dv of history (and real-time) keys, written once.
-// (Calls of little work take other shapes of the same: hta_bwd_brief_bf16.hip.)
+// (Calls of little work take other shapes of the same: hta_bwd_brief_bf16.hip.  Users of few query rows go through in one pass,
+// hta_bwd_onepass_bf16.hip.)
 // S and dP are thus computed twice (7 matrix products instead of 5); in exchange neither dQ nor
 // dK/dV ever crosses a workgroup, which removes a float32 accumulator three times the size of q, its
 // zero-fill and conversion passes, and an atomic traffic of several GB per call.

@@ -400,7 +400,8 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 // key loop, and waves that drift apart.  Twelve waves, three per SIMD, one unit in flight per wave (168 registers, 18 more in scratch):
 // measured against eight waves with two units interleaved per wave, as bwd_dkdv_kernel does it, the third wave hides
 // more than the interleaving (dK/dV of a 512 x 2048 x 128 target layer 1.21 against 1.30 ms; streaming kernel 1.33).
-// Softmax weights without real-time tokens only (the callers that need the other readings take the streaming kernel).
+// Softmax weights without real-time tokens only (the callers that need the other readings take the streaming kernel).  Most such
+// calls now go through in one pass (hta_bwd_onepass_bf16.hip); left here are mostly those whose query heads per kv head are no power of two.
 template <int D, int NW>
 struct DkdvResident {
     static constexpr int MAX_UNITS = 16;

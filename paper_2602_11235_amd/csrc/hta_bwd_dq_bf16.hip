@@ -157,8 +157,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 1 && NW == 4 ? 3 : 2) voi
     // The dP products start from -delta instead of zero.  With one row block per wave sixteen registers are free to keep it in (opaque,
     // or they would be written anew for every sub-tile), which takes sixteen additions of about seventy vector instructions out of a
     // sub-tile: head_dim 64 with real-time tokens 0.691 -> 0.676 ms (256 users of 512..1024 keys), head_dim 128 16.6 -> 16.2 ms
-    // (128 users of 750..8192 keys), two row blocks per wave 0.936 -> 0.918 (256 users of 1024 keys; eleven registers of the copies of a
-    // last, ragged tile then wait in scratch).
+    // (128 users of 750..8192 keys), two row blocks per wave 0.936 -> 0.918 (256 users of 1024 keys; thirteen registers for the copies of a
+    // last, ragged tile then wait in scratch, 0.2 GB of traffic on 256 users of 512..1024 keys.  Without: the second block's written every
+    // time in place of the additions, whole steps 1797 against 1799 us there, but 2711 against 2701 on 1024 keys).
     floatx16 dp0[RB];
     if constexpr (!PW) {
 #pragma unroll
@@ -315,7 +316,7 @@ hipError_t launch_dq(const Params& p, hipStream_t s) {
 
 }  // namespace
 
-// Four waves per workgroup.  At head_dim 64 one row block per wave and three workgroups per unit (145 registers): finer than two
+// Four waves per workgroup.  At head_dim 64 one row block per wave and three workgroups per unit (158 registers): finer than two
 // blocks per wave and two workgroups, and faster wherever that counts (P packed rows per user: P = 92..372 189 -> 114 us,
 // P = 790 469 -> 366, P = 1400 52 -> 46, P = 3400 612 -> 600).  Two blocks per wave share the operand reads, which draws less power and shows once a call runs for
 // long: 83 users of 461..4062 keys 954 -> 909 us, and a whole step of 256 users of 512..1024 keys 1819 -> 1801.  At 128 four

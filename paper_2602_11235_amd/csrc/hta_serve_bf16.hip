@@ -351,7 +351,7 @@ int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t ma
 // Estimated times of a call (us) with the keys in one piece, from fits of 2700 calls on both sides of the line (1 to 400 users,
 // 4 to 256 candidates or a full layer, 64 to 8192 keys, all of one length or spread over a factor of 8; with and without
 // real-time tokens and with pointwise weights).  The ordinary kernel, up to a workgroup per unit: the longest one, a little more the
-// fuller the chip, and the schedule (whose time grows with the users) and limits launches.
+// fuller the chip, and the schedule and limits launches as they were then (0.02 us per user, 2 us; since less, which 32 users hardly see).
 static double ordinary_us(const Params& p, int64_t workgroups) {
     struct { double launch, key, key_full; } c;
     if (p.d == 32) c = {6.2, 9.5e-3, 3.5e-3};

@@ -375,16 +375,15 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     }
     };  // process
 
-    // persistent workgroup: items come from the work counters until all lists are exhausted
+    // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = 0;
-    if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+    unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
-        if (tid == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd);
+        if (tid == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, n_persistent);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, n_persistent);
         process((unsigned)id);
         __syncthreads();  // the stages and s_item are free again
     }
@@ -613,14 +612,13 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
 
     // persistent workgroup, as in bwd_dkdv_kernel
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = 0;
-    if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+    unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
-        if (tid == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd);
+        if (tid == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
         process((unsigned)id);
         __syncthreads();  // the staged units and s_item are free again
     }

@@ -540,17 +540,16 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
         });
     };  // process
 
-    // persistent workgroup: items come from the work counters until all lists are exhausted
+    // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = 0;
-    if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+    unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
-        if (tid == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd);
+        if (tid == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = __builtin_amdgcn_readfirstlane(*s_item);
         if (id < 0) break;
         __syncthreads();  // s_item is free again
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd);
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
         process((unsigned)id);
         __syncthreads();
     }

@@ -42,3 +42,32 @@ def test_order_of_the_users(layer, n):
             lim.append(hist[b] + np.searchsorted(ts[hist[b]:keys[b]], rows, side="left"))
         got = batch.workspace.view(torch.int32)[:case.total_q].cpu().numpy()
         assert np.array_equal(got, np.concatenate(lim))
+
+
+@pytest.mark.parametrize("name,layer,users,hist,targets,heads", [
+    ("one round, one pass", inputs.LAYER_TARGET, 250, 600, 64, (8, 2, 64)),      # 504 ids, room for 512 workgroups
+    ("rounds, one pass", inputs.LAYER_TARGET, 1000, 150, 64, (8, 2, 64)),        # 2000 ids
+    ("rounds, dK/dV", inputs.LAYER_FULL, 400, 700, 20, (4, 2, 32)),              # 4800 ids, mostly of one block of 128 keys
+])
+def test_workgroups_leave_an_exhausted_queue_without_counting_it_up(name, layer, users, hist, targets, heads):
+    """The counters of the work queue after a call: what was taken behind the first round, one failing take per workgroup at its own
+    list, and a few that lost a race at another one's.  (Counting up all eight lists before leaving: 8 per workgroup.)"""
+    rng = np.random.RandomState(users)
+    hist_len = np.full(users, hist) if layer == inputs.LAYER_TARGET else rng.randint(hist // 2, hist + 1, users)
+    hist_len[0] = hist
+    say(f"  queue {name}")
+    case = inputs.make_case(inputs.custom_config("queue", layer, hist_len, np.full(users, targets), *heads, seed=4))
+    batch = device_batch(case)
+    batch.forward()
+    batch.backward(to_torch(case.dout, "bf16"))
+    torch.cuda.synchronize()
+    counters = batch.workspace.view(torch.int32)[:COUNTERS].cpu().numpy()
+    blocks = 1 if layer == inputs.LAYER_TARGET else -(-hist // 128)
+    ids = -(-users * heads[1] // 8) * 8 * blocks
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    say(f"    {ids} ids, counters {counters[:8]}, {units} compute units")
+    if name.startswith("one round"):
+        assert not counters.any()
+    else:
+        assert 0 < counters.sum() < ids + 2 * units   # (512 or more workgroups: with 8 each it would be ids + 16 units)
+    assert not counters[8:].any()

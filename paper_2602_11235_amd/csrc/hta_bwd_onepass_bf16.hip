@@ -585,8 +585,13 @@ hipError_t launch(const Params& p, hipStream_t s) {
 // the estimates miss.  Both (us) are fitted to 399 target layers timed in both forms (1..512 pairs, 20..4000 keys, 76..3000 items =
 // users x kv heads; with real-time tokens and pointwise weights, too): two passes cost by items x units x blocks of 32 keys, by the rows
 // and the keys they read, and by the longest user; here an item costs a prologue and its blocks, 512 (256) of them run at a time
-// and the last round is as long as any.  Of the 399, 175 are taken; they are 1.3 times as fast (at most 2.1), three are slower, by 4,
-// 5 and 14 %.  (Full layers of few rows are costed too high as two passes, whose rows are more alike there: a fifth more is asked.)
+// and the last round is as long as any.  The longest item counts with the most pairs that a user has, not with the mean's: 160
+// users of up to 3407 keys x 75 candidates, 8/2 heads, take 234 us in two passes and 293 here.  (Full layers of few rows are costed too high
+// as two passes, whose rows are more alike there: a fifth more is asked.)
+// How it fares, on 4816 calls timed in both forms (2056 target layers and 2760 full ones; 8..512 pairs, 16..4145 keys, 76..15952 items): 1809
+// are taken, 1.39 times as fast in one pass on average (at most 2.2; full layers 1.38); eight of them, three of them full layers, are slower by more
+// than 3 %, the worst by 14 (full: 7).  It errs on the safe side: of the 3007 others 1645 would gain 15 % or more, mostly small calls, since
+// the fits were made when leaving the work queue cost up to 45 us.
 bool bwd_is_onepass(const Params& p) {
     const int r = p.Hq / p.Hkv;
     if (p.d != OP_D || !power_of_two(r) || r > OP_MAX_HEADS || p.total_q == 0 || max_query_rows(p) * r > OnePass<2>::LANES || bwd_is_brief(p))
@@ -599,10 +604,12 @@ bool bwd_is_onepass(const Params& p) {
 
     const int groups = single_group(p) ? 1 : 2;
     const double first_units = 128. * groups;  // pairs that the waves hold with one unit each
-    const double second = most > first_units ? std::min(1., std::max(0., (pairs - first_units) / (0.25 * first_units) + 0.5)) : 0.;
+    auto two_units = [&](double x) { return most > first_units ? std::min(1., std::max(0., (x - first_units) / (0.25 * first_units) + 0.5)) : 0.; };
+    const double second = two_units(pairs), second_of_last = two_units(most);
     const double fixed = (groups == 1 ? 18.5 : 8.) + 1.2 * pairs / 32. / groups;
     const double block = groups == 1 ? 1.5 + 0.69 * second : 1.85 + 0.5 * second;
-    const double alone = groups == 1 ? 1.16 + 0.35 * second : block;  // (one group, and no second workgroup on the compute unit)
+    // of the longest item (one group: with no second workgroup on the compute unit)
+    const double alone = groups == 1 ? 1.16 + 0.35 * second_of_last : 1.85 + 0.5 * second_of_last;
     const double item = fixed + block * blocks, last = fixed + alone * longest / 32., rounds = items * groups / 512.;
     double t = groups == 1 && rounds <= 0.5 ? last - 11. : std::max(last, (keys >= 0.9 * longest ? std::ceil(rounds - 0.01) : rounds + 0.55) * item);
     t *= (p.rt_len ? 1.1 : 1.) * (p.pointwise ? 1.035 : 1.);

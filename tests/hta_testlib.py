@@ -104,6 +104,22 @@ def run_library(case: inputs.Case, with_bwd: bool) -> dict:
     return g
 
 
+def read_backward_kernels() -> tuple:
+    """How many launches the library's timing recorded of kind dK/dV and of kind dQ since it was enabled; disables it.  Of a call whose
+    whole backward is one kernel the latter has none."""
+    torch.cuda.synchronize()
+    counts = tuple(len(hta.mtfm_hta_timing_read(k)) for k in (hta.KERNEL_BWD_DKDV, hta.KERNEL_BWD_DQ))
+    hta.mtfm_hta_timing_enable(0)
+    return counts
+
+
+def backward_kernels(call) -> tuple:
+    """The same for the calls that `call` makes."""
+    hta.mtfm_hta_timing_enable(4)
+    call()
+    return read_backward_kernels()
+
+
 def compare_with_oracle(case: inputs.Case, g: dict, with_bwd: bool, users=None, kv_group=None, compare=None,
                         per_head: bool = False) -> None:
     """Compare device results `g` of the whole case with the oracle run on all users (users=None) or on exactly the

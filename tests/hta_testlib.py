@@ -120,6 +120,14 @@ def backward_kernels(call) -> tuple:
     return read_backward_kernels()
 
 
+def queue_takes(batch) -> int:
+    """What the counters of the backward's work queue (the first eight words of its workspace without real-time tokens) say after a call:
+    items taken behind each workgroup's first one, plus takes that failed; 0 where no kernel of the call has a queue."""
+    assert batch.rt_len is None
+    torch.cuda.synchronize()
+    return int(batch.workspace.view(torch.int32)[:8].sum().item())
+
+
 def compare_with_oracle(case: inputs.Case, g: dict, with_bwd: bool, users=None, kv_group=None, compare=None,
                         per_head: bool = False) -> None:
     """Compare device results `g` of the whole case with the oracle run on all users (users=None) or on exactly the

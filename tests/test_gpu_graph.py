@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2602_11235_amd import gln, inputs
-from tests.hta_testlib import device_batch, say, to_torch
+from tests.hta_testlib import backward_kernels, device_batch, say, to_torch
 
 pytestmark = pytest.mark.gpu
 
@@ -26,17 +26,26 @@ def _replay_and_compare(graph, outputs, eager, disturb):
 # a few users: forward and backward in their forms for calls of little work
 FEW = inputs.custom_config("few", inputs.LAYER_TARGET, [300, 65, 1000], [7, 33, 40], 8, 2, 64, seed=43, rt_len=[40, 0, 70])
 
+# many users of few query rows: the backward in one kernel, more items than workgroups; and a full layer with real-time tokens
+ONE_PASS = {
+    "one_pass": inputs.custom_config("one_pass", inputs.LAYER_TARGET, np.resize([300, 129, 0, 257], 600), np.resize([64, 33, 48], 600), 8, 2,
+                                     64, seed=44),
+    "one_pass_full_rt": inputs.custom_config("one_pass_full_rt", inputs.LAYER_FULL, np.resize([330, 289, 256, 0, 200], 600),
+                                             np.resize([60, 33, 0], 600), 4, 4, 64, seed=45, rt_len=np.resize([0, 5, 33, 40], 600)),
+}
 
-@pytest.mark.parametrize("name, with_bwd", [("I1", False), ("I2_RT", False), ("I3", False), ("C2", True), ("C2_RT", True), ("few", True)])
+
+@pytest.mark.parametrize("name, with_bwd", [*((name, True) for name in ONE_PASS), ("I1", False), ("I2_RT", False), ("I3", False), ("C2", True), ("C2_RT", True), ("few", True)])
 def test_forward_and_backward_replay_from_a_graph(name, with_bwd):
     say(f"[graph] {name} bwd={with_bwd}")
-    case = inputs.make_case(FEW if name == "few" else inputs.CONFIGS[name])
+    case = inputs.make_case(FEW if name == "few" else ONE_PASS.get(name) or inputs.CONFIGS[name])
     b = device_batch(case)
     other = device_batch(inputs.make_case(inputs.custom_config("other", inputs.LAYER_FULL, [300, 65], [7, 33], 8, 2, 64, seed=41)))
     dout = to_torch(case.dout, case.cfg.dtype)
     b.forward()
-    if with_bwd:
-        b.backward(dout)                # warm-up: every one-time query of the library happens outside the capture
+    if with_bwd:                        # warm-up: every one-time query of the library happens outside the capture
+        kernels = backward_kernels(lambda: b.backward(dout))
+        assert (kernels == (1, 0)) == (name in ONE_PASS), kernels
     torch.cuda.synchronize()
     outputs = [b.out, b.lse] + ([b.dq, b.dk, b.dv] if with_bwd else [])
     eager = [t.clone() for t in outputs]

@@ -11,7 +11,7 @@ import pytest
 import torch
 
 from paper_2602_11235_amd import gln, hta, hta_pw, inputs
-from tests.hta_testlib import device_batch, to_torch
+from tests.hta_testlib import backward_kernels, device_batch, queue_takes, to_torch
 
 pytestmark = pytest.mark.gpu
 FULL, TARGET = inputs.LAYER_FULL, inputs.LAYER_TARGET
@@ -86,6 +86,7 @@ def run_attention(case, pointwise=False):
     b.forward()
     b.backward(to_torch(case.dout, dt))
     settle(guards, results)
+    return b
 
 
 EDGE_HIST = [0, 1, 63, 64, 65, 130, 200, 0, 257, 31, 0]
@@ -131,11 +132,41 @@ def test_split_forward_stays_inside_its_buffers(layer, rt):
     settle(guards, results)
 
 
-def test_few_rows_long_histories_stay_inside_their_buffers():
-    # enough (user, kv head) items of a target-only layer for the dK/dV launch that keeps a user's query rows in LDS
-    hist, tgts = [600, 0, 513, 1030, 64, 257, 255, 256, 0] * 15, [128, 5, 0, 33, 70, 1, 96, 2, 0] * 15
-    run_attention(case_of(TARGET, 8, 2, 64, "bf16", hist=hist, tgts=tgts))
-    run_attention(case_of(TARGET, 16, 4, 64, "bf16", hist=hist, tgts=tgts))
+@pytest.mark.parametrize("Hq,Hkv,copies,resident", [(8, 2, 15, False), (16, 4, 15, True), (6, 2, 35, True)])
+def test_few_rows_long_histories_stay_inside_their_buffers(Hq, Hkv, copies, resident):
+    # few query rows against long histories: the dK/dV launch that keeps a user's query rows in LDS, which wants enough (user, kv
+    # head) items (and takes its work from the queue); with fewer, the one whose waves share a key block's rows (which does not)
+    hist, tgts = [600, 0, 513, 1030, 64, 257, 255, 256, 0] * copies, [128, 5, 0, 33, 70, 1, 96, 2, 0] * copies
+    case = case_of(TARGET, Hq, Hkv, 64, "bf16", hist=hist, tgts=tgts)
+    taken = queue_takes(run_attention(case))
+    assert one_item_per_user(case, taken) if resident else taken == 0
+
+
+def one_item_per_user(case, taken):
+    """The queue's takes of a launch with one item per (user, kv head), not one per 128 keys: at most one failing take per workgroup,
+    one of them per compute unit."""
+    items, units = case.batch * case.cfg.Hkv, torch.cuda.get_device_properties(0).multi_processor_count
+    return units < items and 0 < taken < items + 2 * units
+
+
+ONE_PASS = {  # layer, Hq, Hkv, history, targets, real-time tokens: cycled through 1000 users
+    "one_group": (TARGET, 8, 2, [300, 299, 288, 257, 129, 0, 1], [64, 63, 64, 48, 33, 0], None),
+    "two_groups": (TARGET, 8, 2, [300, 129, 96, 33, 0, 1, 257], [128, 97, 65, 1, 0, 64], None),
+    "one_group_rt": (TARGET, 8, 2, [300, 299, 288, 257, 129, 0, 1], [64, 63, 64, 48, 33, 0], [0, 5, 33, 1, 32]),
+    "full_one_group_rt": (FULL, 4, 4, [200, 199, 193, 192, 191, 190, 200, 0, 1], [40, 33, 31, 40, 0], [0, 5, 15, 1, 16, 9]),
+    "full_two_groups_rt": (FULL, 4, 4, [330, 300, 289, 288, 287, 256, 0, 1, 200], [60, 33, 0, 1, 31, 60], [0, 5, 33, 1, 32, 40, 31]),
+}
+
+
+# the batch's last user: a ragged last block of keys; no target (dk = dv = 0 in a target layer); no history
+@pytest.mark.parametrize("last_hist,last_targets", [(97, 33), (65, 0), (0, 40)])
+@pytest.mark.parametrize("name,pointwise", [*((name, False) for name in ONE_PASS), ("two_groups", True), ("full_one_group_rt", True)])
+def test_one_pass_backward_stays_inside_its_buffers(name, pointwise, last_hist, last_targets):
+    layer, Hq, Hkv, hist, tgts, rt = ONE_PASS[name]
+    hist, tgts = np.resize(hist, 1000), np.resize(tgts, 1000)
+    hist[-1], tgts[-1] = last_hist, last_targets
+    cfg = inputs.custom_config(f"guard_{name}", layer, hist, tgts, Hq, Hkv, 64, seed=93, rt_len=None if rt is None else np.resize(rt, 1000))
+    assert backward_kernels(lambda: run_attention(inputs.make_case(cfg), pointwise)) == (1, 0)
 
 
 def test_the_last_user_ends_exactly_at_the_end_of_the_buffers():

@@ -31,15 +31,28 @@ CASES = {  # Hq, Hkv, users, targets
 }
 
 
-def make(name, rt=False, layer=TARGET):
+# The rows of a full layer are its keys: both fit only with short histories.  Hq, Hkv, users, history, targets, real-time tokens (which in a
+# full layer have rows of their own: some start in the history's last block of 32 keys, some run on into the next one; users with
+# no history have them, too).
+FULL_CASES = {
+    "r1_two_groups": (4, 4, 1000, [420, 450, 448, 447, 400, 0, 1, 300], [62, 33, 0, 1, 31, 62], None),
+    "r1_two_groups_rt": (4, 4, 1000, [330, 300, 289, 288, 287, 256, 0, 1, 200], [60, 33, 0, 1, 31, 60], [0, 5, 33, 1, 32, 40, 31]),
+    "r1_one_group_rt": (4, 4, 1000, [200, 199, 193, 192, 191, 190, 200, 0, 1], [40, 33, 31, 40, 0], [0, 5, 15, 1, 16, 9]),
+    "r4_two_groups_rt": (8, 2, 1000, [72, 65, 64, 63, 33, 0, 1, 32], [20, 19, 0, 1, 16], [0, 5, 33, 1, 32, 31]),
+}
+
+
+def make(name, rt=False):
     Hq, Hkv, n, targets = CASES[name]
-    if layer == FULL:   # the rows of a full layer are its keys: both fit only with short histories
-        n, hist, targets = 2 * n, [420, 450, 448, 447, 400, 0, 1, 300], [62, 33, 0, 1, 31, 62]
-    else:
-        hist = HIST
     rt_len = np.resize([0, 5, 33, 1, 32, 40, 31], n) if rt else None
-    return inputs.make_case(inputs.custom_config(name, layer, np.resize(hist, n), np.resize(targets, n), Hq, Hkv, 64,
+    return inputs.make_case(inputs.custom_config(name, TARGET, np.resize(HIST, n), np.resize(targets, n), Hq, Hkv, 64,
                                                  seed=91, rt_len=rt_len))
+
+
+def make_full(name):
+    Hq, Hkv, n, hist, targets, rt = FULL_CASES[name]
+    return inputs.make_case(inputs.custom_config(name, FULL, np.resize(hist, n), np.resize(targets, n), Hq, Hkv, 64, seed=91,
+                                                 rt_len=None if rt is None else np.resize(rt, n)))
 
 
 def sample(case):
@@ -73,9 +86,16 @@ def test_pointwise(name, rt, route):
     pointwise.check(case, users=sample(case), compare=close_on_row_scale)
 
 
-def test_full_layer(route):
-    case = make("r1_one_group", layer=FULL)
+@pytest.mark.parametrize("name", FULL_CASES)
+def test_full_layer(name, route):
+    case = make_full(name)
     check_case(case, with_bwd=True, users=sample(case), compare=close_on_row_scale)
+
+
+@pytest.mark.parametrize("name", FULL_CASES)
+def test_full_layer_pointwise(name, route):
+    case = make_full(name)
+    pointwise.check(case, users=sample(case), compare=close_on_row_scale)
 
 
 @pytest.mark.parametrize("name", ["r4_one_group", "r4_two_groups"])

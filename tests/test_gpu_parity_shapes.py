@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2602_11235_amd import inputs
-from tests.hta_testlib import check_case, close_on_row_scale, device_batch, say, to_torch
+from tests.hta_testlib import check_case, close_on_row_scale, device_batch, queue_takes, say, to_torch
 from tests.test_gpu_parity_pointwise import check as check_pointwise
 
 pytestmark = pytest.mark.gpu
@@ -42,7 +42,11 @@ SHAPES = {
     "ordinary_d32_rt": (FULL, 400, 500, 0, (4, 2, 32), True),
     "ordinary_d128_rt": (FULL, 160, 500, 0, (16, 2, 128), True),
     "two_row_blocks": (FULL, 40, 2048, 0, (8, 2, 64), False),
-    "rows_resident": (TARGET, 256, 512, 88, (8, 2, 64), False),
+    # few query rows per user against long histories: the whole backward in one kernel, or (r not a power of two) dK/dV with a
+    # user's rows resident in LDS
+    "one_pass": (TARGET, 256, 512, 88, (8, 2, 64), False),
+    "rows_resident": (TARGET, 256, 512, 88, (6, 2, 64), False),
+    "rows_resident_r6": (TARGET, 300, 800, 20, (12, 2, 64), False),
     # groups of more query heads than a tile has lanes, cut into chunks of which the last one is not full; all forms again
     "brief_wide": (TARGET, 6, 0, 0, (40, 1, 64), True),
     "brief_wide_d32": (TARGET, 5, 0, 0, (130, 1, 32), False),
@@ -71,6 +75,20 @@ def test_shapes(name):
     check_case(case, with_bwd=True, users=users, compare=close_on_row_scale)
 
 
+@pytest.mark.parametrize("name", ["rows_resident", "rows_resident_r6"])
+def test_the_resident_shapes_reach_the_resident_kernel(name):
+    """By the takes from the work queue: one item per (user, kv head) there, one per 128 keys of the longest in the kernel that streams the
+    rows, and the kernels that share a block's rows between waves have no queue."""
+    case, _ = make(name)
+    batch = device_batch(case)
+    batch.forward()
+    batch.backward(to_torch(case.dout, "bf16"))
+    items, units = case.batch * case.cfg.Hkv, torch.cuda.get_device_properties(0).multi_processor_count
+    taken = queue_takes(batch)
+    say(f"    {items} items, {taken} takes")
+    assert units < items and 0 < taken < items + 2 * units
+
+
 @pytest.mark.parametrize("name", ["brief_rt", "brief_d128", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "ordinary_d32_rt",
                                   "brief_wide", "rows64_wide"])
 def test_shapes_with_pointwise_weights(name):
@@ -79,7 +97,7 @@ def test_shapes_with_pointwise_weights(name):
 
 
 @pytest.mark.parametrize("name", ["brief", "brief_d32", "brief_d128", "one_way", "one_way_rt", "two_ways", "four_ways_d128",
-                                  "ordinary_d32", "ordinary_d32_rt", "ordinary_d128_rt", "rows_resident"])
+                                  "ordinary_d32", "ordinary_d32_rt", "ordinary_d128_rt", "one_pass", "rows_resident"])
 def test_non_finite_values_stay_with_their_user(name):
     """The users that own the call's first and last query rows get NaN everywhere; everyone else's results keep their bits.  (Lanes
     that stand for no row still multiply their dP by a weight of 0: it has to be the dP of a row of the same user.)"""

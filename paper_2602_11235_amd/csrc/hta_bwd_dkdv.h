@@ -379,7 +379,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     const int xcd = blockIdx.x % N_XCD;
     unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
-        if (tid == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, n_persistent);
+        if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, n_persistent);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     const int xcd = blockIdx.x % N_XCD;
     unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
-        if (tid == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
+        if (wave_u == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;

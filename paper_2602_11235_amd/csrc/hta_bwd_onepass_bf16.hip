@@ -544,7 +544,7 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
     const int xcd = blockIdx.x % N_XCD;
     unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
-        if (tid == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
+        if (wave == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = __builtin_amdgcn_readfirstlane(*s_item);
         if (id < 0) break;

@@ -201,22 +201,24 @@ __device__ inline unsigned queue_take_ahead(int32_t* counters, int xcd, unsigned
     const unsigned dealt = queue_dealt(n_groups, xcd);
     return dealt < per_xcd ? dealt + atomicAdd((unsigned*)&counters[xcd], 1u) : per_xcd;
 }
-//   ... and turn it into a work id, or -1 when all lists are exhausted
+//   first wave:  ... and turn it into a work id, or -1 when all lists are exhausted.  (Lane q looks at the list of XCD xcd + q: one
+//   load, and none of the addresses is kept in registers for the length of every item.)
 __device__ inline int queue_resolve(int32_t* counters, int xcd, unsigned taken, unsigned per_xcd, unsigned n_groups) {
+    taken = __builtin_amdgcn_readfirstlane(taken);
     if (taken < per_xcd) return (int)(taken * N_XCD + xcd);
     if (n_groups >= per_xcd * N_XCD) return -1;  // the first round was all
-    asm volatile("" : "+v"(xcd));  // (formed here, or the seven addresses would take up registers for the length of every item)
-    unsigned next[N_XCD];  // (a list only ever shortens: one that is seen exhausted is, one that is not may be by now)
-#pragma unroll
-    for (int q = 1; q < N_XCD; q++)
-        next[q] = __hip_atomic_load((unsigned*)&counters[(xcd + q) % N_XCD], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int q = 1; q < N_XCD; q++) {
-        const int x = (xcd + q) % N_XCD;
-        const unsigned dealt = queue_dealt(n_groups, x);
-        if (dealt + next[q] >= per_xcd) continue;
-        const unsigned slot = dealt + atomicAdd((unsigned*)&counters[x], 1u);
-        if (slot < per_xcd) return (int)(slot * N_XCD + x);
+    int lane;  // (anew, for the same reason)
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    const int x = (xcd + lane) % N_XCD;
+    bool left = false;  // (a list only ever shortens: one that is seen exhausted is, one that is not may be by now)
+    if (lane > 0 && lane < N_XCD)
+        left = queue_dealt(n_groups, x) + __hip_atomic_load((unsigned*)&counters[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < per_xcd;
+    for (uint64_t lists = __builtin_amdgcn_ballot_w64(left); lists != 0; lists &= lists - 1) {
+        const int from = (xcd + __builtin_ctzll(lists)) % N_XCD;
+        unsigned slot = 0;
+        if (lane == 0) slot = queue_dealt(n_groups, from) + atomicAdd((unsigned*)&counters[from], 1u);
+        slot = __builtin_amdgcn_readfirstlane(slot);
+        if (slot < per_xcd) return (int)(slot * N_XCD + from);
     }
     return -1;
 }

@@ -401,6 +401,9 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 // more than the interleaving (dK/dV of a 512 x 2048 x 128 target layer 1.21 against 1.30 ms; streaming kernel 1.33).
 // Softmax weights without real-time tokens only (the callers that need the other readings take the streaming kernel).  Most such
 // calls now go through in one pass (hta_bwd_onepass_bf16.hip); left here are mostly those whose query heads per kv head are no power of two.
+// There it is worth its place: of 562 calls that take it (3 to 16 query heads per kv head, 512..4000 keys, 256..3000 items) the whole backward
+// is 1.08 times as fast on average as with the next best form (3 heads: 1.09, 6: 1.09, 12: 1.17; 870 users of up to 1764 keys x 31,
+// 12/2 heads, 816 -> 626 us; at most 0.77 times, on little more than 256 items of unlike lengths).
 template <int D, int NW>
 struct DkdvResident {
     static constexpr int MAX_UNITS = 16;

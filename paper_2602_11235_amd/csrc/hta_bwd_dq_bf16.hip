@@ -157,9 +157,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 1 && NW == 4 ? 3 : 2) voi
     // The dP products start from -delta instead of zero.  With one row block per wave sixteen registers are free to keep it in (opaque,
     // or they would be written anew for every sub-tile), which takes sixteen additions of about seventy vector instructions out of a
     // sub-tile: head_dim 64 with real-time tokens 0.691 -> 0.676 ms (256 users of 512..1024 keys), head_dim 128 16.6 -> 16.2 ms
-    // (128 users of 750..8192 keys), two row blocks per wave 0.936 -> 0.918 (256 users of 1024 keys; thirteen registers for the copies of a
-    // last, ragged tile then wait in scratch, 0.2 GB of traffic on 256 users of 512..1024 keys.  Without: the second block's written every
-    // time in place of the additions, whole steps 1797 against 1799 us there, but 2711 against 2701 on 1024 keys).
+    // (128 users of 750..8192 keys).  With two row blocks thirteen registers for the copies of a last, ragged tile then wait in scratch, 0.2 GB
+    // of traffic on 256 users of 512..1024 keys, and it pays on longer ones only: whole steps with the additions instead, in turn on one
+    // box, 1807 against 1804 us there (another draw of the lengths 1787 against 1792), 2669 against 2658 on 256 users of 1024
+    // keys, 4680 against 4641 on 83 users of 461..4062.
     floatx16 dp0[RB];
     if constexpr (!PW) {
 #pragma unroll

@@ -16,7 +16,8 @@
 // and a compute unit holds two, whose barriers do not meet; above, two groups share the K/V tiles and exchange their sums of phase 2
 // (16 KB per block) so that each finishes half of it.  (Two groups half a block apart, one's matrix products next to the other's
 // exponentials, took as long as in step; so did S of the next block formed in phase 2.)
-// Whole backward, two passes -> this one: that workload 2.09 -> 1.62 ms; 600 users x 1000 keys x 60, 8/2 heads 428 -> 312 us.  Bound by
+// Backward calls back to back, two passes -> this one, in turn on one box: that workload 2.09 -> 1.63 ms; 600 users x 1000 keys x 60, 8/2
+// heads 399 -> 269 us.  Bound by
 // the sum of matrix and vector work: a SIMD is busy with 2560 cycles of products and 2500 of vector instructions per block of 16
 // units, of about 5200.  (Users of more pairs, taken 512 at a time with float32 dK, dV resting in memory in between, were no faster
 // than two passes: 1.52 against 1.39 ms on a full layer of 256 users x 512..1024 keys.)
@@ -38,7 +39,7 @@ constexpr int OP_D = 64;                // head_dim
 constexpr int OP_TILE = 32 * OP_D * 2;  // bytes of a 32-row tile
 constexpr int OP_UNIT = 32 * 32 * 2;    // bytes of a unit's P (or dS) block, [row][key] bf16
 constexpr int OP_SUMS = 4 * 4096;       // bytes of a block's dV, dK (two halves of the features each) in float32
-// A workgroup of NG groups of four waves: packed pairs of a chunk, byte offsets in LDS.  P and dS of the units; Q and dO of the second
+// A workgroup of NG groups of four waves: packed pairs of a user, byte offsets in LDS.  P and dS of the units; Q and dO of the second
 // units; sums that the groups exchange; K/V.  (Q and dO of the first units are where P and dS go while phase 2's operands are
 // taken from them.)
 template <int NG>
@@ -315,8 +316,8 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
         wait_vmem_loads();
         lds_barrier();
 
-        // What the groups made of a block's dV^T (t < 2) or dK^T: the other group's sums of this wave's part of the tile, and of
-        // earlier chunks, to its own; rows of dk, dv where they are final.
+        // What the groups made of a block's dV^T (t < 2) or dK^T: the other group's sums of this wave's part of the tile added to its
+        // own, and the rows of dk, dv stored.
         constexpr int NQ = 4 / NG;  // registers / 4 of the part: with two groups, half of the tile each
         floatx4 mine[NQ];
         auto finish = [&](int i) __attribute__((always_inline)) {
@@ -524,7 +525,7 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
             lds_barrier();
         }
         if (NG > 1 && n_blocks > 0) finish(n_blocks - 1);
-        // ---- dQ of this chunk
+        // ---- dQ
         static_for<0, 2>([&](auto S) {
             constexpr int s = decltype(S)::value;
             const PackedRows::Row x = pr.at((NW * s + wave) * 32 + l32);

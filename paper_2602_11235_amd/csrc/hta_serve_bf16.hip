@@ -351,7 +351,10 @@ int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t ma
 // Estimated times of a call (us) with the keys in one piece, from fits of 2700 calls on both sides of the line (1 to 400 users,
 // 4 to 256 candidates or a full layer, 64 to 8192 keys, all of one length or spread over a factor of 8; with and without
 // real-time tokens and with pointwise weights).  The ordinary kernel, up to a workgroup per unit: the longest one, a little more the
-// fuller the chip, and the schedule and limits launches as they were then (0.02 us per user, 2 us; since less, which 32 users hardly see).
+// fuller the chip, and the schedule and limits launches as they were then: 0.02 us per user, which 32 users hardly see, and 2 us with real-time
+// tokens, whose launch is gone.  (That leaves the ordinary kernel out of some calls where it is the faster one.  Without the 2 us 860 of
+// 3999 calls with real-time tokens near the line change sides: 0.87 of the time on average, but 228 of them slower, by half at
+// most; the kernel for a few requests takes 3 us longer with real-time tokens than estimated.  Both want a fit of their own.)
 static double ordinary_us(const Params& p, int64_t workgroups) {
     struct { double launch, key, key_full; } c;
     if (p.d == 32) c = {6.2, 9.5e-3, 3.5e-3};

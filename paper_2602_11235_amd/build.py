@@ -33,10 +33,15 @@ MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 # whole steps at head_dim 128: 32 users of 60..120 keys 72.0 -> 69.5 us, 200 target layers of 250..1000 keys 422 -> 416.  (The
 # pointwise dK/dV kernel loses by it, 1243 -> 1259 us per step: its unit keeps the default.)
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+# Kernel arguments in scalar registers when a kernel starts, up to the first one that is a struct: the command processor fetches them with the
+# launch, where a load of the kernel's own takes 1100 cycles (0.45 us) before the first address is known.  For the kernels of a few
+# requests, which live for 3 to 30 us and start with those.
+KERNARG_PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
 FILE_FLAGS = {
     "hta_bwd_dq_bf16.hip": MAX_ILP,
     "hta_bwd_dkdv128_bf16.hip": MAX_ILP + VGPR_FORM,
     "hta_bwd_brief_bf16.hip": VGPR_FORM,
+    "hta_serve_bf16.hip": KERNARG_PRELOAD,
 }
 
 

@@ -51,12 +51,6 @@ struct OnePass {
     static_assert(BYTES * (NG > 1 ? 1 : 2) == 160 * 1024, "LDS");
 };
 
-// x summed over aligned groups of W lanes, by exchanges inside the rows of 16 lanes
-template <int CTRL>
-__device__ inline float add_dpp(float x) {
-#pragma clang fp contract(off)  // (a product in x would go into a multiply-add, and the exchange into an instruction of its own)
-    return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
 // Accumulator registers 8 k .. of a tile whose rows are features: a lane of half hf holds features 4 hf .. + 3 (lo) and 8 + 4 hf .. (hi)
 // of 16.  Rounded and exchanged between the halves, it has features 8 hf .. + 7: one store of 16 bytes.
 __device__ inline bf16x8 rows_of_16(floatx4 lo, floatx4 hi, float f) {
@@ -75,15 +69,6 @@ __device__ inline bf16x8 rows_of_16(floatx4 lo, floatx4 hi, float f) {
     return __builtin_bit_cast(bf16x8, o);
 }
 constexpr int OP_MAX_HEADS = 8;
-template <int W>
-__device__ inline float sum_heads(float x) {
-    static_assert(W <= OP_MAX_HEADS, "a mirrored row would follow");
-    if (W > 1) x = add_dpp<0xB1>(x);    // quad_perm [1, 0, 3, 2]
-    if (W > 2) x = add_dpp<0x4E>(x);    // quad_perm [2, 3, 0, 1]
-    if (W > 4) x = add_dpp<0x141>(x);   // row_half_mirror: the quads of an 8-group hold equal sums by now
-    return x;
-}
-
 template <int NG, bool RT, bool PW>
 __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowMap map, unsigned per_xcd) {
     using OP = OnePass<NG>;
@@ -276,8 +261,8 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
                         bf16x8 dk8, dv8;
 #pragma unroll
                         for (int j = 0; j < 8; j++) {
-                            dk8[j] = (__bf16)sum_heads<decltype(W)::value>(fk[s] * (float)q8[j]);
-                            dv8[j] = (__bf16)sum_heads<decltype(W)::value>(fv[s] * (float)do8[j]);
+                            dk8[j] = (__bf16)sum_lanes<decltype(W)::value>(fk[s] * (float)q8[j]);
+                            dv8[j] = (__bf16)sum_lanes<decltype(W)::value>(fv[s] * (float)do8[j]);
                         }
                         if (stores) {
                             *(bf16x8*)((__bf16*)p.dk + koff + ks * 16) = dk8;

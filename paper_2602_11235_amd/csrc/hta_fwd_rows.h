@@ -65,6 +65,16 @@ struct FwdRows {
         }
     }
 
+    // Q fragments out of a swizzled tile of the wave's rows in LDS; L: the history length
+    __device__ __forceinline__ void take_q(const __bf16* tile, int L) {
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+#pragma unroll
+            for (int ks = 0; ks < NKS; ks++) qf[rb][ks] = *(const bf16x8*)(tile + rb * 32 * D + nat[ks]);
+            lim[rb] = L;
+        }
+    }
+
     // Own key of target rows (rule 3) and of real-time rows, straight from global memory: where these rows' softmax starts
     // (reference = the own logit, weight 1), so the loads travel together with the Q fragments instead of in an
     // epilogue.  tok_shift: token index of query row 0.

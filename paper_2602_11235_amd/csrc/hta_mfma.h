@@ -91,6 +91,35 @@ __device__ inline float dot_bf16x8(float acc, bf16x8 x, bf16x8 y) {
     return acc;
 }
 
+__device__ inline float dot_bf16x4(float acc, bf16x4 x, bf16x4 y) {
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 0, 1), __builtin_shufflevector(y, y, 0, 1), acc, false);
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 2, 3), __builtin_shufflevector(y, y, 2, 3), acc, false);
+    return acc;
+}
+
+// x summed over aligned groups of W lanes (a power of two up to 32), every lane of which gets the sum: exchanges inside the rows of
+// 16 lanes, and between two such rows
+template <int CTRL>
+__device__ inline float add_dpp(float x) {
+#pragma clang fp contract(off)  // (a product in x would go into a multiply-add, and the exchange into an instruction of its own)
+    return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+template <int W>
+__device__ inline float sum_lanes(float x) {
+    static_assert(W <= 32, "the other half of the wave would follow");
+    if (W > 1) x = add_dpp<0xB1>(x);    // quad_perm [1, 0, 3, 2]
+    if (W > 2) x = add_dpp<0x4E>(x);    // quad_perm [2, 3, 0, 1]
+    if (W > 4) x = add_dpp<0x141>(x);   // row_half_mirror: the quads of an 8-group hold equal sums by now
+    if (W > 8) x = add_dpp<0x140>(x);   // row_mirror
+    if (W > 16) {
+        const unsigned u = __builtin_bit_cast(unsigned, x);
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        const unsigned lo = r[0], hi = r[1];
+        x = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+    }
+    return x;
+}
+
 // wait until every outstanding vector-memory load of this wave has landed
 __device__ inline void wait_vmem_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 

@@ -41,43 +41,66 @@ struct Serve {
     static constexpr int RPC = 64 / CPR;               // rows per 1 KB copy
     static constexpr int KW = NW / RW;                 // key ways
     static constexpr int COPIES = BLK / RPC / RW;      // copies per wave of its K, and of its V
+    static constexpr int ROWS = RW * RB * SUB;         // packed rows of the workgroup
+    static constexpr int Q_COPIES = ROWS / RPC;        // copies of their Q, dealt to the waves
+    static constexpr int QUADS = D / 4, MERGED = RW * SUB * QUADS;  // 4 features each, of a row block
+    static constexpr int NIT = (MERGED + NW * 64 - 1) / (NW * 64);               // a thread's share of them
     static constexpr int PITCH = D + 4;                // floats per row of the merge buffer (16-byte words spread over the banks)
     static constexpr int MERGE_BYTES = NW * SUB * (PITCH + 2) * 4;
     static constexpr int KV_BYTES = KW * NST * 2 * TILE * 2;
-    static constexpr int BYTES = KV_BYTES > MERGE_BYTES ? KV_BYTES : MERGE_BYTES;
+    static constexpr int Q = KV_BYTES, BEFORE = Q + ROWS * D * 2;
+    static constexpr int BYTES = BEFORE > MERGE_BYTES ? BEFORE : MERGE_BYTES;
 };
 constexpr int TS_CAP = 512;  // real-time tokens of a user whose timestamps are searched in LDS
 
+// How a launch's workgroups map to work, with what takes the place of divisions in the kernel (a workgroup of a small call lives for 3 us,
+// of which the divisions of a general decode took 0.3).  Grid: x = XCD + 8 * (tile / spread), y = group / 8.  A group is (user, kv
+// head, head chunk, split, one of `spread` shares of the tiles): its row tiles read the same keys and stay on one XCD, the splits of an item
+// go to different ones.
+struct ServeGrid {
+    uint32_t n_groups, spread_log2;       // spread: 1 or 2
+    uint32_t ny, ny_magic;               // groups of a user; 2^32 / ny, rounded up (0: ny is 1)
+    uint32_t n_splits, splits_magic;     // likewise
+    int32_t per;                         // blocks of keys per split
+};
+inline uint32_t div_magic(uint32_t d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / d + 1); }
+// n / d for n d < 2^32
+__device__ inline uint32_t div_by(uint32_t n, uint32_t magic) { return magic == 0 ? n : __umulhi(n, magic); }
+
+// The arrays that the first loads go to and what finds the user stand alone at the front: arguments in scalar registers when the kernel
+// starts (build.py, KERNARG_PRELOAD), while those inside Params take a load that costs 0.45 us at the start of a launch.
 template <int D, int RB, int RW, int NW, int SPS, int NST, bool RT, bool PW>
-__global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(Params p, RowMap map, int spread) {
+__global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* hist_len, const int32_t* n_targets, const int32_t* q_off,
+                                                                const int32_t* kv_off, const int32_t* rt_len, uint32_t ny, uint32_t ny_magic,
+                                                                ServeGrid sg, Params p, RowMap map) {
     using SV = Serve<D, RB, RW, NW, SPS, NST>;
-    constexpr int BLK = SV::BLK, CP = SV::COPIES, KW = SV::KW;
+    constexpr int BLK = SV::BLK, CP = SV::COPIES, KW = SV::KW, QUADS = SV::QUADS, NIT = SV::NIT;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[SV::BYTES];
-    __shared__ int ts_s[RT ? TS_CAP : 1];
+    __shared__ __attribute__((aligned(256))) int ts_s[RT ? TS_CAP : 1], row_ts[RT ? SV::ROWS * 2 : 1];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-    // A group here is (user, kv head, head chunk, split): its row tiles, which read the same keys, go to `spread` XCDs, and the
-    // splits of an item to different ones.
-    const int ny = p.Hkv * map.n_chunks * p.n_splits * spread;
-    WorkItem w = decode_work(blockIdx.x, p.batch * ny, ny, (map.n_tiles + spread - 1) / spread);
-    if (!w.valid) return;
-    const int b = w.user_slot;
-    w.tile = w.tile * spread + w.y % spread;
-    w.y /= spread;
-    const int gc = p.n_splits == 1 ? w.y : w.y / p.n_splits, split = w.y - gc * p.n_splits;
+    const uint32_t group = blockIdx.y * N_XCD + blockIdx.x % N_XCD;
+    if (group >= sg.n_groups) return;
+    const int b = (int)div_by(group, ny_magic);
+    const int L = hist_len[b], T = n_targets[b], R = RT ? rt_len[b] : 0;
+    const int64_t q_base = q_off[b], kv_base = kv_off[b];
+    const uint32_t y = (group - (uint32_t)b * ny) >> sg.spread_log2;
+    const int tile = (int)((blockIdx.x / N_XCD << sg.spread_log2) + (group & ((1u << sg.spread_log2) - 1u)));
+    const int gc = (int)div_by(y, sg.splits_magic), split = (int)y - gc * (int)sg.n_splits;
     const int g = map.n_chunks == 1 ? gc : gc / map.n_chunks, chunk = gc - g * map.n_chunks;
-    const int L = p.hist_len[b], T = p.n_targets[b], R = RT ? p.rt_len[b] : 0;
-    const int64_t q_base = p.q_off[b], kv_base = p.kv_off[b];
     const int LK = L + R;  // keys that run through the tile loop: history, then real-time
     const int n_rows = p.layer == 0 ? LK + T : T;
-    if (w.tile * map.rows >= n_rows) return;  // uniform for the whole workgroup
-    const PackedRows pr(map, w.tile, chunk, n_rows, g, p.Hq / p.Hkv);
+    const int n_all = (LK + BLK - 1) / BLK, lo = min(split * sg.per, n_all), hi = min(lo + sg.per, n_all);
+    if (tile * map.rows >= n_rows) return;  // uniform for the whole workgroup
+    const PackedRows pr(map, tile, chunk, n_rows, g, p.Hq / p.Hkv);
+    if (!PW && split > 0 && lo >= n_all) {  // a user whose keys end before this split
+        const PackedRows::Row x = pr.at(tid);
+        if (tid < SV::ROWS && x.live) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + q_base + x.row] = -INFINITY;
+        return;
+    }
     const int tok_shift = p.layer == 0 ? 0 : LK;  // token index of query row 0
     const int rw = wave / KW, kw = wave % KW, rho0 = rw * RB * 32;
     const bool wave_live = RW == 1 || pr.any_from(rho0);
-
-    const int n_all = (LK + BLK - 1) / BLK;
-    const int lo = (int)((int64_t)split * n_all / p.n_splits), hi = (int)((int64_t)(split + 1) * n_all / p.n_splits);
     const int n_mine = hi - lo > kw ? (hi - lo - kw + KW - 1) / KW : 0;  // steps of this key way: blocks lo + kw + i KW
 
     // K or V of step i to its slot.  Keys past the end repeat the last one (their weight is forced to zero).
@@ -107,8 +130,39 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(Params p, RowMap
             }
         }
     };
-    if (RT && R <= TS_CAP && wave * 64 < R && wave < TS_CAP / 64)
-        copy4_global_to_lds_at(p.ts + kv_base + L + min(wave * 64 + lane, R - 1), lds_address(ts_s) + wave * 256u);
+    // (from the tile's first row on 32 bits suffice for a lane's offset)
+    const __bf16* const q_tile = (const __bf16*)p.q + (q_base + pr.row0) * p.Hq * D;
+    const int64_t own_tile = ((kv_base + tok_shift + pr.row0) * p.Hkv + g) * D;
+    // What the rows need comes first, the K and V behind it: 128 KB of copies per unit take their time to be issued alone.
+    if constexpr (RT) {
+        if (R <= TS_CAP && wave * 64 < R && wave < TS_CAP / 64)
+            copy4_global_to_lds_at(p.ts + kv_base + L + min(wave * 64 + lane, R - 1), lds_address(ts_s) + wave * 256u);
+        if (wave < SV::ROWS / 32)  // (one row to two lanes)
+            copy4_global_to_lds_at(p.ts + kv_base + tok_shift + pr.at(wave * 32 + l32).row, lds_address(row_ts) + wave * 256u);
+    }
+    for (int j = wave; j < SV::Q_COPIES; j += NW) {
+        const int trow = j * SV::RPC + lane / SV::CPR;
+        const PackedRows::Row x = pr.at(trow);
+        copy16_global_to_lds_at(q_tile, (uint32_t)(((x.row - pr.row0) * p.Hq + x.h) * D + ((lane % SV::CPR) ^ swizzle<D>(trow)) * 8) * 2u,
+                                lds_address(smem) + (uint32_t)(SV::Q + j * 1024));
+    }
+    // The own key of target rows (rule 3) and of real-time rows joins in the merge: its logit and weight are formed by the threads that
+    // hold 4 features of the row there.  Requested here, used behind the key loop.
+    bf16x4 own_q[RB][NIT], own_k[RB][NIT], own_v[RB][NIT];
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+        for (int it = 0; it < NIT; it++) {
+            own_q[rb][it] = own_k[rb][it] = own_v[rb][it] = bf16x4{};
+            if (split == 0) {
+                const int id = tid + it * NW * 64, c = id % QUADS, rl = id / QUADS;
+                const PackedRows::Row x = pr.at((rl / SUB * RB + rb) * 32 + rl % SUB);
+                const uint32_t koff = (uint32_t)((x.row - pr.row0) * p.Hkv * D + 4 * c);
+                own_q[rb][it] = *(const bf16x4*)(q_tile + (uint32_t)(((x.row - pr.row0) * p.Hq + x.h) * D + 4 * c));
+                own_k[rb][it] = *(const bf16x4*)((const __bf16*)p.k + own_tile + koff);
+                own_v[rb][it] = *(const bf16x4*)((const __bf16*)p.v + own_tile + koff);
+            }
+        }
 #pragma unroll
     for (int i = 0; i < NST; i++) {
         fetch(kg, i, 0);
@@ -117,30 +171,26 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(Params p, RowMap
 
     FwdRows<D, RB, RT, PW> rows;
     rows.init_lane(p, lane);
-    rows.load_q(p, pr, rho0, q_base, L, lane);
     rows.reset();
-    if (split == 0 && kw == 0) rows.start_from_own_key(p, pr, rho0, kv_base, g, tok_shift, L, lane);
+    if (n_mine >= NST) wait_vmem_outstanding<2 * CP * NST>(); else wait_vmem_outstanding<0>();
+    lds_barrier();
+    rows.take_q((const __bf16*)(smem + SV::Q) + rw * RB * SUB * D, L);
     if constexpr (RT) {
         // mask rule 2: the row sees the history and the real-time tokens strictly earlier than itself, a prefix
         const int32_t* ts = p.ts + kv_base + L;
-        int t[RB];
-#pragma unroll
-        for (int rb = 0; rb < RB; rb++) t[rb] = p.ts[kv_base + tok_shift + pr.at(rho0 + rb * 32 + l32).row];
-        wait_vmem_loads();
-        lds_barrier();
 #pragma unroll
         for (int rb = 0; rb < RB; rb++) {
+            const int t = row_ts[(rw * RB + rb) * 64 + lane];
             int a = 0, e = R;
             while (a < e) {
                 const int mid = (a + e) >> 1;
                 const int v = R <= TS_CAP ? ts_s[mid] : ts[mid];
-                if (v < t[rb]) a = mid + 1; else e = mid;
+                if (v < t) a = mid + 1; else e = mid;
             }
             rows.lim[rb] = L + a;
         }
     }
 
-    wait_vmem_loads();  // from here on the only vector-memory traffic of the loop are the copies, counted below
     // wait until at most n steps' K and V, and then (Half: V, or the K of one more step), are in flight
     auto wait_copies = [&](int steps, bool half) __attribute__((always_inline)) {
         if (NST > 1 && steps >= 1) {
@@ -177,6 +227,18 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(Params p, RowMap
     for (int i = 0; i < n_whole; i++) step(i, std::false_type{});
     for (int i = n_whole; i < n_rounds; i++) step(i, std::true_type{});
 
+    // ---- the own keys' logits, summed over the threads of a row: log2 units (PW: the weight itself), -inf (0) where there is none
+    float own[RB][NIT];
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+        for (int it = 0; it < NIT; it++) {
+            const int rl = (tid + it * NW * 64) / QUADS;
+            const bool has = split == 0 && tok_shift + pr.at((rl / SUB * RB + rb) * 32 + rl % SUB).row >= L;
+            float dot = dot_bf16x4(0.f, own_q[rb][it], own_k[rb][it]);
+            dot = sum_lanes<QUADS>(dot);
+            own[rb][it] = PW ? (has ? pw_silu(dot, pw_sigmoid(dot, rows.neg_c2)) : 0.f) : (has ? dot * rows.c2 : -INFINITY);
+        }
     // ---- merge the waves' results through LDS, one row block after the other
     float* acc = (float*)smem;                          // [wave][row][PITCH]
     float* stat = acc + NW * SUB * SV::PITCH;           // [wave][row][m, l]
@@ -201,34 +263,41 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(Params p, RowMap
             }
     }
     lds_barrier();
-    constexpr int QUADS = D / 4;
-    for (int id = tid; id < RW * SUB * QUADS; id += NW * 64) {
-        const int c = id % QUADS, rl = id / QUADS, l = rl % SUB, w0 = rl / SUB * KW;  // 4 features of a row; its first wave
+#pragma unroll
+    for (int it = 0; it < NIT; it++) {
+        const int id = tid + it * NW * 64;
+        const int c = id % QUADS, rl = id / QUADS, l = rl % SUB, w0 = rl / SUB % RW * KW;  // 4 features of a row; its first wave
         const PackedRows::Row x = pr.at((rl / SUB * RB + rb) * 32 + l);
-        float mx = -1e30f;
-        float mk[KW];
+        float mx = PW ? 0.f : fmaxf(own[rb][it], -1e30f);
+        float2 ml[KW];
         if constexpr (!PW) {
 #pragma unroll
             for (int k = 0; k < KW; k++) {
-                mk[k] = stat[((w0 + k) * SUB + l) * 2];
-                mx = fmaxf(mx, mk[k]);
+                ml[k] = *(const float2*)(stat + ((w0 + k) * SUB + l) * 2);
+                mx = fmaxf(mx, ml[k].x);
             }
         }
-        float sum = 0.f;
         floatx4 o = {0.f, 0.f, 0.f, 0.f};
+        float sum = 0.f;
+        if (PW || own[rb][it] > -INFINITY) {
+            const float f = PW ? own[rb][it] : fast_exp2(own[rb][it] - mx);
+            sum = f;
+#pragma unroll
+            for (int j = 0; j < 4; j++) o[j] = f * (float)own_v[rb][it][j];
+        }
 #pragma unroll
         for (int k = 0; k < KW; k++) {
-            const float f = PW ? 1.f : fast_exp2(mk[k] - mx);  // 0 for a wave that saw no key
+            const float f = PW ? 1.f : fast_exp2(ml[k].x - mx);  // 0 for a wave that saw no key
             const floatx4 ok = *(const floatx4*)(acc + ((w0 + k) * SUB + l) * SV::PITCH + 4 * c);
-            if constexpr (!PW) sum = fmaf(f, stat[((w0 + k) * SUB + l) * 2 + 1], sum);
+            if constexpr (!PW) sum = fmaf(f, ml[k].y, sum);
 #pragma unroll
             for (int j = 0; j < 4; j++) o[j] = fmaf(f, ok[j], o[j]);
         }
-        if (!x.live) continue;
+        if (!x.live || id >= SV::MERGED) continue;
         const float inv = PW ? p.norm * p.scale : (sum > 0.f ? 1.f / sum : 0.f);
         const float lse = sum > 0.f ? (mx + __builtin_amdgcn_logf(sum)) * LN2 : -INFINITY;
         const int64_t row = q_base + x.row;
-        if (p.n_splits == 1) {
+        if (sg.n_splits == 1) {
             bf16x4 o4;
 #pragma unroll
             for (int j = 0; j < 4; j++) o4[j] = (__bf16)(o[j] * inv);
@@ -248,68 +317,87 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(Params p, RowMap
 // out = sum_s w_s O_s / sum_s w_s with w_s = exp(lse_s - max lse), lse = max lse + log sum_s w_s: the exact
 // combination of softmax results over disjoint key sets.  One thread per 4 features of a (row, head).
 // PW: the partial results are partial sums of non-normalised weights: out = sum_s O_s, no lse.
-template <bool PW>
-__global__ __launch_bounds__(256) void merge_splits_kernel(Params p) {
-    const int64_t quads = p.d / 4;
+// All loads of a thread travel together, AT_ONCE splits of them: one trip to memory is most of what this launch takes.  (Split after split,
+// as the remainder of an unrolled loop is: 2 us more for 4 splits.)
+template <int D, int AT_ONCE, bool PW>
+__global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, const float* lse_part, int64_t total_q, int Hq, int n_splits,
+                                                           void* out, float* lse) {
+    constexpr int QUADS = D / 4;
     const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (id >= p.total_q * p.Hq * quads) return;
-    const int c = (int)(id % quads);
-    const int64_t rh = id / quads;
-    const int h = (int)(rh % p.Hq);
-    const int64_t row = rh / p.Hq;
-    // all loads of a thread are independent: issue them in batches of eight instead of one memory latency per split
-    const float* lp = p.lse_part + (int64_t)h * p.total_q + row;
-    const float* op = p.o_part + (row * p.Hq + h) * p.d + 4 * c;
-    const int64_t l_stride = (int64_t)p.Hq * p.total_q, o_stride = p.total_q * p.Hq * p.d;
-    float mx = -INFINITY;
-    if constexpr (!PW) {
-#pragma unroll 8
-        for (int s = 0; s < p.n_splits; s++) mx = fmaxf(mx, lp[s * l_stride]);
-    }
-    float sum = 0.f;
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int s = 0; s < p.n_splits; s++) {
-        const float w = PW ? 1.f : __expf(lp[s * l_stride] - mx);
-        const floatx4 o = *(const floatx4*)(op + s * o_stride);
-        sum += w;
-        acc += w * o;
+    if (id >= total_q * Hq * QUADS) return;
+    const uint32_t rh = (uint32_t)(id / QUADS), row = rh / (uint32_t)Hq, h = rh - row * (uint32_t)Hq;  // (both below 2^31)
+    const int64_t at_lse = (int64_t)h * total_q + row, l_stride = (int64_t)Hq * total_q, o_stride = total_q * Hq * D;
+    floatx4 o = {0.f, 0.f, 0.f, 0.f};
+    float mx = -INFINITY, sum = 0.f;
+    for (int s0 = 0; s0 < n_splits; s0 += AT_ONCE) {
+        floatx4 os[AT_ONCE];
+        float ls[AT_ONCE];
+#pragma unroll
+        for (int s = 0; s < AT_ONCE; s++) {  // (behind the last one: the last one again)
+            const int i = min(s0 + s, n_splits - 1);
+            ls[s] = PW ? 0.f : lse_part[at_lse + i * l_stride];
+            os[s] = *(const floatx4*)(o_part + id * 4 + i * o_stride);
+        }
+        const float before = mx;
+        if constexpr (!PW) {
+#pragma unroll
+            for (int s = 0; s < AT_ONCE; s++) mx = fmaxf(mx, ls[s]);
+            const float f = before > -INFINITY ? __expf(before - mx) : 0.f;
+            sum *= f;
+            o *= f;
+        }
+#pragma unroll
+        for (int s = 0; s < AT_ONCE; s++) {
+            const float w = s0 + s >= n_splits ? 0.f : PW ? 1.f : __expf(ls[s] - mx);
+            sum += w;
+#pragma unroll
+            for (int j = 0; j < 4; j++) o[j] = s0 + s >= n_splits || (!PW && ls[s] == -INFINITY) ? o[j] : fmaf(w, os[s][j], o[j]);  // (-inf: nothing was left)
+        }
     }
     const float inv = PW ? 1.f : 1.f / sum;
     bf16x4 o4;
 #pragma unroll
-    for (int j = 0; j < 4; j++) o4[j] = (__bf16)(acc[j] * inv);
-    *(bf16x4*)((__bf16*)p.out + (row * p.Hq + h) * p.d + 4 * c) = o4;
-    if (!PW && c == 0) p.lse[(int64_t)h * p.total_q + row] = mx + __logf(sum);
+    for (int j = 0; j < 4; j++) o4[j] = (__bf16)(o[j] * inv);
+    *(bf16x4*)((__bf16*)out + id * 4) = o4;
+    if (!PW && id % QUADS == 0) lse[at_lse] = mx + __logf(sum);
 }
 
 template <int D, int RB, int RW, int NW, int SPS, int NST>
 hipError_t launch(const Params& p, hipStream_t s) {
-    void (*kernel)(Params, RowMap, int);
+    auto kernel = serve_kernel<D, RB, RW, NW, SPS, NST, false, false>;
     if (p.pointwise)
         kernel = p.rt_len ? serve_kernel<D, RB, RW, NW, SPS, NST, true, true> : serve_kernel<D, RB, RW, NW, SPS, NST, false, true>;
-    else
-        kernel = p.rt_len ? serve_kernel<D, RB, RW, NW, SPS, NST, true, false> : serve_kernel<D, RB, RW, NW, SPS, NST, false, false>;
+    else if (p.rt_len)
+        kernel = serve_kernel<D, RB, RW, NW, SPS, NST, true, false>;
     const int64_t rows = max_query_rows(p);
     if (rows <= 0) return hipSuccess;
     const RowMap map = row_map(RW * RB * 32, p.Hq, p.Hkv, rows);
+    const int64_t max_blocks = (max_lead_keys(p) + SUB * SPS - 1) / (SUB * SPS);
+    ServeGrid sg;
+    sg.per = (int32_t)std::max<int64_t>((max_blocks + p.n_splits - 1) / p.n_splits, 1);
+    sg.n_splits = (uint32_t)std::max<int64_t>((max_blocks + sg.per - 1) / sg.per, 1);
     // One XCD per group is best for its L2; two when there are so few groups that an XCD of 32 units can get more
     // workgroups than it has units while others idle (14 requests of 1053 keys, 28 groups: 23 -> 14 us).
-    const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks * p.n_splits;
+    const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks * sg.n_splits;
     const int spread = groups < 64 && (groups + N_XCD - 1) / N_XCD * map.n_tiles > 32 ? 2 : 1;
-    const int64_t n_blocks = work_grid(groups * spread, (map.n_tiles + spread - 1) / spread);
-    if (n_blocks >= (1ll << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p, map, spread);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && p.n_splits > 1) {
-        const int64_t threads = p.total_q * p.Hq * (p.d / 4);
-        if (p.pointwise)
-            hipLaunchKernelGGL(merge_splits_kernel<true>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p);
-        else
-            hipLaunchKernelGGL(merge_splits_kernel<false>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p);
-        e = hipGetLastError();
-    }
-    return e;
+    sg.ny = (uint32_t)(groups / p.batch * spread);
+    sg.spread_log2 = spread / 2;
+    sg.n_groups = sg.ny * (uint32_t)p.batch;
+    sg.ny_magic = div_magic(sg.ny);
+    sg.splits_magic = div_magic(sg.n_splits);
+    const int64_t nx = (int64_t)((map.n_tiles + spread - 1) / spread) * N_XCD, n_y = (sg.n_groups + N_XCD - 1) / N_XCD;
+    if (nx * n_y >= (1ll << 31) || n_y > 65535 || (int64_t)sg.n_groups * sg.ny >= (1ll << 32)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nx, (unsigned)n_y), dim3(NW * 64), 0, s, p.hist_len, p.n_targets, p.q_off, p.kv_off, p.rt_len, sg.ny,
+                       sg.ny_magic, sg, p, map);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || sg.n_splits == 1) return e;
+    const int64_t threads = p.total_q * p.Hq * (p.d / 4);
+    auto merge = merge_splits_kernel<D, 8, false>;
+    if (p.pointwise) merge = sg.n_splits <= 2 ? merge_splits_kernel<D, 2, true> : sg.n_splits <= 4 ? merge_splits_kernel<D, 4, true> : merge_splits_kernel<D, 8, true>;
+    else if (sg.n_splits <= 4) merge = sg.n_splits <= 2 ? merge_splits_kernel<D, 2, false> : merge_splits_kernel<D, 4, false>;
+    hipLaunchKernelGGL(merge, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
+                       p.o_part, p.lse_part, p.total_q, p.Hq, (int)sg.n_splits, p.out, p.lse);
+    return hipGetLastError();
 }
 
 // workgroups with work to do: `lanes` packed rows each, from the bounds and the number of query rows of the call

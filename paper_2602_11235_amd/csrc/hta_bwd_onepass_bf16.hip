@@ -568,16 +568,15 @@ hipError_t launch(const Params& p, hipStream_t s) {
 }  // namespace
 
 // Which calls: those whose users' pairs fit, and whose estimated time is below that of the other forms by a margin that covers what
-// the estimates miss.  Both (us) are fitted to 399 target layers timed in both forms (1..512 pairs, 20..4000 keys, 76..3000 items =
-// users x kv heads; with real-time tokens and pointwise weights, too): two passes cost by items x units x blocks of 32 keys, by the rows
-// and the keys they read, and by the longest user; here an item costs a prologue and its blocks, 512 (256) of them run at a time
-// and the last round is as long as any.  The longest item counts with the most pairs that a user has, not with the mean's: 160
-// users of up to 3407 keys x 75 candidates, 8/2 heads, take 234 us in two passes and 293 here.  (Full layers of few rows are costed too high
-// as two passes, whose rows are more alike there: a fifth more is asked.)
-// How it fares, on 4816 calls timed in both forms (2056 target layers and 2760 full ones; 8..512 pairs, 16..4145 keys, 76..15952 items): 1809
-// are taken, 1.39 times as fast in one pass on average (at most 2.2; full layers 1.38); eight of them, three of them full layers, are slower by more
-// than 3 %, the worst by 14 (full: 7).  It errs on the safe side: of the 3007 others 1645 would gain 15 % or more, mostly small calls, since
-// the fits were made when leaving the work queue cost up to 45 us.
+// the estimates miss.  Both (us): two passes cost by items (users x kv heads) x units x blocks of 32 keys, by the rows and the keys they read,
+// and by the longest user; here an item costs a prologue and its blocks, 512 (256) of them run at a time and the last round takes as long as
+// any.  The longest item counts with the most pairs that a user has, not with the mean's: 160 users of up to 3407 keys x 75
+// candidates, 8/2 heads, take 234 us in two passes and 293 here.  Three fits, since what the passes are made of changes: full layers; target
+// layers on less than 512 keys; and on more, where two passes may keep a user's rows resident.
+// On 7808 calls timed in both forms (full and target layers; 1..512 pairs, 16..4145 keys, 76..15952 items; with real-time tokens
+// and pointwise weights, too) one pass takes 0.79 of the time of two and is faster on nine of ten.  Where it is not, a few workgroups
+// make a second round (there it has to win by a fifth) or most units are idle.  The line takes 6070 of them, 100 of these slower than in two passes by
+// more than 3 %, and leaves 2 % of the time; the one before, fitted when leaving the work queue cost up to 45 us, took 2952 and left 12 %.
 bool bwd_is_onepass(const Params& p) {
     const int r = p.Hq / p.Hkv;
     if (p.d != OP_D || !power_of_two(r) || r > OP_MAX_HEADS || p.total_q == 0 || max_query_rows(p) * r > OnePass<2>::LANES || bwd_is_brief(p))
@@ -585,21 +584,29 @@ bool bwd_is_onepass(const Params& p) {
     const double items = (double)p.batch * p.Hkv, pairs = mean_rows(p) * r, most = (double)max_query_rows(p) * r;
     const double keys = mean_keys(p), longest = (double)max_lead_keys(p);
     const double units = pairs / 32. + 0.5, blocks = keys / 32. + 0.5;
-    const double product = 0.67 * (p.pointwise ? 1.4 : 1.) * (p.rt_len ? 1.43 : 1.);
-    const double two_passes = 10.4 + items / 1024. * (product * units * blocks + 9.4 * units + 4.6 * blocks) + (0.34 * longest + 0.2 * most) / 32.;
+    const bool rt = p.rt_len != nullptr, pw = p.pointwise, full = p.layer == 0, resident = !full && keys >= 512.;
+    struct { double launch, product, pw, rt, unit, block, item, longest, most, rt_launch; } t;
+    if (full) t = {5.7, 0.36, 0.95, 2.5, 6.0, 7.1, 6.4, 0.26, 0.36, 1.0};
+    else if (resident) t = {10.4, 0.67, 1.4, 1.43, 9.4, 4.6, 0., 0.34, 0.2, 0.};
+    else t = {3.9, 0.62, 1.4, 1.2, 8.1, 4.6, 5.1, 0.32, 0.67, 2.8};
+    const double two_passes = t.launch + (rt ? t.rt_launch : 0.) + (t.longest * longest + t.most * most) / 32. +
+                              items / 1024. * (t.product * (pw ? t.pw : 1.) * (rt ? t.rt : 1.) * units * blocks + t.unit * units + t.block * blocks + t.item);
 
     const int groups = single_group(p) ? 1 : 2;
+    const double rounds = items * groups / 512., whole = std::ceil(rounds - 0.01);
+    struct { double launch, fixed, unit, block, second, alone, alone_second, partial, jagged, rt, pw; } c;
+    if (resident && groups == 1) c = {rounds <= 0.5 ? 5.6 : 16.6, 17.9, 1.2, 1.5, 0.69, 1.16, 0.35, 0., 0.55, 1.1, 1.035};
+    else if (resident) c = {16.6, 7.7, 0.6, 1.85, 0.5, 1.85, 0.5, 0., 0.55, 1.1, 1.035};
+    else if (groups == 1) c = {5.6, 7.6, 0.96, 1.8, 0.72, 1.2, 0.34, 0.39, 0.44, 1.1, 0.99};
+    else c = {5.1, 5.9, 0.65, 2.1, 0.47, 1.1, 1.3, 0.18, 0.48, 1.1, 0.93};
     const double first_units = 128. * groups;  // pairs that the waves hold with one unit each
     auto two_units = [&](double x) { return most > first_units ? std::min(1., std::max(0., (x - first_units) / (0.25 * first_units) + 0.5)) : 0.; };
-    const double second = two_units(pairs), second_of_last = two_units(most);
-    const double fixed = (groups == 1 ? 18.5 : 8.) + 1.2 * pairs / 32. / groups;
-    const double block = groups == 1 ? 1.5 + 0.69 * second : 1.85 + 0.5 * second;
-    // of the longest item (one group: with no second workgroup on the compute unit)
-    const double alone = groups == 1 ? 1.16 + 0.35 * second_of_last : 1.85 + 0.5 * second_of_last;
-    const double item = fixed + block * blocks, last = fixed + alone * longest / 32., rounds = items * groups / 512.;
-    double t = groups == 1 && rounds <= 0.5 ? last - 11. : std::max(last, (keys >= 0.9 * longest ? std::ceil(rounds - 0.01) : rounds + 0.55) * item);
-    t *= (p.rt_len ? 1.1 : 1.) * (p.pointwise ? 1.035 : 1.);
-    return 16.6 + t + 14. < two_passes * (p.layer == 0 ? 0.85 : 1.);
+    const double fixed = c.fixed + c.unit * units;
+    const double item = fixed + (c.block + c.second * two_units(pairs)) * blocks;
+    const double last = fixed + (c.alone + c.alone_second * two_units(most)) * longest / 32.;  // of the longest item
+    const double many = keys >= 0.9 * longest ? whole + c.partial * (rounds - whole) : std::max(rounds + c.jagged, 1.);
+    const double one_pass = c.launch + std::max(last, many * item) * (rt ? c.rt : 1.) * (pw ? c.pw : 1.);
+    return resident ? one_pass + 5. < two_passes : one_pass < two_passes * (rounds > 1.02 && rounds < 1.5 ? 0.8 : 0.93);
 }
 
 hipError_t launch_bwd_onepass_bf16(const Params& p, hipStream_t s) {

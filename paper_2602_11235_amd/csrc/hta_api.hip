@@ -297,7 +297,7 @@ static int fwd_impl(const void* q, const void* k, const void* v, void* out, floa
         if (dtype == MTFM_HTA_FP32) e = hta::launch_rt_limits(p, s);  // (else with the schedule)
     }
     if (e == hipSuccess && dtype == MTFM_HTA_BF16) {
-        if (p.n_splits == 0) {
+        if (p.n_splits == 0 && hta::forward_needs_schedule(p)) {
             void* region = (char*)workspace + w.order_off;
             e = hta::launch_schedule(p, region, s);
             p.order = hta::schedule_order(region);
@@ -424,7 +424,7 @@ static int bwd_impl(const void* dout, const void* q, const void* k, const void* 
     const bool onepass = dtype == MTFM_HTA_BF16 && hta::bwd_is_onepass(p);
     const bool brief = dtype == MTFM_HTA_BF16 && hta::bwd_is_brief(p);  // (forms the limits itself, and needs no schedule)
     if (dtype == MTFM_HTA_FP32 && has_rt) e = hta::launch_rt_limits(p, s);  // (bf16: with the schedule)
-    if (e == hipSuccess && dtype == MTFM_HTA_BF16 && !brief) {
+    if (e == hipSuccess && dtype == MTFM_HTA_BF16 && !brief && hta::backward_needs_schedule(p, onepass)) {
         void* region = (char*)workspace + w.order_off;
         e = hta::launch_schedule(p, region, s);
         p.order = hta::schedule_order(region);

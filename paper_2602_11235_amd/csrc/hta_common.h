@@ -132,6 +132,9 @@ constexpr int N_XCD = 8;
 constexpr int QUEUE_DKDV = 0;  // kernel kinds that take their work from counters
 constexpr int QUEUE_WORDS = 64;
 size_t schedule_bytes(int32_t batch);
+// Does it pay for its launch?  (p.order and p.queue stay null otherwise: users in the order given, kernels without a queue.)
+bool forward_needs_schedule(const Params& p);
+bool backward_needs_schedule(const Params& p, bool onepass);
 hipError_t launch_schedule(const Params& p, void* region, hipStream_t s);
 inline int32_t* schedule_order(void* region) { return (int32_t*)region + QUEUE_WORDS; }
 inline int32_t* schedule_queue(void* region, int kind) { return (int32_t*)region + kind * N_XCD; }

@@ -28,6 +28,7 @@ SHAPES = {
     "one_way": (TARGET, 330, 0, 0, (8, 2, 64), False),
     "one_way_rt": (TARGET, 330, 0, 0, (6, 2, 64), True),
     "one_way_single_heads": (FULL, 400, 0, 0, (4, 4, 64), False),
+    "one_way_single_heads_long": (FULL, 400, (500,), 0, (4, 4, 64), False),
     "two_ways": (FULL, 160, 0, 0, (8, 2, 64), False),
     "two_ways_rt": (FULL, 160, 0, 0, (8, 2, 64), True),
     "four_ways": (FULL, 64, 0, 0, (8, 2, 64), True),
@@ -73,6 +74,15 @@ def make(name):
 def test_shapes(name):
     case, users = make(name)
     check_case(case, with_bwd=True, users=users, compare=close_on_row_scale)
+
+
+# users of one length, which the library takes in the order given (no launch that orders them): a few long tiles, a key block's rows shared by
+# four, two and one waves, and (head_dim 32) kernels with a work queue, which have theirs cleared by that launch
+@pytest.mark.parametrize("layer,users,hist,targets,heads", [(FULL, 60, 200, 20, (8, 2, 64)), (FULL, 160, 129, 33, (8, 2, 64)), (FULL, 400, 65, 7, (6, 6, 64)),
+                                                            (TARGET, 300, 500, 20, (16, 2, 128)), (FULL, 500, 520, 9, (4, 2, 32))])
+def test_users_of_one_length(layer, users, hist, targets, heads):
+    cfg = inputs.custom_config("one_length", layer, np.full(users, hist), np.full(users, targets), *heads, seed=78)
+    check_case(inputs.make_case(cfg), with_bwd=True, users=[0, 1, users // 2, users - 1], compare=close_on_row_scale)
 
 
 @pytest.mark.parametrize("name", ["rows_resident", "rows_resident_r6"])

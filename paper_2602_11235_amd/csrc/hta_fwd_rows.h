@@ -157,6 +157,19 @@ struct FwdRows {
             }
     }
 
+    // the same for one sub-tile with the Q fragments in LDS (`tile`: the wave's rows, swizzled), where registers do not hold them
+    __device__ __forceinline__ void scores_of_lds(floatx16 (&S)[1][RB], const __bf16* Ks, const __bf16* tile) {
+#pragma unroll
+        for (int ks = 0; ks < NKS; ks++) {
+            const bf16x8 kf = *(const bf16x8*)(Ks + nat[ks]);
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++) {
+                const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                S[0][rb] = mfma32(kf, *(const bf16x8*)(tile + rb * 32 * D + nat[ks]), ks == 0 ? zero : S[0][rb]);
+            }
+        }
+    }
+
     // mask, weights and the PV products of the sub-tiles whose scores are S
     template <bool TAIL, int NS>
     __device__ __forceinline__ void absorb(floatx16 (&S)[NS][RB], const __bf16* Vs, int n_live, int k0, int L) {

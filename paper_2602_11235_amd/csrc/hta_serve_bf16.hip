@@ -2,13 +2,12 @@
 // candidates of a scenario, or a few of them in one call.  Same mask and products as hta_fwd_bf16.hip; what differs is
 // what bounds it: the work of a call is a few microseconds of the chip, so latencies count and not rates.
 //
-// Work decomposition: one workgroup = (user, kv head, RW * RB blocks of 32 packed (row, head) pairs, key split).  Its eight
-// waves are RW row groups x KW key ways: the waves of a row group take every KW-th block of keys, each with a softmax
-// of its own, and merge their results through LDS at the end.  Splitting the keys inside the workgroup costs no memory
-// traffic and no second launch, so it comes first; only when that leaves units idle long enough to pay for the merge
-// launch are the keys split over workgroups as well.
-// With RW = 1 no two waves read the same key: nothing is shared, a wave waits for its own copies only and the key loop
-// has no barrier.  K and V travel global -> LDS asynchronously; the K of the next block is requested when the scores of
+// Work decomposition: one workgroup = (user, kv head, one or two blocks of 32 packed (row, head) pairs, key split).  Its eight waves
+// take every eighth block of keys, each with a softmax of its own, and merge their results through LDS at the end.  Splitting the
+// keys inside the workgroup costs no memory traffic and no second launch, so it comes first; only when that leaves units idle long
+// enough to pay for the merge launch are the keys split over workgroups as well.
+// No two waves read the same key: nothing is shared, a wave waits for its own copies only and the key loop has no barrier.  K and V travel
+// global -> LDS asynchronously; the K of the next block is requested when the scores of
 // this one have been formed, its V when the products have.
 //
 // What bounds it, at head_dim 64 and one workgroup of 32 rows per compute unit: 2.05 us per 1000 keys, where the copies
@@ -33,75 +32,120 @@ constexpr int SUB = 32;  // keys of a sub-tile
 
 // SPS: 32-key sub-tiles per step (two of them interleave what each waits for); NST: steps resident in LDS.  K and V of a
 // step are requested as soon as their predecessors in the slot have been read, which with NST = 1 is half a step ahead.
-template <int D, int RB, int RW, int NW, int SPS, int NST>
+template <int D, int RB, int NW, int SPS, int NST>
 struct Serve {
     static constexpr int BLK = SUB * SPS;              // keys of a step
     static constexpr int TILE = BLK * D;               // elements of its K or V
     static constexpr int CPR = D / 8;                  // 16-byte chunks per row
     static constexpr int RPC = 64 / CPR;               // rows per 1 KB copy
-    static constexpr int KW = NW / RW;                 // key ways
-    static constexpr int COPIES = BLK / RPC / RW;      // copies per wave of its K, and of its V
-    static constexpr int ROWS = RW * RB * SUB;         // packed rows of the workgroup
+    static constexpr int COPIES = BLK / RPC;           // copies of a step's K, and of its V
+    static constexpr int ROWS = RB * SUB;              // packed rows of the workgroup
     static constexpr int Q_COPIES = ROWS / RPC;        // copies of their Q, dealt to the waves
-    static constexpr int QUADS = D / 4, MERGED = RW * SUB * QUADS;  // 4 features each, of a row block
+    static constexpr int QUADS = D / 4, MERGED = SUB * QUADS;  // 4 features each, of a row block
     static constexpr int NIT = (MERGED + NW * 64 - 1) / (NW * 64);               // a thread's share of them
     static constexpr int PITCH = D + 4;                // floats per row of the merge buffer (16-byte words spread over the banks)
+    // Registers: at head_dim 128 the O of two row blocks leaves no room for their Q, nor for their own keys, which are then requested behind
+    // the key loop.
+    static constexpr bool Q_IN_LDS = D == 128 && RB == 2;
+    static_assert(!Q_IN_LDS || SPS == 1, "scores_of_lds");
     static constexpr int MERGE_BYTES = NW * SUB * (PITCH + 2) * 4;
-    static constexpr int KV_BYTES = KW * NST * 2 * TILE * 2;
+    static constexpr int KV_BYTES = NW * NST * 2 * TILE * 2;
     static constexpr int Q = KV_BYTES, BEFORE = Q + ROWS * D * 2;
     static constexpr int BYTES = BEFORE > MERGE_BYTES ? BEFORE : MERGE_BYTES;
 };
+constexpr int UNITS = 256;   // compute units, each of which holds one workgroup
 constexpr int TS_CAP = 512;  // real-time tokens of a user whose timestamps are searched in LDS
 
-// How a launch's workgroups map to work, with what takes the place of divisions in the kernel (a workgroup of a small call lives for 3 us,
-// of which the divisions of a general decode took 0.3).  Grid: x = XCD + 8 * (tile / spread), y = group / 8.  A group is (user, kv
-// head, head chunk, split, one of `spread` shares of the tiles): its row tiles read the same keys and stay on one XCD, the splits of an item
-// go to different ones.
+// How a launch's workgroups find their work.  An item is (user, kv head, head chunk, split, row tile); a user has as many as its lengths make,
+// and the items of all users are one list: every wave looks at all lengths, a lane to a user, and finds the item of its place by a
+// running sum.  So a launch has no workgroups for tiles and splits that only the longest user has, and its XCDs have equally many whatever
+// the lengths: XCD x takes a stretch of the list, or every eighth piece of `piece` items, whose row tiles read the same keys.
 struct ServeGrid {
-    uint32_t n_groups, spread_log2;       // spread: 1 or 2
-    uint32_t ny, ny_magic;               // groups of a user; 2^32 / ny, rounded up (0: ny is 1)
-    uint32_t n_splits, splits_magic;     // likewise
-    int32_t per;                         // blocks of keys per split
+    uint32_t piece;                   // 0: stretches
+    uint32_t n_heads;                 // kv heads x head chunks
+    uint32_t rows_magic;              // 2^32 / rows of a tile, rounded up (0: that is 1)
+    int32_t n_splits;                 // the most that a user can have
+    int32_t per;                      // blocks of keys of a split; more where these make more than `fit` items (with at most 64 users)
+    int32_t fit, max_per;
 };
 inline uint32_t div_magic(uint32_t d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / d + 1); }
 // n / d for n d < 2^32
 __device__ inline uint32_t div_by(uint32_t n, uint32_t magic) { return magic == 0 ? n : __umulhi(n, magic); }
+// n / d for n < 2^24
+__device__ inline int div_small(int n, int d) {
+    const int q = (int)((float)n * __builtin_amdgcn_rcpf((float)d)), r = n - q * d;
+    return r < 0 ? q - 1 : r >= d ? q + 1 : q;
+}
+// sums over the lanes up to and with this one
+__device__ inline int scan_lanes(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast 15: into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast 31: into rows 2 and 3
+    return x;
+}
 
 // The arrays that the first loads go to and what finds the user stand alone at the front: arguments in scalar registers when the kernel
 // starts (build.py, KERNARG_PRELOAD), while those inside Params take a load that costs 0.45 us at the start of a launch.
-template <int D, int RB, int RW, int NW, int SPS, int NST, bool RT, bool PW>
+template <int D, int RB, int NW, int SPS, int NST, bool RT, bool PW>
 __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* hist_len, const int32_t* n_targets, const int32_t* q_off,
-                                                                const int32_t* kv_off, const int32_t* rt_len, uint32_t ny, uint32_t ny_magic,
+                                                                const int32_t* kv_off, const int32_t* rt_len, int batch, int layer,
                                                                 ServeGrid sg, Params p, RowMap map) {
-    using SV = Serve<D, RB, RW, NW, SPS, NST>;
-    constexpr int BLK = SV::BLK, CP = SV::COPIES, KW = SV::KW, QUADS = SV::QUADS, NIT = SV::NIT;
+    using SV = Serve<D, RB, NW, SPS, NST>;
+    constexpr int BLK = SV::BLK, CP = SV::COPIES, QUADS = SV::QUADS, NIT = SV::NIT;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[SV::BYTES];
     __shared__ __attribute__((aligned(256))) int ts_s[RT ? TS_CAP : 1], row_ts[RT ? SV::ROWS * 2 : 1];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-    const uint32_t group = blockIdx.y * N_XCD + blockIdx.x % N_XCD;
-    if (group >= sg.n_groups) return;
-    const int b = (int)div_by(group, ny_magic);
-    const int L = hist_len[b], T = n_targets[b], R = RT ? rt_len[b] : 0;
-    const int64_t q_base = q_off[b], kv_base = kv_off[b];
-    const uint32_t y = (group - (uint32_t)b * ny) >> sg.spread_log2;
-    const int tile = (int)((blockIdx.x / N_XCD << sg.spread_log2) + (group & ((1u << sg.spread_log2) - 1u)));
-    const int gc = (int)div_by(y, sg.splits_magic), split = (int)y - gc * (int)sg.n_splits;
+    struct User {
+        int L, T, R, q, kv, tiles, splits, items;
+    };
+    int per = sg.per;
+    auto user_of_lane = [&](int first) __attribute__((always_inline)) {
+        const int u = min(first + lane, batch - 1);
+        User x = {hist_len[u], n_targets[u], RT ? rt_len[u] : 0, q_off[u], kv_off[u], 0, 0, 0};
+        const int rows = (layer == 0 ? x.L + x.R : 0) + x.T, blocks = (x.L + x.R + BLK - 1) / BLK;
+        x.tiles = (int)div_by((uint32_t)(rows + map.rows - 1), sg.rows_magic);
+        x.splits = sg.n_splits == 1 ? 1 : max(1, div_small(blocks + per - 1, per));
+        x.items = first + lane < batch ? x.tiles * x.splits * (int)sg.n_heads : 0;
+        return x;
+    };
+    User of = user_of_lane(0);
+    int upto = scan_lanes(of.items), n_here = __builtin_amdgcn_readlane(upto, 63), n_items = n_here;
+    for (int u = 64; u < batch; u += 64) n_items += __builtin_amdgcn_readlane(scan_lanes(user_of_lane(u).items), 63);
+    while (n_items > sg.fit && per < sg.max_per) {
+        per += (per + 7) / 8;
+        of.splits = max(1, div_small((of.L + of.R + BLK - 1) / BLK + per - 1, per));
+        of.items = lane < batch ? of.tiles * of.splits * (int)sg.n_heads : 0;
+        upto = scan_lanes(of.items);
+        n_items = n_here = __builtin_amdgcn_readlane(upto, 63);
+    }
+    const int xcd = blockIdx.x % N_XCD, slot_x = blockIdx.x / N_XCD;
+    int at = sg.piece == 0 ? xcd * ((n_items + N_XCD - 1) / N_XCD) + slot_x
+                           : ((slot_x / (int)sg.piece) * N_XCD + xcd) * (int)sg.piece + slot_x % (int)sg.piece;
+    if (at >= n_items || (sg.piece == 0 && slot_x >= (n_items + N_XCD - 1) / N_XCD)) return;
+    for (int u = 64; at >= n_here; u += 64) {
+        at -= n_here;
+        of = user_of_lane(u);
+        upto = scan_lanes(of.items);
+        n_here = __builtin_amdgcn_readlane(upto, 63);
+    }
+    const int u_lane = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= at));
+    auto of_user = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, u_lane); };
+    at -= of_user(upto - of.items);
+    const int L = of_user(of.L), T = of_user(of.T), R = RT ? of_user(of.R) : 0, n_tiles = of_user(of.tiles), n_live = of_user(of.splits);
+    const int64_t q_base = of_user(of.q), kv_base = of_user(of.kv);
+    const int ts_of = __builtin_amdgcn_readfirstlane(div_small(at, n_tiles)), tile = at - ts_of * n_tiles;
+    const int gc = sg.n_splits == 1 ? ts_of : __builtin_amdgcn_readfirstlane(div_small(ts_of, n_live)), split = ts_of - gc * n_live;
     const int g = map.n_chunks == 1 ? gc : gc / map.n_chunks, chunk = gc - g * map.n_chunks;
     const int LK = L + R;  // keys that run through the tile loop: history, then real-time
-    const int n_rows = p.layer == 0 ? LK + T : T;
-    const int n_all = (LK + BLK - 1) / BLK, lo = min(split * sg.per, n_all), hi = min(lo + sg.per, n_all);
-    if (tile * map.rows >= n_rows) return;  // uniform for the whole workgroup
+    const int n_rows = layer == 0 ? LK + T : T;
+    const int n_all = (LK + BLK - 1) / BLK, lo = split * per, hi = min(lo + per, n_all);
     const PackedRows pr(map, tile, chunk, n_rows, g, p.Hq / p.Hkv);
-    if (!PW && split > 0 && lo >= n_all) {  // a user whose keys end before this split
-        const PackedRows::Row x = pr.at(tid);
-        if (tid < SV::ROWS && x.live) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + q_base + x.row] = -INFINITY;
-        return;
-    }
-    const int tok_shift = p.layer == 0 ? 0 : LK;  // token index of query row 0
-    const int rw = wave / KW, kw = wave % KW, rho0 = rw * RB * 32;
-    const bool wave_live = RW == 1 || pr.any_from(rho0);
-    const int n_mine = hi - lo > kw ? (hi - lo - kw + KW - 1) / KW : 0;  // steps of this key way: blocks lo + kw + i KW
+    const int tok_shift = layer == 0 ? 0 : LK;  // token index of query row 0
+    const int n_mine = max(hi - lo - wave + NW - 1, 0) / NW;  // steps of this wave: blocks lo + wave + i NW
 
     // K or V of step i to its slot.  Keys past the end repeat the last one (their weight is forced to zero).
     const __bf16* kg = (const __bf16*)p.k + (int64_t)g * D;
@@ -109,24 +153,24 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     uint32_t voff[CP];  // byte offsets of the chunks this lane fetches from the first element of the block
 #pragma unroll
     for (int j = 0; j < CP; j++) {
-        const int trow = (j * RW + rw) * SV::RPC + lane / SV::CPR;
+        const int trow = j * SV::RPC + lane / SV::CPR;
         voff[j] = (uint32_t)((trow * p.Hkv * D + ((lane % SV::CPR) ^ swizzle<D>(trow)) * 8) * 2);
     }
-    auto slot = [&](int i) __attribute__((always_inline)) { return (kw * NST + (NST == 1 ? 0 : i % NST)) * (2 * SV::TILE * 2); };
+    auto slot = [&](int i) __attribute__((always_inline)) { return (wave * NST + (NST == 1 ? 0 : i % NST)) * (2 * SV::TILE * 2); };
     auto fetch = [&](const __bf16* src, int i, int part) __attribute__((always_inline)) {
         if (i >= n_mine) return;
-        const int k0 = (lo + kw + i * KW) * BLK;
+        const int k0 = (lo + wave + i * NW) * BLK;
         const __bf16* base = src + (kv_base + k0) * p.Hkv * D;
         const uint32_t dst = lds_address(smem) + (uint32_t)(slot(i) + part * SV::TILE * 2);
         if (k0 + BLK <= LK) {
 #pragma unroll
-            for (int j = 0; j < CP; j++) copy16_global_to_lds_at(base, voff[j], dst + (j * RW + rw) * 1024);
+            for (int j = 0; j < CP; j++) copy16_global_to_lds_at(base, voff[j], dst + j * 1024);
         } else {
 #pragma unroll
             for (int j = 0; j < CP; j++) {
-                const int trow = (j * RW + rw) * SV::RPC + lane / SV::CPR;
+                const int trow = j * SV::RPC + lane / SV::CPR;
                 const uint32_t past = (uint32_t)max(trow - (LK - 1 - k0), 0);
-                copy16_global_to_lds_at(base, voff[j] - past * (uint32_t)(p.Hkv * D * 2), dst + (j * RW + rw) * 1024);
+                copy16_global_to_lds_at(base, voff[j] - past * (uint32_t)(p.Hkv * D * 2), dst + j * 1024);
             }
         }
     };
@@ -149,20 +193,23 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     // The own key of target rows (rule 3) and of real-time rows joins in the merge: its logit and weight are formed by the threads that
     // hold 4 features of the row there.  Requested here, used behind the key loop.
     bf16x4 own_q[RB][NIT], own_k[RB][NIT], own_v[RB][NIT];
+    auto request_own = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int rb = 0; rb < RB; rb++)
+        for (int rb = 0; rb < RB; rb++)
 #pragma unroll
-        for (int it = 0; it < NIT; it++) {
-            own_q[rb][it] = own_k[rb][it] = own_v[rb][it] = bf16x4{};
-            if (split == 0) {
-                const int id = tid + it * NW * 64, c = id % QUADS, rl = id / QUADS;
-                const PackedRows::Row x = pr.at((rl / SUB * RB + rb) * 32 + rl % SUB);
-                const uint32_t koff = (uint32_t)((x.row - pr.row0) * p.Hkv * D + 4 * c);
-                own_q[rb][it] = *(const bf16x4*)(q_tile + (uint32_t)(((x.row - pr.row0) * p.Hq + x.h) * D + 4 * c));
-                own_k[rb][it] = *(const bf16x4*)((const __bf16*)p.k + own_tile + koff);
-                own_v[rb][it] = *(const bf16x4*)((const __bf16*)p.v + own_tile + koff);
+            for (int it = 0; it < NIT; it++) {
+                own_q[rb][it] = own_k[rb][it] = own_v[rb][it] = bf16x4{};
+                if (split == 0) {
+                    const int id = tid + it * NW * 64, c = id % QUADS, rl = id / QUADS;
+                    const PackedRows::Row x = pr.at(rb * 32 + rl);
+                    const uint32_t koff = (uint32_t)((x.row - pr.row0) * p.Hkv * D + 4 * c);
+                    own_q[rb][it] = *(const bf16x4*)(q_tile + (uint32_t)(((x.row - pr.row0) * p.Hq + x.h) * D + 4 * c));
+                    own_k[rb][it] = *(const bf16x4*)((const __bf16*)p.k + own_tile + koff);
+                    own_v[rb][it] = *(const bf16x4*)((const __bf16*)p.v + own_tile + koff);
+                }
             }
-        }
+    };
+    if constexpr (!SV::Q_IN_LDS) request_own();
 #pragma unroll
     for (int i = 0; i < NST; i++) {
         fetch(kg, i, 0);
@@ -174,13 +221,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     rows.reset();
     if (n_mine >= NST) wait_vmem_outstanding<2 * CP * NST>(); else wait_vmem_outstanding<0>();
     lds_barrier();
-    rows.take_q((const __bf16*)(smem + SV::Q) + rw * RB * SUB * D, L);
+    const __bf16* const q_rows = (const __bf16*)(smem + SV::Q);
+    if constexpr (SV::Q_IN_LDS) {
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) rows.lim[rb] = L;
+    } else {
+        rows.take_q(q_rows, L);
+    }
     if constexpr (RT) {
         // mask rule 2: the row sees the history and the real-time tokens strictly earlier than itself, a prefix
         const int32_t* ts = p.ts + kv_base + L;
 #pragma unroll
         for (int rb = 0; rb < RB; rb++) {
-            const int t = row_ts[(rw * RB + rb) * 64 + lane];
+            const int t = row_ts[rb * 64 + lane];
             int a = 0, e = R;
             while (a < e) {
                 const int mid = (a + e) >> 1;
@@ -202,31 +255,28 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     static_assert(NST <= 2, "wait_copies");
     auto step = [&](int i, auto Tail) __attribute__((always_inline)) {
         constexpr bool TAIL = decltype(Tail)::value;
-        const int k0 = (lo + kw + i * KW) * BLK, left = n_mine - 1 - i;
+        const int k0 = (lo + wave + i * NW) * BLK, left = n_mine - 1 - i;
         const __bf16* Ks = (const __bf16*)(smem + slot(i));
         floatx16 S[SPS][RB];
-        const bool work = wave_live && (RW == 1 || i < n_mine);
         wait_copies(min(NST - 1, left), true);  // newer than K_i: V_i and the following steps
-        if (RW > 1) lds_barrier();
-        if (work) rows.template scores<SPS>(S, Ks);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // K_i has been read
-        if (RW > 1) {
-            wait_copies(min(NST - 1, left), false);
-            lds_barrier();
+        if constexpr (SV::Q_IN_LDS) {
+            rows.scores_of_lds(S, Ks, q_rows);
+        } else {
+            rows.template scores<SPS>(S, Ks);
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // K_i has been read
         fetch(kg, i + NST, 0);
-        if (RW == 1) wait_copies(min(NST - 1, left), left >= NST);  // newer than V_i: the following steps, and K_(i + NST)
-        if (work) rows.template absorb<TAIL, SPS>(S, Ks + SV::TILE, LK - k0, k0, L);
+        wait_copies(min(NST - 1, left), left >= NST);  // newer than V_i: the following steps, and K_(i + NST)
+        rows.template absorb<TAIL, SPS>(S, Ks + SV::TILE, LK - k0, k0, L);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (RW > 1) lds_barrier();
         fetch(vg, i + NST, 1);
     };
     // blocks of history keys first, then those that need a mask (the last one; more with real-time tokens)
-    const int n_rounds = RW == 1 ? n_mine : (hi - lo + KW - 1) / KW;  // (barriers: the same number of steps for every wave)
-    const int n_whole = RW == 1 ? min(max(min(hi, L / BLK) - lo - kw + KW - 1, 0) / KW, n_mine) : max(min(hi, L / BLK) - lo, 0) / KW;
+    const int n_whole = min(max(min(hi, L / BLK) - lo - wave + NW - 1, 0) / NW, n_mine);
     for (int i = 0; i < n_whole; i++) step(i, std::false_type{});
-    for (int i = n_whole; i < n_rounds; i++) step(i, std::true_type{});
+    for (int i = n_whole; i < n_mine; i++) step(i, std::true_type{});
 
+    if constexpr (SV::Q_IN_LDS) request_own();
     // ---- the own keys' logits, summed over the threads of a row: log2 units (PW: the weight itself), -inf (0) where there is none
     float own[RB][NIT];
 #pragma unroll
@@ -234,7 +284,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
 #pragma unroll
         for (int it = 0; it < NIT; it++) {
             const int rl = (tid + it * NW * 64) / QUADS;
-            const bool has = split == 0 && tok_shift + pr.at((rl / SUB * RB + rb) * 32 + rl % SUB).row >= L;
+            const bool has = split == 0 && tok_shift + pr.at(rb * 32 + rl).row >= L;
             float dot = dot_bf16x4(0.f, own_q[rb][it], own_k[rb][it]);
             dot = sum_lanes<QUADS>(dot);
             own[rb][it] = PW ? (has ? pw_silu(dot, pw_sigmoid(dot, rows.neg_c2)) : 0.f) : (has ? dot * rows.c2 : -INFINITY);
@@ -266,14 +316,14 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
 #pragma unroll
     for (int it = 0; it < NIT; it++) {
         const int id = tid + it * NW * 64;
-        const int c = id % QUADS, rl = id / QUADS, l = rl % SUB, w0 = rl / SUB % RW * KW;  // 4 features of a row; its first wave
-        const PackedRows::Row x = pr.at((rl / SUB * RB + rb) * 32 + l);
+        const int c = id % QUADS, l = id / QUADS;  // 4 features of a row
+        const PackedRows::Row x = pr.at(rb * 32 + l);
         float mx = PW ? 0.f : fmaxf(own[rb][it], -1e30f);
-        float2 ml[KW];
+        float2 ml[NW];
         if constexpr (!PW) {
 #pragma unroll
-            for (int k = 0; k < KW; k++) {
-                ml[k] = *(const float2*)(stat + ((w0 + k) * SUB + l) * 2);
+            for (int k = 0; k < NW; k++) {
+                ml[k] = *(const float2*)(stat + (k * SUB + l) * 2);
                 mx = fmaxf(mx, ml[k].x);
             }
         }
@@ -286,9 +336,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
             for (int j = 0; j < 4; j++) o[j] = f * (float)own_v[rb][it][j];
         }
 #pragma unroll
-        for (int k = 0; k < KW; k++) {
+        for (int k = 0; k < NW; k++) {
             const float f = PW ? 1.f : fast_exp2(ml[k].x - mx);  // 0 for a wave that saw no key
-            const floatx4 ok = *(const floatx4*)(acc + ((w0 + k) * SUB + l) * SV::PITCH + 4 * c);
+            const floatx4 ok = *(const floatx4*)(acc + (k * SUB + l) * SV::PITCH + 4 * c);
             if constexpr (!PW) sum = fmaf(f, ml[k].y, sum);
 #pragma unroll
             for (int j = 0; j < 4; j++) o[j] = fmaf(f, ok[j], o[j]);
@@ -308,7 +358,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
 #pragma unroll
             for (int j = 0; j < 4; j++) o4[j] = o[j] * inv;
             *(floatx4*)(p.o_part + (((int64_t)split * p.total_q + row) * p.Hq + x.h) * D + 4 * c) = o4;
-            if (!PW && c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = lse;
+            if (c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : lse;
+            // the splits that this user's keys do not reach are nobody's: nothing was left there
+            if (c == 0 && split == 0)
+                for (int k = n_live; k < sg.n_splits; k++) p.lse_part[((int64_t)k * p.Hq + x.h) * p.total_q + row] = -INFINITY;
         }
     }
     });
@@ -335,7 +388,7 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, 
 #pragma unroll
         for (int s = 0; s < AT_ONCE; s++) {  // (behind the last one: the last one again)
             const int i = min(s0 + s, n_splits - 1);
-            ls[s] = PW ? 0.f : lse_part[at_lse + i * l_stride];
+            ls[s] = lse_part[at_lse + i * l_stride];
             os[s] = *(const floatx4*)(o_part + id * 4 + i * o_stride);
         }
         const float before = mx;
@@ -351,7 +404,7 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, 
             const float w = s0 + s >= n_splits ? 0.f : PW ? 1.f : __expf(ls[s] - mx);
             sum += w;
 #pragma unroll
-            for (int j = 0; j < 4; j++) o[j] = s0 + s >= n_splits || (!PW && ls[s] == -INFINITY) ? o[j] : fmaf(w, os[s][j], o[j]);  // (-inf: nothing was left)
+            for (int j = 0; j < 4; j++) o[j] = s0 + s >= n_splits || ls[s] == -INFINITY ? o[j] : fmaf(w, os[s][j], o[j]);  // (-inf: nothing was left)
         }
     }
     const float inv = PW ? 1.f : 1.f / sum;
@@ -362,33 +415,35 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, 
     if (!PW && id % QUADS == 0) lse[at_lse] = mx + __logf(sum);
 }
 
-template <int D, int RB, int RW, int NW, int SPS, int NST>
+// the most row tiles x kv heads x head chunks that a call's users can have, whatever their lengths
+int64_t most_tiles(const Params& p, const RowMap& map) {
+    const int64_t by_rows = (p.total_q + (int64_t)p.batch * (map.rows - 1)) / map.rows;
+    return std::min(by_rows, (int64_t)p.batch * map.n_tiles) * p.Hkv * map.n_chunks;
+}
+
+template <int D, int RB, int NW, int SPS, int NST>
 hipError_t launch(const Params& p, hipStream_t s) {
-    auto kernel = serve_kernel<D, RB, RW, NW, SPS, NST, false, false>;
+    auto kernel = serve_kernel<D, RB, NW, SPS, NST, false, false>;
     if (p.pointwise)
-        kernel = p.rt_len ? serve_kernel<D, RB, RW, NW, SPS, NST, true, true> : serve_kernel<D, RB, RW, NW, SPS, NST, false, true>;
+        kernel = p.rt_len ? serve_kernel<D, RB, NW, SPS, NST, true, true> : serve_kernel<D, RB, NW, SPS, NST, false, true>;
     else if (p.rt_len)
-        kernel = serve_kernel<D, RB, RW, NW, SPS, NST, true, false>;
+        kernel = serve_kernel<D, RB, NW, SPS, NST, true, false>;
     const int64_t rows = max_query_rows(p);
     if (rows <= 0) return hipSuccess;
-    const RowMap map = row_map(RW * RB * 32, p.Hq, p.Hkv, rows);
+    const RowMap map = row_map(RB * 32, p.Hq, p.Hkv, rows);
     const int64_t max_blocks = (max_lead_keys(p) + SUB * SPS - 1) / (SUB * SPS);
     ServeGrid sg;
     sg.per = (int32_t)std::max<int64_t>((max_blocks + p.n_splits - 1) / p.n_splits, 1);
-    sg.n_splits = (uint32_t)std::max<int64_t>((max_blocks + sg.per - 1) / sg.per, 1);
-    // One XCD per group is best for its L2; two when there are so few groups that an XCD of 32 units can get more
-    // workgroups than it has units while others idle (14 requests of 1053 keys, 28 groups: 23 -> 14 us).
-    const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks * sg.n_splits;
-    const int spread = groups < 64 && (groups + N_XCD - 1) / N_XCD * map.n_tiles > 32 ? 2 : 1;
-    sg.ny = (uint32_t)(groups / p.batch * spread);
-    sg.spread_log2 = spread / 2;
-    sg.n_groups = sg.ny * (uint32_t)p.batch;
-    sg.ny_magic = div_magic(sg.ny);
-    sg.splits_magic = div_magic(sg.n_splits);
-    const int64_t nx = (int64_t)((map.n_tiles + spread - 1) / spread) * N_XCD, n_y = (sg.n_groups + N_XCD - 1) / N_XCD;
-    if (nx * n_y >= (1ll << 31) || n_y > 65535 || (int64_t)sg.n_groups * sg.ny >= (1ll << 32)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)nx, (unsigned)n_y), dim3(NW * 64), 0, s, p.hist_len, p.n_targets, p.q_off, p.kv_off, p.rt_len, sg.ny,
-                       sg.ny_magic, sg, p, map);
+    sg.n_splits = (int32_t)std::max<int64_t>((max_blocks + sg.per - 1) / sg.per, 1);
+    sg.fit = sg.n_splits > 1 && p.batch <= 64 ? UNITS : INT32_MAX;
+    sg.max_per = (int32_t)max_blocks;
+    sg.n_heads = (uint32_t)(p.Hkv * map.n_chunks);
+    sg.rows_magic = div_magic((uint32_t)map.rows);
+    const int64_t tiles = most_tiles(p, map), most = sg.fit < INT32_MAX ? std::min(tiles * sg.n_splits, std::max<int64_t>(tiles, sg.fit)) : tiles * sg.n_splits;
+    sg.piece = most <= 320 ? 0 : 4;
+    const int64_t dealt = N_XCD * (sg.piece == 0 ? 1 : sg.piece), n_blocks = (most + dealt - 1) / dealt * dealt;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p.hist_len, p.n_targets, p.q_off, p.kv_off, p.rt_len, p.batch, p.layer,
+                       sg, p, map);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || sg.n_splits == 1) return e;
     const int64_t threads = p.total_q * p.Hq * (p.d / 4);
@@ -406,12 +461,6 @@ int64_t live_tiles(const Params& p, int lanes) {
     const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks;
     return std::min(groups * map.n_tiles, p.total_q * p.Hkv * map.n_chunks / map.rows + groups / 2);
 }
-
-// The shape of a call's workgroups.  Blocks of 32 rows finish soonest while every one gets a unit to itself; once they
-// queue up, 64 rows per workgroup (two row blocks per wave at head_dim 64, two row groups sharing their keys at 128, where
-// the registers do not hold two) halve the traffic of the copies.
-enum Shape { ROWS32, ROWS64 };
-Shape shape_of(const Params& p) { return p.d > 32 && live_tiles(p, 32) > (p.d == 64 ? 256 : 512) ? ROWS64 : ROWS32; }
 
 }  // namespace
 
@@ -436,72 +485,93 @@ int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t ma
     return n > 1 ? (int)n : 1;
 }
 
-// Estimated times of a call (us) with the keys in one piece, from fits of 2700 calls on both sides of the line (1 to 400 users,
-// 4 to 256 candidates or a full layer, 64 to 8192 keys, all of one length or spread over a factor of 8; with and without
-// real-time tokens and with pointwise weights).  The ordinary kernel, up to a workgroup per unit: the longest one, a little more the
-// fuller the chip, and the schedule and limits launches as they were then: 0.02 us per user, which 32 users hardly see, and 2 us with real-time
-// tokens, whose launch is gone.  (That leaves the ordinary kernel out of some calls where it is the faster one.  Without the 2 us 860 of
-// 3999 calls with real-time tokens near the line change sides: 0.87 of the time on average, but 228 of them slower, by half at
-// most; the kernel for a few requests takes 3 us longer with real-time tokens than estimated.  Both want a fit of their own.)
+// Estimated times of a call (us), from fits of 8775 calls timed in every form (1 to 64 users, target layers of 2 to 300 candidates and, a
+// third of the calls, full layers; 64 to 16384 keys, all of one length or spread over a factor of 8; with and without real-time tokens and
+// with pointwise weights; inputs of four calls in turn).
+//
+// The ordinary kernel, up to two workgroups per unit: the longest one, more the fuller the chip, and the schedule's launch.
 static double ordinary_us(const Params& p, int64_t workgroups) {
-    struct { double launch, key, key_full; } c;
-    if (p.d == 32) c = {6.2, 9.5e-3, 3.5e-3};
-    else if (p.d == 128) c = {9.6, 17.6e-3, 4.e-3};
-    else if (fwd_workgroup_rows(p) == 128) c = {7.5, 13.e-3, 2.5e-3};
-    else c = {8., 14.e-3, 5.e-3};
-    return c.launch + 0.02 * p.batch + (p.rt_len ? 2. : 0.) + c.key * max_lead_keys(p) + c.key_full * mean_keys(p) * workgroups / 256.;
+    struct { double launch, schedule, key, key_full, second; } c;
+    if (p.d == 32) c = {3.6, 2.6, 9.3e-3, 5.9e-3, 1.9};
+    else if (p.d == 128) c = {7.5, 1.9, 17.e-3, 8.3e-3, 13.};
+    else if (fwd_workgroup_rows(p) == 128) c = {5.2, 2.6, 12.e-3, 11.e-3, 2.8};
+    else c = {6.7, 1.1, 13.e-3, 17.e-3, 7.4};
+    const double fill = workgroups / (double)UNITS;
+    return c.launch + (forward_needs_schedule(p) ? c.schedule : 0.) + c.key * max_lead_keys(p) + c.key_full * mean_keys(p) * fill + c.second * std::max(0., fill - 1.);
 }
-// The kernel above: one workgroup per unit, so rounds of 256 of them.
-static double serve_us(const Params& p, Shape shape) {
-    struct { double launch, fixed, key; } c;
-    if (p.d == 32) c = {1., 3.7, 2.7e-3};
-    else if (p.d == 64 && shape == ROWS64) c = {1., 7., 5.2e-3};
-    else if (p.d == 64) c = {3., 2.5, 3.e-3};
-    else if (shape == ROWS64) c = {1., 9., 10.e-3};
-    else c = {0., 7., 5.3e-3};
-    const double longest = (double)max_lead_keys(p), mean = mean_keys(p), full = live_tiles(p, shape == ROWS64 ? 64 : 32) / 256.;
-    const double rounds = mean > 0.9 * longest ? std::ceil(full) : std::max(1., full + 0.75);
-    return c.launch + c.fixed * rounds + c.key * std::max(longest, mean * rounds);
+// The kernel above, `row_blocks` blocks of 32 rows per workgroup and the keys of the longest user in `splits` pieces.  One workgroup per unit; a
+// key costs more the fuller the chip (its XCDs' L2s feed all units).  In one piece, more items than units take rounds, whole ones where
+// all have the same keys.  In several, the pieces are as long as it takes for all items to have a unit, and the merge costs a launch and
+// the partial results.
+struct ServeSize {
+    double longest, mean, part;  // keys of the longest user and of the mean; MB of a partial result
+    double items[2];             // workgroups with keys in one piece, of one and two row blocks
+    ServeSize(const Params& p)
+        : longest((double)max_lead_keys(p)), mean(mean_keys(p)), part(1e-6 * p.total_q * p.Hq * p.d * 4), items{(double)live_tiles(p, 32), (double)live_tiles(p, 64)} {}
+};
+static double serve_us(const Params& p, const ServeSize& size, int row_blocks, int splits) {
+    struct { double launch, item, key, key_full, jagged, merge, part, rt, piece, partial; } c;
+    if (p.d == 32) c = {-0.46, 4.6, 2.2, 1.0, 0.43, 2.4, 0.55, 0.48, 0.34, 0.23};
+    else if (p.d == 64 && row_blocks == 1) c = {0.85, 3.8, 2.6, 1.3, 0.66, 2.4, 0.35, 0.49, 0.38, 0.18};
+    else if (p.d == 64) c = {0.89, 5.4, 4.0, 1.7, 0.78, 2.5, 0.35, 0.96, 0.37, 0.13};
+    else if (row_blocks == 1) c = {0.93, 4.9, 5.0, 1.9, 0.77, 2.3, 0.19, 0.41, 0.51, 0.15};
+    else c = {-0.34, 9.3, 5.9, 3.5, 0.73, 2.6, 0.22, 2.2, 0.45, 0.14};
+    const double longest = size.longest, mean = size.mean, items = size.items[row_blocks - 1], rounds = items / UNITS;
+    const bool even = mean > 0.9 * longest;
+    const double fixed = c.launch + (p.rt_len ? c.rt : 0.);
+    double keys = longest, pieces = items;
+    if (splits > 1) {
+        const double fits = items < 250. && p.batch <= 64 ? items * mean / std::max(UNITS - c.piece * items, 16.) : longest;
+        keys = std::min(std::max(longest / splits, fits), longest);
+        const double of_mean = mean / std::max(keys, 1.);
+        pieces = items * (even ? std::ceil(of_mean - 0.01) : of_mean + c.piece);
+    }
+    const double key = 1e-3 * (c.key + c.key_full * std::min(1., pieces / UNITS));
+    const double whole = std::ceil(rounds);
+    const double many = (even ? whole + c.partial * (rounds - whole) : rounds + c.jagged) * (c.item + key * mean);
+    if (splits == 1) return fixed + (rounds <= 1. ? c.item + key * longest : std::max(c.item + key * longest, many));
+    return fixed + c.merge + c.part * splits * size.part + (rounds <= 1. ? c.item + key * keys : std::max(c.item + key * longest, many));
 }
 
-// This kernel or the ordinary one, which shares each K/V tile among 128 or 256 rows and keeps two workgroups on a unit.  Once its
-// workgroups nearly fill the chip, the ordinary one (at head_dim 64, 224 to 330 of them: on average 1.2 times as fast, though
-// not on long histories of unlike lengths; 128: 1.3; 32, 448 to 600: 1.5).  Below that, keys are split over workgroups when the time
-// this takes off the longest item is worth the merge: per key and workgroup 2.05 ns at head_dim 64, 4.4 at 128; merge 4.2 us,
-// partial results at 3 TB/s.  Where it is not, by the estimates above: 64-row workgroups that come in rounds lose to 256-row ones
-// that do not.  (8/2 heads of 64: 27 users x 256 candidates on 512 keys 38 us here against 20 there, on 2048 64 / 45; 13 users on
-// 2048 34 / 43; 40 users x 128 candidates, 16/2 heads of 128, 64..512 keys 60 / 31; 110 x 256, 4/2 heads of 32, 512 keys 63 / 25.
-// Of the 2700 calls 622 had a tenth or more to gain on the other side when only full chips went there, 47 have now.)
-int serve_splits(const Params& p, int room) {
-    const int64_t ordinary = live_tiles(p, fwd_workgroup_rows(p));
-    if (ordinary >= (p.d == 32 ? 448 : 224)) return 0;
-    const Shape shape = shape_of(p);
-    if (room > 1 && shape != ROWS64) {
-        const RowMap map = row_map(32, p.Hq, p.Hkv, max_query_rows(p));
-        const int64_t items = (int64_t)p.batch * p.Hkv * map.n_chunks * map.n_tiles;
-        const double loop = max_lead_keys(p) * (p.d == 128 ? 4.4e-3 : 2.05e-3);
-        const double part = 2.0 * p.total_q * p.Hq * p.d * 4 / 3e6;
-        int best = 1;
-        double best_us = loop;
-        for (int s = 2; s <= room && items * s <= 256; s++) {
-            const double us = loop / s + 4.2 + s * (part + 0.05);
-            if (us < best_us) best = s, best_us = us;
+// What a call takes: this kernel with one or two row blocks per workgroup and the keys in up to `room` pieces, or the ordinary one,
+// which shares each K/V tile among 128 or 256 rows and keeps two workgroups on a unit.  By the estimates above, of which against the best
+// form of each call 1.2 % of the time are lost on target layers (of 6060, 762 lose 3 % or more and 203 a tenth) and 0.6 on full ones.  The
+// rule before, with a line at 256 workgroups of 32 rows and the merge at 4.2 us, lost 5.7 % on the former, and a tenth or more in 1262.
+struct ServeForm {
+    int row_blocks, splits;  // splits 0: the ordinary kernel
+};
+static ServeForm serve_form(const Params& p, int room) {
+    const int64_t ordinary = live_tiles(p, fwd_workgroup_rows(p)), blocks = max_lead_keys(p) / SUB;
+    if (ordinary >= 512 || p.batch > 1024 || max_query_rows(p) >= 1 << 20) return {1, 0};
+    ServeForm best = {1, 0};
+    double best_us = ordinary_us(p, ordinary);
+    const ServeSize size(p);
+    for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+        if (splits > 1 && (splits > room || splits > blocks / 6 || blocks >= 1 << 15)) break;
+        for (int rb = 1; rb <= (p.d == 32 ? 1 : 2); rb++) {
+            const double us = serve_us(p, size, rb, splits);
+            if (us < best_us) best_us = us, best = {rb, splits};
         }
-        if (best > 1) return best;
     }
-    return ordinary_us(p, ordinary) < 0.97 * serve_us(p, shape) ? 0 : 1;
+    return best;
+}
+int serve_splits(const Params& p, int room) { return serve_form(p, room).splits; }
+// (of the same estimates, once the splits are chosen)
+static int serve_row_blocks(const Params& p) {
+    const ServeSize size(p);
+    return p.d != 32 && serve_us(p, size, 2, p.n_splits) < serve_us(p, size, 1, p.n_splits) ? 2 : 1;
 }
 
 hipError_t launch_serve_bf16(const Params& p, hipStream_t s) {
-    const Shape shape = shape_of(p);
+    const bool two = serve_row_blocks(p) == 2;
     // short lists of keys per wave: single sub-tiles divide more evenly than pairs
     const bool brief = max_lead_keys(p) / p.n_splits <= 1024;
     hipError_t e;
     timing_begin(MTFM_HTA_KERNEL_FWD, s);
     switch (p.d) {
-        case 32: e = launch<32, 1, 1, 8, 2, 2>(p, s); break;
-        case 64: e = shape == ROWS64 ? launch<64, 2, 1, 8, 1, 2>(p, s) : brief ? launch<64, 1, 1, 8, 1, 2>(p, s) : launch<64, 1, 1, 8, 2, 1>(p, s); break;
-        case 128: e = shape == ROWS64 ? launch<128, 1, 2, 8, 2, 1>(p, s) : launch<128, 1, 1, 8, 1, 1>(p, s); break;
+        case 32: e = launch<32, 1, 8, 2, 2>(p, s); break;
+        case 64: e = two ? launch<64, 2, 8, 1, 2>(p, s) : brief ? launch<64, 1, 8, 1, 2>(p, s) : launch<64, 1, 8, 2, 1>(p, s); break;
+        case 128: e = two ? launch<128, 2, 8, 1, 1>(p, s) : launch<128, 1, 8, 1, 1>(p, s); break;
         default: e = hipErrorInvalidValue;
     }
     timing_end(MTFM_HTA_KERNEL_FWD, s);

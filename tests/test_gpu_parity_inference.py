@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2602_11235_amd import hta, inputs
+from tests import test_gpu_parity_pointwise as pointwise
 from tests.hta_testlib import check_case, device_batch, host
 
 pytestmark = pytest.mark.gpu
@@ -75,6 +76,36 @@ def test_few_requests_with_many_real_time_tokens(layer, heads):
     c = inputs.make_case(inputs.custom_config("many_rt", layer, [700, 0, 63, 130, 200, 64], [16, 5, 33, 2, 7, 1], *heads, seed=34,
                                               rt_len=[512, 513, 600, 511, 65, 64]))
     check_case(c, with_bwd=True)
+
+
+# The list of work items that a launch for requests makes of the lengths: users without a row or a key anywhere in it, more users than a wave has
+# lanes, more items than compute units, pieces of keys that grow until the items fit, and splits that the shorter users do not reach.
+LISTS = {
+    "many_users": (TARGET, np.resize([0, 1, 31, 700, 64, 0, 1500, 33], 130), np.resize([1, 0, 3, 2, 0, 5, 1], 130), (4, 1, 64)),
+    "a_lane_more": (TARGET, np.resize([40, 300, 0], 65), np.resize([2, 0, 1, 3], 65), (8, 2, 32)),
+    "three_waves_of_users": (TARGET, np.resize([90, 0, 260], 192), np.resize([1, 2, 0], 192), (2, 1, 128)),
+    "pieces_grow": (TARGET, [6000, 300, 0, 4100, 2500, 65, 3300, 5000], [90, 30, 5, 70, 0, 64, 33, 50], (8, 2, 64)),
+    "more_than_units": (TARGET, np.resize([1400, 900, 63, 2000], 20), np.resize([70, 33, 128, 0], 20), (16, 4, 64)),
+    "two_row_blocks_d128": (TARGET, np.resize([1100, 0, 640, 33], 20), np.resize([64, 5, 100, 17], 20), (16, 2, 128)),
+    "two_row_blocks_d128_in_pieces": (TARGET, [8192, 7000, 100, 8000], [64, 60, 3, 50], (16, 2, 128)),
+    "two_row_blocks_d128_full": (FULL, [600, 500, 640, 30], [20, 5, 1, 17], (16, 2, 128)),
+    "many_pieces": (TARGET, [16384, 200], [3, 2], (4, 1, 64)),
+}
+
+
+@pytest.mark.parametrize("with_rt", [False, True])
+@pytest.mark.parametrize("name", LISTS)
+def test_lists_of_items(name, with_rt):
+    layer, hist, targets, heads = LISTS[name]
+    rt = np.resize([40, 0, 7, 130, 1], len(hist)) if with_rt else None
+    case = inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=36, rt_len=rt))
+    check_case(case, with_bwd=False)
+
+
+@pytest.mark.parametrize("name", ["pieces_grow", "two_row_blocks_d128_in_pieces", "many_users"])
+def test_lists_of_items_pointwise(name):
+    layer, hist, targets, heads = LISTS[name]
+    pointwise.check(inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=37)))
 
 
 def test_split_and_unsplit_forward_agree():

@@ -103,12 +103,15 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
         int L, T, R, q, kv, tiles, splits, items;
     };
     int per = sg.per;
+    auto splits_of = [&](int keys) __attribute__((always_inline)) {  // (never more than there is room for, whatever the bounds said)
+        return sg.n_splits == 1 ? 1 : min(max(1, div_small((keys + BLK - 1) / BLK + per - 1, per)), sg.n_splits);
+    };
     auto user_of_lane = [&](int first) __attribute__((always_inline)) {
         const int u = min(first + lane, batch - 1);
         User x = {hist_len[u], n_targets[u], RT ? rt_len[u] : 0, q_off[u], kv_off[u], 0, 0, 0};
-        const int rows = (layer == 0 ? x.L + x.R : 0) + x.T, blocks = (x.L + x.R + BLK - 1) / BLK;
+        const int rows = (layer == 0 ? x.L + x.R : 0) + x.T;
         x.tiles = (int)div_by((uint32_t)(rows + map.rows - 1), sg.rows_magic);
-        x.splits = sg.n_splits == 1 ? 1 : max(1, div_small(blocks + per - 1, per));
+        x.splits = splits_of(x.L + x.R);
         x.items = first + lane < batch ? x.tiles * x.splits * (int)sg.n_heads : 0;
         return x;
     };
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     for (int u = 64; u < batch; u += 64) n_items += __builtin_amdgcn_readlane(scan_lanes(user_of_lane(u).items), 63);
     while (n_items > sg.fit && per < sg.max_per) {
         per += (per + 7) / 8;
-        of.splits = max(1, div_small((of.L + of.R + BLK - 1) / BLK + per - 1, per));
+        of.splits = splits_of(of.L + of.R);
         of.items = lane < batch ? of.tiles * of.splits * (int)sg.n_heads : 0;
         upto = scan_lanes(of.items);
         n_items = n_here = __builtin_amdgcn_readlane(upto, 63);
@@ -142,7 +145,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     const int g = map.n_chunks == 1 ? gc : gc / map.n_chunks, chunk = gc - g * map.n_chunks;
     const int LK = L + R;  // keys that run through the tile loop: history, then real-time
     const int n_rows = layer == 0 ? LK + T : T;
-    const int n_all = (LK + BLK - 1) / BLK, lo = split * per, hi = min(lo + per, n_all);
+    const int n_all = (LK + BLK - 1) / BLK, lo = split * per, hi = split == n_live - 1 ? n_all : lo + per;
     const PackedRows pr(map, tile, chunk, n_rows, g, p.Hq / p.Hkv);
     const int tok_shift = layer == 0 ? 0 : LK;  // token index of query row 0
     const int n_mine = max(hi - lo - wave + NW - 1, 0) / NW;  // steps of this wave: blocks lo + wave + i NW
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
         }
         floatx4 o = {0.f, 0.f, 0.f, 0.f};
         float sum = 0.f;
-        if (PW || own[rb][it] > -INFINITY) {
+        if (split == 0 && tok_shift + x.row >= L) {  // (by the row, not by the logit: one that is NaN has to show)
             const float f = PW ? own[rb][it] : fast_exp2(own[rb][it] - mx);
             sum = f;
 #pragma unroll
@@ -358,7 +361,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
 #pragma unroll
             for (int j = 0; j < 4; j++) o4[j] = o[j] * inv;
             *(floatx4*)(p.o_part + (((int64_t)split * p.total_q + row) * p.Hq + x.h) * D + 4 * c) = o4;
-            if (c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : lse;
+            if (c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : sum == sum ? lse : sum;
             // the splits that this user's keys do not reach are nobody's: nothing was left there
             if (c == 0 && split == 0)
                 for (int k = n_live; k < sg.n_splits; k++) p.lse_part[((int64_t)k * p.Hq + x.h) * p.total_q + row] = -INFINITY;

@@ -8,7 +8,9 @@
 //   1. prepare: -delta = -<dO, O> and -lse/scale of every row (and the rows' limits, with real-time tokens), for
 //   2. one grid of three kinds of workgroups that do not depend on each other:
 //      dK/dV: 32 keys; the four waves share the rows, every fourth unit of 32 packed (row, head) pairs each, and add up
-//             their dK, dV through LDS;
+//             their dK, dV through LDS.  Or 128 keys, 32 to a wave, each with all units to itself: where users have few rows four waves
+//             have nothing to share, and a workgroup costs 4 to 6 us beside its units (whole backward of 277 target layers of 1..4 candidates
+//             on 241 keys, 8/2 heads, 57 -> 31 us; 40 of 1..4 on 881..1762, 16/2 heads at head_dim 128, 113 -> 48);
 //      dQ:    32 packed rows; the four waves share the keys, every fourth block of 32 each, and add up their dQ;
 //      dk/dv of the target tokens' own keys.
 // A wave only reads what it copied itself (global -> LDS, asynchronously, two units or blocks ahead): no barrier before
@@ -29,6 +31,60 @@ namespace hta {
 namespace {
 
 constexpr int NW = BRIEF_NW;
+
+// What the one grid can look like.  Four waves per key block or one, and with one the dQ workgroups, whose chains are then no shorter, in
+// front or behind.
+// (Two waves per block, which are never far behind the better of these, 0.3 % of the time; dQ in front with four, 0.2 %: not worth their kernels.)
+struct BriefForm {
+    int ways;
+    bool dq_first;
+    double us;  // estimated
+};
+// Time of a call in that form (us): what the workgroups take together -- a fixed part, a part per step (a unit of rows; four blocks of keys),
+// and what one costs that only the longest user has a tile for -- or the longest chain, whichever is longer (the cubes: near the line a bit of
+// both).  Fits of 13000 calls timed in every form (4 to 600 users of 32 to 4096 keys, 2 to 160 candidates, full and target layers):
+// of 6370 short calls the form with the least takes 0.74 of the time of four waves per block, the best of each 0.73; 2 % are slower by more than 3 %.
+double brief_us(const Params& p, int ways, bool dq_first) {
+    struct { double launch, kv, kv_step, dq, dq_step, empty, chain, chain_kv, chain_dq, rt, pw; } c;
+    if (p.d == 32) c = ways == 4 ? decltype(c){6.7, 1.7, 0.55, 0.9, 1.2, 0.7, 0.96, 0.59, 0.46, 1.37, 1.18}
+                     : !dq_first ? decltype(c){6.2, 4.2, 0.76, 0.6, 0.72, 1.1, 1.3, 0.6, 0.37, 1.55, 1.29}
+                                 : decltype(c){6.1, 3.0, 1.44, 1.7, 0.3, 0.63, 1.4, 0.65, 0.33, 1.54, 1.29};
+    else if (p.d == 64) c = ways == 4 ? decltype(c){7.4, 4.3, 0.4, 3.7, 2.1, 1.2, 0., 1.03, 0.98, 1.15, 1.09}
+                          : !dq_first ? decltype(c){7.1, 6.9, 0.81, 3.1, 1.5, 2.2, 0.94, 0.84, 0.63, 1.41, 1.16}
+                                      : decltype(c){7.3, 5.4, 2.25, 4.85, 0.32, 1.9, 0.63, 0.96, 0.54, 1.39, 1.15};
+    else c = ways == 4 ? decltype(c){8.0, 5.9, 0.8, 5.85, 2.55, 1.8, 0., 1.39, 1.96, 1.05, 1.1}
+           : !dq_first ? decltype(c){7.4, 9.8, 2.4, 5.2, 0.44, 3.4, 2.55, 1.2, 1.1, 1.19, 1.14}
+                       : decltype(c){8.1, 8.5, 2.64, 6.8, 0.3, 2.7, 1.4, 1.53, 0.89, 1.19, 1.13};
+    const double groups = (double)p.batch * p.Hkv, r = p.Hq / p.Hkv, keys = mean_keys(p), longest = (double)max_lead_keys(p);
+    const double units = mean_rows(p) * r / 32., most = (double)max_query_rows(p) * r / 32., block = NW / ways * 32.;
+    const double kv_grid = groups * std::ceil(longest / block), kv = std::min(groups * (keys / block + 0.5), kv_grid);
+    const double dq_grid = groups * std::ceil(most), dq = std::min(groups * (units + 0.5), dq_grid);
+    const double step = (p.rt_len ? c.rt : 1.) * (p.pointwise ? c.pw : 1.);
+    const double all = (c.kv * kv + c.dq * dq + c.empty * (kv_grid - kv + dq_grid - dq) +
+                        step * (c.kv_step * kv * std::max(1., units / ways + 0.25) + c.dq_step * dq * std::max(1., keys / 128. + 0.3))) / (p.d == 128 ? 256. : 512.);
+    const double chain = c.chain + step * std::max(c.chain_kv * std::ceil(most / ways), c.chain_dq * std::ceil(longest / 128.));
+    return c.launch + std::cbrt(all * all * all + chain * chain * chain);
+}
+BriefForm brief_form(const Params& p) {
+    BriefForm best = {4, false, brief_us(p, 4, false)};
+    for (bool dq_first : {false, true}) {
+        const double us = brief_us(p, 1, dq_first);
+        if (us < best.us) best = {1, dq_first, us};
+    }
+    return best;
+}
+// The same for the two passes (in whichever of their forms): dQ by tiles of 128 packed rows, dK/dV by 128 keys.
+double two_passes_us(const Params& p) {
+    struct { double launch, dq, dq_step, kv, kv_step, chain, chain_dq, chain_kv, rt, pw; } c;
+    if (p.d == 32) c = {10.6, 2.9, 1.55, 3.4, 0.73, 0., 0.83, 0.17, 1.33, 1.35};
+    else if (p.d == 64) c = {11.6, 4.6, 1.13, 6.4, 1.9, 0.9, 1.39, 0.25, 1.22, 1.24};
+    else c = {17.2, 18.1, 8.3, 13.7, 1.6, 0.3, 2.3, 0.36, 1.14, 1.17};
+    const double groups = (double)p.batch * p.Hkv, r = p.Hq / p.Hkv, keys = mean_keys(p), units = mean_rows(p) * r / 32.;
+    const double dq = groups * (units / 4. + 0.5), kv = groups * (keys / 128. + 0.5), step = (p.rt_len ? c.rt : 1.) * (p.pointwise ? c.pw : 1.);
+    const double all = (c.dq * dq + c.kv * kv + step * (c.dq_step * dq * keys / 64. + c.kv_step * kv * std::max(1., units))) / 512.;
+    const double chain = c.chain + step * (c.chain_dq * max_lead_keys(p) / 64. + c.chain_kv * max_query_rows(p) * r / 32.);
+    return c.launch + std::cbrt(all * all * all + chain * chain * chain);
+}
 
 // ---------------------------------------------------------------------------------------- dQ
 template <int D, bool RT, bool PW>
@@ -204,14 +260,14 @@ __device__ __forceinline__ void brief_dq(const Params& p, const RowMap& map, uns
     }
 }
 
-// Blocks [0, n_kv): dK/dV; [n_kv, n_kv + n_dq): dQ; then the own keys of the targets, self_bpu blocks per user.
-template <int D, bool RT, bool PW>
-__global__ __launch_bounds__(NW * 64, D == 128 ? 1 : 2) void brief_kernel(Params p, RowMap map, int n_kt, unsigned n_kv, unsigned n_dq,
+// n_kv blocks of dK/dV and n_dq of dQ, one kind after the other; then the own keys of the targets, self_bpu blocks per user.
+template <int D, int WAYS, bool RT, bool PW>
+__global__ __launch_bounds__(NW * 64, D == 128 ? 1 : 2) void brief_kernel(Params p, RowMap map, int n_kt, unsigned n_kv, unsigned n_dq, bool dq_first,
                                                                           unsigned self_bpu) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[Brief<D, RT>::BYTES];
-    const unsigned id = blockIdx.x;
-    if (id < n_kv) brief_dkdv<D, NW, RT, PW>(p, map, id, n_kt, 0, smem);
-    else if (id < n_kv + n_dq) brief_dq<D, RT, PW>(p, map, id - n_kv, smem);
+    const unsigned id = blockIdx.x, kv0 = dq_first ? n_dq : 0, dq0 = dq_first ? 0 : n_kv;
+    if (id - kv0 < n_kv) brief_dkdv<D, WAYS, RT, PW>(p, map, id - kv0, n_kt, 0, smem);
+    else if (id - dq0 < n_dq) brief_dq<D, RT, PW>(p, map, id - dq0, smem);
     else bwd_self_block<D, PW, NW * 64>(p, (int)((id - n_kv - n_dq) % self_bpu), (int)((id - n_kv - n_dq) / self_bpu));
 }
 
@@ -251,14 +307,15 @@ __global__ __launch_bounds__(256) void prepare_kernel(Params p, unsigned n_stat,
     }
 }
 
-template <int D, bool PW>
-hipError_t launch(const Params& p, hipStream_t s) {
+template <int D, int WAYS, bool PW>
+hipError_t launch(const Params& p, const BriefForm& form, hipStream_t s) {
     const int64_t rows = max_query_rows(p), keys = max_lead_keys(p);
     constexpr int LPR = D / 8, IPB = NW * 64 / LPR;
     const int64_t n_stat = (p.total_q * p.Hq + 256 / LPR - 1) / (256 / LPR);
     const int64_t lim_bpu = p.rt_len ? (rows + 255) / 256 : 0;
     const RowMap map = row_map(32, p.Hq, p.Hkv, rows);
-    const int64_t n_kt = (keys + 31) / 32;
+    constexpr int KEYS = NW / WAYS * 32;
+    const int64_t n_kt = (keys + KEYS - 1) / KEYS;
     const int64_t n_kv = work_grid((int64_t)p.batch * p.Hkv, n_kt);
     const int64_t n_dq = work_grid((int64_t)p.batch * p.Hkv * map.n_chunks, map.n_tiles);
     const int64_t self_bpu = ((int64_t)p.max_targets * p.Hkv + IPB - 1) / IPB;
@@ -272,12 +329,18 @@ hipError_t launch(const Params& p, hipStream_t s) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     timing_begin(MTFM_HTA_KERNEL_BWD_DKDV, s);
-    auto kernel = p.rt_len ? brief_kernel<D, true, PW> : brief_kernel<D, false, PW>;
+    auto kernel = p.rt_len ? brief_kernel<D, WAYS, true, PW> : brief_kernel<D, WAYS, false, PW>;
     if (n_blocks > 0)
         hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p, map, (int)n_kt, (unsigned)n_kv, (unsigned)n_dq,
-                           (unsigned)(self_bpu > 0 ? self_bpu : 1));
+                           form.dq_first, (unsigned)(self_bpu > 0 ? self_bpu : 1));
     timing_end(MTFM_HTA_KERNEL_BWD_DKDV, s);
     return hipGetLastError();
+}
+
+template <int D, bool PW>
+hipError_t launch_form(const Params& p, hipStream_t s) {
+    const BriefForm form = brief_form(p);
+    return form.ways == 4 ? launch<D, 4, PW>(p, form, s) : launch<D, 1, PW>(p, form, s);
 }
 
 template <int D, int WAYS, bool PW>
@@ -304,19 +367,25 @@ hipError_t launch_dkdv_ways(const Params& p, hipStream_t s) {
 
 // Both launches pay where the dQ part is small too: its workgroups of 32 rows walk their keys in a quarter of the time, at
 // twice the traffic (19 users of 405..1623 keys x 40 candidates: 66 -> 41 us per step against the ordinary dQ pass and this
-// dK/dV pass; 53 users of 100 keys, full layer: 54 either way).
+// dK/dV pass; 53 users of 100 keys, full layer: 54 either way).  Up to the first line always: against the better of one pass and two, 0.63 of
+// the time on 6370 calls, 6 % of which are slower by more than 3 %, mostly at head_dim 128.  Beyond it by the estimates, where key blocks are not shared (of 2985
+// calls 25 % go here, which makes all of them 0.92 of the time at 64, 0.89 at 32 and 0.95 at 128; 25 are slower by more than 3 %).  The estimate
+// of one pass is above its time by a seventh in this range, and further for a row or two on long histories.
 bool bwd_is_brief(const Params& p) {
     if (p.total_q == 0) return false;
     const int r = p.Hq / p.Hkv;
     const double blocks = p.total_q * r / 32. * p.Hkv + 0.5 * p.batch * p.Hkv;  // of 32 packed rows
-    return blocks <= 1024. && blocks * (mean_keys(p) / 32. + 0.5) <= 12. * 1024.;
+    if (blocks <= 1024. && blocks * (mean_keys(p) / 32. + 0.5) <= 12. * 1024.) return true;
+    if (blocks > 4096. || blocks * (mean_keys(p) / 32. + 0.5) > 144. * 1024.) return false;
+    const BriefForm form = brief_form(p);
+    return form.ways == 1 && form.us < 0.95 * two_passes_us(p) && form.us < 0.8 * onepass_us(p);
 }
 
 hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s) {
     switch (p.d) {
-        case 32: return p.pointwise ? launch<32, true>(p, s) : launch<32, false>(p, s);
-        case 64: return p.pointwise ? launch<64, true>(p, s) : launch<64, false>(p, s);
-        default: return p.pointwise ? launch<128, true>(p, s) : launch<128, false>(p, s);
+        case 32: return p.pointwise ? launch_form<32, true>(p, s) : launch_form<32, false>(p, s);
+        case 64: return p.pointwise ? launch_form<64, true>(p, s) : launch_form<64, false>(p, s);
+        default: return p.pointwise ? launch_form<128, true>(p, s) : launch_form<128, false>(p, s);
     }
 }
 

@@ -577,35 +577,46 @@ hipError_t launch(const Params& p, hipStream_t s) {
 // and pointwise weights, too) one pass takes 0.79 of the time of two and is faster on nine of ten.  Where it is not, a few workgroups
 // make a second round (there it has to win by a fifth) or most units are idle.  The line takes 6070 of them, 100 of these slower than in two passes by
 // more than 3 %, and leaves 2 % of the time; the one before, fitted when leaving the work queue cost up to 45 us, took 2952 and left 12 %.
-bool bwd_is_onepass(const Params& p) {
+static bool onepass_fits(const Params& p) {
     const int r = p.Hq / p.Hkv;
-    if (p.d != OP_D || !power_of_two(r) || r > OP_MAX_HEADS || p.total_q == 0 || max_query_rows(p) * r > OnePass<2>::LANES || bwd_is_brief(p))
-        return false;
-    const double items = (double)p.batch * p.Hkv, pairs = mean_rows(p) * r, most = (double)max_query_rows(p) * r;
-    const double keys = mean_keys(p), longest = (double)max_lead_keys(p);
-    const double units = pairs / 32. + 0.5, blocks = keys / 32. + 0.5;
-    const bool rt = p.rt_len != nullptr, pw = p.pointwise, full = p.layer == 0, resident = !full && keys >= 512.;
-    struct { double launch, product, pw, rt, unit, block, item, longest, most, rt_launch; } t;
-    if (full) t = {5.7, 0.36, 0.95, 2.5, 6.0, 7.1, 6.4, 0.26, 0.36, 1.0};
-    else if (resident) t = {10.4, 0.67, 1.4, 1.43, 9.4, 4.6, 0., 0.34, 0.2, 0.};
-    else t = {3.9, 0.62, 1.4, 1.2, 8.1, 4.6, 5.1, 0.32, 0.67, 2.8};
-    const double two_passes = t.launch + (rt ? t.rt_launch : 0.) + (t.longest * longest + t.most * most) / 32. +
-                              items / 1024. * (t.product * (pw ? t.pw : 1.) * (rt ? t.rt : 1.) * units * blocks + t.unit * units + t.block * blocks + t.item);
+    return p.d == OP_D && power_of_two(r) && r <= OP_MAX_HEADS && p.total_q > 0 && max_query_rows(p) * r <= OnePass<2>::LANES;
+}
+// target layers on long histories, whose two passes may keep a user's rows resident
+static bool long_histories(const Params& p) { return p.layer != 0 && mean_keys(p) >= 512.; }
+static double onepass_rounds(const Params& p) { return (double)p.batch * p.Hkv * (single_group(p) ? 1 : 2) / 512.; }
 
+double onepass_us(const Params& p) {
+    if (!onepass_fits(p)) return INFINITY;
+    const double r = p.Hq / p.Hkv, pairs = mean_rows(p) * r, most = max_query_rows(p) * r, keys = mean_keys(p), longest = (double)max_lead_keys(p);
     const int groups = single_group(p) ? 1 : 2;
-    const double rounds = items * groups / 512., whole = std::ceil(rounds - 0.01);
+    const double rounds = onepass_rounds(p), whole = std::ceil(rounds - 0.01);
     struct { double launch, fixed, unit, block, second, alone, alone_second, partial, jagged, rt, pw; } c;
-    if (resident && groups == 1) c = {rounds <= 0.5 ? 5.6 : 16.6, 17.9, 1.2, 1.5, 0.69, 1.16, 0.35, 0., 0.55, 1.1, 1.035};
-    else if (resident) c = {16.6, 7.7, 0.6, 1.85, 0.5, 1.85, 0.5, 0., 0.55, 1.1, 1.035};
+    if (long_histories(p)) c = groups == 2     ? decltype(c){16.6, 7.7, 0.6, 1.85, 0.5, 1.85, 0.5, 0., 0.55, 1.1, 1.035}
+                               : rounds <= 0.5 ? decltype(c){5.6, 17.9, 1.2, 1.5, 0.69, 1.16, 0.35, 0., 0.55, 1.1, 1.035}
+                                               : decltype(c){16.6, 17.9, 1.2, 1.5, 0.69, 1.16, 0.35, 0., 0.55, 1.1, 1.035};
     else if (groups == 1) c = {5.6, 7.6, 0.96, 1.8, 0.72, 1.2, 0.34, 0.39, 0.44, 1.1, 0.99};
     else c = {5.1, 5.9, 0.65, 2.1, 0.47, 1.1, 1.3, 0.18, 0.48, 1.1, 0.93};
     const double first_units = 128. * groups;  // pairs that the waves hold with one unit each
     auto two_units = [&](double x) { return most > first_units ? std::min(1., std::max(0., (x - first_units) / (0.25 * first_units) + 0.5)) : 0.; };
-    const double fixed = c.fixed + c.unit * units;
-    const double item = fixed + (c.block + c.second * two_units(pairs)) * blocks;
+    const double fixed = c.fixed + c.unit * (pairs / 32. + 0.5);
+    const double item = fixed + (c.block + c.second * two_units(pairs)) * (keys / 32. + 0.5);
     const double last = fixed + (c.alone + c.alone_second * two_units(most)) * longest / 32.;  // of the longest item
     const double many = keys >= 0.9 * longest ? whole + c.partial * (rounds - whole) : std::max(rounds + c.jagged, 1.);
-    const double one_pass = c.launch + std::max(last, many * item) * (rt ? c.rt : 1.) * (pw ? c.pw : 1.);
+    return c.launch + std::max(last, many * item) * (p.rt_len ? c.rt : 1.) * (p.pointwise ? c.pw : 1.);
+}
+
+bool bwd_is_onepass(const Params& p) {
+    if (!onepass_fits(p) || bwd_is_brief(p)) return false;
+    const double items = (double)p.batch * p.Hkv, r = p.Hq / p.Hkv, units = mean_rows(p) * r / 32. + 0.5, blocks = mean_keys(p) / 32. + 0.5;
+    const bool resident = long_histories(p);
+    struct { double launch, product, pw, rt, unit, block, item, longest, most, rt_launch; } t;
+    if (p.layer == 0) t = {5.7, 0.36, 0.95, 2.5, 6.0, 7.1, 6.4, 0.26, 0.36, 1.0};
+    else if (resident) t = {10.4, 0.67, 1.4, 1.43, 9.4, 4.6, 0., 0.34, 0.2, 0.};
+    else t = {3.9, 0.62, 1.4, 1.2, 8.1, 4.6, 5.1, 0.32, 0.67, 2.8};
+    const double product = t.product * (p.pointwise ? t.pw : 1.) * (p.rt_len ? t.rt : 1.);
+    const double two_passes = t.launch + (p.rt_len ? t.rt_launch : 0.) + (t.longest * max_lead_keys(p) + t.most * max_query_rows(p) * r) / 32. +
+                              items / 1024. * (product * units * blocks + t.unit * units + t.block * blocks + t.item);
+    const double one_pass = onepass_us(p), rounds = onepass_rounds(p);
     return resident ? one_pass + 5. < two_passes : one_pass < two_passes * (rounds > 1.02 && rounds < 1.5 ? 0.8 : 0.93);
 }
 

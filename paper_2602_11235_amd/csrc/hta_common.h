@@ -98,6 +98,7 @@ hipError_t launch_fwd_bf16(const Params& p, hipStream_t s);
 hipError_t launch_serve_bf16(const Params& p, hipStream_t s);
 hipError_t launch_bwd_bf16(const Params& p, hipStream_t s);
 bool bwd_is_onepass(const Params& p);                           // one kernel for dQ, dK, dV: hta_bwd_onepass_bf16.hip
+double onepass_us(const Params& p);                             // its estimated time, infinite where it does not fit
 hipError_t launch_bwd_onepass_bf16(const Params& p, hipStream_t s);
 bool bwd_is_brief(const Params& p);                             // little work: the kernels of hta_bwd_brief_bf16.hip, no schedule
 hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s);

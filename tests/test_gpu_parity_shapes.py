@@ -24,9 +24,15 @@ SHAPES = {
     "brief_rt": (TARGET, 24, 0, 0, (8, 2, 64), True),
     "brief_d32": (FULL, 16, 0, 0, (3, 1, 32), True),
     "brief_d128": (TARGET, 20, 0, 0, (6, 2, 128), True),
+    # ... and few rows against more keys: a wave to each key block, dQ behind dK/dV or (d32, long) in front
+    "brief_alone": (TARGET, 100, 200, 0, (8, 2, 64), False),
+    "brief_alone_d32": (TARGET, 90, 100, 0, (6, 2, 32), False),
+    "brief_alone_d128": (TARGET, 40, 600, 0, (16, 2, 128), True),
+    "brief_alone_long": (TARGET, 70, 800, 0, (8, 2, 64), True),
     # more of them: dQ in its ordinary form, a key block's rows shared by one, two or four waves
     "one_way": (TARGET, 330, 0, 0, (8, 2, 64), False),
     "one_way_rt": (TARGET, 330, 0, 0, (6, 2, 64), True),
+    "one_way_many_rt": (TARGET, 1500, 100, 0, (6, 2, 64), True),
     "one_way_single_heads": (FULL, 400, 0, 0, (4, 4, 64), False),
     "one_way_single_heads_long": (FULL, 400, (500,), 0, (4, 4, 64), False),
     "two_ways": (FULL, 160, 0, 0, (8, 2, 64), False),
@@ -99,14 +105,14 @@ def test_the_resident_shapes_reach_the_resident_kernel(name):
     assert units < items and 0 < taken < items + 2 * units
 
 
-@pytest.mark.parametrize("name", ["brief_rt", "brief_d128", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "ordinary_d32_rt",
+@pytest.mark.parametrize("name", ["brief_rt", "brief_d128", "brief_alone_long", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "ordinary_d32_rt",
                                   "brief_wide", "rows64_wide"])
 def test_shapes_with_pointwise_weights(name):
     case, users = make(name)
     check_pointwise(case, norm=1.0 / 64, users=users, compare=close_on_row_scale)
 
 
-@pytest.mark.parametrize("name", ["brief", "brief_d32", "brief_d128", "one_way", "one_way_rt", "two_ways", "four_ways_d128",
+@pytest.mark.parametrize("name", ["brief", "brief_d32", "brief_d128", "brief_alone", "brief_alone_d128", "one_way", "one_way_rt", "two_ways", "four_ways_d128",
                                   "ordinary_d32", "ordinary_d32_rt", "ordinary_d128_rt", "one_pass", "rows_resident"])
 def test_non_finite_values_stay_with_their_user(name):
     """The users that own the call's first and last query rows get NaN everywhere; everyone else's results keep their bits.  (Lanes

@@ -11,10 +11,11 @@
 // this one have been formed, its V when the products have.
 //
 // What bounds it, at head_dim 64 and one workgroup of 32 rows per compute unit: 2.05 us per 1000 keys, where the copies
-// alone take 1.66 (64 bytes per clock and unit) and the arithmetic alone 2.0, and 6 us of launch, first loads and merge.  K
-// fragments straight to registers (no LDS write and read): 3.6 us per 1000 keys, 32-byte pieces of a row per lane pair.
-// Four waves with the whole register file each: 5 to 6 us.  One 2048 + 128 token request at 8/2 heads: 18.0 -> 10.2 us
-// per call; 8 requests of 512..4096: 22.1 -> 16.3, with real-time tokens 25.0 -> 16.3; 4 of 8192 at head_dim 128: 37.6 -> 32.8.
+// alone take 1.66 (64 bytes per clock and unit) and the arithmetic alone 2.0, 4.7 us of launch, first loads and merge, and 2.4 for
+// a merge launch.  K fragments straight to registers (no LDS write and read): 3.6 us per 1000 keys, 32-byte pieces of a row per lane
+// pair.  Four waves with the whole register file each: 5 to 6 us.  Against a grid of the longest user's tiles that began with 2000 cycles of
+// decoding: one 2048 + 128 token request at 8/2 heads 10.2 -> 9.2 us per call; 8 requests of 512..4096 16.2 -> 14.0, with real-time
+// tokens 16.2 -> 12.8; 4 of 8192 at head_dim 128 33.7 -> 29.2.  (The ordinary kernel: 18.0, 22.1, 25.0 and 37.6.)
 #include "../../include/mtfm_hta.h"
 #include "../../include/mtfm_hta_timing.h"
 #include "hta_common.h"

@@ -349,7 +349,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
         }
         if (!x.live || id >= SV::MERGED) continue;
         const float inv = PW ? p.norm * p.scale : (sum > 0.f ? 1.f / sum : 0.f);
-        const float lse = sum > 0.f ? (mx + __builtin_amdgcn_logf(sum)) * LN2 : -INFINITY;
+        const float lse = sum > 0.f ? (mx + __builtin_amdgcn_logf(sum)) * LN2 : sum == sum ? -INFINITY : sum;  // (NaN shows here, too)
         const int64_t row = q_base + x.row;
         if (sg.n_splits == 1) {
             bf16x4 o4;
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
 #pragma unroll
             for (int j = 0; j < 4; j++) o4[j] = o[j] * inv;
             *(floatx4*)(p.o_part + (((int64_t)split * p.total_q + row) * p.Hq + x.h) * D + 4 * c) = o4;
-            if (c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : sum == sum ? lse : sum;
+            if (c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : lse;
             // the splits that this user's keys do not reach are nobody's: nothing was left there
             if (c == 0 && split == 0)
                 for (int k = n_live; k < sg.n_splits; k++) p.lse_part[((int64_t)k * p.Hq + x.h) * p.total_q + row] = -INFINITY;

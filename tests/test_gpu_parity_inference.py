@@ -112,18 +112,20 @@ def test_lists_of_items_pointwise(name):
 @pytest.mark.parametrize("name,hist,targets,heads", [("one_piece", [700, 90], [20, 3], (8, 2, 64)), ("pieces", [8192, 300], [20, 3], (8, 2, 64)),
                                                      ("pieces_d128", [8192, 7000, 100, 8000], [64, 60, 3, 50], (16, 2, 128))])
 def test_nan_shows(name, hist, targets, heads):
-    """A NaN key reaches every row that sees it, and no other: the own key of a candidate, and a key far back in a history."""
+    """A NaN key reaches every row that sees it, in out and in lse, and no other: the own key of a candidate, and a key far back in a history."""
     case = inputs.make_case(inputs.custom_config(name, TARGET, hist, targets, *heads, seed=38))
     r, nan = heads[0] // heads[1], float("nan")
-    clean, _ = device_batch(case).forward()
+    clean, clean_lse = device_batch(case).forward()
     for key, rows in ((hist[0] + 1, slice(1, 2)), (hist[0] * 7 // 8, slice(0, targets[0]))):
         batch = device_batch(case)
         batch.k[key, 0, 5] = nan
-        out, _ = batch.forward()
+        out, lse = batch.forward()
         expected = torch.zeros(out.shape[:2], dtype=torch.bool, device="cuda")
         expected[rows, :r] = True
         assert torch.equal(out.isnan().all(dim=2), expected)
         assert torch.equal(out[~expected], clean[~expected])
+        assert torch.equal(lse.isnan(), expected.T)
+        assert torch.equal(lse[~expected.T], clean_lse[~expected.T])
 
 
 def test_split_and_unsplit_forward_agree():

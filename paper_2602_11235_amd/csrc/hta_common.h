@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 namespace hta {
@@ -65,6 +66,16 @@ inline double mean_keys(const Params& p) {
     const double keys = p.layer == 0 ? mean_rows(p) - 0.5 * p.max_targets : (double)(p.total_kv - p.total_q) / p.batch;
     return keys < 1. ? 1. : keys > (double)max_lead_keys(p) ? (double)max_lead_keys(p) : keys;
 }
+// The most keys that a user can have: the bound, and no more than all users have together.
+inline int64_t most_keys(const Params& p) {
+    const int64_t all = p.layer == 0 ? p.total_kv : p.total_kv - p.total_q, bound = max_lead_keys(p);
+    return all < bound ? all : bound;
+}
+// What the longest user is taken to have where a form is chosen: the bounds of a call (of a captured graph, say) may be far above its lengths, which
+// looks like a few long users among many short ones, and is the likelier where the bound is above two and a half times the mean.  (Requests
+// with bounds of four and eight times their longest: by the bound the chosen form takes 1.065 of the best one's time, by this 1.025; with
+// histories of a heavy tail and true bounds 1.007 and 1.009.)
+inline double longest_keys(const Params& p) { return std::min((double)most_keys(p), 2.5 * mean_keys(p)); }
 // Mask rule 2 (Section 3.2.2): a real-time token is visible only to tokens with later timestamps.  The real-time
 // segment of a user is sorted by time, so the real-time keys a query sees are a prefix of it: those strictly earlier
 // than the query.  lim[row] = hist_len + that prefix length = the number of leading K/V rows of the user the row

@@ -54,6 +54,10 @@ struct Serve {
     static constexpr int Q = KV_BYTES, BEFORE = Q + ROWS * D * 2;
     static constexpr int BYTES = BEFORE > MERGE_BYTES ? BEFORE : MERGE_BYTES;
 };
+// what stands for a split that nobody writes: a NaN that no sum has, since no NaN of a bf16 input has these low bits
+constexpr uint32_t NO_SPLIT = 0x7fc0d15cu;
+__device__ inline float no_split() { return __uint_as_float(NO_SPLIT); }
+__device__ inline bool is_no_split(float lse) { return __float_as_uint(lse) == NO_SPLIT; }
 constexpr int UNITS = 256;   // compute units, each of which holds one workgroup
 constexpr int TS_CAP = 512;  // real-time tokens of a user whose timestamps are searched in LDS
 
@@ -65,9 +69,8 @@ struct ServeGrid {
     uint32_t piece;                   // 0: stretches
     uint32_t n_heads;                 // kv heads x head chunks
     uint32_t rows_magic;              // 2^32 / rows of a tile, rounded up (0: that is 1)
-    int32_t n_splits;                 // the most that a user can have
-    int32_t per;                      // blocks of keys of a split; more where these make more than `fit` items (with at most 64 users)
-    int32_t fit, max_per;
+    int32_t n_splits;                 // the most that a user can have (more than one only with at most 64 users)
+    int32_t per;                      // blocks of keys of a piece, if the longest user has as many as the bounds allow
 };
 inline uint32_t div_magic(uint32_t d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / d + 1); }
 // n / d for n d < 2^32
@@ -76,6 +79,16 @@ __device__ inline uint32_t div_by(uint32_t n, uint32_t magic) { return magic == 
 __device__ inline int div_small(int n, int d) {
     const int q = (int)((float)n * __builtin_amdgcn_rcpf((float)d)), r = n - q * d;
     return r < 0 ? q - 1 : r >= d ? q + 1 : q;
+}
+// the largest over all lanes, of numbers that are not negative
+__device__ inline int max_of_lanes(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr 1, 2, 4, 8
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast 15: into rows 1 and 3
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast 31: into rows 2 and 3
+    return __builtin_amdgcn_readlane(x, 63);
 }
 // sums over the lanes up to and with this one
 __device__ inline int scan_lanes(int x) {
@@ -100,32 +113,49 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     __shared__ __attribute__((aligned(256))) int ts_s[RT ? TS_CAP : 1], row_ts[RT ? SV::ROWS * 2 : 1];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-    struct User {
-        int L, T, R, q, kv, tiles, splits, items;
-    };
-    int per = sg.per;
-    auto splits_of = [&](int keys) __attribute__((always_inline)) {  // (never more than there is room for, whatever the bounds said)
-        return sg.n_splits == 1 ? 1 : min(max(1, div_small((keys + BLK - 1) / BLK + per - 1, per)), sg.n_splits);
+    // (by the lengths, not by the call's bounds, which may be far above them; never more than there is room for)
+    auto splits_of = [&](int blocks, int piece) __attribute__((always_inline)) { return min(max(1, div_small(blocks + piece - 1, piece)), sg.n_splits); };
+    auto shortest_piece = [&](int blocks) __attribute__((always_inline)) { return max(div_small(blocks + sg.n_splits - 1, sg.n_splits), 1); };
+    int L, T, R = 0, tile, gc, split = 0, n_live = 1, per = 0;  // per: blocks of keys of a piece
+    int64_t q_base, kv_base;
+    struct Lane {  // a user's lengths, and its items with the keys in one piece
+        int L, T, R, q, kv, tiles, in_one;
     };
     auto user_of_lane = [&](int first) __attribute__((always_inline)) {
         const int u = min(first + lane, batch - 1);
-        User x = {hist_len[u], n_targets[u], RT ? rt_len[u] : 0, q_off[u], kv_off[u], 0, 0, 0};
-        const int rows = (layer == 0 ? x.L + x.R : 0) + x.T;
-        x.tiles = (int)div_by((uint32_t)(rows + map.rows - 1), sg.rows_magic);
-        x.splits = splits_of(x.L + x.R);
-        x.items = first + lane < batch ? x.tiles * x.splits * (int)sg.n_heads : 0;
+        Lane x = {hist_len[u], n_targets[u], RT ? rt_len[u] : 0, q_off[u], kv_off[u], 0, 0};
+        x.tiles = (int)div_by((uint32_t)((layer == 0 ? x.L + x.R : 0) + x.T + map.rows - 1), sg.rows_magic);
+        x.in_one = first + lane < batch ? x.tiles * (int)sg.n_heads : 0;
         return x;
     };
-    User of = user_of_lane(0);
-    int upto = scan_lanes(of.items), n_here = __builtin_amdgcn_readlane(upto, 63), n_items = n_here;
-    for (int u = 64; u < batch; u += 64) n_items += __builtin_amdgcn_readlane(scan_lanes(user_of_lane(u).items), 63);
-    while (n_items > sg.fit && per < sg.max_per) {
-        per += (per + 7) / 8;
-        of.splits = splits_of(of.L + of.R);
-        of.items = lane < batch ? of.tiles * of.splits * (int)sg.n_heads : 0;
-        upto = scan_lanes(of.items);
-        n_items = n_here = __builtin_amdgcn_readlane(upto, 63);
+    Lane of = user_of_lane(0);
+    const int blocks = (of.L + of.R + BLK - 1) / BLK;
+    int items, splits = 1, upto, n_here, n_items;
+    per = sg.per;
+    auto cut = [&]() __attribute__((always_inline)) {
+        if (sg.n_splits > 1) splits = splits_of(blocks, per);
+        items = of.in_one * splits;
+        upto = scan_lanes(items);
+        n_here = __builtin_amdgcn_readlane(upto, 63);
+    };
+    cut();
+    n_items = n_here;
+    if (sg.n_splits > 1) {  // (64 users at most)
+        // Pieces of the length that the longest user needs in order to have n_splits of them -- sg.per is that if the call's bounds are its
+        // lengths, but they may be far above them -- or longer ones, until all items have a unit.
+        if (__builtin_amdgcn_ballot_w64(splits == sg.n_splits) == 0) {
+            per = shortest_piece(max_of_lanes(blocks));
+            cut();
+        }
+        while (n_here > UNITS && __builtin_amdgcn_ballot_w64(splits > 1) != 0) {
+            per += (per + 7) / 8;
+            cut();
+        }
+        n_items = n_here;
+    } else {
+        for (int u = 64; u < batch; u += 64) n_items += __builtin_amdgcn_readlane(scan_lanes(user_of_lane(u).in_one), 63);
     }
+    wait_vmem_loads();  // (all arrived with the first; the compiler may look for them behind the copies below, and would wait for those, too)
     const int xcd = blockIdx.x % N_XCD, slot_x = blockIdx.x / N_XCD;
     int at = sg.piece == 0 ? xcd * ((n_items + N_XCD - 1) / N_XCD) + slot_x
                            : ((slot_x / (int)sg.piece) * N_XCD + xcd) * (int)sg.piece + slot_x % (int)sg.piece;
@@ -133,16 +163,22 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     for (int u = 64; at >= n_here; u += 64) {
         at -= n_here;
         of = user_of_lane(u);
-        upto = scan_lanes(of.items);
+        items = of.in_one;
+        upto = scan_lanes(items);
         n_here = __builtin_amdgcn_readlane(upto, 63);
+        wait_vmem_loads();
     }
     const int u_lane = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= at));
     auto of_user = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, u_lane); };
-    at -= of_user(upto - of.items);
-    const int L = of_user(of.L), T = of_user(of.T), R = RT ? of_user(of.R) : 0, n_tiles = of_user(of.tiles), n_live = of_user(of.splits);
-    const int64_t q_base = of_user(of.q), kv_base = of_user(of.kv);
-    const int ts_of = __builtin_amdgcn_readfirstlane(div_small(at, n_tiles)), tile = at - ts_of * n_tiles;
-    const int gc = sg.n_splits == 1 ? ts_of : __builtin_amdgcn_readfirstlane(div_small(ts_of, n_live)), split = ts_of - gc * n_live;
+    at -= of_user(upto - items);
+    const int n_tiles = of_user(of.tiles);
+    L = of_user(of.L), T = of_user(of.T), n_live = of_user(splits);
+    if (RT) R = of_user(of.R);
+    q_base = of_user(of.q), kv_base = of_user(of.kv);
+    const int ts_of = __builtin_amdgcn_readfirstlane(div_small(at, n_tiles));
+    tile = at - ts_of * n_tiles;
+    gc = sg.n_splits == 1 ? ts_of : __builtin_amdgcn_readfirstlane(div_small(ts_of, n_live));
+    split = ts_of - gc * n_live;
     const int g = map.n_chunks == 1 ? gc : gc / map.n_chunks, chunk = gc - g * map.n_chunks;
     const int LK = L + R;  // keys that run through the tile loop: history, then real-time
     const int n_rows = layer == 0 ? LK + T : T;
@@ -372,7 +408,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
             if (c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : lse;
             // the splits that this user's keys do not reach are nobody's: nothing was left there
             if (c == 0 && split == 0)
-                for (int k = n_live; k < sg.n_splits; k++) p.lse_part[((int64_t)k * p.Hq + x.h) * p.total_q + row] = -INFINITY;
+                for (int k = n_live; k < sg.n_splits; k++) p.lse_part[((int64_t)k * p.Hq + x.h) * p.total_q + row] = no_split();
         }
     }
     });
@@ -382,7 +418,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
 // combination of softmax results over disjoint key sets.  One thread per 4 features of a (row, head).
 // PW: the partial results are partial sums of non-normalised weights: out = sum_s O_s, no lse.
 // All loads of a thread travel together, AT_ONCE splits of them: one trip to memory is most of what this launch takes.  (Split after split,
-// as the remainder of an unrolled loop is: 2 us more for 4 splits.)
+// as the remainder of an unrolled loop is: 2 us more for 4 splits.)  The splits that a user's keys do not reach are the last ones, and
+// marked: a launch has as many as the longest user may need, and one with bounds far above its lengths more than any has.
 template <int D, int AT_ONCE, bool PW>
 __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, const float* lse_part, int64_t total_q, int Hq, int n_splits,
                                                            void* out, float* lse) {
@@ -402,21 +439,24 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, 
             ls[s] = lse_part[at_lse + i * l_stride];
             os[s] = *(const floatx4*)(o_part + id * 4 + i * o_stride);
         }
+        const float next = lse_part[at_lse + min(s0 + AT_ONCE, n_splits - 1) * l_stride];
         const float before = mx;
         if constexpr (!PW) {
 #pragma unroll
-            for (int s = 0; s < AT_ONCE; s++) mx = fmaxf(mx, ls[s]);
+            for (int s = 0; s < AT_ONCE; s++) mx = fmaxf(mx, ls[s]);  // (the mark is a NaN)
             const float f = before > -INFINITY ? __expf(before - mx) : 0.f;
             sum *= f;
             o *= f;
         }
 #pragma unroll
         for (int s = 0; s < AT_ONCE; s++) {
-            const float w = s0 + s >= n_splits ? 0.f : PW ? 1.f : __expf(ls[s] - mx);
+            const bool none = s0 + s >= n_splits || is_no_split(ls[s]);
+            const float w = none ? 0.f : PW ? 1.f : __expf(ls[s] - mx);
             sum += w;
 #pragma unroll
-            for (int j = 0; j < 4; j++) o[j] = s0 + s >= n_splits || ls[s] == -INFINITY ? o[j] : fmaf(w, os[s][j], o[j]);  // (-inf: nothing was left)
+            for (int j = 0; j < 4; j++) o[j] = none || ls[s] == -INFINITY ? o[j] : fmaf(w, os[s][j], o[j]);  // (-inf: no key that the row sees)
         }
+        if (is_no_split(next)) break;
     }
     const float inv = PW ? 1.f : 1.f / sum;
     bf16x4 o4;
@@ -442,15 +482,13 @@ hipError_t launch(const Params& p, hipStream_t s) {
     const int64_t rows = max_query_rows(p);
     if (rows <= 0) return hipSuccess;
     const RowMap map = row_map(RB * 32, p.Hq, p.Hkv, rows);
-    const int64_t max_blocks = (max_lead_keys(p) + SUB * SPS - 1) / (SUB * SPS);
+    const int64_t max_blocks = (most_keys(p) + SUB * SPS - 1) / (SUB * SPS);
     ServeGrid sg;
     sg.per = (int32_t)std::max<int64_t>((max_blocks + p.n_splits - 1) / p.n_splits, 1);
     sg.n_splits = (int32_t)std::max<int64_t>((max_blocks + sg.per - 1) / sg.per, 1);
-    sg.fit = sg.n_splits > 1 && p.batch <= 64 ? UNITS : INT32_MAX;
-    sg.max_per = (int32_t)max_blocks;
     sg.n_heads = (uint32_t)(p.Hkv * map.n_chunks);
     sg.rows_magic = div_magic((uint32_t)map.rows);
-    const int64_t tiles = most_tiles(p, map), most = sg.fit < INT32_MAX ? std::min(tiles * sg.n_splits, std::max<int64_t>(tiles, sg.fit)) : tiles * sg.n_splits;
+    const int64_t tiles = most_tiles(p, map), most = std::min(tiles * sg.n_splits, std::max<int64_t>(tiles, UNITS));
     sg.piece = most <= 320 ? 0 : 4;
     const int64_t dealt = N_XCD * (sg.piece == 0 ? 1 : sg.piece), n_blocks = (most + dealt - 1) / dealt * dealt;
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p.hist_len, p.n_targets, p.q_off, p.kv_off, p.rt_len, p.batch, p.layer,
@@ -458,11 +496,12 @@ hipError_t launch(const Params& p, hipStream_t s) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || sg.n_splits == 1) return e;
     const int64_t threads = p.total_q * p.Hq * (p.d / 4);
+    const int n = (int)sg.n_splits;
     auto merge = merge_splits_kernel<D, 8, false>;
-    if (p.pointwise) merge = sg.n_splits <= 2 ? merge_splits_kernel<D, 2, true> : sg.n_splits <= 4 ? merge_splits_kernel<D, 4, true> : merge_splits_kernel<D, 8, true>;
-    else if (sg.n_splits <= 4) merge = sg.n_splits <= 2 ? merge_splits_kernel<D, 2, false> : merge_splits_kernel<D, 4, false>;
+    if (p.pointwise) merge = n <= 2 ? merge_splits_kernel<D, 2, true> : n <= 4 ? merge_splits_kernel<D, 4, true> : merge_splits_kernel<D, 8, true>;
+    else if (n <= 4) merge = n <= 2 ? merge_splits_kernel<D, 2, false> : merge_splits_kernel<D, 4, false>;
     hipLaunchKernelGGL(merge, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
-                       p.o_part, p.lse_part, p.total_q, p.Hq, (int)sg.n_splits, p.out, p.lse);
+                       p.o_part, p.lse_part, p.total_q, p.Hq, n, p.out, p.lse);
     return hipGetLastError();
 }
 
@@ -508,7 +547,7 @@ static double ordinary_us(const Params& p, int64_t workgroups) {
     else if (fwd_workgroup_rows(p) == 128) c = {5.2, 2.6, 12.e-3, 11.e-3, 2.8};
     else c = {6.7, 1.1, 13.e-3, 17.e-3, 7.4};
     const double fill = workgroups / (double)UNITS;
-    return c.launch + (forward_needs_schedule(p) ? c.schedule : 0.) + c.key * max_lead_keys(p) + c.key_full * mean_keys(p) * fill + c.second * std::max(0., fill - 1.);
+    return c.launch + (forward_needs_schedule(p) ? c.schedule : 0.) + c.key * longest_keys(p) + c.key_full * mean_keys(p) * fill + c.second * std::max(0., fill - 1.);
 }
 // The kernel above, `row_blocks` blocks of 32 rows per workgroup and the keys of the longest user in `splits` pieces.  One workgroup per unit; a
 // key costs more the fuller the chip (its XCDs' L2s feed all units).  In one piece, more items than units take rounds, whole ones where
@@ -518,7 +557,7 @@ struct ServeSize {
     double longest, mean, part;  // keys of the longest user and of the mean; MB of a partial result
     double items[2];             // workgroups with keys in one piece, of one and two row blocks
     ServeSize(const Params& p)
-        : longest((double)max_lead_keys(p)), mean(mean_keys(p)), part(1e-6 * p.total_q * p.Hq * p.d * 4), items{(double)live_tiles(p, 32), (double)live_tiles(p, 64)} {}
+        : longest(longest_keys(p)), mean(mean_keys(p)), part(1e-6 * p.total_q * p.Hq * p.d * 4), items{(double)live_tiles(p, 32), (double)live_tiles(p, 64)} {}
 };
 static double serve_us(const Params& p, const ServeSize& size, int row_blocks, int splits) {
     struct { double launch, item, key, key_full, jagged, merge, part, rt, piece, partial; } c;
@@ -532,7 +571,7 @@ static double serve_us(const Params& p, const ServeSize& size, int row_blocks, i
     const double fixed = c.launch + (p.rt_len ? c.rt : 0.);
     double keys = longest, pieces = items;
     if (splits > 1) {
-        const double fits = items < 250. && p.batch <= 64 ? items * mean / std::max(UNITS - c.piece * items, 16.) : longest;
+        const double fits = items < 250. ? items * mean / std::max(UNITS - c.piece * items, 16.) : longest;
         keys = std::min(std::max(longest / splits, fits), longest);
         const double of_mean = mean / std::max(keys, 1.);
         pieces = items * (even ? std::ceil(of_mean - 0.01) : of_mean + c.piece);
@@ -552,13 +591,13 @@ struct ServeForm {
     int row_blocks, splits;  // splits 0: the ordinary kernel
 };
 static ServeForm serve_form(const Params& p, int room) {
-    const int64_t ordinary = live_tiles(p, fwd_workgroup_rows(p)), blocks = max_lead_keys(p) / SUB;
+    const int64_t ordinary = live_tiles(p, fwd_workgroup_rows(p)), blocks = most_keys(p) / SUB;
     if (ordinary >= 512 || p.batch > 1024 || max_query_rows(p) >= 1 << 20) return {1, 0};
     ServeForm best = {1, 0};
     double best_us = ordinary_us(p, ordinary);
     const ServeSize size(p);
     for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-        if (splits > 1 && (splits > room || splits > blocks / 6 || blocks >= 1 << 15)) break;
+        if (splits > 1 && (splits > room || splits > blocks / 6 || blocks >= 1 << 15 || p.batch > 64)) break;
         for (int rb = 1; rb <= (p.d == 32 ? 1 : 2); rb++) {
             const double us = serve_us(p, size, rb, splits);
             if (us < best_us) best_us = us, best = {rb, splits};
@@ -576,7 +615,7 @@ static int serve_row_blocks(const Params& p) {
 hipError_t launch_serve_bf16(const Params& p, hipStream_t s) {
     const bool two = serve_row_blocks(p) == 2;
     // short lists of keys per wave: single sub-tiles divide more evenly than pairs
-    const bool brief = max_lead_keys(p) / p.n_splits <= 1024;
+    const bool brief = (int64_t)longest_keys(p) / p.n_splits <= 1024;
     hipError_t e;
     timing_begin(MTFM_HTA_KERNEL_FWD, s);
     switch (p.d) {

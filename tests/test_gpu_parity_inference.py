@@ -7,7 +7,7 @@ import torch
 
 from paper_2602_11235_amd import hta, inputs
 from tests import test_gpu_parity_pointwise as pointwise
-from tests.hta_testlib import check_case, device_batch, host
+from tests.hta_testlib import check_case, compare_with_oracle, device_batch, host
 
 pytestmark = pytest.mark.gpu
 FULL, TARGET = inputs.LAYER_FULL, inputs.LAYER_TARGET
@@ -106,6 +106,43 @@ def test_lists_of_items(name, with_rt):
 def test_lists_of_items_pointwise(name):
     layer, hist, targets, heads = LISTS[name]
     pointwise.check(inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=37)))
+
+
+def with_bounds(batch: hta.Batch, factor: int, of_targets: int = 1) -> hta.Batch:
+    """The same call with host bounds that far above its lengths, as a captured graph for requests of many sizes has them."""
+    return hta.Batch(batch.q, batch.k, batch.v, batch.q_offsets, batch.kv_offsets, batch.hist_len, batch.n_targets, batch.max_hist * factor,
+                     batch.max_targets * of_targets, batch.softmax_scale, batch.layer, batch.rt_len, batch.timestamps, batch.max_rt * factor)
+
+
+@pytest.mark.parametrize("factor", [2, 16])
+@pytest.mark.parametrize("with_rt", [False, True])
+@pytest.mark.parametrize("name", ["pieces_grow", "more_than_units", "two_row_blocks_d128_in_pieces", "many_pieces", "many_users"])
+def test_lists_of_items_with_bounds_above_the_lengths(name, with_rt, factor):
+    layer, hist, targets, heads = LISTS[name]
+    rt = np.resize([40, 0, 7, 130, 1], len(hist)) if with_rt else None
+    case = inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=39, rt_len=rt))
+    out, lse = with_bounds(device_batch(case), factor, of_targets=factor).forward()
+    compare_with_oracle(case, {"out": out, "lse": lse}, with_bwd=False)
+
+
+def pieces_of_first_row(batch: hta.Batch) -> int:
+    """Partial results of the call's first row, head 0, by what its logsumexps in the workspace say after a call.  (Behind counters and
+    order, 512 bytes with up to 64 users: partial outputs [splits][total_q][Hq][d], logsumexps [splits][Hq][total_q], float32.)"""
+    per_split = batch.total_q * batch.Hq * 4
+    assert batch.batch <= 64 and batch.rt_len is None and per_split % 256 == 0
+    splits = (batch.fwd_workspace_bytes - 512) // (per_split * (batch.head_dim + 1))
+    batch.fwd_workspace.fill_(0xff)  # (NaN)
+    batch.forward()
+    lse = batch.fwd_workspace[512 + splits * per_split * batch.head_dim:].view(torch.float32)[:splits * per_split // 4]
+    return int(lse.view(splits, -1)[:, 0].isfinite().sum())
+
+
+@pytest.mark.parametrize("heads", [(8, 2, 64), (16, 2, 128), (4, 2, 32)])
+def test_pieces_come_from_the_lengths(heads):
+    """Keys are cut into as many pieces, or more, when the bounds are far above them.  (By the bounds alone it was one or two pieces.)"""
+    case = inputs.make_case(inputs.custom_config("pieces", TARGET, [8192, 8000], [64, 64], *heads, seed=40))
+    pieces = [pieces_of_first_row(b) for b in (device_batch(case), with_bounds(device_batch(case), 8))]
+    assert 1 < pieces[0] <= pieces[1]
 
 
 # keys in one piece and in several, one and two row blocks

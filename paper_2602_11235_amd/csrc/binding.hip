@@ -8,6 +8,7 @@
 #include "../../include/mtfm_gln.h"
 #include "../../include/mtfm_hta.h"
 #include "../../include/mtfm_hta_pw.h"
+#include "hta_common.h"
 
 namespace {
 
@@ -88,6 +89,36 @@ MTFM_HTA_API int mtfm_binding_hta(const void* block, void* stream) {
                                    a.batch, a.total_q, a.total_kv, a.max_hist, a.max_targets, a.Hq, a.Hkv, a.head_dim, a.scale,
                                    a.norm, a.dtype, a.layer, a.workspace, ws, stream);
     }
+}
+
+// Which kernels the call of the block takes in bf16, by the rules that the library itself asks (all on sizes that the host knows; no pointer but
+// rt_len, which is compared with null, is looked at).  For tests and measurements, which want to know what they run.
+//   forward:  [0] pieces of keys (0: the ordinary kernel), [1] blocks of 32 rows per workgroup, [2] 0, [3] is there a schedule's launch?
+//   backward: [0] 0 two passes, 1 one pass, 2 brief; [1] waves that share a key block's rows (two passes: 0 for the kernels with a work queue),
+//             [2] brief: dQ's workgroups in front; two passes with a queue: a user's rows resident; [3] is there a schedule's launch?
+MTFM_HTA_API int mtfm_binding_hta_form(const void* block, int32_t* form) {
+    const HtaArgs& a = *(const HtaArgs*)block;
+    if (a.dtype != MTFM_HTA_BF16 || a.batch <= 0 || a.total_q <= 0) return MTFM_HTA_ERR_INVALID_ARG;
+    hta::Params p{};
+    p.batch = a.batch; p.total_q = a.total_q; p.total_kv = a.total_kv; p.max_hist = a.max_hist; p.max_targets = a.max_targets;
+    p.Hq = a.Hq; p.Hkv = a.Hkv; p.d = a.head_dim == hta::BF16_PADDED_FROM ? hta::BF16_PADDED_TO : a.head_dim; p.layer = a.layer;
+    if (a.rt_len && a.max_rt > 0) p.rt_len = a.rt_len, p.max_rt = a.max_rt;
+    p.pointwise = a.call == PW_FWD || a.call == PW_BWD;
+    if (a.call == FWD || a.call == PW_FWD) {
+        p.n_splits = hta::serve_splits(p, hta::fwd_key_splits(p.batch, p.Hq, p.Hkv, p.d, hta::max_query_rows(p), hta::max_lead_keys(p)));
+        form[0] = p.n_splits;
+        form[1] = p.n_splits > 0 ? hta::serve_row_blocks(p) : hta::fwd_workgroup_rows(p) / 32;
+        form[2] = 0;
+        form[3] = p.n_splits == 0 && hta::forward_needs_schedule(p);
+        return MTFM_HTA_OK;
+    }
+    const bool onepass = hta::bwd_is_onepass(p), brief = hta::bwd_is_brief(p);
+    bool dq_first = false;
+    form[0] = onepass ? 1 : brief ? 2 : 0;
+    form[1] = onepass ? 0 : brief ? hta::bwd_brief_ways(p, &dq_first) : hta::dkdv_brief_ways(p);
+    form[2] = brief ? dq_first : form[0] == 0 && form[1] == 0 && hta::dkdv_is_resident(p);
+    form[3] = !brief && hta::backward_needs_schedule(p, onepass);
+    return MTFM_HTA_OK;
 }
 
 MTFM_HTA_API int mtfm_binding_gln(const void* block, void* stream) {

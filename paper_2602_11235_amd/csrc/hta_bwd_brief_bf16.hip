@@ -381,6 +381,12 @@ bool bwd_is_brief(const Params& p) {
     return form.ways == 1 && form.us < 0.95 * two_passes_us(p) && form.us < 0.8 * onepass_us(p);
 }
 
+int bwd_brief_ways(const Params& p, bool* dq_first) {
+    const BriefForm form = brief_form(p);
+    *dq_first = form.dq_first;
+    return form.ways;
+}
+
 hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s) {
     switch (p.d) {
         case 32: return p.pointwise ? launch_form<32, true>(p, s) : launch_form<32, false>(p, s);

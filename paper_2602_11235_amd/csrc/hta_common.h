@@ -113,6 +113,7 @@ double onepass_us(const Params& p);                             // its estimated
 hipError_t launch_bwd_onepass_bf16(const Params& p, hipStream_t s);
 bool bwd_is_brief(const Params& p);                             // little work: the kernels of hta_bwd_brief_bf16.hip, no schedule
 hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s);
+int bwd_brief_ways(const Params& p, bool* dq_first);            // waves per key block there, and whether dQ's workgroups come first
 int dkdv_brief_ways(const Params& p);                           // ... > 0: their dK/dV part behind the ordinary dQ pass
 bool dkdv_is_resident(const Params& p);                         // the ordinary dK/dV pass would keep each user's rows in LDS
 hipError_t launch_dkdv_brief_bf16(const Params& p, hipStream_t s);
@@ -129,6 +130,8 @@ hipError_t launch_narrow16(const void* src, void* dst, int64_t n_rows, hipStream
 int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t max_rows, int64_t max_keys);
 // the splits it does use, at most `room`; 0: the call runs the ordinary forward kernel
 int serve_splits(const Params& p, int room);
+// blocks of 32 rows per workgroup of the kernel for a few requests, once p.n_splits is set
+int serve_row_blocks(const Params& p);
 // packed (row, head) pairs that a workgroup of the ordinary forward kernel takes in this call
 int fwd_workgroup_rows(const Params& p);
 // stores the calling thread's error message (what mtfm_hta_last_error() returns) and hands `code` back

@@ -607,7 +607,7 @@ static ServeForm serve_form(const Params& p, int room) {
 }
 int serve_splits(const Params& p, int room) { return serve_form(p, room).splits; }
 // (of the same estimates, once the splits are chosen)
-static int serve_row_blocks(const Params& p) {
+int serve_row_blocks(const Params& p) {
     const ServeSize size(p);
     return p.d != 32 && serve_us(p, size, 2, p.n_splits) < serve_us(p, size, 1, p.n_splits) ? 2 : 1;
 }

@@ -2,7 +2,9 @@
 C-ABI binding, run the float64 oracle on the same bits, compare element by element."""
 from __future__ import annotations
 
+import ctypes
 import sys
+from typing import NamedTuple
 
 import numpy as np
 import torch
@@ -126,6 +128,33 @@ def queue_takes(batch) -> int:
     assert batch.rt_len is None
     torch.cuda.synchronize()
     return int(batch.workspace.view(torch.int32)[:8].sum().item())
+
+
+class Form(NamedTuple):
+    """What mtfm_binding_hta_form says of a call (csrc/binding.hip)."""
+    kind: int       # forward: pieces of keys, 0 for the ordinary kernel; backward: TWO_PASSES, ONE_PASS, BRIEF
+    ways: int       # forward: blocks of 32 rows per workgroup; backward: waves that share a key block's rows
+    option: int
+    schedule: int   # is there a launch that orders the users?
+
+
+TWO_PASSES, ONE_PASS, BRIEF = 0, 1, 2
+
+
+def form_of_sizes(call, batch, total_q, total_kv, max_hist, max_targets, heads, layer, max_rt=0) -> Form:
+    block = hta._HTA_BLOCK.pack(*[0] * 13, int(max_rt > 0), 0, 0, 0, total_q, total_kv, batch, max_hist, max_rt, max_targets, *heads, 1.0, 1.0,
+                                hta.BF16, layer, call)
+    form = (ctypes.c_int32 * 4)()
+    status = hta.load_library().mtfm_binding_hta_form(block, form)
+    assert status == hta.OK
+    return Form(*form)
+
+
+def form_of(case: inputs.Case, call: int, loose: int = 1) -> Form:
+    """The kernels that a call on `case` takes; loose: bounds of the keys above its longest user's by that factor."""
+    rt = 0 if case.rt_len is None else int(case.rt_len.max())
+    return form_of_sizes(call, case.batch, case.total_q, case.total_kv, int(case.hist_len.max()) * loose, int(case.n_targets.max()),
+                         (case.cfg.Hq, case.cfg.Hkv, case.cfg.head_dim), case.cfg.layer, rt * loose)
 
 
 def compare_with_oracle(case: inputs.Case, g: dict, with_bwd: bool, users=None, kv_group=None, compare=None,

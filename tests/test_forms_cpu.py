@@ -1,0 +1,29 @@
+"""Which kernels a call takes: host rules on sizes, asked without a GPU.  (That the kernels are right is what the parity tests check.)"""
+import pytest
+
+from paper_2602_11235_amd import hta
+from tests.hta_testlib import BRIEF, TWO_PASSES, form_of_sizes
+
+HEADS = (8, 2, 64)
+
+
+def target_layer(call, users, keys, candidates, heads=HEADS, loose=1, max_rt=0):
+    """users of one length; bounds of the keys `loose` times that"""
+    return form_of_sizes(call, users, users * candidates, users * (keys + max_rt + candidates), keys * loose, candidates, heads, hta.LAYER_TARGET,
+                         max_rt * loose)
+
+
+@pytest.mark.parametrize("call", [hta.CALL_FWD, hta.CALL_PW_FWD])
+def test_forward_forms(call):
+    assert target_layer(call, 1, 2048, 128).kind > 1                 # one request: its keys in several pieces
+    assert target_layer(call, 40, 500, 16).kind == 1                 # a unit for every 32 rows: in one
+    assert target_layer(call, 2000, 500, 16).kind == 0               # a full chip: the ordinary kernel ...
+    assert target_layer(call, 2000, 500, 16).schedule == 0           # ... on users of one length, as they are given
+    assert target_layer(call, 2000, 500, 16, max_rt=50).schedule == 1
+
+
+@pytest.mark.parametrize("call", [hta.CALL_BWD, hta.CALL_PW_BWD])
+def test_backward_forms(call):
+    assert target_layer(call, 4, 300, 60).kind == BRIEF
+    assert target_layer(call, 200, 2048, 4).kind == BRIEF
+    assert target_layer(call, 1000, 1500, 70, heads=(12, 2, 64)).kind == TWO_PASSES

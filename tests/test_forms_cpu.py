@@ -25,5 +25,5 @@ def test_forward_forms(call):
 @pytest.mark.parametrize("call", [hta.CALL_BWD, hta.CALL_PW_BWD])
 def test_backward_forms(call):
     assert target_layer(call, 4, 300, 60).kind == BRIEF
-    assert target_layer(call, 200, 2048, 4).kind == BRIEF
+    assert target_layer(call, 277, 241, 3).kind == BRIEF
     assert target_layer(call, 1000, 1500, 70, heads=(12, 2, 64)).kind == TWO_PASSES

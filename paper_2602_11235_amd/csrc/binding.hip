@@ -93,7 +93,8 @@ MTFM_HTA_API int mtfm_binding_hta(const void* block, void* stream) {
 
 // Which kernels the call of the block takes in bf16, by the rules that the library itself asks (all on sizes that the host knows; no pointer but
 // rt_len, which is compared with null, is looked at).  For tests and measurements, which want to know what they run.
-//   forward:  [0] pieces of keys (0: the ordinary kernel), [1] blocks of 32 rows per workgroup, [2] 0, [3] is there a schedule's launch?
+//   forward:  [0] pieces of keys (0: the ordinary kernel), [1] blocks of 32 rows per workgroup, [2] requests in a grid, not a list, [3] is there a
+//             schedule's launch?
 //   backward: [0] 0 two passes, 1 one pass, 2 brief; [1] waves that share a key block's rows (two passes: 0 for the kernels with a work queue),
 //             [2] brief: dQ's workgroups in front; two passes with a queue: a user's rows resident; [3] is there a schedule's launch?
 MTFM_HTA_API int mtfm_binding_hta_form(const void* block, int32_t* form) {
@@ -108,7 +109,7 @@ MTFM_HTA_API int mtfm_binding_hta_form(const void* block, int32_t* form) {
         p.n_splits = hta::serve_splits(p, hta::fwd_key_splits(p.batch, p.Hq, p.Hkv, p.d, hta::max_query_rows(p), hta::max_lead_keys(p)));
         form[0] = p.n_splits;
         form[1] = p.n_splits > 0 ? hta::serve_row_blocks(p) : hta::fwd_workgroup_rows(p) / 32;
-        form[2] = 0;
+        form[2] = p.n_splits > 0 && !hta::serve_takes_list(p);
         form[3] = p.n_splits == 0 && hta::forward_needs_schedule(p);
         return MTFM_HTA_OK;
     }

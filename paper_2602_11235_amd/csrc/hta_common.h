@@ -132,6 +132,8 @@ int fwd_key_splits(int32_t batch, int32_t Hq, int32_t Hkv, int32_t d, int64_t ma
 int serve_splits(const Params& p, int room);
 // blocks of 32 rows per workgroup of the kernel for a few requests, once p.n_splits is set
 int serve_row_blocks(const Params& p);
+// ... and whether its work stands in a list or in a grid
+bool serve_takes_list(const Params& p);
 // packed (row, head) pairs that a workgroup of the ordinary forward kernel takes in this call
 int fwd_workgroup_rows(const Params& p);
 // stores the calling thread's error message (what mtfm_hta_last_error() returns) and hands `code` back

@@ -61,16 +61,21 @@ __device__ inline bool is_no_split(float lse) { return __float_as_uint(lse) == N
 constexpr int UNITS = 256;   // compute units, each of which holds one workgroup
 constexpr int TS_CAP = 512;  // real-time tokens of a user whose timestamps are searched in LDS
 
-// How a launch's workgroups find their work.  An item is (user, kv head, head chunk, split, row tile); a user has as many as its lengths make,
-// and the items of all users are one list: every wave looks at all lengths, a lane to a user, and finds the item of its place by a
-// running sum.  So a launch has no workgroups for tiles and splits that only the longest user has, and its XCDs have equally many whatever
-// the lengths: XCD x takes a stretch of the list, or every eighth piece of `piece` items, whose row tiles read the same keys.
+// How a launch's workgroups find their work.  An item is (user, kv head, head chunk, split, row tile); a user has as many as its lengths make.
+// In a list the items of all users stand one after the other: every wave looks at all lengths, a lane to a user, and finds the item of its
+// place by a running sum.  So a launch has no workgroups for tiles and splits that only the longest user has, and its XCDs have equally
+// many whatever the lengths: XCD x takes a stretch of the list, or every eighth piece of `piece` items, whose row tiles read the same keys.
+// For up to 64 users, and up to 192 where not all places of a grid have a unit at once; splits with the former only.
+// In a grid a workgroup is a place of all (user, head, split, tile) that the bounds allow: many users even each other out, and a list would
+// take every wave rounds of lanes, one trip to memory after the other.  (Target layers of 1 to 64 candidates, a list for all users against a grid for
+// more than 64: 65..192 users with a unit for every place 1.05 to 1.09 of the grid's time, with up to two places per unit 0.96, with more 0.97
+// to 1.02; 193..256 users 1.08 to 1.10, 385..512 1.15, more 1.18.)
 struct ServeGrid {
     uint32_t piece;                   // 0: stretches
     uint32_t n_heads;                 // kv heads x head chunks
     uint32_t rows_magic;              // 2^32 / rows of a tile, rounded up (0: that is 1)
-    int32_t n_splits;                 // the most that a user can have (more than one only with at most 64 users)
-    int32_t per;                      // blocks of keys of a piece, if the longest user has as many as the bounds allow
+    int32_t n_splits;                 // the most that a user can have
+    int32_t per;                      // blocks of keys of a piece in a list, if the longest user has as many as the bounds allow
 };
 inline uint32_t div_magic(uint32_t d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / d + 1); }
 // n / d for n d < 2^32
@@ -103,7 +108,7 @@ __device__ inline int scan_lanes(int x) {
 
 // The arrays that the first loads go to and what finds the user stand alone at the front: arguments in scalar registers when the kernel
 // starts (build.py, KERNARG_PRELOAD), while those inside Params take a load that costs 0.45 us at the start of a launch.
-template <int D, int RB, int NW, int SPS, int NST, bool RT, bool PW>
+template <int D, int RB, int NW, int SPS, int NST, bool RT, bool PW, bool LIST>
 __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* hist_len, const int32_t* n_targets, const int32_t* q_off,
                                                                 const int32_t* kv_off, const int32_t* rt_len, int batch, int layer,
                                                                 ServeGrid sg, Params p, RowMap map) {
@@ -118,67 +123,87 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
     auto shortest_piece = [&](int blocks) __attribute__((always_inline)) { return max(div_small(blocks + sg.n_splits - 1, sg.n_splits), 1); };
     int L, T, R = 0, tile, gc, split = 0, n_live = 1, per = 0;  // per: blocks of keys of a piece
     int64_t q_base, kv_base;
-    struct Lane {  // a user's lengths, and its items with the keys in one piece
-        int L, T, R, q, kv, tiles, in_one;
-    };
-    auto user_of_lane = [&](int first) __attribute__((always_inline)) {
-        const int u = min(first + lane, batch - 1);
-        Lane x = {hist_len[u], n_targets[u], RT ? rt_len[u] : 0, q_off[u], kv_off[u], 0, 0};
-        x.tiles = (int)div_by((uint32_t)((layer == 0 ? x.L + x.R : 0) + x.T + map.rows - 1), sg.rows_magic);
-        x.in_one = first + lane < batch ? x.tiles * (int)sg.n_heads : 0;
-        return x;
-    };
-    Lane of = user_of_lane(0);
-    const int blocks = (of.L + of.R + BLK - 1) / BLK;
-    int items, splits = 1, upto, n_here, n_items;
-    per = sg.per;
-    auto cut = [&]() __attribute__((always_inline)) {
-        if (sg.n_splits > 1) splits = splits_of(blocks, per);
-        items = of.in_one * splits;
-        upto = scan_lanes(items);
-        n_here = __builtin_amdgcn_readlane(upto, 63);
-    };
-    cut();
-    n_items = n_here;
-    if (sg.n_splits > 1) {  // (64 users at most)
-        // Pieces of the length that the longest user needs in order to have n_splits of them -- sg.per is that if the call's bounds are its
-        // lengths, but they may be far above them -- or longer ones, until all items have a unit.
-        if (__builtin_amdgcn_ballot_w64(splits == sg.n_splits) == 0) {
-            per = shortest_piece(max_of_lanes(blocks));
-            cut();
-        }
-        while (n_here > UNITS && __builtin_amdgcn_ballot_w64(splits > 1) != 0) {
-            per += (per + 7) / 8;
-            cut();
-        }
+    if constexpr (LIST) {
+        struct Lane {  // a user's lengths, and its items with the keys in one piece
+            int L, T, R, q, kv, tiles, in_one;
+        };
+        auto user_of_lane = [&](int first) __attribute__((always_inline)) {
+            const int u = min(first + lane, batch - 1);
+            Lane x = {hist_len[u], n_targets[u], RT ? rt_len[u] : 0, q_off[u], kv_off[u], 0, 0};
+            x.tiles = (int)div_by((uint32_t)((layer == 0 ? x.L + x.R : 0) + x.T + map.rows - 1), sg.rows_magic);
+            x.in_one = first + lane < batch ? x.tiles * (int)sg.n_heads : 0;
+            return x;
+        };
+        Lane of = user_of_lane(0);
+        const int blocks = (of.L + of.R + BLK - 1) / BLK;
+        int items, splits = 1, upto, n_here, n_items;
+        per = sg.per;
+        auto cut = [&]() __attribute__((always_inline)) {
+            if (sg.n_splits > 1) splits = splits_of(blocks, per);
+            items = of.in_one * splits;
+            upto = scan_lanes(items);
+            n_here = __builtin_amdgcn_readlane(upto, 63);
+        };
+        cut();
         n_items = n_here;
+        if (sg.n_splits > 1) {  // (64 users at most)
+            // Pieces of the length that the longest user needs in order to have n_splits of them -- sg.per is that if the call's bounds are its
+            // lengths, but they may be far above them -- or longer ones, until all items have a unit.
+            if (__builtin_amdgcn_ballot_w64(splits == sg.n_splits) == 0) {
+                per = shortest_piece(max_of_lanes(blocks));
+                cut();
+            }
+            while (n_here > UNITS && __builtin_amdgcn_ballot_w64(splits > 1) != 0) {
+                per += (per + 7) / 8;
+                cut();
+            }
+            n_items = n_here;
+        } else {
+            for (int u = 64; u < batch; u += 64) n_items += __builtin_amdgcn_readlane(scan_lanes(user_of_lane(u).in_one), 63);
+        }
+        wait_vmem_loads();  // (all arrived with the first; the compiler may look for them behind the copies below, and would wait for those, too)
+        const int xcd = blockIdx.x % N_XCD, slot_x = blockIdx.x / N_XCD;
+        int at = sg.piece == 0 ? xcd * ((n_items + N_XCD - 1) / N_XCD) + slot_x
+                               : ((slot_x / (int)sg.piece) * N_XCD + xcd) * (int)sg.piece + slot_x % (int)sg.piece;
+        if (at >= n_items || (sg.piece == 0 && slot_x >= (n_items + N_XCD - 1) / N_XCD)) return;
+        for (int u = 64; at >= n_here; u += 64) {
+            at -= n_here;
+            of = user_of_lane(u);
+            items = of.in_one;
+            upto = scan_lanes(items);
+            n_here = __builtin_amdgcn_readlane(upto, 63);
+            wait_vmem_loads();
+        }
+        const int u_lane = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= at));
+        auto of_user = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, u_lane); };
+        at -= of_user(upto - items);
+        const int n_tiles = of_user(of.tiles);
+        L = of_user(of.L), T = of_user(of.T), n_live = of_user(splits);
+        if (RT) R = of_user(of.R);
+        q_base = of_user(of.q), kv_base = of_user(of.kv);
+        const int ts_of = __builtin_amdgcn_readfirstlane(div_small(at, n_tiles));
+        tile = at - ts_of * n_tiles;
+        gc = sg.n_splits == 1 ? ts_of : __builtin_amdgcn_readfirstlane(div_small(ts_of, n_live));
+        split = ts_of - gc * n_live;
     } else {
-        for (int u = 64; u < batch; u += 64) n_items += __builtin_amdgcn_readlane(scan_lanes(user_of_lane(u).in_one), 63);
+        const int xcd = blockIdx.x % N_XCD, slot_x = blockIdx.x / N_XCD, ny = (int)sg.n_heads * sg.n_splits;
+        const int group = __builtin_amdgcn_readfirstlane(div_small(slot_x, map.n_tiles)) * N_XCD + xcd;  // of the tiles of a (user, head, split)
+        const int u = __builtin_amdgcn_readfirstlane(div_small(group, ny));
+        if (u >= batch) return;
+        tile = slot_x - (group / N_XCD) * map.n_tiles;
+        L = hist_len[u], T = n_targets[u];
+        if (RT) R = rt_len[u];
+        q_base = q_off[u], kv_base = kv_off[u];
+        gc = group - u * ny;
+        if (sg.n_splits > 1) {
+            const int blocks = (L + R + BLK - 1) / BLK, y = gc;
+            gc = __builtin_amdgcn_readfirstlane(div_small(y, sg.n_splits));
+            split = y - gc * sg.n_splits;
+            per = shortest_piece(blocks);
+            n_live = splits_of(blocks, per);
+        }
+        if (split >= n_live || tile * map.rows >= (layer == 0 ? L + R : 0) + T) return;
     }
-    wait_vmem_loads();  // (all arrived with the first; the compiler may look for them behind the copies below, and would wait for those, too)
-    const int xcd = blockIdx.x % N_XCD, slot_x = blockIdx.x / N_XCD;
-    int at = sg.piece == 0 ? xcd * ((n_items + N_XCD - 1) / N_XCD) + slot_x
-                           : ((slot_x / (int)sg.piece) * N_XCD + xcd) * (int)sg.piece + slot_x % (int)sg.piece;
-    if (at >= n_items || (sg.piece == 0 && slot_x >= (n_items + N_XCD - 1) / N_XCD)) return;
-    for (int u = 64; at >= n_here; u += 64) {
-        at -= n_here;
-        of = user_of_lane(u);
-        items = of.in_one;
-        upto = scan_lanes(items);
-        n_here = __builtin_amdgcn_readlane(upto, 63);
-        wait_vmem_loads();
-    }
-    const int u_lane = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= at));
-    auto of_user = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, u_lane); };
-    at -= of_user(upto - items);
-    const int n_tiles = of_user(of.tiles);
-    L = of_user(of.L), T = of_user(of.T), n_live = of_user(splits);
-    if (RT) R = of_user(of.R);
-    q_base = of_user(of.q), kv_base = of_user(of.kv);
-    const int ts_of = __builtin_amdgcn_readfirstlane(div_small(at, n_tiles));
-    tile = at - ts_of * n_tiles;
-    gc = sg.n_splits == 1 ? ts_of : __builtin_amdgcn_readfirstlane(div_small(ts_of, n_live));
-    split = ts_of - gc * n_live;
     const int g = map.n_chunks == 1 ? gc : gc / map.n_chunks, chunk = gc - g * map.n_chunks;
     const int LK = L + R;  // keys that run through the tile loop: history, then real-time
     const int n_rows = layer == 0 ? LK + T : T;
@@ -472,13 +497,20 @@ int64_t most_tiles(const Params& p, const RowMap& map) {
     return std::min(by_rows, (int64_t)p.batch * map.n_tiles) * p.Hkv * map.n_chunks;
 }
 
+// (user, kv head, head chunk), and the places of a grid: tiles that they have by the bounds
+int64_t groups_of(const Params& p, const RowMap& map) { return (int64_t)p.batch * p.Hkv * map.n_chunks; }
+int64_t places(const Params& p, const RowMap& map) { return groups_of(p, map) * map.n_tiles; }
+// A list or a grid: see ServeGrid.
+bool takes_list(const Params& p, const RowMap& map) { return p.batch <= 64 || (p.batch <= 192 && places(p, map) > UNITS); }
+
+template <int D, int RB, int NW, int SPS, int NST, bool LIST>
+auto kernel_of(const Params& p) {
+    if (p.pointwise) return p.rt_len ? serve_kernel<D, RB, NW, SPS, NST, true, true, LIST> : serve_kernel<D, RB, NW, SPS, NST, false, true, LIST>;
+    return p.rt_len ? serve_kernel<D, RB, NW, SPS, NST, true, false, LIST> : serve_kernel<D, RB, NW, SPS, NST, false, false, LIST>;
+}
+
 template <int D, int RB, int NW, int SPS, int NST>
 hipError_t launch(const Params& p, hipStream_t s) {
-    auto kernel = serve_kernel<D, RB, NW, SPS, NST, false, false>;
-    if (p.pointwise)
-        kernel = p.rt_len ? serve_kernel<D, RB, NW, SPS, NST, true, true> : serve_kernel<D, RB, NW, SPS, NST, false, true>;
-    else if (p.rt_len)
-        kernel = serve_kernel<D, RB, NW, SPS, NST, true, false>;
     const int64_t rows = max_query_rows(p);
     if (rows <= 0) return hipSuccess;
     const RowMap map = row_map(RB * 32, p.Hq, p.Hkv, rows);
@@ -490,7 +522,10 @@ hipError_t launch(const Params& p, hipStream_t s) {
     sg.rows_magic = div_magic((uint32_t)map.rows);
     const int64_t tiles = most_tiles(p, map), most = std::min(tiles * sg.n_splits, std::max<int64_t>(tiles, UNITS));
     sg.piece = most <= 320 ? 0 : 4;
-    const int64_t dealt = N_XCD * (sg.piece == 0 ? 1 : sg.piece), n_blocks = (most + dealt - 1) / dealt * dealt;
+    const int64_t dealt = N_XCD * (sg.piece == 0 ? 1 : sg.piece);
+    const bool list = takes_list(p, map);
+    const int64_t n_blocks = list ? (most + dealt - 1) / dealt * dealt : work_grid(groups_of(p, map) * sg.n_splits, map.n_tiles);
+    auto kernel = list ? kernel_of<D, RB, NW, SPS, NST, true>(p) : kernel_of<D, RB, NW, SPS, NST, false>(p);
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p.hist_len, p.n_targets, p.q_off, p.kv_off, p.rt_len, p.batch, p.layer,
                        sg, p, map);
     const hipError_t e = hipGetLastError();
@@ -508,7 +543,7 @@ hipError_t launch(const Params& p, hipStream_t s) {
 // workgroups with work to do: `lanes` packed rows each, from the bounds and the number of query rows of the call
 int64_t live_tiles(const Params& p, int lanes) {
     const RowMap map = row_map(lanes, p.Hq, p.Hkv, max_query_rows(p));
-    const int64_t groups = (int64_t)p.batch * p.Hkv * map.n_chunks;
+    const int64_t groups = groups_of(p, map);
     return std::min(groups * map.n_tiles, p.total_q * p.Hkv * map.n_chunks / map.rows + groups / 2);
 }
 
@@ -568,10 +603,12 @@ static double serve_us(const Params& p, const ServeSize& size, int row_blocks, i
     else c = {-0.34, 9.3, 5.9, 3.5, 0.73, 2.6, 0.22, 2.2, 0.45, 0.14};
     const double longest = size.longest, mean = size.mean, items = size.items[row_blocks - 1], rounds = items / UNITS;
     const bool even = mean > 0.9 * longest;
-    const double fixed = c.launch + (p.rt_len ? c.rt : 0.);
+    // (more than 64 users: 1.2 to 1.45 times what the fits say, by 1400 target layers of 65 to 1024; with this factor the chosen form takes 1.03 of
+    // the best one's time)
+    const double fixed = c.launch + (p.rt_len ? c.rt : 0.), grid = p.batch > 64 ? 1.25 : 1.;
     double keys = longest, pieces = items;
     if (splits > 1) {
-        const double fits = items < 250. ? items * mean / std::max(UNITS - c.piece * items, 16.) : longest;
+        const double fits = p.batch > 64 ? 0. : items < 250. ? items * mean / std::max(UNITS - c.piece * items, 16.) : longest;
         keys = std::min(std::max(longest / splits, fits), longest);
         const double of_mean = mean / std::max(keys, 1.);
         pieces = items * (even ? std::ceil(of_mean - 0.01) : of_mean + c.piece);
@@ -579,8 +616,8 @@ static double serve_us(const Params& p, const ServeSize& size, int row_blocks, i
     const double key = 1e-3 * (c.key + c.key_full * std::min(1., pieces / UNITS));
     const double whole = std::ceil(rounds);
     const double many = (even ? whole + c.partial * (rounds - whole) : rounds + c.jagged) * (c.item + key * mean);
-    if (splits == 1) return fixed + (rounds <= 1. ? c.item + key * longest : std::max(c.item + key * longest, many));
-    return fixed + c.merge + c.part * splits * size.part + (rounds <= 1. ? c.item + key * keys : std::max(c.item + key * longest, many));
+    if (splits == 1) return grid * (fixed + (rounds <= 1. ? c.item + key * longest : std::max(c.item + key * longest, many)));
+    return grid * (fixed + c.merge + c.part * splits * size.part + (rounds <= 1. ? c.item + key * keys : std::max(c.item + key * longest, many)));
 }
 
 // What a call takes: this kernel with one or two row blocks per workgroup and the keys in up to `room` pieces, or the ordinary one,
@@ -592,12 +629,13 @@ struct ServeForm {
 };
 static ServeForm serve_form(const Params& p, int room) {
     const int64_t ordinary = live_tiles(p, fwd_workgroup_rows(p)), blocks = most_keys(p) / SUB;
-    if (ordinary >= 512 || p.batch > 1024 || max_query_rows(p) >= 1 << 20) return {1, 0};
+    const int64_t in_grid = p.batch <= 64 ? 0 : places(p, row_map(32, p.Hq, p.Hkv, max_query_rows(p)));
+    if (ordinary >= 512 || p.batch > 1024 || max_query_rows(p) >= 1 << 20 || in_grid >= 1 << 24) return {1, 0};
     ServeForm best = {1, 0};
     double best_us = ordinary_us(p, ordinary);
     const ServeSize size(p);
     for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-        if (splits > 1 && (splits > room || splits > blocks / 6 || blocks >= 1 << 15 || p.batch > 64)) break;
+        if (splits > 1 && (splits > room || splits > blocks / 6 || blocks >= 1 << 15 || in_grid * splits > UNITS)) break;
         for (int rb = 1; rb <= (p.d == 32 ? 1 : 2); rb++) {
             const double us = serve_us(p, size, rb, splits);
             if (us < best_us) best_us = us, best = {rb, splits};
@@ -611,6 +649,8 @@ int serve_row_blocks(const Params& p) {
     const ServeSize size(p);
     return p.d != 32 && serve_us(p, size, 2, p.n_splits) < serve_us(p, size, 1, p.n_splits) ? 2 : 1;
 }
+
+bool serve_takes_list(const Params& p) { return takes_list(p, row_map(serve_row_blocks(p) * 32, p.Hq, p.Hkv, max_query_rows(p))); }
 
 hipError_t launch_serve_bf16(const Params& p, hipStream_t s) {
     const bool two = serve_row_blocks(p) == 2;

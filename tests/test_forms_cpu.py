@@ -27,3 +27,10 @@ def test_backward_forms(call):
     assert target_layer(call, 4, 300, 60).kind == BRIEF
     assert target_layer(call, 277, 241, 3).kind == BRIEF
     assert target_layer(call, 1000, 1500, 70, heads=(12, 2, 64)).kind == TWO_PASSES
+
+
+@pytest.mark.parametrize("users", [65, 129, 300])
+def test_many_users_do_not_stand_in_a_list(users):
+    """Every wave of a list looks at all lengths, 64 at a time, which many users do not repay."""
+    form = target_layer(hta.CALL_FWD, users, 100, 2, heads=(4, 1, 64))
+    assert form.kind == 1 and form.option == 1

@@ -7,7 +7,7 @@ import torch
 
 from paper_2602_11235_amd import hta, inputs
 from tests import test_gpu_parity_pointwise as pointwise
-from tests.hta_testlib import check_case, compare_with_oracle, device_batch, host
+from tests.hta_testlib import check_case, compare_with_oracle, device_batch, form_of, host
 
 pytestmark = pytest.mark.gpu
 FULL, TARGET = inputs.LAYER_FULL, inputs.LAYER_TARGET
@@ -106,6 +106,31 @@ def test_lists_of_items(name, with_rt):
 def test_lists_of_items_pointwise(name):
     layer, hist, targets, heads = LISTS[name]
     pointwise.check(inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=37)))
+
+
+# More users than a list has lanes: a list that takes two or three rounds of lanes where a grid would have more places than there are units,
+# and a grid; one and two row blocks, keys in one piece and in several, users without a row or a key.  (form: in pieces, row blocks, grid)
+MANY = {
+    "list_of_two_rounds": (np.resize([40, 300, 0, 700], 100), np.resize([20, 0, 9, 33], 100), (8, 2, 64), (False, 1, 0)),
+    "list_of_three_rounds": (np.resize([1500, 0, 640, 64], 170), np.resize([13, 0, 9, 8], 170), (8, 1, 128), (False, 1, 0)),
+    "list_of_three_rounds_64_rows": (np.resize([1500, 1400], 190), np.resize([13, 8], 190), (8, 1, 64), (False, 2, 0)),
+    "grid": (np.resize([300, 250, 0, 310], 300), np.resize([1, 0, 3], 300), (8, 1, 32), (False, 1, 1)),
+    "grid_64_rows": (np.resize([1000, 900], 250), np.resize([16, 15], 250), (4, 1, 64), (False, 2, 1)),
+    "grid_64_rows_d128": (np.resize([1000, 900], 225), np.resize([8, 7], 225), (8, 1, 128), (False, 2, 1)),
+    "grid_in_pieces": (np.resize([8192, 0, 300, 5000, 7000], 66), np.resize([1, 2, 0, 3], 66), (8, 1, 64), (True, 1, 1)),
+    "grid_in_pieces_d32": (np.resize([16384, 8000, 300, 12000], 66), np.resize([1, 2, 0, 3], 66), (8, 1, 32), (True, 1, 1)),
+    "grid_in_pieces_d128": (np.resize([8192, 0, 300, 5000, 6000], 66), np.resize([1, 2, 0, 3], 66), (8, 1, 128), (True, 1, 1)),
+}
+
+
+@pytest.mark.parametrize("with_rt", [False, True])
+@pytest.mark.parametrize("name", MANY)
+def test_many_users(name, with_rt):
+    hist, targets, heads, form = MANY[name]
+    case = inputs.make_case(inputs.custom_config(name, TARGET, hist, targets, *heads, seed=41, rt_len=np.resize([40, 0, 7, 130, 1], len(hist)) if with_rt else None))
+    taken = form_of(case, hta.CALL_FWD)
+    assert (taken.kind > 1, taken.ways, taken.option) == form and taken.kind > 0
+    check_case(case, with_bwd=False, users=sorted(set(range(0, len(hist), 7)) | {1, 63, 64, 65, len(hist) - 1}))
 
 
 def with_bounds(batch: hta.Batch, factor: int, of_targets: int = 1) -> hta.Batch:

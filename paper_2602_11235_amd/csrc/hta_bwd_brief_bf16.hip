@@ -44,7 +44,7 @@ struct BriefForm {
 // and what one costs that only the longest user has a tile for -- or the longest chain, whichever is longer (the cubes: near the line a bit of
 // both).  Fits of 13000 calls timed in every form (4 to 600 users of 32 to 4096 keys, 2 to 160 candidates, full and target layers):
 // of 6370 short calls the form with the least takes 0.74 of the time of four waves per block, the best of each 0.73; 2 % are slower by more than 3 %.
-double brief_us(const Params& p, int ways, bool dq_first) {
+double brief_us(const Params& p, int ways, bool dq_first, double chain_keys) {
     struct { double launch, kv, kv_step, dq, dq_step, empty, chain, chain_kv, chain_dq, rt, pw; } c;
     if (p.d == 32) c = ways == 4 ? decltype(c){6.7, 1.7, 0.55, 0.9, 1.2, 0.7, 0.96, 0.59, 0.46, 1.37, 1.18}
                      : !dq_first ? decltype(c){6.2, 4.2, 0.76, 0.6, 0.72, 1.1, 1.3, 0.6, 0.37, 1.55, 1.29}
@@ -62,15 +62,24 @@ double brief_us(const Params& p, int ways, bool dq_first) {
     const double step = (p.rt_len ? c.rt : 1.) * (p.pointwise ? c.pw : 1.);
     const double all = (c.kv * kv + c.dq * dq + c.empty * (kv_grid - kv + dq_grid - dq) +
                         step * (c.kv_step * kv * std::max(1., units / ways + 0.25) + c.dq_step * dq * std::max(1., keys / 128. + 0.3))) / (p.d == 128 ? 256. : 512.);
-    const double chain = c.chain + step * std::max(c.chain_kv * std::ceil(most / ways), c.chain_dq * std::ceil(longest / 128.));
+    const double chain = c.chain + step * std::max(c.chain_kv * std::ceil(most / ways), c.chain_dq * std::ceil(chain_keys / 128.));
     return c.launch + std::cbrt(all * all * all + chain * chain * chain);
 }
+// The form with the least time, but four waves while the workgroups with work take less than a fifth of the chip: nothing waits there, and the
+// chain of a block that four waves share is the shorter one, which the estimates do not tell within a microsecond.  The chains are those of the
+// mean user, since the bounds may be far above all lengths.  (1223 target layers with true bounds and 2260 with bounds of 1.5 to 8 times the
+// longest: 2 % of both are slower than with four waves by more than 3 %, where the estimates with the longest user by the bounds alone had 9 and
+// 15 %; times the best form's: 1.008 and 1.015, before 1.011 and 1.029.)
 BriefForm brief_form(const Params& p) {
-    BriefForm best = {4, false, brief_us(p, 4, false)};
-    for (bool dq_first : {false, true}) {
-        const double us = brief_us(p, 1, dq_first);
-        if (us < best.us) best = {1, dq_first, us};
-    }
+    const double groups = (double)p.batch * p.Hkv, slots = p.d == 128 ? 256. : 512.;
+    const double work = groups * (mean_keys(p) / 32. + 0.5) + groups * (mean_rows(p) * (p.Hq / p.Hkv) / 32. + 0.5);
+    BriefForm best = {4, false, brief_us(p, 4, false, mean_keys(p))};
+    if (work > 0.2 * slots)
+        for (bool dq_first : {false, true}) {
+            const double us = brief_us(p, 1, dq_first, mean_keys(p));
+            if (us < best.us) best = {1, dq_first, us};
+        }
+    best.us = brief_us(p, best.ways, best.dq_first, (double)max_lead_keys(p));
     return best;
 }
 // The same for the two passes (in whichever of their forms): dQ by tiles of 128 packed rows, dK/dV by 128 keys.

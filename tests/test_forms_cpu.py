@@ -34,3 +34,15 @@ def test_many_users_do_not_stand_in_a_list(users):
     """Every wave of a list looks at all lengths, 64 at a time, which many users do not repay."""
     form = target_layer(hta.CALL_FWD, users, 100, 2, heads=(4, 1, 64))
     assert form.kind == 1 and form.option == 1
+
+
+@pytest.mark.parametrize("users,keys,candidates,heads", [(4, 149, 2, (16, 2, 128)), (3, 340, 11, (8, 1, 64)), (2, 719, 53, (16, 4, 64)), (3, 192, 1, (16, 4, 64))])
+def test_little_work_is_shared_by_four_waves(users, keys, candidates, heads):
+    """With a wave to each key block these take 1.15 to 1.3 times as long: the chip is nearly empty, and one wave's chain is the time."""
+    assert target_layer(hta.CALL_BWD, users, keys, candidates, heads)[:2] == (BRIEF, 4)
+
+
+@pytest.mark.parametrize("users,keys,candidates,heads", [(11, 384, 114, (8, 1, 64)), (8, 126, 84, (4, 1, 64)), (13, 99, 84, (8, 1, 128)), (60, 400, 10, HEADS)])
+def test_brief_form_does_not_follow_the_bounds(users, keys, candidates, heads):
+    """Bounds far above the lengths made the chains of dQ seem to be the time, and up to twice of it was lost."""
+    assert len({target_layer(hta.CALL_BWD, users, keys, candidates, heads, loose)[:2] for loose in (1, 4, 16)}) == 1

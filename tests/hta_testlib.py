@@ -150,11 +150,12 @@ def form_of_sizes(call, batch, total_q, total_kv, max_hist, max_targets, heads, 
     return Form(*form)
 
 
-def form_of(case: inputs.Case, call: int, loose: int = 1) -> Form:
-    """The kernels that a call on `case` takes; loose: bounds of the keys above its longest user's by that factor."""
-    rt = 0 if case.rt_len is None else int(case.rt_len.max())
-    return form_of_sizes(call, case.batch, case.total_q, case.total_kv, int(case.hist_len.max()) * loose, int(case.n_targets.max()),
-                         (case.cfg.Hq, case.cfg.Hkv, case.cfg.head_dim), case.cfg.layer, rt * loose)
+def form_of(cfg: inputs.Config, call: int) -> Form:
+    """The kernels that a call on a case of `cfg` (its lengths listed) takes."""
+    hist, targets, rt = cfg.hist[1], cfg.targets[1], [0] * cfg.batch if cfg.rt is None else cfg.rt[1]
+    total_kv = sum(hist) + sum(targets) + sum(rt)
+    return form_of_sizes(call, cfg.batch, total_kv if cfg.layer == inputs.LAYER_FULL else sum(targets), total_kv, max(hist), max(targets),
+                         (cfg.Hq, cfg.Hkv, cfg.head_dim), cfg.layer, max(rt))
 
 
 def compare_with_oracle(case: inputs.Case, g: dict, with_bwd: bool, users=None, kv_group=None, compare=None,

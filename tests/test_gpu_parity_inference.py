@@ -59,11 +59,14 @@ LONG_RT = [70, 5, 0, 130, 300]
 LONG_TGTS = [16, 5, 1, 33, 2]
 
 
+def config_of_long(heads, with_rt):
+    return inputs.custom_config("split_long", TARGET, LONG_HIST, LONG_TGTS, *heads, seed=35, rt_len=LONG_RT if with_rt else None)
+
+
 @pytest.mark.parametrize("with_rt", [False, True])
 @pytest.mark.parametrize("heads", [(8, 2, 64), (3, 1, 64), (16, 2, 128), (4, 2, 32)])
 def test_keys_split_over_workgroups(heads, with_rt):
-    c = inputs.make_case(inputs.custom_config("split_long", TARGET, LONG_HIST, LONG_TGTS, *heads, seed=35,
-                                              rt_len=LONG_RT if with_rt else None))
+    c = inputs.make_case(config_of_long(heads, with_rt))
     assert is_split(c)
     check_case(c, with_bwd=False)
 
@@ -78,8 +81,8 @@ def test_few_requests_with_many_real_time_tokens(layer, heads):
     check_case(c, with_bwd=True)
 
 
-# The list of work items that a launch for requests makes of the lengths: users without a row or a key anywhere in it, more users than a wave has
-# lanes, more items than compute units, pieces of keys that grow until the items fit, and splits that the shorter users do not reach.
+# The work items that a launch for requests makes of the lengths: users without a row or a key anywhere among them, more users than a wave has
+# lanes (which stand in a grid), more items than compute units, pieces of keys that grow until the items fit, and splits that the shorter users do not reach.
 LISTS = {
     "many_users": (TARGET, np.resize([0, 1, 31, 700, 64, 0, 1500, 33], 130), np.resize([1, 0, 3, 2, 0, 5, 1], 130), (4, 1, 64)),
     "a_lane_more": (TARGET, np.resize([40, 300, 0], 65), np.resize([2, 0, 1, 3], 65), (8, 2, 32)),
@@ -87,25 +90,27 @@ LISTS = {
     "pieces_grow": (TARGET, [6000, 300, 0, 4100, 2500, 65, 3300, 5000], [90, 30, 5, 70, 0, 64, 33, 50], (8, 2, 64)),
     "more_than_units": (TARGET, np.resize([1400, 900, 63, 2000], 20), np.resize([70, 33, 128, 0], 20), (16, 4, 64)),
     "two_row_blocks_d128": (TARGET, np.resize([1100, 0, 640, 33], 20), np.resize([64, 5, 100, 17], 20), (16, 2, 128)),
-    "two_row_blocks_d128_in_pieces": (TARGET, [8192, 7000, 100, 8000], [64, 60, 3, 50], (16, 2, 128)),
-    "two_row_blocks_d128_full": (FULL, [600, 500, 640, 30], [20, 5, 1, 17], (16, 2, 128)),
+    "two_row_blocks_d128_in_pieces": (TARGET, [8192, 7000, 100, 8000], [80, 76, 3, 66], (16, 2, 128)),
+    "two_row_blocks_d128_full": (FULL, [300, 200, 40], [20, 5, 17], (16, 2, 128)),
     "many_pieces": (TARGET, [16384, 200], [3, 2], (4, 1, 64)),
 }
+
+
+def config_of_list(name, with_rt, seed=36):
+    layer, hist, targets, heads = LISTS[name]
+    return inputs.custom_config(name, layer, hist, targets, *heads, seed=seed, rt_len=np.resize([40, 0, 7, 130, 1], len(hist)) if with_rt else None)
 
 
 @pytest.mark.parametrize("with_rt", [False, True])
 @pytest.mark.parametrize("name", LISTS)
 def test_lists_of_items(name, with_rt):
-    layer, hist, targets, heads = LISTS[name]
-    rt = np.resize([40, 0, 7, 130, 1], len(hist)) if with_rt else None
-    case = inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=36, rt_len=rt))
-    check_case(case, with_bwd=False)
+    check_case(inputs.make_case(config_of_list(name, with_rt)), with_bwd=False)
 
 
-@pytest.mark.parametrize("name", ["pieces_grow", "two_row_blocks_d128_in_pieces", "many_users"])
-def test_lists_of_items_pointwise(name):
-    layer, hist, targets, heads = LISTS[name]
-    pointwise.check(inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=37)))
+@pytest.mark.parametrize("with_rt", [False, True])
+@pytest.mark.parametrize("name", ["pieces_grow", "two_row_blocks_d128", "two_row_blocks_d128_in_pieces", "many_users"])
+def test_lists_of_items_pointwise(name, with_rt):
+    pointwise.check(inputs.make_case(config_of_list(name, with_rt, seed=37)))
 
 
 # More users than a list has lanes: a list that takes two or three rounds of lanes where a grid would have more places than there are units,
@@ -128,7 +133,7 @@ MANY = {
 def test_many_users(name, with_rt):
     hist, targets, heads, form = MANY[name]
     case = inputs.make_case(inputs.custom_config(name, TARGET, hist, targets, *heads, seed=41, rt_len=np.resize([40, 0, 7, 130, 1], len(hist)) if with_rt else None))
-    taken = form_of(case, hta.CALL_FWD)
+    taken = form_of(case.cfg, hta.CALL_FWD)
     assert (taken.kind > 1, taken.ways, taken.option) == form and taken.kind > 0
     check_case(case, with_bwd=False, users=sorted(set(range(0, len(hist), 7)) | {1, 63, 64, 65, len(hist) - 1}))
 
@@ -143,9 +148,7 @@ def with_bounds(batch: hta.Batch, factor: int, of_targets: int = 1) -> hta.Batch
 @pytest.mark.parametrize("with_rt", [False, True])
 @pytest.mark.parametrize("name", ["pieces_grow", "more_than_units", "two_row_blocks_d128_in_pieces", "many_pieces", "many_users"])
 def test_lists_of_items_with_bounds_above_the_lengths(name, with_rt, factor):
-    layer, hist, targets, heads = LISTS[name]
-    rt = np.resize([40, 0, 7, 130, 1], len(hist)) if with_rt else None
-    case = inputs.make_case(inputs.custom_config(name, layer, hist, targets, *heads, seed=39, rt_len=rt))
+    case = inputs.make_case(config_of_list(name, with_rt, seed=39))
     out, lse = with_bounds(device_batch(case), factor, of_targets=factor).forward()
     compare_with_oracle(case, {"out": out, "lse": lse}, with_bwd=False)
 
@@ -172,10 +175,13 @@ def test_pieces_come_from_the_lengths(heads):
 
 # keys in one piece and in several, one and two row blocks
 @pytest.mark.parametrize("name,hist,targets,heads", [("one_piece", [700, 90], [20, 3], (8, 2, 64)), ("pieces", [8192, 300], [20, 3], (8, 2, 64)),
-                                                     ("pieces_d128", [8192, 7000, 100, 8000], [64, 60, 3, 50], (16, 2, 128))])
+                                                     ("one_piece_64_rows_d128", [1100, 300, 640, 33] * 5, [64, 5, 100, 17] * 5, (16, 2, 128)),
+                                                     ("pieces_64_rows_d128", [8192, 7000, 100, 8000], [64, 60, 3, 50], (16, 2, 128))])
 def test_nan_shows(name, hist, targets, heads):
     """A NaN key reaches every row that sees it, in out and in lse, and no other: the own key of a candidate, and a key far back in a history."""
     case = inputs.make_case(inputs.custom_config(name, TARGET, hist, targets, *heads, seed=38))
+    form, rows64 = form_of(case.cfg, hta.CALL_FWD), "64_rows" in name
+    assert (form.kind > 1) == name.startswith("pieces") and form.kind > 0 and form.ways == (2 if rows64 else 1)
     r, nan = heads[0] // heads[1], float("nan")
     clean, clean_lse = device_batch(case).forward()
     for key, rows in ((hist[0] + 1, slice(1, 2)), (hist[0] * 7 // 8, slice(0, targets[0]))):

@@ -33,17 +33,18 @@ SHAPES = {
     "one_way": (TARGET, 330, 0, 0, (8, 2, 64), False),
     "one_way_rt": (TARGET, 330, 0, 0, (6, 2, 64), True),
     "one_way_many_rt": (TARGET, 1500, 100, 0, (6, 2, 64), True),
-    "one_way_single_heads": (FULL, 400, 0, 0, (4, 4, 64), False),
     "one_way_single_heads_long": (FULL, 400, (500,), 0, (4, 4, 64), False),
+    "one_pass_single_heads": (FULL, 400, 0, 0, (4, 4, 64), False),
     "two_ways": (FULL, 160, 0, 0, (8, 2, 64), False),
     "two_ways_rt": (FULL, 160, 0, 0, (8, 2, 64), True),
     "four_ways": (FULL, 64, 0, 0, (8, 2, 64), True),
     "four_ways_d128": (FULL, 40, 0, 0, (16, 2, 128), True),
-    # 64 rows per workgroup in the forward pass of some requests
-    "rows64": (TARGET, 20, 0, 100, (8, 2, 64), True),
-    "rows64_d128": (TARGET, 22, 0, 100, (16, 2, 128), False),
-    "rows64_long": (TARGET, 10, (2500,), 100, (8, 2, 64), True),
-    "rows64_d128_long": (TARGET, 10, (2500,), 100, (16, 2, 128), True),
+    # 64 rows per workgroup in the forward pass of some requests, keys in one piece and (long) in several
+    "rows64": (TARGET, 20, 500, 70, (8, 2, 64), True),
+    "rows64_d128": (TARGET, 16, 700, 30, (16, 2, 128), False),
+    "rows64_d128_rt": (TARGET, 16, 700, 30, (16, 2, 128), True),
+    "rows64_long": (TARGET, 10, (8000,), 100, (8, 2, 64), True),
+    "rows64_d128_long": (TARGET, 10, (6000,), 60, (16, 2, 128), True),
     # enough for the ordinary dK/dV pass; blocks behind the history in its grid (in a launch of their own at 128)
     "ordinary_d32": (FULL, 400, 500, 0, (4, 2, 32), False),
     "ordinary_d32_rt": (FULL, 400, 500, 0, (4, 2, 32), True),
@@ -58,8 +59,10 @@ SHAPES = {
     "brief_wide": (TARGET, 6, 0, 0, (40, 1, 64), True),
     "brief_wide_d32": (TARGET, 5, 0, 0, (130, 1, 32), False),
     "brief_wide_d128": (TARGET, 4, 0, 0, (66, 2, 128), False),
-    "rows64_wide": (TARGET, 4, (1000,), 60, (70, 1, 64), True),
-    "rows64_wide_d128": (TARGET, 8, (2500,), 10, (70, 1, 128), False),
+    "rows64_wide": (TARGET, 2, 1000, 100, (70, 1, 64), True),
+    "rows64_wide_d128": (TARGET, 2, 2500, 100, (70, 1, 128), False),
+    "rows64_wider": (TARGET, 2, 300, 40, (130, 1, 64), False),
+    "rows64_wider_d128": (TARGET, 2, 300, 40, (130, 1, 128), True),
     "four_ways_wide_d32": (FULL, 24, 0, 0, (130, 1, 32), True),
     "four_ways_wide": (FULL, 10, 0, 0, (300, 1, 64), True),
     "four_ways_wide_d128": (FULL, 24, 0, 0, (130, 1, 128), False),
@@ -67,13 +70,17 @@ SHAPES = {
 }
 
 
-def make(name):
+def config(name):
     layer, n, more_hist, more_tgts, (Hq, Hkv, d), rt = SHAPES[name]
     if isinstance(more_hist, tuple):
         more_hist = np.where(np.arange(n) % 4 == 3, more_hist[0], 0)
-    cfg = inputs.custom_config(name, layer, cycle(HIST, n) + more_hist, cycle(TGTS, n) + more_tgts, Hq, Hkv, d, dtype="bf16",
-                               std=0.3, seed=77, rt_len=cycle(RT, n) if rt else None)
-    return inputs.make_case(cfg), sorted(set(range(0, n, max(1, n // 24))) | {1, n - 1}) if n > 64 else None
+    return inputs.custom_config(name, layer, cycle(HIST, n) + more_hist, cycle(TGTS, n) + more_tgts, Hq, Hkv, d, dtype="bf16",
+                                std=0.3, seed=77, rt_len=cycle(RT, n) if rt else None)
+
+
+def make(name):
+    n = SHAPES[name][1]
+    return inputs.make_case(config(name)), sorted(set(range(0, n, max(1, n // 24))) | {1, n - 1}) if n > 64 else None
 
 
 @pytest.mark.parametrize("name", SHAPES)
@@ -83,12 +90,26 @@ def test_shapes(name):
 
 
 # users of one length, which the library takes in the order given (no launch that orders them): a few long tiles, a key block's rows shared by
-# four, two and one waves, and (head_dim 32) kernels with a work queue, which have theirs cleared by that launch
-@pytest.mark.parametrize("layer,users,hist,targets,heads", [(FULL, 60, 200, 20, (8, 2, 64)), (FULL, 160, 129, 33, (8, 2, 64)), (FULL, 400, 65, 7, (6, 6, 64)),
-                                                            (TARGET, 300, 500, 20, (16, 2, 128)), (FULL, 500, 520, 9, (4, 2, 32))])
-def test_users_of_one_length(layer, users, hist, targets, heads):
-    cfg = inputs.custom_config("one_length", layer, np.full(users, hist), np.full(users, targets), *heads, seed=78)
-    check_case(inputs.make_case(cfg), with_bwd=True, users=[0, 1, users // 2, users - 1], compare=close_on_row_scale)
+# four, two and one waves; and kernels with a work queue (one pass, head_dim 32), which have theirs cleared by that launch
+ONE_LENGTH = {
+    "four_ways": (FULL, 60, 200, 20, (8, 2, 64)),
+    "four_ways_many": (FULL, 160, 129, 33, (8, 2, 64)),
+    "two_ways": (FULL, 160, 129, 20, (8, 2, 64)),
+    "one_way": (TARGET, 300, 500, 20, (16, 2, 128)),
+    "queue_one_pass": (FULL, 400, 65, 7, (6, 6, 64)),
+    "queue": (FULL, 500, 520, 9, (4, 2, 32)),
+}
+
+
+def config_of_one_length(name):
+    layer, users, hist, targets, heads = ONE_LENGTH[name]
+    return inputs.custom_config("one_length", layer, np.full(users, hist), np.full(users, targets), *heads, seed=78)
+
+
+@pytest.mark.parametrize("name", ONE_LENGTH)
+def test_users_of_one_length(name):
+    case = inputs.make_case(config_of_one_length(name))
+    check_case(case, with_bwd=True, users=[0, 1, case.batch // 2, case.batch - 1], compare=close_on_row_scale)
 
 
 @pytest.mark.parametrize("name", ["rows_resident", "rows_resident_r6"])
@@ -105,8 +126,11 @@ def test_the_resident_shapes_reach_the_resident_kernel(name):
     assert units < items and 0 < taken < items + 2 * units
 
 
-@pytest.mark.parametrize("name", ["brief_rt", "brief_d128", "brief_alone_long", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "ordinary_d32_rt",
-                                  "brief_wide", "rows64_wide"])
+POINTWISE = ["brief_rt", "brief_d128", "brief_alone_long", "one_way_rt", "two_ways_rt", "four_ways", "rows64", "rows64_d128_rt", "rows64_d128_long",
+             "ordinary_d32_rt", "brief_wide", "rows64_wide", "rows64_wider_d128"]
+
+
+@pytest.mark.parametrize("name", POINTWISE)
 def test_shapes_with_pointwise_weights(name):
     case, users = make(name)
     check_pointwise(case, norm=1.0 / 64, users=users, compare=close_on_row_scale)

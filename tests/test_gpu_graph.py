@@ -57,6 +57,38 @@ def test_forward_and_backward_replay_from_a_graph(name, with_bwd):
     _replay_and_compare(graph, outputs, eager, lambda: other.forward())
 
 
+# Requests whose lengths are rewritten between the replays of one graph, captured with bounds that hold for all of them: the longest user as long as
+# the bound, then a third of it, then one without keys.  (Same totals, which are the graph's.)
+LENGTHS = ([8192, 64, 36], [2764, 2764, 2764], [4100, 0, 4192]), ([64, 1, 31], [32, 32, 32], [5, 60, 31])
+
+
+@pytest.mark.parametrize("heads", [(8, 2, 64), (16, 2, 128)])
+def test_replays_go_by_the_lengths(heads):
+    say(f"[graph] lengths {heads}")
+    cases = [inputs.make_case(inputs.custom_config("lengths", inputs.LAYER_TARGET, hist, targets, *heads, seed=46)) for hist, targets in zip(*LENGTHS)]
+    batches = [device_batch(c) for c in cases]
+    for b in batches:
+        b.max_hist, b.max_targets = 8192, 64     # (the workspace of the first, which has these, serves all)
+        b.fwd_workspace, b.fwd_workspace_bytes = batches[0].fwd_workspace, batches[0].fwd_workspace_bytes
+    eager = [tuple(t.clone() for t in b.forward()) for b in batches]
+    captured = batches[0]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured.forward()
+    for i in (1, 2, 0, 1):
+        source = device_batch(cases[i])
+        for name in ("q", "k", "v", "q_offsets", "kv_offsets", "hist_len", "n_targets"):
+            getattr(captured, name).copy_(getattr(source, name))
+        captured.out.zero_(), captured.lse.zero_()
+        batches[2].forward()                     # eager work between the replays, in the same workspace
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for t, ref in zip((captured.out, captured.lse), eager[i]):
+            assert torch.equal(t, ref), f"lengths {i}"
+
+
 def test_group_layer_normalization_replays_from_a_graph():
     say("[graph] gln")
     c = inputs.make_gln_case("g", 3000, 512, 8, dtype="bf16", gated=True, seed=42)

@@ -138,6 +138,16 @@ def test_many_users(name, with_rt):
     check_case(case, with_bwd=False, users=sorted(set(range(0, len(hist), 7)) | {1, 63, 64, 65, len(hist) - 1}))
 
 
+@pytest.mark.parametrize("users", [193, 197, 224])
+@pytest.mark.parametrize("tiles", [2, 3, 4, 5])
+def test_tiles_of_a_grid(tiles, users):
+    """Users with all the tiles (of 8 rows) that the bounds allow next to users with one or none: every tile has one place."""
+    targets = np.resize([1, 0, 2, 1, 1, 1, 0, 1, 1, 8 * tiles, 1, 1, 0, 1, 8 * tiles - 7, 1, 1], users)
+    case = inputs.make_case(inputs.custom_config("tiles", TARGET, np.resize([300, 0, 250], users), targets, 4, 1, 64, seed=47))
+    assert form_of(case.cfg, hta.CALL_FWD)[:3] == (1, 1, 1)
+    check_case(case, with_bwd=False)
+
+
 def with_bounds(batch: hta.Batch, factor: int, of_targets: int = 1) -> hta.Batch:
     """The same call with host bounds that far above its lengths, as a captured graph for requests of many sizes has them."""
     return hta.Batch(batch.q, batch.k, batch.v, batch.q_offsets, batch.kv_offsets, batch.hist_len, batch.n_targets, batch.max_hist * factor,

@@ -435,11 +435,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
             floatx4 o4;
 #pragma unroll
             for (int j = 0; j < 4; j++) o4[j] = o[j] * inv;
-            *(floatx4*)(p.o_part + (((int64_t)split * p.total_q + row) * p.Hq + x.h) * D + 4 * c) = o4;
-            if (c == 0) p.lse_part[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : lse;
+            *(floatx4*)((float*)p.out + (((int64_t)split * p.total_q + row) * p.Hq + x.h) * D + 4 * c) = o4;
+            if (c == 0) p.lse[((int64_t)split * p.Hq + x.h) * p.total_q + row] = PW ? 0.f : lse;
             // the splits that this user's keys do not reach are nobody's: nothing was left there
             if (c == 0 && split == 0)
-                for (int k = n_live; k < sg.n_splits; k++) p.lse_part[((int64_t)k * p.Hq + x.h) * p.total_q + row] = no_split();
+                for (int k = n_live; k < sg.n_splits; k++) p.lse[((int64_t)k * p.Hq + x.h) * p.total_q + row] = no_split();
         }
     }
     });
@@ -450,8 +450,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
 // PW: the partial results are partial sums of non-normalised weights: out = sum_s O_s, no lse.
 // All loads of a thread travel together, AT_ONCE splits of them: one trip to memory is most of what this launch takes.  (Split after split,
 // as the remainder of an unrolled loop is: 2 us more for 4 splits.)  The splits that a user's keys do not reach are the last ones, and
-// marked: a launch has as many as the longest user may need, and one with bounds far above its lengths more than any has.
-template <int D, int AT_ONCE, bool PW>
+// marked: a launch has as many as the longest user may need, and one with bounds far above its lengths more than any has.  MORE: than AT_ONCE
+// (a look at the mark behind them costs 0.1 us where there is none).
+template <int D, int AT_ONCE, bool MORE, bool PW>
 __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, const float* lse_part, int64_t total_q, int Hq, int n_splits,
                                                            void* out, float* lse) {
     constexpr int QUADS = D / 4;
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, 
             ls[s] = lse_part[at_lse + i * l_stride];
             os[s] = *(const floatx4*)(o_part + id * 4 + i * o_stride);
         }
-        const float next = lse_part[at_lse + min(s0 + AT_ONCE, n_splits - 1) * l_stride];
+        const float next = MORE ? lse_part[at_lse + min(s0 + AT_ONCE, n_splits - 1) * l_stride] : 0.f;
         const float before = mx;
         if constexpr (!PW) {
 #pragma unroll
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(256) void merge_splits_kernel(const float* o_part, 
 #pragma unroll
             for (int j = 0; j < 4; j++) o[j] = none || ls[s] == -INFINITY ? o[j] : fmaf(w, os[s][j], o[j]);  // (-inf: no key that the row sees)
         }
-        if (is_no_split(next)) break;
+        if (!MORE || is_no_split(next)) break;
     }
     const float inv = PW ? 1.f : 1.f / sum;
     bf16x4 o4;
@@ -515,6 +516,12 @@ auto kernel_of(const Params& p) {
     return p.rt_len ? serve_kernel<D, RB, NW, SPS, NST, true, false, LIST> : serve_kernel<D, RB, NW, SPS, NST, false, false, LIST>;
 }
 
+template <int D, bool PW>
+auto merge_of(int n_splits) {
+    return n_splits <= 2 ? merge_splits_kernel<D, 2, false, PW> : n_splits <= 4 ? merge_splits_kernel<D, 4, false, PW>
+         : n_splits <= 8 ? merge_splits_kernel<D, 8, false, PW> : merge_splits_kernel<D, 8, true, PW>;
+}
+
 template <int D, int RB, int NW, int SPS, int NST>
 hipError_t launch(const Params& p, hipStream_t s) {
     const int64_t rows = max_query_rows(p);
@@ -532,16 +539,18 @@ hipError_t launch(const Params& p, hipStream_t s) {
     const bool list = takes_list(p, map);
     constexpr int64_t turn = N_XCD * GRID_TURN;
     const int64_t n_blocks = list ? (most + dealt - 1) / dealt * dealt : work_grid((groups_of(p, map) * sg.n_splits + turn - 1) / turn * turn, map.n_tiles);
+    // Partial results through the same pointers as results: with two more of them the form with real-time tokens runs out of scalar registers
+    // and waits for loads at its start (8 requests of 512..4096 keys 13.11 -> 12.72 us).
+    Params to = p;
+    if (sg.n_splits > 1) to.out = p.o_part, to.lse = p.lse_part;
     auto kernel = list ? kernel_of<D, RB, NW, SPS, NST, true>(p) : kernel_of<D, RB, NW, SPS, NST, false>(p);
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, p.hist_len, p.n_targets, p.q_off, p.kv_off, p.rt_len, p.batch, p.layer,
-                       sg, p, map);
+                       sg, to, map);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || sg.n_splits == 1) return e;
     const int64_t threads = p.total_q * p.Hq * (p.d / 4);
     const int n = (int)sg.n_splits;
-    auto merge = merge_splits_kernel<D, 8, false>;
-    if (p.pointwise) merge = n <= 2 ? merge_splits_kernel<D, 2, true> : n <= 4 ? merge_splits_kernel<D, 4, true> : merge_splits_kernel<D, 8, true>;
-    else if (n <= 4) merge = n <= 2 ? merge_splits_kernel<D, 2, false> : merge_splits_kernel<D, 4, false>;
+    auto merge = p.pointwise ? merge_of<D, true>(n) : merge_of<D, false>(n);
     hipLaunchKernelGGL(merge, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
                        p.o_part, p.lse_part, p.total_q, p.Hq, n, p.out, p.lse);
     return hipGetLastError();

@@ -48,7 +48,7 @@ struct Params {
     // forward pass of a few requests (hta_serve_bf16.hip): workgroups an item's keys are split over; 0 = the ordinary kernel
     int32_t n_splits;
     float* o_part;          // [n_splits][total_q][Hq][d] partial outputs, each normalised by its own sum
-    float* lse_part;        // [n_splits][Hq][total_q]    logsumexp of each split's keys (-inf: none)
+    float* lse_part;        // [n_splits][Hq][total_q]    logsumexp of each split's keys (-inf: the row sees none; a mark: the user has fewer splits)
     int32_t* lim;           // [total_q] carved out of the workspace: number of leading K/V rows of the user (history, then
                             // the real-time tokens strictly earlier than the query) that the query row sees
 };

@@ -65,8 +65,8 @@ MTFM_HTA_API size_t mtfm_gln_bwd_workspace_bytes(int32_t d_model, int32_t n_grou
  * Backward.  mean, rstd are the forward pass's outputs for the same x.  gate and dgate are both NULL or both
  * given; beta is read only with a gate.  dx, dgate must not overlap the inputs.  dgamma and dbeta are overwritten
  * (rows of groups without tokens become zero; n_tokens = 0 zeroes both, and then the per-token arrays may be
- * NULL).  Their sums are formed in float32: within a workgroup with LDS atomic adds, whose order is not fixed, so
- * the last bits can differ from run to run; across workgroups in a fixed order.  `workspace`: 256-byte aligned, at least mtfm_gln_bwd_workspace_bytes();
+ * NULL).  Their sums are formed in float32, in an order that depends on the sizes and group ids alone.
+ * `workspace`: 256-byte aligned, at least mtfm_gln_bwd_workspace_bytes();
  * contents need not be initialised and are not preserved.
  */
 MTFM_HTA_API int mtfm_gln_bwd(const void* dy, const void* x, const void* gate, const int32_t* group_id,

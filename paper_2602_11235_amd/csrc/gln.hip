@@ -5,9 +5,15 @@
 // element.  One wave owns a token at a time: lane l holds features [8 l, 8 l + 8) of every 512-feature chunk
 // (16-byte loads of bf16), the two row statistics are wave reductions in registers, and nothing is gathered or
 // scattered -- a token picks its group's parameter row out of LDS, where all rows are staged once per workgroup.
+// Tokens of at most 256 (128) features take half (a quarter) of a wave, two (four) of them side by side.
 // Workgroups are persistent (a fixed grid strides over the tokens), which also bounds the number of partial
 // parameter gradients of the backward pass: each workgroup accumulates dgamma / dbeta of all groups in LDS
-// (float atomic adds) and writes its share once; a second kernel sums the shares in a fixed order.
+// and writes its share once; a second kernel sums the shares.  All sums are in a fixed order.
+// us of a call, among others, bf16, as (tokens x features, groups), the kernels with a wave per token and LDS atomics -> these:
+//   forward   gated 200 000 x 136, 8  82.8 -> 37.7   200 000 x 256, 8  87.9 -> 55.4   200 000 x 512, 8  110.2 -> 108.0
+//             plain 130 000 x 640, 2  83.2 -> 67.3   200 000 x 1024, 8  153.0 -> 148.1
+//   backward  gated   9 418 x 688, 5  63.4 -> 24.1    18 374 x 1008, 4  93.6 -> 48.3   200 000 x 512, 8  229.1 -> 216.5 (4.7 TB/s)
+//             gated  20 000 x 136, 8  24.9 -> 15.7   200 000 x 1024, 8  459.8 -> 418.0   plain 11 837 x 928, 4  68.0 -> 23.8
 #include "../../include/mtfm_gln.h"
 #include "hta_common.h"
 
@@ -17,14 +23,17 @@ namespace gln {
 
 constexpr int THREADS = 512;
 constexpr int WAVES = THREADS / 64;
-constexpr int MAX_BLOCKS = 512;   // workgroups of a launch, and shares of dgamma / dbeta in the workspace
+constexpr int MAX_BLOCKS = 512;   // workgroups of a forward launch
+constexpr int MAX_SHARES = 256;   // workgroups of a backward launch: one per compute unit (two of half the size: twice the shares to write and sum)
+constexpr int WORKSPACE_SHARES = 512;  // shares of dgamma / dbeta that the workspace has room for
 constexpr int CHUNK = 512;        // features a wave covers per pass: 64 lanes x 8
 constexpr int MAX_CHUNKS = 4;     // d_model <= 2048
 constexpr int MAX_TABLE = 8192;   // n_groups x padded row length, in floats
 constexpr int MAX_GROUPS = MAX_TABLE / CHUNK;
 constexpr int REDUCE_THREADS = 512, REDUCE_WAVES = REDUCE_THREADS / 64, REDUCE_COLS = 32, REDUCE_SLICES = REDUCE_THREADS / (REDUCE_COLS / 4);
-static_assert(MAX_BLOCKS % REDUCE_SLICES == 0, "a lane's shares");
+static_assert(MAX_SHARES % REDUCE_SLICES == 0, "a lane's shares");
 
+constexpr int LDS_FLOATS = 32768;  // of the backward kernel's parameter rows and accumulators (the rest of the 160 KB: its sort)
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -35,10 +44,19 @@ struct Args {
     void *y, *dx, *dgate;
     float *mean, *rstd, *partials;
     int64_t n;
-    int32_t d, n_groups, row;  // row = d rounded up to whole chunks: the stride of a group's row in LDS
-    int32_t span;              // backward: tokens a wave takes per pass, at most 64 (a workgroup: WAVES times that)
+    int32_t d, n_groups, row;  // row = d rounded up to what a token's lanes hold: the stride of a group's row in LDS
+    int32_t span;              // backward: tokens a wave takes per pass, at most 64
+    int32_t rep;               // backward: copies of the accumulators in LDS
     float eps;
 };
+
+// Backward: threads of a workgroup, one per compute unit with as many waves as the registers of a token's chunks and sums allow without scratch
+// (which costs a small call 4 to 10 us by itself), and sets of tokens that a wave has in flight.  Two chunks in bf16, eight waves with two tokens
+// in flight against twelve with one or sixteen with one and scratch: 60 000 x 736, 8 groups, gated 104 / 104 / 112 us, 9418 x 688 24.2 / 24.8 / 33.7.
+template <typename T, int CPL>
+constexpr int bwd_threads() { return CPL == 1 ? 1024 : 512; }
+template <typename T, int CPL, int LPT, bool GATED>
+constexpr int bwd_depth() { return sizeof(T) == 2 && (CPL == 2 || (CPL == 1 && (LPT == 64 || !GATED))) ? 2 : 1; }
 
 // eight consecutive features as they lie in memory; converted where they are used, so that tokens waiting for
 // their turn occupy half the registers in bf16
@@ -49,24 +67,16 @@ struct Raw<__bf16> {
     bf16x8 v;
     __device__ void load(const __bf16* p) { v = __builtin_nontemporal_load((const bf16x8*)p); }
     __device__ float operator[](int j) const { return (float)v[j]; }
+    __device__ void forget() { asm volatile("" : "+v"(v)); }  // what follows is formed from these registers again, not kept from before
 };
 template <>
 struct Raw<float> {
     floatx4 lo, hi;
     __device__ void load(const float* p) { lo = *(const floatx4*)p, hi = *(const floatx4*)(p + 4); }
     __device__ float operator[](int j) const { return j < 4 ? lo[j] : hi[j - 4]; }
+    __device__ void forget() { asm volatile("" : "+v"(lo), "+v"(hi)); }
 };
 
-__device__ inline void load8(const __bf16* p, float (&f)[8]) {
-    const bf16x8 v = __builtin_nontemporal_load((const bf16x8*)p);
-#pragma unroll
-    for (int j = 0; j < 8; j++) f[j] = (float)v[j];
-}
-__device__ inline void load8(const float* p, float (&f)[8]) {
-    const floatx4 a = *(const floatx4*)p, b = *(const floatx4*)(p + 4);
-#pragma unroll
-    for (int j = 0; j < 4; j++) f[j] = a[j], f[4 + j] = b[j];
-}
 __device__ inline void store8(__bf16* p, const float (&f)[8]) {
     bf16x8 v;
 #pragma unroll
@@ -85,159 +95,186 @@ template <int CTRL>
 __device__ inline float dpp(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
-// sum over the 64 lanes in a fixed order, the same value in every lane: exchanges inside the 16-lane rows
-// (lane ^ 1, lane ^ 2, mirror of each half row, mirror of the row), then the four row sums
-__device__ inline float wave_sum(float v) {
+// Sum over the LPT lanes of a token, the same value in all of them, in a fixed order: exchanges inside the 16-lane rows (lane ^ 1, lane ^ 2,
+// mirror of each half row, mirror of the row), then the sums of the token's rows.
+template <int LPT>
+__device__ inline float token_sum(float v) {
     v += dpp<0xB1>(v);   // quad_perm [1,0,3,2]
     v += dpp<0x4E>(v);   // quad_perm [2,3,0,1]
     v += dpp<0x141>(v);  // row_half_mirror
     v += dpp<0x140>(v);  // row_mirror
+    if constexpr (LPT == 16) return v;
     const int u = __builtin_bit_cast(int, v);
     const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(u, 0));
     const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(u, 16));
     const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(u, 32));
     const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(u, 48));
+    if constexpr (LPT == 32) return (threadIdx.x & 32) ? r2 + r3 : r0 + r1;
     return (r0 + r1) + (r2 + r3);
 }
 
-// Where feature e of a parameter row lies in LDS.  A lane reads its 8 features of a chunk as two 16-byte words:
-// the first words of the 64 lanes are contiguous, then the second words, so neither read has a bank conflict.
+// Where feature e of a parameter or accumulator row lies in LDS, for chunks of CH features.  A lane reads its 8 features of a chunk as
+// two 16-byte words: the first words of a token's lanes are contiguous, then the second words, so neither read has a bank conflict.
+template <int CH>
 __device__ inline int quad_slot(int e) {
-    const int r = e & (CHUNK - 1);
-    return (e - r) + ((r >> 2) & 1) * 256 + (r >> 3) * 4 + (r & 3);
-}
-// Where the accumulator of feature e lies: feature j of lane l at word j * 64 + l of the chunk, so the 64
-// atomic adds of one instruction fall into 64 different banks.
-__device__ inline int word_slot(int e) {
-    const int r = e & (CHUNK - 1);
-    return (e - r) + (r & 7) * 64 + (r >> 3);
+    const int r = e & (CH - 1);
+    return (e - r) + ((r >> 2) & 1) * (CH / 2) + (r >> 3) * 4 + (r & 3);
 }
 
+template <int CH, int NTHR>
 __device__ inline void stage_rows(float* table, const float* src, int n_groups, int d, int row) {
-    for (int i = threadIdx.x * 4; i < n_groups * d; i += THREADS * 4) {
-        const int g = i / d, e = i - g * d;
-        *(floatx4*)&table[g * row + quad_slot(e)] = *(const floatx4*)&src[i];
+    const int quads = d / 4;
+    for (int i = threadIdx.x; i < n_groups * quads; i += NTHR) {
+        const int g = i / quads, e = (i - g * quads) * 4;
+        *(floatx4*)&table[g * row + quad_slot<CH>(e)] = *(const floatx4*)&src[i * 4];
     }
 }
 
-__device__ inline void read_row8(const float* table_row, int c, int lane, float (&f)[8]) {
-    const floatx4 a = *(const floatx4*)&table_row[c * CHUNK + lane * 4];
-    const floatx4 b = *(const floatx4*)&table_row[c * CHUNK + 256 + lane * 4];
+template <int LPT>
+__device__ inline void read_row8(const float* table_row, int c, int fl, float (&f)[8]) {
+    const floatx4 a = *(const floatx4*)&table_row[c * LPT * 8 + fl * 4];
+    const floatx4 b = *(const floatx4*)&table_row[c * LPT * 8 + LPT * 4 + fl * 4];
 #pragma unroll
     for (int j = 0; j < 4; j++) f[j] = a[j], f[4 + j] = b[j];
 }
 
-__device__ inline int group_of(const Args& a, int64_t t) {
-    const int g = __builtin_amdgcn_readfirstlane(a.group_id[t]);
-    return g < 0 ? 0 : (g >= a.n_groups ? a.n_groups - 1 : g);
-}
+__device__ inline int clamp_group(int g, int n_groups) { return g < 0 ? 0 : (g >= n_groups ? n_groups - 1 : g); }
 
-// TPW tokens per wave and iteration: their loads are all issued before the first is used
-template <typename T, int CPL, bool GATED>
+// LPT lanes hold a token (64 of 512 features and CPL such chunks, 32 of at most 256 features, 16 of at most 128); 64 / LPT tokens lie side by
+// side in a wave, and TPW such sets are in flight: their loads are all issued before the first is used, those of the first iteration before the
+// parameters are staged and, where tokens lie side by side (200 000 x 136: 45 -> 37.7 us), those of the next while the current one is worked on.
+template <typename T, int CPL, int LPT, bool GATED>
 __global__ __launch_bounds__(THREADS, CPL <= 2 ? 4 : 2) void fwd_kernel(const Args a) {
-    constexpr int TPW = CPL == 1 ? 2 : 1;
+    constexpr int TPW = CPL == 1 ? 2 : 1, NT = 64 / LPT, CH = LPT * 8;
     extern __shared__ __attribute__((aligned(16))) float smem[];
     float* gamma_s = smem;
     float* beta_s = smem + a.n_groups * a.row;
-    stage_rows(gamma_s, a.gamma, a.n_groups, a.d, a.row);
-    stage_rows(beta_s, a.beta, a.n_groups, a.d, a.row);
-    __syncthreads();
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, fl = lane % LPT, sub = lane / LPT;
     const int d = a.d;
     const float inv_d = 1.f / (float)d;
     const T* xg = (const T*)a.x;
     const T* ug = (const T*)a.gate;
     T* yg = (T*)a.y;
-    const int64_t stride = (int64_t)gridDim.x * WAVES * TPW;
-    for (int64_t t0 = ((int64_t)blockIdx.x * WAVES + wave) * TPW; t0 < a.n; t0 += stride) {
-        float xv[TPW][CPL][8], uv[TPW][CPL][8];
+    Raw<T> xr[TPW][CPL], ur[TPW][CPL];
+    int gr[TPW];
+    const auto fetch = [&](int64_t t0, bool ids) {
 #pragma unroll
         for (int k = 0; k < TPW; k++) {
-            const int64_t t = t0 + k;
+            const int64_t t = t0 + k * NT + (NT > 1 ? sub : 0);
+            if (ids) gr[k] = t < a.n ? a.group_id[t] : 0;
 #pragma unroll
-            for (int c = 0; c < CPL; c++) {
-                const int col = (c * 64 + lane) * 8;
-                if (t < a.n && col < d) {
-                    load8(xg + t * d + col, xv[k][c]);
-                    if (GATED) load8(ug + t * d + col, uv[k][c]);
-                } else {
+            for (int c = 0; c < CPL; c++)
+                if (t < a.n && (c * LPT + fl) * 8 < d) xr[k][c].load(xg + t * d + (c * LPT + fl) * 8);
 #pragma unroll
-                    for (int j = 0; j < 8; j++) xv[k][c][j] = 0.f;
-                }
-            }
+            for (int c = 0; c < CPL; c++)
+                if (GATED && t < a.n && (c * LPT + fl) * 8 < d) ur[k][c].load(ug + t * d + (c * LPT + fl) * 8);
         }
+    };
+    const auto work = [&](int64_t t0, const Raw<T> (&xs)[TPW][CPL], const Raw<T> (&us)[TPW][CPL], const int (&gs)[TPW], bool late) {
 #pragma unroll
         for (int k = 0; k < TPW; k++) {
-            const int64_t t = t0 + k;
-            if (t >= a.n) break;
-            float s = 0.f;
+            const int64_t t = t0 + k * NT + (NT > 1 ? sub : 0);
+            if (NT == 1 && t >= a.n) break;
+            float xv[CPL][8], s = 0.f;
 #pragma unroll
             for (int c = 0; c < CPL; c++)
 #pragma unroll
-                for (int j = 0; j < 8; j++) s += xv[k][c][j];
+                for (int j = 0; j < 8; j++) {
+                    xv[c][j] = t < a.n && (c * LPT + fl) * 8 < d ? xs[k][c][j] : 0.f;
+                    s += xv[c][j];
+                }
             // Centre on a first mean m, then correct it by the mean of the centred values: x - m is exact for a
             // token whose spread is small against its offset, where the rounding of m itself would dominate.
-            const float m = wave_sum(s) * inv_d;
+            const float m = token_sum<LPT>(s) * inv_d;
             float q = 0.f, r = 0.f;
 #pragma unroll
             for (int c = 0; c < CPL; c++) {
-                if ((c * 64 + lane) * 8 < d) {
+                if ((c * LPT + fl) * 8 < d) {
 #pragma unroll
                     for (int j = 0; j < 8; j++) {
-                        xv[k][c][j] -= m;
-                        r += xv[k][c][j];
-                        q += xv[k][c][j] * xv[k][c][j];
+                        xv[c][j] -= m;
+                        r += xv[c][j];
+                        q += xv[c][j] * xv[c][j];
                     }
                 }
             }
-            const float delta = wave_sum(r) * inv_d;
-            const float var = fmaxf(wave_sum(q) * inv_d - delta * delta, 0.f);
+            const float delta = token_sum<LPT>(r) * inv_d;
+            const float var = fmaxf(token_sum<LPT>(q) * inv_d - delta * delta, 0.f);
             const float mean = m + delta;
             const float rstd = 1.f / sqrtf(var + a.eps);
-            const int g = group_of(a, t);
+            if (NT > 1 && t >= a.n) break;  // (behind the sums: lanes of the same token leave together)
+                        const int id = late ? a.group_id[t] : gs[k];
+            const int g = clamp_group(NT == 1 ? __builtin_amdgcn_readfirstlane(id) : id, a.n_groups);
 #pragma unroll
             for (int c = 0; c < CPL; c++) {
-                const int col = (c * 64 + lane) * 8;
+                const int col = (c * LPT + fl) * 8;
                 if (col < d) {
                     float gm[8], bt[8], out[8];
-                    read_row8(gamma_s + g * a.row, c, lane, gm);
-                    read_row8(beta_s + g * a.row, c, lane, bt);
+                    read_row8<LPT>(gamma_s + g * a.row, c, fl, gm);
+                    read_row8<LPT>(beta_s + g * a.row, c, fl, bt);
 #pragma unroll
                     for (int j = 0; j < 8; j++) {
-                        out[j] = gm[j] * ((xv[k][c][j] - delta) * rstd) + bt[j];
-                        if (GATED) out[j] *= uv[k][c][j];
+                        out[j] = gm[j] * ((xv[c][j] - delta) * rstd) + bt[j];
+                        if (GATED) out[j] *= us[k][c][j];
                     }
                     store8(yg + t * d + col, out);
                 }
             }
-            if (lane == 0) {
+            if (fl == 0) {
                 if (a.mean) a.mean[t] = mean;
                 if (a.rstd) a.rstd[t] = rstd;
             }
         }
+    };
+    const int64_t stride = (int64_t)gridDim.x * WAVES * TPW * NT;
+    int64_t t0 = ((int64_t)blockIdx.x * WAVES + wave) * (TPW * NT);
+    fetch(t0, true);
+    stage_rows<CH, THREADS>(gamma_s, a.gamma, a.n_groups, d, a.row);
+    stage_rows<CH, THREADS>(beta_s, a.beta, a.n_groups, d, a.row);
+    __syncthreads();
+    if constexpr (NT > 1) {
+        for (; t0 < a.n; t0 += stride) {
+            Raw<T> xs[TPW][CPL], us[TPW][CPL];
+            int gs[TPW];
+#pragma unroll
+            for (int k = 0; k < TPW; k++) {
+                gs[k] = gr[k];
+#pragma unroll
+                for (int c = 0; c < CPL; c++) xs[k][c] = xr[k][c], us[k][c] = ur[k][c];
+            }
+            if (t0 + stride < a.n) fetch(t0 + stride, true);
+            work(t0, xs, us, gs, false);
+        }
+    } else {
+        // (no further ahead: two workgroups per compute unit have enough in flight.  Two chunks and a gate: the id is asked for behind the sums;
+        // with the loads, 200 000 x 1024 took 233 us in place of 216, without a gate 148 in place of 152.)
+        if (t0 < a.n) work(t0, xr, ur, gr, false);
+        for (t0 += stride; t0 < a.n; t0 += stride) {
+            fetch(t0, !(CPL > 1 && GATED));
+            work(t0, xr, ur, gr, CPL > 1 && GATED);
+        }
     }
 }
 
-// Backward.  A wave takes up to 64 tokens at a time (lane l holds the group and position of the l-th of them)
-// and works through them group by group: the tokens of one group add their dz (.) xhat and dz into registers, and
-// only when the group is done do these go to the workgroup's accumulators in LDS -- a few atomic adds per span
-// instead of sixteen per token.
-template <typename T, int CPL, bool GATED>
-__global__ __launch_bounds__(THREADS, CPL == 1 ? 4 : 2) void bwd_kernel(const Args a) {
-    constexpr int TPW = CPL == 1 && sizeof(T) == 2 ? 2 : 1;  // tokens in flight per wave
+// Backward.  A workgroup takes a span of up to 64 consecutive tokens per wave and orders it by group (a counting sort of the ids in LDS);
+// each wave then takes an equal share of the ordered span (lane l holds the group and position of its l-th token) and works
+// through it group by group: the tokens of one group add their dz (.) xhat and dz into registers, which go to the workgroup's accumulators in
+// LDS when the group is done.  A wave adds there without atomics: a group that ends inside its share is nobody else's to end, and the last group of
+// its share, which the next waves may go on with, waits until all waves are through; then the waves of one group take turns, `rep` of
+// them at a time in copies of the accumulators of their own.  (LDS float atomics run at a lane per clock: with them the flushes of 1.6 groups per
+// wave took 30 to 45 us of a call, whatever its size.)
+template <typename T, int CPL, int LPT, bool GATED>
+__global__ __launch_bounds__((bwd_threads<T, CPL>())) void bwd_kernel(const Args a) {
+    constexpr int NTHR = bwd_threads<T, CPL>(), NW = NTHR / 64, NT = 64 / LPT, CH = LPT * 8;
+    constexpr int DEPTH = bwd_depth<T, CPL, LPT, GATED>();
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const int table = a.n_groups * a.row;
     float* gamma_s = smem;
-    float* dgamma_s = smem + table;
-    float* dbeta_s = smem + 2 * table;
-    float* beta_s = smem + 3 * table;  // present only with a gate
-    stage_rows(gamma_s, a.gamma, a.n_groups, a.d, a.row);
-    if (GATED) stage_rows(beta_s, a.beta, a.n_groups, a.d, a.row);
-    for (int i = threadIdx.x; i < 2 * table; i += THREADS) dgamma_s[i] = 0.f;
-    __syncthreads();
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float* beta_s = smem + table;                   // present only with a gate
+    float* acc_s = smem + (GATED ? 2 : 1) * table;  // rep x [dgamma | dbeta]
+    __shared__ int sorted_s[NTHR];                                        // (group << 16) | offset of the token in the span
+    __shared__ __attribute__((aligned(16))) int counts_s[MAX_GROUPS * NW];  // tokens of each group among a wave's 64 candidates
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, fl = lane % LPT, sub = lane / LPT;
     const int d = a.d;
     const float inv_d = 1.f / (float)d;
     const T* dyg = (const T*)a.dy;
@@ -245,152 +282,221 @@ __global__ __launch_bounds__(THREADS, CPL == 1 ? 4 : 2) void bwd_kernel(const Ar
     const T* ug = (const T*)a.gate;
     T* dxg = (T*)a.dx;
     T* dug = (T*)a.dgate;
-    // A workgroup takes a span of up to 512 consecutive tokens per pass and orders it by group (a counting sort of
-    // the ids in LDS); each wave then takes an equal share of the ordered span, so it meets only the few groups
-    // its share straddles, however skewed the group sizes are.
-    __shared__ int sorted_s[THREADS];           // (group << 16) | offset of the token in the span
-    __shared__ int counts_s[WAVES][MAX_GROUPS];  // tokens of each group among a wave's 64 candidates
-    const int block_span = a.span * WAVES;
-    for (int64_t base = (int64_t)blockIdx.x * block_span; base < a.n; base += (int64_t)gridDim.x * block_span) {
-        const int live = (int)(a.n - base < block_span ? a.n - base : block_span);
-        int g_me = -1;
-        if ((int)threadIdx.x < live) {
-            const int g = a.group_id[base + threadIdx.x];
-            g_me = g < 0 ? 0 : (g >= a.n_groups ? a.n_groups - 1 : g);
-        }
+    const int block_span = a.span * NW;
+    int64_t base = (int64_t)blockIdx.x * block_span;
+    int g_me = -1;
+    if (base < a.n && (int)threadIdx.x < (int)min((int64_t)block_span, a.n - base)) g_me = a.group_id[base + threadIdx.x];
+    stage_rows<CH, NTHR>(gamma_s, a.gamma, a.n_groups, d, a.row);
+    if (GATED) stage_rows<CH, NTHR>(beta_s, a.beta, a.n_groups, d, a.row);
+    for (int i = threadIdx.x * 4; i < 2 * a.rep * table; i += NTHR * 4) *(floatx4*)&acc_s[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int i = a.n_groups * NW + threadIdx.x; i < MAX_GROUPS * NW; i += NTHR) counts_s[i] = 0;
+
+    for (; base < a.n; base += (int64_t)gridDim.x * block_span) {
+        const int live = (int)min((int64_t)block_span, a.n - base);
+        if (base != (int64_t)blockIdx.x * block_span) g_me = (int)threadIdx.x < live ? a.group_id[base + threadIdx.x] : -1;
+        const bool mine = (int)threadIdx.x < live;
+        g_me = mine ? clamp_group(g_me, a.n_groups) : -1;
         int rank = 0;
         for (int g = 0; g < a.n_groups; g++) {
             const uint64_t m = __ballot(g_me == g);
             if (g_me == g) rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-            if (lane == 0) counts_s[wave][g] = __builtin_popcountll(m);
+            if (lane == 0) counts_s[g * NW + wave] = __builtin_popcountll(m);
         }
         __syncthreads();
-        if (g_me >= 0) {
-            int pos = rank;
-            for (int g = 0; g < g_me; g++)
-                for (int w = 0; w < WAVES; w++) pos += counts_s[w][g];
-            for (int w = 0; w < wave; w++) pos += counts_s[w][g_me];
-            sorted_s[pos] = (g_me << 16) | (int)threadIdx.x;
+        {   // every wave sums up the counts, a few consecutive ones to a lane, and each lane fetches where its (group, wave) starts
+            constexpr int PER = MAX_GROUPS * NW / 64;
+            int c[PER], before = 0;
+#pragma unroll
+            for (int i = 0; i < PER; i++) c[i] = counts_s[lane * PER + i], before += c[i];
+            const int own = before;
+#pragma unroll
+            for (int m = 1; m < 64; m *= 2) {
+                const int up = __shfl_up(before, m);
+                if (lane >= m) before += up;
+            }
+            before -= own;
+            int start = before;
+#pragma unroll
+            for (int i = 0; i + 1 < PER; i++) start += i < wave % PER ? c[i] : 0;
+            static_assert(NW % PER == 0, "a lane's counts are of one group");
+            const int pos = __shfl(start, (max(g_me, 0) * NW + wave) / PER) + rank;
+            if (mine) sorted_s[pos] = (g_me << 16) | (int)threadIdx.x;
         }
         __syncthreads();
-        const int per_wave = (live + WAVES - 1) / WAVES;
+        const int per_wave = (live + NW - 1) / NW;
         int g_lane = -1, off_lane = 0;
         if (lane < per_wave && wave * per_wave + lane < live) {
             const int e = sorted_s[wave * per_wave + lane];
             g_lane = e >> 16, off_lane = e & 0xFFFF;
         }
-        uint64_t todo = __ballot(g_lane >= 0);
-        while (todo) {
-            const int g = __builtin_amdgcn_readlane(g_lane, __builtin_ctzll(todo));
-            uint64_t members = __ballot(g_lane == g);
-            todo &= ~members;
-            float acc_g[CPL][8], acc_b[CPL][8];
+        // the last groups of the waves' shares, a lane to a wave: where a run of equal ones starts, and the longest run
+        const bool there = lane < NW && lane * per_wave < live;
+        const int last = there ? sorted_s[min((lane + 1) * per_wave, live) - 1] >> 16 : -1;
+        const int last_before = __shfl_up(last, 1);
+        const uint32_t goes_on = (uint32_t)__ballot(there && lane > 0 && last == last_before);
+        const uint32_t starts = ~goes_on & ((2u << wave) - 1);
+        const int turn = wave - (31 - __builtin_clz(starts));  // (wave 0 always starts a run)
+        int longest = 1;
+        for (uint32_t m = goes_on; m; m &= m << 1) longest++;
+
+        float acc_g[CPL][8], acc_b[CPL][8];
+        const auto add_to = [&](float* acc, int g) {  // this wave's sums to the accumulators
+            if (NT > 1) {
 #pragma unroll
-            for (int c = 0; c < CPL; c++)
+                for (int m = LPT; m < 64; m *= 2)
 #pragma unroll
-                for (int j = 0; j < 8; j++) acc_g[c][j] = 0.f, acc_b[c][j] = 0.f;
-            while (members) {
-                int64_t tok[TPW];
-#pragma unroll
-                for (int k = 0; k < TPW; k++) {
-                    tok[k] = members ? base + __builtin_amdgcn_readlane(off_lane, __builtin_ctzll(members)) : -1;
-                    members &= members - 1;  // stays 0 once empty
-                }
-                Raw<T> gv[TPW][CPL], xv[TPW][CPL], uv[TPW][CPL];
-                float mean[TPW], rstd[TPW];
-#pragma unroll
-                for (int k = 0; k < TPW; k++) {
-                    const int64_t t = tok[k];
-                    if (t >= 0) {
-                        mean[k] = a.mean_in[t];
-                        rstd[k] = a.rstd_in[t];
-                    }
-#pragma unroll
-                    for (int c = 0; c < CPL; c++) {
-                        const int col = (c * 64 + lane) * 8;
-                        if (t >= 0 && col < d) {
-                            gv[k][c].load(dyg + t * d + col);
-                            xv[k][c].load(xg + t * d + col);
-                            if (GATED) uv[k][c].load(ug + t * d + col);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < TPW; k++) {
-                    const int64_t t = tok[k];
-                    if (t < 0) break;
-                    float s1 = 0.f, s2 = 0.f;
-                    float w[CPL][8], xh[CPL][8];
-#pragma unroll
-                    for (int c = 0; c < CPL; c++) {
-                        const int col = (c * 64 + lane) * 8;
-                        if (col < d) {
-                            float gm[8];
-                            read_row8(gamma_s + g * a.row, c, lane, gm);
-#pragma unroll
-                            for (int j = 0; j < 8; j++) {
-                                xh[c][j] = (xv[k][c][j] - mean[k]) * rstd[k];
-                                const float dz = GATED ? gv[k][c][j] * uv[k][c][j] : gv[k][c][j];
-                                w[c][j] = dz * gm[j];
-                                s1 += w[c][j];
-                                s2 += w[c][j] * xh[c][j];
-                                acc_g[c][j] += dz * xh[c][j];
-                                acc_b[c][j] += dz;
-                            }
-                            if (GATED) {
-                                float bt[8], du[8];
-                                read_row8(beta_s + g * a.row, c, lane, bt);
-#pragma unroll
-                                for (int j = 0; j < 8; j++) du[j] = gv[k][c][j] * (gm[j] * xh[c][j] + bt[j]);
-                                store8(dug + t * d + col, du);
-                            }
-                        } else {
-#pragma unroll
-                            for (int j = 0; j < 8; j++) w[c][j] = 0.f, xh[c][j] = 0.f;
-                        }
-                    }
-                    s1 = wave_sum(s1) * inv_d;
-                    s2 = wave_sum(s2) * inv_d;
-#pragma unroll
-                    for (int c = 0; c < CPL; c++) {
-                        const int col = (c * 64 + lane) * 8;
-                        if (col < d) {
-                            float out[8];
-#pragma unroll
-                            for (int j = 0; j < 8; j++) out[j] = rstd[k] * (w[c][j] - s1 - xh[c][j] * s2);
-                            store8(dxg + t * d + col, out);
-                        }
-                    }
-                }
+                    for (int j = 0; j < 8; j++) acc_g[0][j] += __shfl_xor(acc_g[0][j], m), acc_b[0][j] += __shfl_xor(acc_b[0][j], m);
             }
 #pragma unroll
             for (int c = 0; c < CPL; c++) {
-                if ((c * 64 + lane) * 8 < d) {
-                    float* slot_g = dgamma_s + g * a.row + c * CHUNK + lane;
-                    float* slot_b = dbeta_s + g * a.row + c * CHUNK + lane;
+                if ((NT == 1 || sub == 0) && (c * LPT + fl) * 8 < d) {
 #pragma unroll
-                    for (int j = 0; j < 8; j++) {
-                        atomicAdd(slot_g + j * 64, acc_g[c][j]);
-                        atomicAdd(slot_b + j * 64, acc_b[c][j]);
+                    for (int h = 0; h < 2; h++) {
+                        floatx4* pg = (floatx4*)&acc[g * a.row + c * CH + h * (CH / 2) + fl * 4];
+                        floatx4* pb = (floatx4*)&acc[table + g * a.row + c * CH + h * (CH / 2) + fl * 4];
+                        floatx4 vg = *pg, vb = *pb;
+#pragma unroll
+                        for (int j = 0; j < 4; j++) vg[j] += acc_g[c][4 * h + j], vb[j] += acc_b[c][4 * h + j];
+                        *pg = vg;
+                        *pb = vb;
                     }
                 }
             }
+        };
+        // The tokens in order, NT of one group at a time, DEPTH such sets in flight.
+        float mean_lane = 0.f, rstd_lane = 0.f;
+        if (g_lane >= 0) mean_lane = a.mean_in[base + off_lane], rstd_lane = a.rstd_in[base + off_lane];
+        const T* dy0 = dyg + base * d;
+        const T* x0 = xg + base * d;
+        const T* u0 = ug + base * d;
+        T* dx0 = dxg + base * d;
+        T* du0 = dug + base * d;
+        uint64_t todo = __ballot(g_lane >= 0), members = 0;
+        int g_next = -1;
+        Raw<T> gv[DEPTH][CPL], xv[DEPTH][CPL], uv[DEPTH][CPL];
+        int group[DEPTH], index[DEPTH], offset[DEPTH];  // group: -1 behind the last set; offset: of the lane's token in the span, -1 for none
+        const auto fetch = [&](int k) {
+            if (!members) {
+                g_next = todo ? __builtin_amdgcn_readlane(g_lane, __builtin_ctzll(todo)) : -1;
+                members = todo ? __ballot(g_lane == g_next) : 0;
+                todo &= ~members;
+            }
+            group[k] = g_next;
+            if (g_next < 0) return;
+            index[k] = 0, offset[k] = -1;
+#pragma unroll
+            for (int i = 0; i < NT; i++) {
+                const int at = members ? __builtin_ctzll(members) : 0;
+                const int off = members ? __builtin_amdgcn_readlane(off_lane, at) : -1;
+                members &= members - 1;  // stays 0 once empty
+                if (i == 0 || sub == i) index[k] = at, offset[k] = off;
+            }
+#pragma unroll
+            for (int c = 0; c < CPL; c++) {
+                const int col = (c * LPT + fl) * 8;
+                if ((NT == 1 || offset[k] >= 0) && col < d) {
+                    gv[k][c].load(dy0 + offset[k] * d + col);
+                    xv[k][c].load(x0 + offset[k] * d + col);
+                    if (GATED) uv[k][c].load(u0 + offset[k] * d + col);
+                }
+            }
+        };
+#pragma unroll
+        for (int k = 0; k < DEPTH; k++) fetch(k);
+        int g = -1;  // the group that the sums in registers are of
+        const auto work = [&](int k) {
+            if (group[k] != g) {
+                if (g >= 0) add_to(acc_s, g);
+                g = group[k];
+#pragma unroll
+                for (int c = 0; c < CPL; c++)
+#pragma unroll
+                    for (int j = 0; j < 8; j++) acc_g[c][j] = 0.f, acc_b[c][j] = 0.f;
+            }
+            float mean, rstd;
+            if constexpr (NT == 1) {
+                mean = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mean_lane), index[k]));
+                rstd = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rstd_lane), index[k]));
+            } else {
+                mean = __shfl(mean_lane, index[k]), rstd = __shfl(rstd_lane, index[k]);
+            }
+            const bool there = NT == 1 || offset[k] >= 0;
+            int fo = fl;
+            asm volatile("" : "+v"(fo));  // (the group's parameters are read from LDS for each token: kept, they would be 32 registers)
+            float s1 = 0.f, s2 = 0.f;
+            float w[CPL][8];
+#pragma unroll
+            for (int c = 0; c < CPL; c++) {
+                const int col = (c * LPT + fl) * 8;
+                if (there && col < d) {
+                    float gm[8];
+                    read_row8<LPT>(gamma_s + g * a.row, c, fo, gm);
+#pragma unroll
+                    for (int j = 0; j < 8; j++) {
+                        const float xh = (xv[k][c][j] - mean) * rstd;
+                        const float dz = GATED ? gv[k][c][j] * uv[k][c][j] : gv[k][c][j];
+                        w[c][j] = dz * gm[j];
+                        s1 += w[c][j];
+                        s2 += w[c][j] * xh;
+                        acc_g[c][j] += dz * xh;
+                        acc_b[c][j] += dz;
+                    }
+                    if (GATED) {
+                        float bt[8], du[8];
+                        gv[k][c].forget();
+                        xv[k][c].forget();
+                        read_row8<LPT>(beta_s + g * a.row, c, fo, bt);
+#pragma unroll
+                        for (int j = 0; j < 8; j++) du[j] = gv[k][c][j] * (gm[j] * ((xv[k][c][j] - mean) * rstd) + bt[j]);
+                        store8(du0 + offset[k] * d + col, du);
+                    }
+                }
+                if (CPL > 1) __builtin_amdgcn_sched_barrier(0);  // (chunk by chunk: interleaved they want more than 128 registers)
+            }
+            s1 = token_sum<LPT>(s1) * inv_d;
+            s2 = token_sum<LPT>(s2) * inv_d;
+#pragma unroll
+            for (int c = 0; c < CPL; c++) {
+                const int col = (c * LPT + fl) * 8;
+                if (there && col < d) {
+                    float out[8];
+                    xv[k][c].forget();
+#pragma unroll
+                    for (int j = 0; j < 8; j++) out[j] = rstd * (w[c][j] - s1 - (xv[k][c][j] - mean) * rstd * s2);
+                    store8(dx0 + offset[k] * d + col, out);
+                }
+            }
+        };
+        for (bool more = group[0] >= 0; more;) {
+#pragma unroll
+            for (int k = 0; k < DEPTH; k++) {
+                more = group[k] >= 0;
+                if (!more) break;
+                work(k);
+                fetch(k);
+            }
+        }
+        __syncthreads();
+        for (int r = 0; r * a.rep < longest; r++) {
+            if (r) __syncthreads();
+            if (g >= 0 && turn / a.rep == r) add_to(acc_s + (turn % a.rep) * 2 * table, g);
         }
     }
     __syncthreads();
     // this workgroup's share, features in their natural order: [dgamma | dbeta][n_groups][d]
-    const int gd = a.n_groups * d;
+    const int gd = a.n_groups * d, quads = d / 4;
     float* share = a.partials + (size_t)blockIdx.x * 2 * gd;
-    for (int i = threadIdx.x; i < gd; i += THREADS) {
-        const int g = i / d, e = i - g * d;
-        share[i] = dgamma_s[g * a.row + word_slot(e)];
-        share[gd + i] = dbeta_s[g * a.row + word_slot(e)];
+    for (int i = threadIdx.x; i < 2 * a.n_groups * quads; i += NTHR) {
+        const int g = i / quads, e = (i - g * quads) * 4;  // (rows of dgamma, then those of dbeta, as in LDS)
+        floatx4 v = *(const floatx4*)&acc_s[g * a.row + quad_slot<CH>(e)];
+        for (int r = 1; r < a.rep; r++) v += *(const floatx4*)&acc_s[r * 2 * table + g * a.row + quad_slot<CH>(e)];
+        *(floatx4*)&share[i * 4] = v;
     }
 }
 
 // dgamma | dbeta = the sum of the workgroups' shares, in a fixed order: lane l of a wave takes columns 4 (l % 8) .. of the workgroup's
 // and every 64th share, the eight lanes of a column add up, then the eight waves.  All latency, so every lane has its (at most
-// eight) loads of 16 bytes in flight at once and the columns are spread over the chip (512 shares of 2 x 8 x 512: 10.1 -> 4.8 us,
+// four) loads of 16 bytes in flight at once and the columns are spread over the chip (512 shares of 2 x 8 x 512: 10.1 -> 4.8 us,
 // against 1024 threads that walked 32 shares each, four bytes at a time, on half of the compute units).
 __global__ __launch_bounds__(REDUCE_THREADS) void reduce_kernel(const float* partials, int n_shares, int gd, float* dgamma, float* dbeta) {
     __shared__ floatx4 part[REDUCE_WAVES][REDUCE_COLS / 4];
@@ -398,13 +504,13 @@ __global__ __launch_bounds__(REDUCE_THREADS) void reduce_kernel(const float* par
     const int first = blockIdx.x * REDUCE_COLS, e = first + 4 * quad;  // (gd is a multiple of 8: no quad has columns of both)
     const int slice = (int)threadIdx.x / (REDUCE_COLS / 4);
     const float* col4 = partials + min(e, 2 * gd - 4);  // (no branches: what is not there repeats what is, and does not count)
-    floatx4 v[MAX_BLOCKS / REDUCE_SLICES];
+    floatx4 v[MAX_SHARES / REDUCE_SLICES];
 #pragma unroll
-    for (int i = 0; i < MAX_BLOCKS / REDUCE_SLICES; i++)
+    for (int i = 0; i < MAX_SHARES / REDUCE_SLICES; i++)
         v[i] = *(const floatx4*)(col4 + (size_t)max(0, min(i * REDUCE_SLICES + slice, n_shares - 1)) * 2 * gd);
     floatx4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < MAX_BLOCKS / REDUCE_SLICES; i++)
+    for (int i = 0; i < MAX_SHARES / REDUCE_SLICES; i++)
 #pragma unroll
         for (int j = 0; j < 4; j++) s[j] += i * REDUCE_SLICES + slice < n_shares ? v[i][j] : 0.f;
 #pragma unroll
@@ -423,10 +529,9 @@ __global__ __launch_bounds__(REDUCE_THREADS) void reduce_kernel(const float* par
     }
 }
 
-int grid_for(int64_t n_tokens, int tokens_per_wave) {
-    const int64_t per_block = (int64_t)WAVES * tokens_per_wave;
-    const int64_t blocks = (n_tokens + per_block - 1) / per_block;
-    return (int)(blocks < MAX_BLOCKS ? blocks : MAX_BLOCKS);
+int grid_for(int64_t n_tokens, int tokens_per_block, int most) {
+    const int64_t blocks = (n_tokens + tokens_per_block - 1) / tokens_per_block;
+    return (int)(blocks < most ? blocks : most);
 }
 
 // Lets `kernel` use the whole 160 KB of LDS as dynamic shared memory.  Asked for once per kernel (the first call is
@@ -437,39 +542,56 @@ hipError_t allow_lds(KernelT kernel) {
     return state;
 }
 
-template <typename T, int CPL, bool GATED>
+template <typename T, int CPL, int LPT, bool GATED>
 hipError_t launch_fwd_as(const Args& a, hipStream_t s) {
     const size_t lds = (size_t)2 * a.n_groups * a.row * sizeof(float);
-    hipError_t e = allow_lds(fwd_kernel<T, CPL, GATED>);
+    hipError_t e = allow_lds(fwd_kernel<T, CPL, LPT, GATED>);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((fwd_kernel<T, CPL, GATED>), dim3(grid_for(a.n, CPL == 1 ? 2 : 1)), dim3(THREADS), lds, s, a);
+    const int grid = grid_for(a.n, WAVES * (CPL == 1 ? 2 : 1) * (64 / LPT), MAX_BLOCKS);
+    hipLaunchKernelGGL((fwd_kernel<T, CPL, LPT, GATED>), dim3(grid), dim3(THREADS), lds, s, a);
     return hipGetLastError();
 }
 
-template <typename T, int CPL, bool GATED>
-hipError_t launch_bwd_as(const Args& a, hipStream_t s) {
-    const size_t lds = (size_t)(GATED ? 4 : 3) * a.n_groups * a.row * sizeof(float);
-    hipError_t e = allow_lds(bwd_kernel<T, CPL, GATED>);
+template <typename T, int CPL, int LPT, bool GATED>
+hipError_t launch_bwd_as(Args& a, int* shares, hipStream_t s) {
+    constexpr int NTHR = bwd_threads<T, CPL>(), NW = NTHR / 64;
+    // every wave of the grid gets one span when the tokens allow it, several passes of at most 64 and alike otherwise
+    *shares = grid_for(a.n, NW * (64 / LPT), MAX_SHARES);
+    const int64_t even = (a.n + (int64_t)*shares * NW - 1) / ((int64_t)*shares * NW), passes = (even + 63) / 64;
+    a.span = (int32_t)((even + passes - 1) / passes);
+    // accumulators for as many waves as end in the same group when groups are even, within 128 KB with the parameters
+    const int room = (LDS_FLOATS / (a.n_groups * a.row) - (GATED ? 2 : 1)) / 2, want = (NW + a.n_groups - 1) / a.n_groups;
+    a.rep = room < want ? room : want;
+    const size_t lds = (size_t)((GATED ? 2 : 1) + 2 * a.rep) * a.n_groups * a.row * sizeof(float);
+    hipError_t e = allow_lds(bwd_kernel<T, CPL, LPT, GATED>);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bwd_kernel<T, CPL, GATED>), dim3(grid_for(a.n, 1)), dim3(THREADS), lds, s, a);
+    hipLaunchKernelGGL((bwd_kernel<T, CPL, LPT, GATED>), dim3(*shares), dim3(NTHR), lds, s, a);
     return hipGetLastError();
+}
+
+template <typename T, int CPL, int LPT, bool GATED>
+hipError_t launch_as(int* shares, Args& a, hipStream_t s) {
+    a.row = (a.d + LPT * 8 - 1) / (LPT * 8) * (LPT * 8);
+    return shares ? launch_bwd_as<T, CPL, LPT, GATED>(a, shares, s) : launch_fwd_as<T, CPL, LPT, GATED>(a, s);
 }
 
 template <typename T, bool GATED>
-hipError_t dispatch_chunks(bool bwd, const Args& a, hipStream_t s) {
-    switch (a.row / CHUNK) {
-        case 1: return bwd ? launch_bwd_as<T, 1, GATED>(a, s) : launch_fwd_as<T, 1, GATED>(a, s);
-        case 2: return bwd ? launch_bwd_as<T, 2, GATED>(a, s) : launch_fwd_as<T, 2, GATED>(a, s);
-        case 3: return bwd ? launch_bwd_as<T, 3, GATED>(a, s) : launch_fwd_as<T, 3, GATED>(a, s);
-        default: return bwd ? launch_bwd_as<T, 4, GATED>(a, s) : launch_fwd_as<T, 4, GATED>(a, s);
+hipError_t dispatch_width(int* shares, Args& a, hipStream_t s) {
+    if (a.d <= 128) return launch_as<T, 1, 16, GATED>(shares, a, s);
+    if (a.d <= 256) return launch_as<T, 1, 32, GATED>(shares, a, s);
+    switch ((a.d + CHUNK - 1) / CHUNK) {
+        case 1: return launch_as<T, 1, 64, GATED>(shares, a, s);
+        case 2: return launch_as<T, 2, 64, GATED>(shares, a, s);
+        case 3: return launch_as<T, 3, 64, GATED>(shares, a, s);
+        default: return launch_as<T, 4, 64, GATED>(shares, a, s);
     }
 }
 
-hipError_t dispatch(bool bwd, int dtype, const Args& a, hipStream_t s) {
+// shares: null for the forward pass; for the backward pass, how many shares of dgamma / dbeta it leaves
+hipError_t dispatch(int* shares, int dtype, Args& a, hipStream_t s) {
     const bool gated = a.gate != nullptr;
-    if (dtype == MTFM_HTA_BF16)
-        return gated ? dispatch_chunks<__bf16, true>(bwd, a, s) : dispatch_chunks<__bf16, false>(bwd, a, s);
-    return gated ? dispatch_chunks<float, true>(bwd, a, s) : dispatch_chunks<float, false>(bwd, a, s);
+    if (dtype == MTFM_HTA_BF16) return gated ? dispatch_width<__bf16, true>(shares, a, s) : dispatch_width<__bf16, false>(shares, a, s);
+    return gated ? dispatch_width<float, true>(shares, a, s) : dispatch_width<float, false>(shares, a, s);
 }
 
 int padded_row(int32_t d) { return (d + CHUNK - 1) / CHUNK * CHUNK; }
@@ -508,10 +630,10 @@ int mtfm_gln_fwd(const void* x, const void* gate, const int32_t* group_id, const
         return hta::report_error(MTFM_HTA_ERR_INVALID_ARG, "x, gate, y, gamma, beta must be 16-byte aligned");
     gln::Args a = {};
     a.x = x, a.gate = gate, a.group_id = group_id, a.gamma = gamma, a.beta = beta, a.y = y, a.mean = mean, a.rstd = rstd;
-    a.n = n_tokens, a.d = d_model, a.n_groups = n_groups, a.row = gln::padded_row(d_model), a.eps = eps;
+    a.n = n_tokens, a.d = d_model, a.n_groups = n_groups, a.eps = eps;
     hipStream_t s = (hipStream_t)stream;
     hta::timing_begin(MTFM_GLN_KERNEL_FWD, s);
-    const hipError_t e = gln::dispatch(false, dtype, a, s);
+    const hipError_t e = gln::dispatch(nullptr, dtype, a, s);
     hta::timing_end(MTFM_GLN_KERNEL_FWD, s);
     if (e != hipSuccess) return hta::report_error(MTFM_HTA_ERR_LAUNCH, "gln forward launch: %s", hipGetErrorString(e));
     return MTFM_HTA_OK;
@@ -519,7 +641,7 @@ int mtfm_gln_fwd(const void* x, const void* gate, const int32_t* group_id, const
 
 size_t mtfm_gln_bwd_workspace_bytes(int32_t d_model, int32_t n_groups) {
     if (gln::check_shape(0, d_model, n_groups, MTFM_HTA_BF16) != MTFM_HTA_OK) return 0;
-    return (size_t)gln::MAX_BLOCKS * 2 * n_groups * d_model * sizeof(float);
+    return (size_t)gln::WORKSPACE_SHARES * 2 * n_groups * d_model * sizeof(float);
 }
 
 int mtfm_gln_bwd(const void* dy, const void* x, const void* gate, const int32_t* group_id, const float* gamma,
@@ -547,18 +669,13 @@ int mtfm_gln_bwd(const void* dy, const void* x, const void* gate, const int32_t*
     gln::Args a = {};
     a.dy = dy, a.x = x, a.gate = gate, a.group_id = group_id, a.gamma = gamma, a.beta = beta, a.mean_in = mean, a.rstd_in = rstd;
     a.dx = dx, a.dgate = dgate, a.partials = (float*)workspace;
-    a.n = n_tokens, a.d = d_model, a.n_groups = n_groups, a.row = gln::padded_row(d_model);
+    a.n = n_tokens, a.d = d_model, a.n_groups = n_groups;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     int shares = 0;
     if (n_tokens > 0) {
-        // every wave of the grid gets one span when the tokens allow it, several passes of 64 otherwise
-        shares = gln::grid_for(n_tokens, 1);
-        const int64_t waves = (int64_t)shares * gln::WAVES;
-        const int64_t even = (n_tokens + waves - 1) / waves;
-        a.span = (int32_t)(even < 64 ? even : 64);
         hta::timing_begin(MTFM_GLN_KERNEL_BWD, s);
-        e = gln::dispatch(true, dtype, a, s);
+        e = gln::dispatch(&shares, dtype, a, s);
         hta::timing_end(MTFM_GLN_KERNEL_BWD, s);
         if (e != hipSuccess) return hta::report_error(MTFM_HTA_ERR_LAUNCH, "gln backward launch: %s", hipGetErrorString(e));
     }

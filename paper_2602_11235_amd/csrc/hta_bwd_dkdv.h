@@ -39,7 +39,7 @@ struct DkdvSmem {
 // PW: the pointwise reading of phi2 -- P = silu(scale S), dS = dP o silu'(scale S); the staged row statistics are
 // zeros for rows that exist (the sentinel for rows that do not still removes them), norm is applied at the store.
 template <int D, int NW, bool TAILS, bool PW = false>
-__global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Params p, int tpg, unsigned per_xcd, unsigned n_persistent,
+__global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Params p, int tpg, int spread, unsigned per_xcd, unsigned n_persistent,
                                                                        RowMap map, int tail_tpg) {
     using SM = DkdvSmem<D, NW>;
     constexpr int UPI = SM::UPI, NSTAGE = SM::NSTAGE;
@@ -63,9 +63,21 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     __shared__ int s_item;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
 
+    // The next item is taken shortly before the current one ends, early enough for the atomic to have returned by then.  (Taken with the
+    // start of the current one, the last items of the lists waited behind items in progress while other workgroups left.  Whole steps: 256 users
+    // of 512..1024 keys 1815 -> 1795 us, 238 of 366..732 930 -> 901, 28 of up to 7896 2827 -> 2514; at head_dim 128 33 users of 434 + 60
+    // keys 584 -> 497, 23 of 715..2379 2749 -> 2496, 128 of 750..8192 50.2 -> 49.7 ms; of 40 sampled calls one 1 % slower.)
+    const int xcd = blockIdx.x % N_XCD;
+    unsigned taken = blockIdx.x / N_XCD;
+    bool asked;
+    auto ask = [&]() __attribute__((always_inline)) {
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, n_persistent);
+        asked = true;
+    };
+
     // one work item: a (user, kv head, key tile) triple
     auto process = [&](unsigned id) {
-    const WorkItem w = decode_work(id, p.batch * p.Hkv, p.Hkv, tpg);
+    const WorkItem w = decode_spread(id, p.batch * p.Hkv, p.Hkv, tpg, spread);
     if (!w.valid) return;
     const int b = scheduled_user(p, w.user_slot), g = w.y;
     const int L = p.hist_len[b], T = p.n_targets[b];
@@ -332,6 +344,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
             accumulate(wt, f);
         };
         for (int it = 0; it < n_iter; it += 3) {
+            if (it + 6 >= n_iter && !asked) ask();
             iteration(it, st0);
             if (it + 1 < n_iter) iteration(it + 1, st1);
             if (it + 2 < n_iter) iteration(it + 2, st2);
@@ -376,15 +389,14 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     };  // process
 
     // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
-    const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
         if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, n_persistent);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, n_persistent);
+        asked = false;
         process((unsigned)id);
+        if (!asked) ask();  // (no such item, or a wave that only helped staging)
         __syncthreads();  // the stages and s_item are free again
     }
 }
@@ -633,12 +645,21 @@ __global__ __launch_bounds__(BRIEF_NW * 64, 1) void dkdv_tails_kernel(Params p, 
     brief_dkdv<D, BRIEF_NW, true, PW, true>(p, map, blockIdx.x, tail_tpg, 0, smem);
 }
 
+// Spread of the lists (decode_spread): an XCD starts what is in its own list first, so where a few long users have much of the work their tiles
+// go to four lists.  22 users of up to 4315 keys, 1413 in the mean, 16/2 heads of 128: whole step 3.48 -> 2.74 ms; 28 of up to 6611 keys, 8/2
+// heads 2.39 -> 2.31; 20 of up to 6055 5.63 -> 5.43; five others of that kind within 1 %.  Users alike, or many, gain nothing and read their operands
+// into more L2s (256 users of 512..1024 keys 1806 -> 1825 us, 233 of up to 1195 3413 -> 3479).
+inline int list_spread(const Params& p, int64_t n_kt) {
+    return (int64_t)p.batch * p.Hkv < 128 && n_kt >= 8 && (double)most_keys(p) > 2.5 * mean_keys(p) ? 2 : 0;
+}
+
 template <int D, int NW, bool TAILS, bool PW = false>
 hipError_t launch_dkdv_as(const Params& p, hipStream_t s) {
     const int64_t keys = p.max_hist;
     if (max_lead_keys(p) <= 0) return hipSuccess;
     const int64_t n_kt = (keys + NW * 32 - 1) / (NW * 32);
-    const int64_t n_items = work_grid((int64_t)p.batch * p.Hkv, n_kt);
+    const int spread = list_spread(p, n_kt);
+    const int64_t n_items = work_grid((int64_t)p.batch * p.Hkv, n_kt, spread);
     const RowMap map = row_map(32, p.Hq, p.Hkv, max_query_rows(p));
     const int64_t resident = resident_workgroups<bwd_dkdv_kernel<D, NW, TAILS, PW>>(NW * 64);
     const int64_t persistent = n_items < resident ? n_items : resident;
@@ -649,7 +670,7 @@ hipError_t launch_dkdv_as(const Params& p, hipStream_t s) {
     pk.queue = p.queue + QUEUE_DKDV * N_XCD;
     const int64_t n_blocks = persistent + (TAILS ? n_tails : 0);
     if (n_blocks > 0)
-        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, TAILS, PW>), dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, pk, (int)n_kt,
+        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, TAILS, PW>), dim3((unsigned)n_blocks), dim3(NW * 64), 0, s, pk, (int)n_kt, spread,
                            (unsigned)(n_items / N_XCD), (unsigned)persistent, map, (int)tail_kt);
     if constexpr (D == 128) {
         if (n_tails == 0) return hipGetLastError();

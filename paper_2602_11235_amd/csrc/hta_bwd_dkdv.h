@@ -123,7 +123,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
             vf[ks] = *(const bf16x8*)((const __bf16*)p.v + off + ks * 16);
         }
     }
-    floatx16 dK[NDB], dV[NDB];  // [key (registers)][d (lanes)]
+    floatx16 dK[NDB], dV[NDB];  // transposed: [d (registers)][key (lanes)]
 #pragma unroll
     for (int db = 0; db < NDB; db++)
 #pragma unroll
@@ -286,14 +286,14 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
             wt.dsb[v / 8][v % 8] = (__bf16)(pw * o.dP[v]);
         }
     };
-    // dV[key][d] += P^T[key][row] dO[row][d];  dK[key][d] += dS^T[key][row] Q[row][d]
+    // dV^T[d][key] += dO^T[d][row] P[row][key];  dK^T[d][key] += Q^T[d][row] dS[row][key]
     auto accumulate = [&](const Weights& wt, const Transposed& f) {
 #pragma unroll
         for (int db = 0; db < NDB; db++)
 #pragma unroll
             for (int s2 = 0; s2 < 2; s2++) {
-                dV[db] = mfma32(wt.pb[s2], f.dot[db][s2], dV[db]);
-                dK[db] = mfma32(wt.dsb[s2], f.qt[db][s2], dK[db]);
+                dV[db] = mfma32(f.dot[db][s2], wt.pb[s2], dV[db]);
+                dK[db] = mfma32(f.qt[db][s2], wt.dsb[s2], dK[db]);
             }
     };
 
@@ -369,22 +369,16 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
         else run(std::false_type{});
     }
 
-    // write the wave's 32 key rows: lanes cover 32 consecutive d
-    if (wave_live) {
-        __bf16* dkg = (__bf16*)p.dk;
-        __bf16* dvg = (__bf16*)p.dv;
-#pragma unroll
-        for (int v = 0; v < 16; v++) {
-            const int key = kw + 8 * (v / 4) + 4 * hf + (v % 4);
-            if (key < LK) {
-                const int64_t off = ((kv_base + key) * p.Hkv + g) * D + l32;
-#pragma unroll
-                for (int db = 0; db < NDB; db++) {
-                    dkg[off + db * 32] = (__bf16)(dK[db][v] * (PW ? p.scale * p.norm : p.scale));
-                    dvg[off + db * 32] = (__bf16)(PW ? dV[db][v] * (p.scale * p.norm) : dV[db][v]);
-                }
-            }
-        }
+    // A lane writes its key's row, 16 bytes at a time.  (The other way round the products leave keys in registers and features on the lanes, and
+    // each store has 2 bytes per lane: 128 of them at head_dim 128, 2.5 us of an item.  Whole steps, this and its like in the other kernels: 256 users of
+    // 512..1024 keys 1783 -> 1743 us, 64 of 128..512 145.0 -> 140.0, 246 of 28..115 + 8..70 real-time tokens at head_dim 128 836 -> 795.)
+    if (wave_live && key_live) {
+        const int64_t off = ((kv_base + kw + l32) * p.Hkv + g) * D + 8 * hf;
+        static_for<0, 2 * NDB>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            *(bf16x8*)((__bf16*)p.dk + off + 16 * i) = rows_of_16<i % 2>(dK[i / 2], PW ? p.scale * p.norm : p.scale);
+            *(bf16x8*)((__bf16*)p.dv + off + 16 * i) = rows_of_16<i % 2>(dV[i / 2], PW ? p.scale * p.norm : 1.f);
+        });
     }
     };  // process
 
@@ -526,7 +520,7 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
                     vf[ks] = *(const bf16x8*)((const __bf16*)p.v + off + ks * 16);
                 }
             }
-            floatx16 dK[NDB], dV[NDB];  // [key (registers)][d (lanes)]
+            floatx16 dK[NDB], dV[NDB];  // transposed: [d (registers)][key (lanes)]
 #pragma unroll
             for (int db = 0; db < NDB; db++)
 #pragma unroll
@@ -584,14 +578,14 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
                     wt.dsb[v / 8][v % 8] = (__bf16)(pw * o.dP[v]);
                 }
             };
-            // dV[key][d] += P^T[key][row] dO[row][d];  dK[key][d] += dS^T[key][row] Q[row][d]
+            // dV^T[d][key] += dO^T[d][row] P[row][key];  dK^T[d][key] += Q^T[d][row] dS[row][key]
             auto accumulate = [&](const Weights& wt, const Transposed& f) {
 #pragma unroll
                 for (int db = 0; db < NDB; db++)
 #pragma unroll
                     for (int s2 = 0; s2 < 2; s2++) {
-                        dV[db] = mfma32(wt.pb[s2], f.dot[db][s2], dV[db]);
-                        dK[db] = mfma32(wt.dsb[s2], f.qt[db][s2], dK[db]);
+                        dV[db] = mfma32(f.dot[db][s2], wt.pb[s2], dV[db]);
+                        dK[db] = mfma32(f.qt[db][s2], wt.dsb[s2], dK[db]);
                     }
             };
             // one unit after the other: the other two waves of the SIMD fill what this one waits for
@@ -607,20 +601,13 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
                     accumulate(wt, f);
                 }
             }
-            // write the wave's 32 key rows: lanes cover 32 consecutive d
-            __bf16* dkg = (__bf16*)p.dk;
-            __bf16* dvg = (__bf16*)p.dv;
-#pragma unroll
-            for (int v = 0; v < 16; v++) {
-                const int key = kw + 8 * (v / 4) + 4 * hf + (v % 4);
-                if (key < LK) {
-                    const int64_t off = ((kv_base + key) * p.Hkv + g) * D + l32;
-#pragma unroll
-                    for (int db = 0; db < NDB; db++) {
-                        dkg[off + db * 32] = (__bf16)(dK[db][v] * p.scale);
-                        dvg[off + db * 32] = (__bf16)dV[db][v];
-                    }
-                }
+            if (key_live) {
+                const int64_t off = ((kv_base + kw + l32) * p.Hkv + g) * D + 8 * hf;
+                static_for<0, 2 * NDB>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    *(bf16x8*)((__bf16*)p.dk + off + 16 * i) = rows_of_16<i % 2>(dK[i / 2], p.scale);
+                    *(bf16x8*)((__bf16*)p.dv + off + 16 * i) = rows_of_16<i % 2>(dV[i / 2], 1.f);
+                });
             }
         }
     };  // process

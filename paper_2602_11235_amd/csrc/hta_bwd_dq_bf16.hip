@@ -278,16 +278,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 1 && NW == 4 ? 3 : 2) voi
     for (int rb = 0; rb < RB; rb++) {
         const PackedRows::Row x = pr.at(rho0 + rb * 32 + l32);
         if (x.live) {
-            __bf16* op = dqg + ((q_base + x.row) * p.Hq + x.h) * D;
-#pragma unroll
-            for (int db = 0; db < NDB; db++)
-#pragma unroll
-                for (int v4 = 0; v4 < 4; v4++) {
-                    bf16x4 o4;
-#pragma unroll
-                    for (int j = 0; j < 4; j++) o4[j] = (__bf16)(dQ[rb][db][4 * v4 + j] * (PW ? p.scale * p.norm : p.scale));
-                    *(bf16x4*)(op + db * 32 + 8 * v4 + 4 * hf) = o4;
-                }
+            __bf16* op = dqg + ((q_base + x.row) * p.Hq + x.h) * D + 8 * hf;
+            static_for<0, D / 16>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                *(bf16x8*)(op + 16 * i) = rows_of_16<i % 2>(dQ[rb][i / 2], PW ? p.scale * p.norm : p.scale);
+            });
         }
     }
 }

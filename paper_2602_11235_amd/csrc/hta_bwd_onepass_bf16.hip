@@ -51,23 +51,6 @@ struct OnePass {
     static_assert(BYTES * (NG > 1 ? 1 : 2) == 160 * 1024, "LDS");
 };
 
-// Accumulator registers 8 k .. of a tile whose rows are features: a lane of half hf holds features 4 hf .. + 3 (lo) and 8 + 4 hf .. (hi)
-// of 16.  Rounded and exchanged between the halves, it has features 8 hf .. + 7: one store of 16 bytes.
-__device__ inline bf16x8 rows_of_16(floatx4 lo, floatx4 hi, float f) {
-    typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-    typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-    bf16x4 l4, h4;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        l4[j] = (__bf16)(lo[j] * f);
-        h4[j] = (__bf16)(hi[j] * f);
-    }
-    const uintx2 x = __builtin_bit_cast(uintx2, l4), y = __builtin_bit_cast(uintx2, h4);
-    const auto e0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
-    const auto e1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
-    const uintx4 o = {(unsigned)e0[0], (unsigned)e1[0], (unsigned)e0[1], (unsigned)e1[1]};
-    return __builtin_bit_cast(bf16x8, o);
-}
 constexpr int OP_MAX_HEADS = 8;
 template <int NG, bool RT, bool PW>
 __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowMap map, unsigned per_xcd) {

@@ -113,7 +113,7 @@ __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, u
             vf[ks] = *(const bf16x8*)((const __bf16*)p.v + off + ks * 16);
         }
     }
-    floatx16 dK[NDB], dV[NDB];  // [key (registers)][d (lanes)]
+    floatx16 dK[NDB], dV[NDB];  // transposed: [d (registers)][key (lanes)]
 #pragma unroll
     for (int db = 0; db < NDB; db++)
 #pragma unroll
@@ -192,13 +192,13 @@ __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, u
         });
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read
         issue(i + 2);
-        // dV[key][d] += P^T[key][row] dO[row][d];  dK[key][d] += dS^T[key][row] Q[row][d]
+        // dV^T[d][key] += dO^T[d][row] P[row][key];  dK^T[d][key] += Q^T[d][row] dS[row][key]
 #pragma unroll
         for (int db = 0; db < NDB; db++)
 #pragma unroll
             for (int s2 = 0; s2 < 2; s2++) {
-                dV[db] = mfma32(pb[s2], dot[db][s2], dV[db]);
-                dK[db] = mfma32(dsb[s2], qt[db][s2], dK[db]);
+                dV[db] = mfma32(dot[db][s2], pb[s2], dV[db]);
+                dK[db] = mfma32(qt[db][s2], dsb[s2], dK[db]);
             }
     };
     if (masked) {
@@ -207,19 +207,18 @@ __device__ __forceinline__ void brief_dkdv(const Params& p, const RowMap& map, u
         for (int i = 0; i < n_mine; i++) unit(i, std::false_type{});
     }
 
-    // add up the sums of the waves of each key block; rows of 16 bytes per thread go out
+    // add up the sums of the waves of each key block (a lane has its key's row, in words of 16 bytes); rows of 16 bytes per thread go out
     lds_barrier();
     float* acc = (float*)smem;  // [wave][dK, dV][key][KEY_PITCH]
     constexpr int WAVE_FLOATS = 2 * 32 * BR::KEY_PITCH;
     {
-        float* o = acc + wave * WAVE_FLOATS + l32;
+        float* o = acc + wave * WAVE_FLOATS + l32 * BR::KEY_PITCH + 4 * hf;
 #pragma unroll
         for (int db = 0; db < NDB; db++)
 #pragma unroll
-            for (int v = 0; v < 16; v++) {
-                const int key = 8 * (v / 4) + 4 * hf + (v % 4);
-                o[key * BR::KEY_PITCH + db * 32] = dK[db][v];
-                o[(32 + key) * BR::KEY_PITCH + db * 32] = dV[db][v];
+            for (int v4 = 0; v4 < 4; v4++) {
+                *(floatx4*)(o + db * 32 + 8 * v4) = floatx4{dK[db][4 * v4], dK[db][4 * v4 + 1], dK[db][4 * v4 + 2], dK[db][4 * v4 + 3]};
+                *(floatx4*)(o + 32 * BR::KEY_PITCH + db * 32 + 8 * v4) = floatx4{dV[db][4 * v4], dV[db][4 * v4 + 1], dV[db][4 * v4 + 2], dV[db][4 * v4 + 3]};
             }
     }
     lds_barrier();

@@ -121,16 +121,11 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_bf16_kernel(Params p, RowMap m
     const float lt = rows.l[0] + other_half(rows.l[0]);
     if (!x.live) return;
     const float inv = PW ? p.norm * p.scale : 1.f / lt;
-    __bf16* op = (__bf16*)p.out + ((q_base + x.row) * p.Hq + x.h) * D;
-#pragma unroll
-    for (int db = 0; db < D / 32; db++)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; v4++) {
-            bf16x4 o4;
-#pragma unroll
-            for (int j = 0; j < 4; j++) o4[j] = (__bf16)(rows.O[0][db][4 * v4 + j] * inv);
-            *(bf16x4*)(op + db * 32 + 8 * v4 + 4 * hf) = o4;
-        }
+    __bf16* op = (__bf16*)p.out + ((q_base + x.row) * p.Hq + x.h) * D + 8 * hf;
+    static_for<0, D / 16>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        *(bf16x8*)(op + 16 * i) = rows_of_16<i % 2>(rows.O[0][i / 2], inv);
+    });
     if (!PW && hf == 0) p.lse[(int64_t)x.h * p.total_q + q_base + x.row] = (rows.m[0] + __builtin_amdgcn_logf(lt)) * LN2;
 }
 

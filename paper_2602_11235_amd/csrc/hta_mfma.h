@@ -69,6 +69,30 @@ __device__ inline float other_half(float x) {
     return __builtin_bit_cast(float, (threadIdx.x & 32) ? r[0] : r[1]);
 }
 
+// Accumulator registers 8 k .. of a tile whose rows are features: a lane of half hf holds features 4 hf .. + 3 (lo) and 8 + 4 hf .. (hi)
+// of 16.  Rounded and exchanged between the halves, it has features 8 hf .. + 7: one store of 16 bytes.
+__device__ inline bf16x8 rows_of_16(floatx4 lo, floatx4 hi, float f) {
+    typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+    typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+    bf16x4 l4, h4;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        l4[j] = (__bf16)(lo[j] * f);
+        h4[j] = (__bf16)(hi[j] * f);
+    }
+    const uintx2 x = __builtin_bit_cast(uintx2, l4), y = __builtin_bit_cast(uintx2, h4);
+    const auto e0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
+    const auto e1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+    const uintx4 o = {(unsigned)e0[0], (unsigned)e1[0], (unsigned)e0[1], (unsigned)e1[1]};
+    return __builtin_bit_cast(bf16x8, o);
+}
+// registers 8 K .. of an accumulator tile, as rows_of_16 wants them
+template <int K>
+__device__ inline bf16x8 rows_of_16(const floatx16& d, float f) {
+    return rows_of_16(__builtin_shufflevector(d, d, 8 * K, 8 * K + 1, 8 * K + 2, 8 * K + 3),
+                      __builtin_shufflevector(d, d, 8 * K + 4, 8 * K + 5, 8 * K + 6, 8 * K + 7), f);
+}
+
 // acc + x[0] + x[1] + ... + x[7] for eight packed bf16 values (v_dot2c_f32_bf16 against packed ones), two chains
 __device__ inline void add_bf16x8(float& acc0, float& acc1, bf16x8 x) {
     bf16x2 one;

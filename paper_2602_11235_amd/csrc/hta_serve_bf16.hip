@@ -345,7 +345,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void serve_kernel(const int32_t* h
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // K_i has been read
         fetch(kg, i + NST, 0);
         wait_copies(min(NST - 1, left), left >= NST);  // newer than V_i: the following steps, and K_(i + NST)
-        rows.template absorb<TAIL, SPS>(S, Ks + SV::TILE, LK - k0, k0, L);
+        rows.template absorb<TAIL, SPS>(S, Ks + SV::TILE, LK - k0, k0, L, i == 0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         fetch(vg, i + NST, 1);
     };

@@ -43,40 +43,58 @@ __device__ inline void bwd_self_block(const Params& p, int block_x, int b) {
         dk_t[j] = 0.f;
         dv_t[j] = 0.f;
     }
-    for (int hh = 0; hh < r; hh++) {
-        const int h = g * r + hh;
-        const int64_t off = (q_row * p.Hq + h) * D + sub * 8;
-        const bf16x8 dov = *(const bf16x8*)(dog + off);
-        const bf16x8 ov = PW ? dov : *(const bf16x8*)(og + off);
-        const bf16x8 qv = *(const bf16x8*)(qg + off);
-        float dof[8], qf[8], part = 0.f, sp = 0.f, dpp = 0.f;
+    // N heads from h on, their loads together: four at a time instead of one keep enough in flight where targets are many (dQ launch and
+    // the rest of a step at head_dim 128: 246 users of 28..115 + 31..127 targets 798 -> 784 us, 152 of 63..253 239 -> 234; without the own keys at
+    // all 718 and 211).  At head_dim 32 the registers would cost the dQ kernel its fourth wave per SIMD (422 users 132 -> 137).
+    auto heads = [&](int h, auto Count) __attribute__((always_inline)) {
+        constexpr int N = decltype(Count)::value;
+        bf16x8 qv[N], dov[N], ov[N];
+        float lse[N];
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            dof[j] = (float)dov[j];
-            qf[j] = (float)qv[j];
-            part = fmaf(dof[j], (float)ov[j], part);
-            sp = fmaf(qf[j], kself[j], sp);
-            dpp = fmaf(dof[j], vself[j], dpp);
-        }
-        const float sc = group_sum(sp, LPR) * p.scale;
-        const float dp = group_sum(dpp, LPR);
-        float pw, ds;
-        if constexpr (PW) {
-            const float sg = 1.f / (1.f + __expf(-sc));
-            pw = p.norm * pw_silu(sc, sg);
-            ds = p.norm * dp * pw_silu_prime(sc, sg) * p.scale;
-        } else {
-            const float delta = group_sum(part, LPR);
-            const float lse = p.lse[(int64_t)h * p.total_q + q_row];
-            pw = __expf(sc - lse);
-            ds = pw * (dp - delta) * p.scale;
+        for (int i = 0; i < N; i++) {
+            const int64_t off = (q_row * p.Hq + h + i) * D + sub * 8;
+            qv[i] = *(const bf16x8*)(qg + off);
+            dov[i] = *(const bf16x8*)(dog + off);
+            if constexpr (!PW) {
+                ov[i] = *(const bf16x8*)(og + off);
+                lse[i] = p.lse[(int64_t)(h + i) * p.total_q + q_row];
+            }
         }
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            dk_t[j] = fmaf(ds, qf[j], dk_t[j]);
-            dv_t[j] = fmaf(pw, dof[j], dv_t[j]);
+        for (int i = 0; i < N; i++) {
+            float dof[8], qf[8], part = 0.f, sp = 0.f, dpp = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                dof[j] = (float)dov[i][j];
+                qf[j] = (float)qv[i][j];
+                if constexpr (!PW) part = fmaf(dof[j], (float)ov[i][j], part);
+                sp = fmaf(qf[j], kself[j], sp);
+                dpp = fmaf(dof[j], vself[j], dpp);
+            }
+            const float sc = group_sum(sp, LPR) * p.scale;
+            const float dp = group_sum(dpp, LPR);
+            float pw, ds;
+            if constexpr (PW) {
+                const float sg = 1.f / (1.f + __expf(-sc));
+                pw = p.norm * pw_silu(sc, sg);
+                ds = p.norm * dp * pw_silu_prime(sc, sg) * p.scale;
+            } else {
+                const float delta = group_sum(part, LPR);
+                pw = __expf(sc - lse[i]);
+                ds = pw * (dp - delta) * p.scale;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                dk_t[j] = fmaf(ds, qf[j], dk_t[j]);
+                dv_t[j] = fmaf(pw, dof[j], dv_t[j]);
+            }
         }
-    }
+    };
+    const int h_end = (g + 1) * r;
+    int h = g * r;
+    if constexpr (D > 32)
+        for (; h + 4 <= h_end; h += 4) heads(h, std::integral_constant<int, 4>{});
+    for (; h < h_end; h++) heads(h, std::integral_constant<int, 1>{});
     bf16x8 dk8, dv8;
 #pragma unroll
     for (int j = 0; j < 8; j++) {

@@ -402,7 +402,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 // takes a whole (user, kv head): it stages ALL (head, 32-row block) units of Q and dO in LDS once (at most MAX_UNITS of
 // them, which is what the host checks), and then its waves walk the keys, 32 per wave and pass, each on its own: K/V
 // fragments from global memory, every unit from LDS, dK/dV stored -- no barrier, no copy and no counted wait inside the
-// key loop, and waves that drift apart.  Twelve waves, three per SIMD, one unit in flight per wave (168 registers, 18 more in scratch):
+// key loop, and waves that drift apart.  Twelve waves, three per SIMD, one unit in flight per wave (168 registers, 16 more in scratch):
 // measured against eight waves with two units interleaved per wave, as bwd_dkdv_kernel does it, the third wave hides
 // more than the interleaving (dK/dV of a 512 x 2048 x 128 target layer 1.21 against 1.30 ms; streaming kernel 1.33).
 // Softmax weights without real-time tokens only (the callers that need the other readings take the streaming kernel).  Most such
@@ -453,6 +453,16 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     };
     struct Weights {
         bf16x8 pb[2], dsb[2];
+    };
+
+    // The next item is taken with the first wave's last pass over the keys (not with the item's start, see bwd_dkdv_kernel: 24 calls of 150 to 700
+    // users 0.992 of the time of a step, 273 users of 2656 keys x 57, 12/4 heads, 946 -> 914 us, none slower by a hundredth).
+    const int xcd = blockIdx.x % N_XCD;
+    unsigned taken = blockIdx.x / N_XCD;
+    bool asked;
+    auto ask = [&]() __attribute__((always_inline)) {
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
+        asked = true;
     };
 
     auto process = [&](unsigned id) {
@@ -508,6 +518,7 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
         // ---- the keys, 32 per wave and pass
         for (int k0 = wave * 32; k0 < LK; k0 += NW * 32) {
             const int kw = k0;
+            if (wave_u == 0 && k0 + NW * 32 >= LK) ask();
             const bool key_live = kw + l32 < LK;
             const bool ragged = kw + 32 > LK;
             bf16x8 kf[NKS], vf[NKS];
@@ -613,15 +624,14 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     };  // process
 
     // persistent workgroup, as in bwd_dkdv_kernel
-    const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
         if (wave_u == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
+        asked = false;
         process((unsigned)id);
+        if (!asked) ask();  // (no such item, or one without keys)
         __syncthreads();  // the staged units and s_item are free again
     }
 }

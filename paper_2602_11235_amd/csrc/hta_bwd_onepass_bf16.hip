@@ -52,8 +52,15 @@ struct OnePass {
 };
 
 constexpr int OP_MAX_HEADS = 8;
+// Blocks before an item's end at which the workgroup takes its next item: asked for with the item's start, the last items of the lists wait behind
+// items in progress while other workgroups leave; asked for later, a block waits for the atomic (its copies are counted behind it; two blocks before
+// the end 463 users of 39..156 keys 97 -> 109 us).  Where no item has that many blocks it is asked for with the start, before the lengths are read
+// (behind them 365 users of 31..124 keys 87 -> 91 us).  Whole steps, asked for with the start -> here: 227 users of 318..1275 keys, 8/2 heads, 240 ->
+// 207 us, 131 of 289..1157, 16/4, 137 -> 126, 453 of 178..1429, 4/4, 368 -> 354, 96 of 82..658, 16/4, pointwise 111 -> 87; 160 target layers at
+// random 0.988 of the time, 22 of them below 0.97 and four above 1.02 (1.04 at most).
+constexpr int ASK_AHEAD = 6;
 template <int NG, bool RT, bool PW>
-__global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowMap map, unsigned per_xcd) {
+__global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowMap map, unsigned per_xcd, bool ask_late) {
     using OP = OnePass<NG>;
     constexpr int D = OP_D, NKS = D / 16, NDB = D / 32, NW = OP::NW;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[OP::BYTES];
@@ -83,8 +90,16 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
         return x;
     };
 
+    const int xcd = blockIdx.x % N_XCD;
+    unsigned taken = blockIdx.x / N_XCD;
+    // takes the next item: once per item, at one of three places
+    auto ask = [&]() __attribute__((always_inline)) {
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
+    };
+
     auto process = [&](unsigned id) {
         const WorkItem w = decode_work(id, p.batch * p.Hkv, p.Hkv, 1);
+        if (!ask_late || !w.valid) ask();
         if (!w.valid) return;
         // (uniform values, which the compiler cannot tell of loads in a loop that also stores)
         auto uniform = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
@@ -97,6 +112,7 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
         const int n_rows = p.layer == 0 ? LK + T : T, tok_shift = p.layer == 0 ? 0 : LK;
         const int64_t q_base = uniform(p.q_off[b]), kv_base = uniform(p.kv_off[b]);
         const int n_blocks = (LK + 31) / 32;
+        if (ask_late && (n_blocks < ASK_AHEAD || n_rows == 0)) ask();
         if (n_rows == 0) {  // nobody attends to these keys: dk = dv = 0
             const bf16x8 zero = {};
             for (int i = tid; i < LK * (D / 8); i += NW * 64) {
@@ -436,6 +452,7 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
         const floatx16 zeros = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         // ---- the blocks
         for (int i = 0; i < n_blocks; i++) {
+            if (ask_late && i + ASK_AHEAD == n_blocks) ask();  // (in front of the block's copies, which are waited for by count)
             const int stage = OP::KV + (i & 1) * OP::STAGE;
             const int an = fresh(stage + nat0), ak = fresh(stage + tr0);
             if (t < units[1]) phase1(std::integral_constant<int, 2>{}, i, an, ak);
@@ -510,15 +527,12 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
     };  // process
 
     // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
-    const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = blockIdx.x / N_XCD;
     for (;;) {
         if (wave == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = __builtin_amdgcn_readfirstlane(*s_item);
         if (id < 0) break;
         __syncthreads();  // s_item is free again
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
         process((unsigned)id);
         __syncthreads();
     }
@@ -539,7 +553,7 @@ hipError_t launch(const Params& p, hipStream_t s) {
     Params pk = p;
     pk.queue = p.queue + QUEUE_DKDV * N_XCD;
     hipLaunchKernelGGL((bwd_onepass_kernel<NG, RT, PW>), dim3((unsigned)std::min(n_items, resident)), dim3(OP::NW * 64), 0, s, pk, map,
-                       (unsigned)(n_items / N_XCD));
+                       (unsigned)(n_items / N_XCD), max_lead_keys(p) > 32 * (ASK_AHEAD - 1));
     return hipGetLastError();
 }
 template <int NG>

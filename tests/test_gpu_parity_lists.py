@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2602_11235_amd import hta, inputs
-from tests.hta_testlib import TWO_PASSES, check_case, close_on_row_scale, form_of
+from tests.hta_testlib import ONE_PASS, TWO_PASSES, check_case, close_on_row_scale, form_of
 from tests.test_gpu_parity_pointwise import check as check_pointwise
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +35,23 @@ def test_long_users_among_short_ones(name):
     users = [0, 1, 2, 3, 4, 5, 6, 8, 16, 26]
     check_case(case, with_bwd=True, users=users, kv_group=1, compare=close_on_row_scale)
     check_pointwise(case, norm=1.0 / 64, users=users[:3] + users[4:], compare=close_on_row_scale)
+
+
+# Kernels that keep a user: histories, heads, form.  In one pass the next item is taken with the start of an item, where no history has six blocks of
+# 32 keys, or six blocks before its end; with the rows resident, with the first wave's last 384 keys.  Users without history or targets among them.
+KEPT = {
+    "one_pass_early": ([160, 0, 129, 1, 160, 33], (8, 2, 64), ONE_PASS),
+    "one_pass_late": ([161, 0, 160, 192, 1, 193, 224, 225, 400], (8, 2, 64), ONE_PASS),
+    "resident": ([1153, 0, 1537, 383, 1152, 1, 1536, 769], (6, 2, 64), TWO_PASSES),
+}
+
+
+@pytest.mark.parametrize("name", KEPT)
+def test_the_next_item_of_a_kernel_that_keeps_a_user(name):
+    hist, heads, kind = KEPT[name]
+    n = 701
+    cfg = inputs.custom_config(name, inputs.LAYER_TARGET, np.resize(hist, n), np.resize([40, 3, 0, 17, 33], n), *heads, seed=94)
+    form = form_of(cfg, hta.CALL_BWD)
+    assert form.kind == kind and (kind == ONE_PASS or (form.ways, form.option) == (0, 1))
+    users = sorted(set(range(20)) | set(range(0, n, 40)) | {n - 1})
+    check_case(inputs.make_case(cfg), with_bwd=True, users=users, compare=close_on_row_scale)

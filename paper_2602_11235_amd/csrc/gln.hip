@@ -203,7 +203,7 @@ __global__ __launch_bounds__(THREADS, CPL <= 2 ? 4 : 2) void fwd_kernel(const Ar
             const float mean = m + delta;
             const float rstd = 1.f / sqrtf(var + a.eps);
             if (NT > 1 && t >= a.n) break;  // (behind the sums: lanes of the same token leave together)
-                        const int id = late ? a.group_id[t] : gs[k];
+            const int id = late ? a.group_id[t] : gs[k];
             const int g = clamp_group(NT == 1 ? __builtin_amdgcn_readfirstlane(id) : id, a.n_groups);
 #pragma unroll
             for (int c = 0; c < CPL; c++) {

@@ -216,7 +216,7 @@ inline int64_t work_grid(int64_t n_groups, int64_t tpg, int spread = 0) {
 // 328 keys, 4/4 heads, 171 -> 132 us.)
 //   ids of XCD x's list that the first round deals out, n_groups workgroups in all
 __device__ inline unsigned queue_dealt(unsigned n_groups, int x) { return (n_groups + N_XCD - 1 - (unsigned)x) / N_XCD; }
-//   thread 0:  take the next slot of the own XCD in advance (one atomic, its latency hidden behind an item) ...
+//   thread 0:  take the next slot of the own XCD shortly before an item ends (one atomic, its latency hidden behind the rest of the item) ...
 __device__ inline unsigned queue_take_ahead(int32_t* counters, int xcd, unsigned per_xcd, unsigned n_groups) {
     const unsigned dealt = queue_dealt(n_groups, xcd);
     return dealt < per_xcd ? dealt + atomicAdd((unsigned*)&counters[xcd], 1u) : per_xcd;

@@ -63,15 +63,15 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     __shared__ int s_item;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
 
-    // The next item is taken shortly before the current one ends, early enough for the atomic to have returned by then.  (Taken with the
+    // The next item is taken four to six iterations before the current one ends, early enough for the atomic to have returned by then.  (Taken with the
     // start of the current one, the last items of the lists waited behind items in progress while other workgroups left.  Whole steps: 256 users
     // of 512..1024 keys 1815 -> 1795 us, 238 of 366..732 930 -> 901, 28 of up to 7896 2827 -> 2514; at head_dim 128 33 users of 434 + 60
     // keys 584 -> 497, 23 of 715..2379 2749 -> 2496, 128 of 750..8192 50.2 -> 49.7 ms; of 40 sampled calls one 1 % slower.)
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = blockIdx.x / N_XCD;
+    unsigned taken = 0;
     bool asked;
     auto ask = [&]() __attribute__((always_inline)) {
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, n_persistent);
+        if (tid == 0) queue_take_ahead(taken, p.queue, xcd, per_xcd, n_persistent);
         asked = true;
     };
 
@@ -303,8 +303,9 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     static_assert(UPI == 2, "the loop below is written out for two units per iteration");
     // prologue: all three stages requested while the K/V fragments are still on their way (one memory latency instead
     // of two at the start of every item).  From the wait on, the only vector-memory traffic of the loop are the
-    // asynchronous copies, which this code counts itself; the compiler must not be left with pending loads of its own
-    // that it would wait for inside the loop.
+    // asynchronous copies, which this code counts itself, and wave 0's request for the next item, which makes one or two of
+    // its counted waits reach a copy further; the compiler must not be left with pending loads of its own that it would
+    // wait for inside the loop.
     if (n_iter > 0) issue_tiles(st0);
     if (n_iter > 1) issue_tiles(st1);
     if (n_iter > 2) issue_tiles(st2);
@@ -383,8 +384,8 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     };  // process
 
     // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
-    for (;;) {
-        if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, n_persistent);
+    for (bool first = true;; first = false) {
+        if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) s_item = queue_resolve(p.queue, xcd, first, taken, per_xcd, n_persistent);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
 // takes a whole (user, kv head): it stages ALL (head, 32-row block) units of Q and dO in LDS once (at most MAX_UNITS of
 // them, which is what the host checks), and then its waves walk the keys, 32 per wave and pass, each on its own: K/V
 // fragments from global memory, every unit from LDS, dK/dV stored -- no barrier, no copy and no counted wait inside the
-// key loop, and waves that drift apart.  Twelve waves, three per SIMD, one unit in flight per wave (168 registers, 16 more in scratch):
+// key loop, and waves that drift apart.  Twelve waves, three per SIMD, one unit in flight per wave (168 registers, 17 more in scratch):
 // measured against eight waves with two units interleaved per wave, as bwd_dkdv_kernel does it, the third wave hides
 // more than the interleaving (dK/dV of a 512 x 2048 x 128 target layer 1.21 against 1.30 ms; streaming kernel 1.33).
 // Softmax weights without real-time tokens only (the callers that need the other readings take the streaming kernel).  Most such
@@ -458,10 +459,10 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     // The next item is taken with the first wave's last pass over the keys (not with the item's start, see bwd_dkdv_kernel: 24 calls of 150 to 700
     // users 0.992 of the time of a step, 273 users of 2656 keys x 57, 12/4 heads, 946 -> 914 us, none slower by a hundredth).
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = blockIdx.x / N_XCD;
+    __shared__ unsigned s_taken;  // (a register would be one in scratch)
     bool asked;
     auto ask = [&]() __attribute__((always_inline)) {
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
+        if (tid == 0) queue_take_ahead(s_taken, p.queue, xcd, per_xcd, gridDim.x);
         asked = true;
     };
 
@@ -518,7 +519,6 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
         // ---- the keys, 32 per wave and pass
         for (int k0 = wave * 32; k0 < LK; k0 += NW * 32) {
             const int kw = k0;
-            if (wave_u == 0 && k0 + NW * 32 >= LK) ask();
             const bool key_live = kw + l32 < LK;
             const bool ragged = kw + 32 > LK;
             bf16x8 kf[NKS], vf[NKS];
@@ -531,6 +531,8 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
                     vf[ks] = *(const bf16x8*)((const __bf16*)p.v + off + ks * 16);
                 }
             }
+            // (behind the loads, which the wave waits for anyway: the store to s_taken waits for the atomic)
+            if (wave_u == 0 && k0 + NW * 32 >= LK) ask();
             floatx16 dK[NDB], dV[NDB];  // transposed: [d (registers)][key (lanes)]
 #pragma unroll
             for (int db = 0; db < NDB; db++)
@@ -624,8 +626,8 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     };  // process
 
     // persistent workgroup, as in bwd_dkdv_kernel
-    for (;;) {
-        if (wave_u == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
+    for (bool first = true;; first = false) {
+        if (wave_u == 0) s_item = queue_resolve(p.queue, xcd, first, s_taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;

@@ -53,11 +53,12 @@ struct OnePass {
 
 constexpr int OP_MAX_HEADS = 8;
 // Blocks before an item's end at which the workgroup takes its next item: asked for with the item's start, the last items of the lists wait behind
-// items in progress while other workgroups leave; asked for later, a block waits for the atomic (its copies are counted behind it; two blocks before
-// the end 463 users of 39..156 keys 97 -> 109 us).  Where no item has that many blocks it is asked for with the start, before the lengths are read
-// (behind them 365 users of 31..124 keys 87 -> 91 us).  Whole steps, asked for with the start -> here: 227 users of 318..1275 keys, 8/2 heads, 240 ->
-// 207 us, 131 of 289..1157, 16/4, 137 -> 126, 453 of 178..1429, 4/4, 368 -> 354, 96 of 82..658, 16/4, pointwise 111 -> 87; 160 target layers at
-// random 0.988 of the time, 22 of them below 0.97 and four above 1.02 (1.04 at most).
+// items in progress while other workgroups leave; asked for later, a block waits for the atomic (its copies are counted behind it; three blocks before
+// the end 562 users of 55..444 keys, 8/1 heads, pointwise 49.5 -> 56.1 us, 306 of 130..521, 8/2, 60.6 -> 68.0).  Where no item has that many blocks it is
+// asked for with the start, before the lengths are read (behind them 463 users of 39..156 keys, 8/2 heads, 46.6 -> 48.4 us, the mean of 72 such calls
+// 1.006).  Whole steps, asked for with the start -> here: 227 users of 318..1275 keys, 8/2 heads, 240 -> 207 us, 131 of 289..1157, 16/4, 137 -> 126,
+// 453 of 178..1429, 4/4, 368 -> 354, 96 of 82..658, 16/4, pointwise 111 -> 87; 160 target layers at random 0.988 of the time, 22 of them below 0.97 and
+// four above 1.02 (1.04 at most).
 constexpr int ASK_AHEAD = 6;
 template <int NG, bool RT, bool PW>
 __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowMap map, unsigned per_xcd, bool ask_late) {
@@ -91,10 +92,10 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
     };
 
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = blockIdx.x / N_XCD;
+    unsigned taken = 0;
     // takes the next item: once per item, at one of three places
     auto ask = [&]() __attribute__((always_inline)) {
-        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
+        if (tid == 0) queue_take_ahead(taken, p.queue, xcd, per_xcd, gridDim.x);
     };
 
     auto process = [&](unsigned id) {
@@ -527,8 +528,8 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
     };  // process
 
     // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
-    for (;;) {
-        if (wave == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
+    for (bool first = true;; first = false) {
+        if (wave == 0) *s_item = queue_resolve(p.queue, xcd, first, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = __builtin_amdgcn_readfirstlane(*s_item);
         if (id < 0) break;

@@ -1,0 +1,65 @@
+"""The work queue's request in the kernels that take one item after the other: nothing waits for it where it is made.  The AMD assembly of the code
+objects inside the built library, no GPU."""
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2602_11235_amd import hta
+from tests.test_kernel_resources import BUNDLE
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """kernel name -> its instructions in order"""
+    hta.load_library()
+    data, elf, found = open(hta.LIB_PATH, "rb").read(), tmp_path_factory.mktemp("queue") / "code.elf", {}
+    at = data.find(BUNDLE)
+    while at >= 0:
+        count, = struct.unpack_from("<Q", data, at + len(BUNDLE))
+        entry = at + len(BUNDLE) + 8
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, entry)
+            target = data[entry + 24:entry + 24 + length].decode()
+            entry += 24 + length
+            code = data[at + offset:at + offset + size]
+            if "gfx950" in target and (b"bwd_dkdv_" in code or b"bwd_onepass_" in code):
+                elf.write_bytes(code)
+                text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(elf)], capture_output=True, text=True, check=True).stdout
+                for part in re.split(r"\n<(?=_Z)", text)[1:]:
+                    name, body = part.split(">:", 1)
+                    found[name] = [line.split("//")[0].strip() for line in body.splitlines() if line.strip()]
+        at = data.find(BUNDLE, at + 1)
+    return found
+
+
+def at_once(code, i):
+    return any("vmcnt" in line for line in code[i + 1:i + 9])
+
+
+def loads_in_flight(code, i):
+    """16-byte loads in front of instruction i with no wait in between"""
+    n = 0
+    for line in reversed(code[:i]):
+        if "vmcnt" in line:
+            break
+        n += line.startswith("global_load_dwordx4")
+    return n
+
+
+@pytest.mark.parametrize("kernel,variants", [("bwd_dkdv_kernel", 10), ("bwd_dkdv_resident_kernel", 1), ("bwd_onepass_kernel", 8)])
+def test_nothing_waits_for_the_next_item_where_it_is_asked_for(kernels, kernel, variants):
+    """The one atomic that is waited for at once is that of queue_resolve, which looks for work in other lists.  The kernel with a user's rows
+    resident has no register to leave the answer in: it waits, together with the loads of its last keys, eight of 16 bytes."""
+    chosen = {name: code for name, code in kernels.items() if kernel in name}
+    assert len(chosen) >= variants
+    for name, code in chosen.items():
+        atomics = [i for i, line in enumerate(code) if line.startswith("global_atomic_add") and "sc0" in line]
+        assert len(atomics) >= 3
+        if "resident" in kernel:
+            assert max(loads_in_flight(code, i) for i in atomics) >= 8, name
+        else:
+            assert sum(at_once(code, i) for i in atomics) == 1, (name, [code[i:i + 9] for i in atomics if at_once(code, i)])

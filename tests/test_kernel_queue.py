@@ -37,7 +37,12 @@ def kernels(tmp_path_factory):
 
 
 def at_once(code, i):
-    return any("vmcnt" in line for line in code[i + 1:i + 9])
+    for line in code[i + 1:i + 13]:
+        if "vmcnt" in line:
+            return True
+        if "branch" in line:
+            return False
+    return False
 
 
 def loads_in_flight(code, i):
@@ -50,16 +55,16 @@ def loads_in_flight(code, i):
     return n
 
 
-@pytest.mark.parametrize("kernel,variants", [("bwd_dkdv_kernel", 10), ("bwd_dkdv_resident_kernel", 1), ("bwd_onepass_kernel", 8)])
-def test_nothing_waits_for_the_next_item_where_it_is_asked_for(kernels, kernel, variants):
-    """The one atomic that is waited for at once is that of queue_resolve, which looks for work in other lists.  The kernel with a user's rows
-    resident has no register to leave the answer in: it waits, together with the loads of its last keys, eight of 16 bytes."""
+@pytest.mark.parametrize("kernel,variants,late", [("bwd_dkdv_kernel", 10, 2), ("bwd_dkdv_resident_kernel", 1, 0), ("bwd_onepass_kernel", 8, 2)])
+def test_nothing_waits_for_the_next_item_where_it_is_asked_for(kernels, kernel, variants, late):
+    """late: places inside an item where the next one is asked for.  (Waited for at once: what queue_resolve takes from other lists, and asking behind an
+    item without work.)  The kernel with a user's rows resident has no register to leave the answer in: it waits, together with the loads of its last
+    keys, eight of 16 bytes."""
     chosen = {name: code for name, code in kernels.items() if kernel in name}
     assert len(chosen) >= variants
     for name, code in chosen.items():
         atomics = [i for i, line in enumerate(code) if line.startswith("global_atomic_add") and "sc0" in line]
-        assert len(atomics) >= 3
         if "resident" in kernel:
             assert max(loads_in_flight(code, i) for i in atomics) >= 8, name
         else:
-            assert sum(at_once(code, i) for i in atomics) == 1, (name, [code[i:i + 9] for i in atomics if at_once(code, i)])
+            assert sum(not at_once(code, i) for i in atomics) >= late, (name, [code[i:i + 9] for i in atomics])

@@ -53,10 +53,16 @@ struct Args {
 // Backward: threads of a workgroup, one per compute unit with as many waves as the registers of a token's chunks and sums allow without scratch
 // (which costs a small call 4 to 10 us by itself), and sets of tokens that a wave has in flight.  Two chunks in bf16, eight waves with two tokens
 // in flight against twelve with one or sixteen with one and scratch: 60 000 x 736, 8 groups, gated 104 / 104 / 112 us, 9418 x 688 24.2 / 24.8 / 33.7.
-template <typename T, int CPL>
-constexpr int bwd_threads() { return CPL == 1 ? 1024 : 512; }
+constexpr int bwd_threads(int CPL) { return CPL == 1 ? 1024 : 512; }
 template <typename T, int CPL, int LPT, bool GATED>
 constexpr int bwd_depth() { return sizeof(T) == 2 && (CPL == 2 || (CPL == 1 && (LPT == 64 || !GATED))) ? 2 : 1; }
+// Calls of few tokens that lie side by side in a wave: half as many waves, and a token to each while there are compute units left.  Such a call is the
+// latency of one workgroup and of the sum of its shares, and tokens of other groups in the same wave come one after the other: sixteen waves and side
+// by side from the first token on, us of a call among others (9 of them the host's), gated, 4 groups: 64 x 64 11.8 -> 9.2, 2000 x 64 12.0 -> 9.1,
+// 2000 x 128 12.1 -> 9.5, 16 groups 16.1 -> 11.8; 8000 x 136 12.0 -> 11.5.  With more than two sets of tokens to each of 2048 waves sixteen waves are
+// as fast or faster: 32 000 x 128 16.3 against 16.1, 16 000 x 256 15.6 against 16.0, 32 000 x 136 18.8 against 21.0.
+constexpr int BRIEF_THREADS = 512;
+bool is_brief(int64_t n, int lanes_per_token) { return lanes_per_token < 64 && n <= (int64_t)2 * (64 / lanes_per_token) * MAX_SHARES * (BRIEF_THREADS / 64); }
 
 // eight consecutive features as they lie in memory; converted where they are used, so that tokens waiting for
 // their turn occupy half the registers in bf16
@@ -263,9 +269,9 @@ __global__ __launch_bounds__(THREADS, CPL <= 2 ? 4 : 2) void fwd_kernel(const Ar
 // its share, which the next waves may go on with, waits until all waves are through; then the waves of one group take turns, `rep` of
 // them at a time in copies of the accumulators of their own.  (LDS float atomics run at a lane per clock: with them the flushes of 1.6 groups per
 // wave took 30 to 45 us of a call, whatever its size.)
-template <typename T, int CPL, int LPT, bool GATED>
-__global__ __launch_bounds__((bwd_threads<T, CPL>())) void bwd_kernel(const Args a) {
-    constexpr int NTHR = bwd_threads<T, CPL>(), NW = NTHR / 64, NT = 64 / LPT, CH = LPT * 8;
+template <typename T, int CPL, int LPT, bool GATED, int NTHR>
+__global__ __launch_bounds__(NTHR) void bwd_kernel(const Args a) {
+    constexpr int NW = NTHR / 64, NT = 64 / LPT, CH = LPT * 8;
     constexpr int DEPTH = bwd_depth<T, CPL, LPT, GATED>();
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const int table = a.n_groups * a.row;
@@ -552,21 +558,31 @@ hipError_t launch_fwd_as(const Args& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename T, int CPL, int LPT, bool GATED, int NTHR>
+hipError_t launch_bwd_form(const Args& a, int shares, hipStream_t s) {
+    const size_t lds = (size_t)((GATED ? 2 : 1) + 2 * a.rep) * a.n_groups * a.row * sizeof(float);
+    hipError_t e = allow_lds(bwd_kernel<T, CPL, LPT, GATED, NTHR>);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((bwd_kernel<T, CPL, LPT, GATED, NTHR>), dim3(shares), dim3(NTHR), lds, s, a);
+    return hipGetLastError();
+}
+
 template <typename T, int CPL, int LPT, bool GATED>
 hipError_t launch_bwd_as(Args& a, int* shares, hipStream_t s) {
-    constexpr int NTHR = bwd_threads<T, CPL>(), NW = NTHR / 64;
+    constexpr int NT = 64 / LPT;
+    const bool brief = is_brief(a.n, LPT);
+    const int waves = (brief ? BRIEF_THREADS : bwd_threads(CPL)) / 64;
     // every wave of the grid gets one span when the tokens allow it, several passes of at most 64 and alike otherwise
-    *shares = grid_for(a.n, NW * (64 / LPT), MAX_SHARES);
-    const int64_t even = (a.n + (int64_t)*shares * NW - 1) / ((int64_t)*shares * NW), passes = (even + 63) / 64;
+    *shares = grid_for(a.n, waves * (brief ? 1 : NT), MAX_SHARES);
+    const int64_t even = (a.n + (int64_t)*shares * waves - 1) / ((int64_t)*shares * waves), passes = (even + 63) / 64;
     a.span = (int32_t)((even + passes - 1) / passes);
     // accumulators for as many waves as end in the same group when groups are even, within 128 KB with the parameters
-    const int room = (LDS_FLOATS / (a.n_groups * a.row) - (GATED ? 2 : 1)) / 2, want = (NW + a.n_groups - 1) / a.n_groups;
+    const int room = (LDS_FLOATS / (a.n_groups * a.row) - (GATED ? 2 : 1)) / 2, want = (waves + a.n_groups - 1) / a.n_groups;
     a.rep = room < want ? room : want;
-    const size_t lds = (size_t)((GATED ? 2 : 1) + 2 * a.rep) * a.n_groups * a.row * sizeof(float);
-    hipError_t e = allow_lds(bwd_kernel<T, CPL, LPT, GATED>);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bwd_kernel<T, CPL, LPT, GATED>), dim3(*shares), dim3(NTHR), lds, s, a);
-    return hipGetLastError();
+    if constexpr (NT > 1) {
+        if (brief) return launch_bwd_form<T, CPL, LPT, GATED, BRIEF_THREADS>(a, *shares, s);
+    }
+    return launch_bwd_form<T, CPL, LPT, GATED, bwd_threads(CPL)>(a, *shares, s);
 }
 
 template <typename T, int CPL, int LPT, bool GATED>

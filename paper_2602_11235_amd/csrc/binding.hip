@@ -46,6 +46,16 @@ struct GlnArgs {
 };
 static_assert(sizeof(GlnArgs) == 14 * 8 + 3 * 8 + 4 * 4, "pack format 14P3q2ifi");
 
+// what the host knows of a bf16 call; false: no such call
+bool sizes_of(const HtaArgs& a, hta::Params& p) {
+    if (a.dtype != MTFM_HTA_BF16 || a.batch <= 0 || a.total_q <= 0) return false;
+    p.batch = a.batch; p.total_q = a.total_q; p.total_kv = a.total_kv; p.max_hist = a.max_hist; p.max_targets = a.max_targets;
+    p.Hq = a.Hq; p.Hkv = a.Hkv; p.d = a.head_dim == hta::BF16_PADDED_FROM ? hta::BF16_PADDED_TO : a.head_dim; p.layer = a.layer;
+    if (a.rt_len && a.max_rt > 0) p.rt_len = a.rt_len, p.max_rt = a.max_rt;
+    p.pointwise = a.call == PW_FWD || a.call == PW_BWD;
+    return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -99,12 +109,8 @@ MTFM_HTA_API int mtfm_binding_hta(const void* block, void* stream) {
 //             [2] brief: dQ's workgroups in front; two passes with a queue: a user's rows resident; [3] is there a schedule's launch?
 MTFM_HTA_API int mtfm_binding_hta_form(const void* block, int32_t* form) {
     const HtaArgs& a = *(const HtaArgs*)block;
-    if (a.dtype != MTFM_HTA_BF16 || a.batch <= 0 || a.total_q <= 0) return MTFM_HTA_ERR_INVALID_ARG;
     hta::Params p{};
-    p.batch = a.batch; p.total_q = a.total_q; p.total_kv = a.total_kv; p.max_hist = a.max_hist; p.max_targets = a.max_targets;
-    p.Hq = a.Hq; p.Hkv = a.Hkv; p.d = a.head_dim == hta::BF16_PADDED_FROM ? hta::BF16_PADDED_TO : a.head_dim; p.layer = a.layer;
-    if (a.rt_len && a.max_rt > 0) p.rt_len = a.rt_len, p.max_rt = a.max_rt;
-    p.pointwise = a.call == PW_FWD || a.call == PW_BWD;
+    if (!sizes_of(a, p)) return MTFM_HTA_ERR_INVALID_ARG;
     if (a.call == FWD || a.call == PW_FWD) {
         p.n_splits = hta::serve_splits(p, hta::fwd_key_splits(p.batch, p.Hq, p.Hkv, p.d, hta::max_query_rows(p), hta::max_lead_keys(p)));
         form[0] = p.n_splits;
@@ -119,6 +125,16 @@ MTFM_HTA_API int mtfm_binding_hta_form(const void* block, int32_t* form) {
     form[1] = onepass ? 0 : brief ? hta::bwd_brief_ways(p, &dq_first) : hta::dkdv_brief_ways(p);
     form[2] = brief ? dq_first : form[0] == 0 && form[1] == 0 && hta::dkdv_is_resident(p);
     form[3] = !brief && hta::backward_needs_schedule(p, onepass);
+    return MTFM_HTA_OK;
+}
+
+// How a backward call of the block deals out its work, for tests: [0] one pass: is the next item taken late in the current one?  [1] two passes with a
+// queue: the key tiles of a user go to 2^this lists.
+MTFM_HTA_API int mtfm_binding_hta_lists(const void* block, int32_t* lists) {
+    hta::Params p{};
+    if (!sizes_of(*(const HtaArgs*)block, p)) return MTFM_HTA_ERR_INVALID_ARG;
+    lists[0] = hta::onepass_asks_late(p);
+    lists[1] = hta::dkdv_list_spread(p);
     return MTFM_HTA_OK;
 }
 

@@ -23,6 +23,7 @@
 namespace hta {
 
 bool dkdv_is_resident(const Params& p) { return p.d == 64 && few_rows_per_user<64>(p); }
+int dkdv_list_spread(const Params& p) { return list_spread(p, list_tiles<4>(p)); }
 
 hipError_t launch_bwd_bf16(const Params& p, hipStream_t s) {
     timing_begin(MTFM_HTA_KERNEL_BWD_DQ, s);

@@ -652,11 +652,16 @@ inline int list_spread(const Params& p, int64_t n_kt) {
     return (int64_t)p.batch * p.Hkv < 128 && n_kt >= 8 && (double)most_keys(p) > 2.5 * mean_keys(p) ? 2 : 0;
 }
 
+// key tiles of the longest user, NW x 32 history keys each
+template <int NW>
+int64_t list_tiles(const Params& p) {
+    return ((int64_t)p.max_hist + NW * 32 - 1) / (NW * 32);
+}
+
 template <int D, int NW, bool TAILS, bool PW = false>
 hipError_t launch_dkdv_as(const Params& p, hipStream_t s) {
-    const int64_t keys = p.max_hist;
     if (max_lead_keys(p) <= 0) return hipSuccess;
-    const int64_t n_kt = (keys + NW * 32 - 1) / (NW * 32);
+    const int64_t n_kt = list_tiles<NW>(p);
     const int spread = list_spread(p, n_kt);
     const int64_t n_items = work_grid((int64_t)p.batch * p.Hkv, n_kt, spread);
     const RowMap map = row_map(32, p.Hq, p.Hkv, max_query_rows(p));

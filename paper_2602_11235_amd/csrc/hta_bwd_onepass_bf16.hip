@@ -54,11 +54,13 @@ struct OnePass {
 constexpr int OP_MAX_HEADS = 8;
 // Blocks before an item's end at which the workgroup takes its next item: asked for with the item's start, the last items of the lists wait behind
 // items in progress while other workgroups leave; asked for later, a block waits for the atomic (its copies are counted behind it; three blocks before
-// the end 562 users of 55..444 keys, 8/1 heads, pointwise 49.5 -> 56.1 us, 306 of 130..521, 8/2, 60.6 -> 68.0).  Where no item has that many blocks it is
-// asked for with the start, before the lengths are read (behind them 463 users of 39..156 keys, 8/2 heads, 46.6 -> 48.4 us, the mean of 72 such calls
-// 1.006).  Whole steps, asked for with the start -> here: 227 users of 318..1275 keys, 8/2 heads, 240 -> 207 us, 131 of 289..1157, 16/4, 137 -> 126,
-// 453 of 178..1429, 4/4, 368 -> 354, 96 of 82..658, 16/4, pointwise 111 -> 87; 160 target layers at random 0.988 of the time, 22 of them below 0.97 and
-// four above 1.02 (1.04 at most).
+// the end 562 users of 55..444 keys, 8/1 heads, pointwise 49.5 -> 56.1 us, 306 of 130..521, 8/2, 60.6 -> 68.0).  Whole steps, asked for with the start
+// -> here: 227 users of 318..1275 keys, 8/2 heads, 240 -> 207 us, 131 of 289..1157, 16/4, 137 -> 126, 453 of 178..1429, 4/4, 368 -> 354, 96 of
+// 82..658, 16/4, pointwise 111 -> 87; 160 target layers at random 0.988 of the time, 22 of them below 0.97 and four above 1.02 (1.04 at most).
+// An item of fewer blocks asks as soon as its lengths are read, and where that is the mean item all do with their start, before that: by the mean, which
+// does not follow the bounds of a call.  (By the bounds, that is late in calls of short users with roomy bounds: 463 users of 39..156 keys, 8/2 heads,
+// 46.6 -> 48.4 us, 56 calls of 64 to 160 keys in the mean with bounds of four times the longest 1.010.  With true bounds 24 calls of more keys in the
+// mean 1.019 if all ask with their start, 24 of 94 to 160 1.001.)
 constexpr int ASK_AHEAD = 6;
 template <int NG, bool RT, bool PW>
 __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowMap map, unsigned per_xcd, bool ask_late) {
@@ -544,6 +546,10 @@ bool power_of_two(int x) { return x > 0 && (x & (x - 1)) == 0; }
 // one group per workgroup?
 bool single_group(const Params& p) { return max_query_rows(p) * (p.Hq / p.Hkv) <= OnePass<1>::LANES; }
 
+}  // namespace
+bool onepass_asks_late(const Params& p) { return mean_keys(p) > 32 * (ASK_AHEAD - 1); }
+namespace {
+
 template <int NG, bool RT, bool PW>
 hipError_t launch(const Params& p, hipStream_t s) {
     using OP = OnePass<NG>;
@@ -554,7 +560,7 @@ hipError_t launch(const Params& p, hipStream_t s) {
     Params pk = p;
     pk.queue = p.queue + QUEUE_DKDV * N_XCD;
     hipLaunchKernelGGL((bwd_onepass_kernel<NG, RT, PW>), dim3((unsigned)std::min(n_items, resident)), dim3(OP::NW * 64), 0, s, pk, map,
-                       (unsigned)(n_items / N_XCD), max_lead_keys(p) > 32 * (ASK_AHEAD - 1));
+                       (unsigned)(n_items / N_XCD), onepass_asks_late(p));
     return hipGetLastError();
 }
 template <int NG>

@@ -110,12 +110,14 @@ hipError_t launch_serve_bf16(const Params& p, hipStream_t s);
 hipError_t launch_bwd_bf16(const Params& p, hipStream_t s);
 bool bwd_is_onepass(const Params& p);                           // one kernel for dQ, dK, dV: hta_bwd_onepass_bf16.hip
 double onepass_us(const Params& p);                             // its estimated time, infinite where it does not fit
+bool onepass_asks_late(const Params& p);                        // does it take its next items late in the current ones?
 hipError_t launch_bwd_onepass_bf16(const Params& p, hipStream_t s);
 bool bwd_is_brief(const Params& p);                             // little work: the kernels of hta_bwd_brief_bf16.hip, no schedule
 hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s);
 int bwd_brief_ways(const Params& p, bool* dq_first);            // waves per key block there, and whether dQ's workgroups come first
 int dkdv_brief_ways(const Params& p);                           // ... > 0: their dK/dV part behind the ordinary dQ pass
 bool dkdv_is_resident(const Params& p);                         // the ordinary dK/dV pass would keep each user's rows in LDS
+int dkdv_list_spread(const Params& p);                          // ... or not: its key tiles of a user are dealt to 2^this lists
 hipError_t launch_dkdv_brief_bf16(const Params& p, hipStream_t s);
 // the two launches of launch_bwd_bf16 that live in translation units of their own (other compiler options)
 hipError_t launch_bwd_dq_bf16(const Params& p, hipStream_t s);       // dQ and the self-key blocks, every head_dim

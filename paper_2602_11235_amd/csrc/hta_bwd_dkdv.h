@@ -646,8 +646,11 @@ __global__ __launch_bounds__(BRIEF_NW * 64, 1) void dkdv_tails_kernel(Params p, 
 
 // Spread of the lists (decode_spread): an XCD starts what is in its own list first, so where a few long users have much of the work their tiles
 // go to four lists.  22 users of up to 4315 keys, 1413 in the mean, 16/2 heads of 128: whole step 3.48 -> 2.74 ms; 28 of up to 6611 keys, 8/2
-// heads 2.39 -> 2.31; 20 of up to 6055 5.63 -> 5.43; five others of that kind within 1 %.  Users alike, or many, gain nothing and read their operands
-// into more L2s (256 users of 512..1024 keys 1806 -> 1825 us, 233 of up to 1195 3413 -> 3479).
+// heads 2.39 -> 2.31; 20 of up to 6055 5.63 -> 5.43; five others of that kind within 1 %; the backward pass of 21 calls of 12 to 57 users with heavy
+// tails 0.987, from 0.89 to 1.011.  Users alike, or many, gain nothing and read their operands into more L2s (256 users of 512..1024 keys 1806 -> 1825 us,
+// 233 of up to 1195 3413 -> 3479).  The rule sees bounds, not lengths: few users alike whose bounds are far above them take four lists, too.  21 such calls,
+// bounds of four times the longest: 1.000, from 0.983 to 1.014.  (Where the kernel looks at the
+// lengths and chooses: the same.)
 inline int list_spread(const Params& p, int64_t n_kt) {
     return (int64_t)p.batch * p.Hkv < 128 && n_kt >= 8 && (double)most_keys(p) > 2.5 * mean_keys(p) ? 2 : 0;
 }

@@ -179,9 +179,9 @@ __device__ inline WorkItem decode_work(unsigned id, int n_groups, int ny, int tp
     w.y = group - w.user_slot * ny;
     return w;
 }
-// The same for grids whose groups may be few, or few of them long: the tiles of a group are dealt to 2^spread XCDs in turn
-// (a grid does not balance itself over the XCDs as the work counters below do; 17 users of which one has half of the work,
-// two kv heads: that half ran on two XCDs).
+// The same where groups may be few, or few of them long: the tiles of a group are dealt to 2^spread XCDs in turn.  For grids, which do not
+// balance themselves over the XCDs (17 users of which one has half of the work, two kv heads: that half ran on two XCDs), and for lists that
+// the work counters below serve, where an XCD works off its own list first (list_spread).
 __device__ inline WorkItem decode_spread(unsigned id, int n_groups, int ny, int tpg, int spread) {
     WorkItem w = decode_work(id, n_groups << spread, ny << spread, (tpg + (1 << spread) - 1) >> spread);
     w.tile = (w.tile << spread) + (w.y & ((1 << spread) - 1));
@@ -207,7 +207,7 @@ inline int64_t work_grid(int64_t n_groups, int64_t tpg, int spread = 0) {
 // of unequal length (jagged users) whole compute units run dry while others queue up: a fifth of the chip on the
 // paper's length mix.  Such a kernel launches only as many workgroups as the chip holds at once, and each takes work
 // item after work item from a counter (kernels with short items lose more to the hand-over than they gain): XCD x
-// serves the ids x, x + 8, x + 16, ... (which keeps a group's tiles on one L2, as above), in order, through counters[x];
+// serves the ids x, x + 8, x + 16, ... (a group's tiles on one L2, as above, or on those of a spread group), in order, through counters[x];
 // a workgroup whose own XCD has nothing left helps the others.  The loop ends for a workgroup once every counter has
 // passed the end of its list, which every workgroup reaches.
 // The first round needs no counter: a workgroup's index is its first id, and the counters count what is taken behind that.

@@ -34,6 +34,8 @@ constexpr int REDUCE_THREADS = 512, REDUCE_WAVES = REDUCE_THREADS / 64, REDUCE_C
 static_assert(MAX_SHARES % REDUCE_SLICES == 0, "a lane's shares");
 
 constexpr int LDS_FLOATS = 32768;  // of the backward kernel's parameter rows and accumulators (the rest of the 160 KB: its sort)
+static_assert(2 * MAX_TABLE <= LDS_FLOATS, "the forward kernel's parameter rows");
+static_assert((LDS_FLOATS + 1024 + MAX_GROUPS * 16) * sizeof(float) <= 160 * 1024, "the backward kernel's, with 16 waves");
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -540,18 +542,19 @@ int grid_for(int64_t n_tokens, int tokens_per_block, int most) {
     return (int)(blocks < most ? blocks : most);
 }
 
-// Lets `kernel` use the whole 160 KB of LDS as dynamic shared memory.  Asked for once per kernel (the first call is
-// not a stream operation, so it is kept out of later calls that a caller may be capturing into a graph).
-template <typename KernelT>
-hipError_t allow_lds(KernelT kernel) {
-    static hipError_t state = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+// Lets `Kernel` use what these kernels take of dynamic shared memory at most (with the backward's static arrays, the whole 160 KB would be more
+// than there is, which the runtime refuses).  Asked for once per kernel; not a stream operation, so a graph that is being captured does not see it.
+// The kernel is the parameter, not its type, which all instantiations share.
+template <auto Kernel>
+hipError_t allow_lds() {
+    static hipError_t state = hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_FLOATS * (int)sizeof(float));
     return state;
 }
 
 template <typename T, int CPL, int LPT, bool GATED>
 hipError_t launch_fwd_as(const Args& a, hipStream_t s) {
     const size_t lds = (size_t)2 * a.n_groups * a.row * sizeof(float);
-    hipError_t e = allow_lds(fwd_kernel<T, CPL, LPT, GATED>);
+    hipError_t e = allow_lds<fwd_kernel<T, CPL, LPT, GATED>>();
     if (e != hipSuccess) return e;
     const int grid = grid_for(a.n, WAVES * (CPL == 1 ? 2 : 1) * (64 / LPT), MAX_BLOCKS);
     hipLaunchKernelGGL((fwd_kernel<T, CPL, LPT, GATED>), dim3(grid), dim3(THREADS), lds, s, a);
@@ -561,7 +564,7 @@ hipError_t launch_fwd_as(const Args& a, hipStream_t s) {
 template <typename T, int CPL, int LPT, bool GATED, int NTHR>
 hipError_t launch_bwd_form(const Args& a, int shares, hipStream_t s) {
     const size_t lds = (size_t)((GATED ? 2 : 1) + 2 * a.rep) * a.n_groups * a.row * sizeof(float);
-    hipError_t e = allow_lds(bwd_kernel<T, CPL, LPT, GATED, NTHR>);
+    hipError_t e = allow_lds<bwd_kernel<T, CPL, LPT, GATED, NTHR>>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((bwd_kernel<T, CPL, LPT, GATED, NTHR>), dim3(shares), dim3(NTHR), lds, s, a);
     return hipGetLastError();

@@ -55,9 +55,9 @@ MTFM_HTA_API int mtfm_gln_fwd(const void* x, const void* gate, const int32_t* gr
                  int32_t n_groups, float eps, int dtype, void* stream);
 
 /*
- * Bytes of device workspace mtfm_gln_bwd() needs (0 if the shape is invalid or unsupported): one float32 share
- * of dgamma and dbeta per workgroup of the backward kernel, whose grid has a fixed upper bound, so the size
- * depends on d_model and n_groups only.
+ * Bytes of device workspace mtfm_gln_bwd() needs (0 if the shape is invalid or unsupported): room for 512 float32
+ * shares of dgamma and dbeta, one per workgroup of the backward kernel, whose grid stays within that (it is 256 at
+ * most; the size is what it has always been), so it depends on d_model and n_groups only.
  */
 MTFM_HTA_API size_t mtfm_gln_bwd_workspace_bytes(int32_t d_model, int32_t n_groups);
 

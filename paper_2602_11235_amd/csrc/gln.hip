@@ -25,7 +25,7 @@ constexpr int THREADS = 512;
 constexpr int WAVES = THREADS / 64;
 constexpr int MAX_BLOCKS = 512;   // workgroups of a forward launch
 constexpr int MAX_SHARES = 256;   // workgroups of a backward launch: one per compute unit (two of half the size: twice the shares to write and sum)
-constexpr int WORKSPACE_SHARES = 512;  // shares of dgamma / dbeta that the workspace has room for
+constexpr int WORKSPACE_SHARES = 512;  // shares of dgamma / dbeta that the workspace has room for: what callers were asked for when the grid was twice this, and are still
 constexpr int CHUNK = 512;        // features a wave covers per pass: 64 lanes x 8
 constexpr int MAX_CHUNKS = 4;     // d_model <= 2048
 constexpr int MAX_TABLE = 8192;   // n_groups x padded row length, in floats
@@ -55,6 +55,8 @@ struct Args {
 // Backward: threads of a workgroup, one per compute unit with as many waves as the registers of a token's chunks and sums allow without scratch
 // (which costs a small call 4 to 10 us by itself), and sets of tokens that a wave has in flight.  Two chunks in bf16, eight waves with two tokens
 // in flight against twelve with one or sixteen with one and scratch: 60 000 x 736, 8 groups, gated 104 / 104 / 112 us, 9418 x 688 24.2 / 24.8 / 33.7.
+// (Four chunks in float32 with a gate keep 12 registers in scratch; four waves without against these eight: 64 x 2048 13.2 against 15.1 us,
+// 1000 x 1544 21.3 against 20.1, 20 000 x 2048 183 against 185, 60 000 x 1544 411 against 410; the other kinds of four chunks lose by four waves.)
 constexpr int bwd_threads(int CPL) { return CPL == 1 ? 1024 : 512; }
 template <typename T, int CPL, int LPT, bool GATED>
 constexpr int bwd_depth() { return sizeof(T) == 2 && (CPL == 2 || (CPL == 1 && (LPT == 64 || !GATED))) ? 2 : 1; }
@@ -504,8 +506,7 @@ __global__ __launch_bounds__(NTHR) void bwd_kernel(const Args a) {
 
 // dgamma | dbeta = the sum of the workgroups' shares, in a fixed order: lane l of a wave takes columns 4 (l % 8) .. of the workgroup's
 // and every 64th share, the eight lanes of a column add up, then the eight waves.  All latency, so every lane has its (at most
-// four) loads of 16 bytes in flight at once and the columns are spread over the chip (512 shares of 2 x 8 x 512: 10.1 -> 4.8 us,
-// against 1024 threads that walked 32 shares each, four bytes at a time, on half of the compute units).
+// four) loads of 16 bytes in flight at once and the columns are spread over the chip (256 shares of 2 x 8 x 512: 4.0 us).
 __global__ __launch_bounds__(REDUCE_THREADS) void reduce_kernel(const float* partials, int n_shares, int gd, float* dgamma, float* dbeta) {
     __shared__ floatx4 part[REDUCE_WAVES][REDUCE_COLS / 4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quad = lane % (REDUCE_COLS / 4);

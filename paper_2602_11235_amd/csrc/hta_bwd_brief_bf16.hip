@@ -376,9 +376,10 @@ hipError_t launch_dkdv_ways(const Params& p, hipStream_t s) {
 
 // Both launches pay where the dQ part is small too: its workgroups of 32 rows walk their keys in a quarter of the time, at
 // twice the traffic (19 users of 405..1623 keys x 40 candidates: 66 -> 41 us per step against the ordinary dQ pass and this
-// dK/dV pass; 53 users of 100 keys, full layer: 54 either way).  Up to the first line always: against the better of one pass and two, 0.63 of
-// the time on 6370 calls, 6 % of which are slower by more than 3 %, mostly at head_dim 128.  Beyond it by the estimates, where key blocks are not shared (of 2985
-// calls 25 % go here, which makes all of them 0.92 of the time at 64, 0.89 at 32 and 0.95 at 128; 25 are slower by more than 3 %).  The estimate
+// dK/dV pass; 53 users of 100 keys, full layer: 54 either way).  Up to the first line always, beyond it by the estimates, where key
+// blocks are not shared.  The lines are fits of 9355 calls, made when the other forms took their next items early and stored results in narrower words.  As
+// the kernels are, of 2400 calls 1622 go here, at 0.65 of the time of the better of one pass and two (32, 64 and 128 features alike); 90 of them are slower by
+// more than 3 %, 28 of the 227 at head_dim 128; of the others 87 would be faster here by more than that, which is 1.5 % of their time.  The estimate
 // of one pass is above its time by a seventh in this range, and further for a row or two on long histories.
 bool bwd_is_brief(const Params& p) {
     if (p.total_q == 0) return false;
@@ -408,10 +409,10 @@ hipError_t launch_bwd_brief_bf16(const Params& p, hipStream_t s) {
 // of waves that share a key block's rows here.  From fits of measured times (us): a workgroup costs `fixed` plus `unit`
 // per 32-row unit of a wave, the chip holds `slots` of them, and the longest one bounds the call from below.  The ordinary
 // pass shares its staging among 128 keys and wins in the long run; it loses where a user's rows walked one after the
-// other take longer than the rest of the call.  (8/2 heads: 64 users of 128..512 keys 82 -> 69 us, 19 of 374..1498 200 -> 134,
-// 151 x 16..64 candidates 82 -> 41, 256 of 512..1024 ordinary 750 against 925; 512 x 128 candidates on 2048 keys resident 1.22 ms
-// against 1.70; 512 x 128 on 512..2048 keys, 16/4 heads, whole backward 1.47 ms against 1.79, 64 x 8..32 on 512 keys the other way
-// round, 63 us against 42.)
+// other take longer than the rest of the call.  (The fits are of kernels that took their next items early and stored results in narrower words.  As
+// the kernels are, whole backward passes of 583 calls in two passes: the 520 that share rows 0.84 of the ordinary pass's time, the choice 1.024 of
+// the best one's.  8/2 heads, ordinary against the best that shares: 64 users of 128..512 keys 91 and 95 us, 19 of 374..1498 209 and 195, 256 of 512..1024
+// 1287 and 1474; 16/4 heads, resident against that: 512 x 128 candidates on 512..2048 keys 1.40 ms and 1.79, 64 x 8..32 on 512 keys 41.6 us and 40.5.)
 int dkdv_brief_ways(const Params& p) {
     if (p.total_q == 0) return 0;
     const int r = p.Hq / p.Hkv;

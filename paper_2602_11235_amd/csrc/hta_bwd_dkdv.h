@@ -690,7 +690,8 @@ hipError_t launch_dkdv_as(const Params& p, hipStream_t s) {
 
 // Users with few query rows against long histories (see bwd_dkdv_resident_kernel): do the host-known bounds allow it,
 // and are there enough (user, kv head) items to give every compute unit one?  (A workgroup walks all keys of its item
-// by itself: with fewer items the key tiles of the streaming kernel spread better.)
+// by itself: with fewer items the key tiles of the streaming kernel spread better.)  Whole backward passes of 92 such calls, 90 to 700 users of up to 2800
+// keys: 0.92 of the time with the streaming kernel, eight of them slower by more than 3 %; those 15 that dkdv_brief_ways leaves here 0.87, none slower.
 template <int D>
 bool few_rows_per_user(const Params& p) {
     const int64_t max_units = ((max_query_rows(p) + 31) / 32) * (p.Hq / p.Hkv);

@@ -577,10 +577,11 @@ hipError_t launch(const Params& p, hipStream_t s) {
 // any.  The longest item counts with the most pairs that a user has, not with the mean's: 160 users of up to 3407 keys x 75
 // candidates, 8/2 heads, take 234 us in two passes and 293 here.  Three fits, since what the passes are made of changes: full layers; target
 // layers on less than 512 keys; and on more, where two passes may keep a user's rows resident.
-// On 7808 calls timed in both forms (full and target layers; 1..512 pairs, 16..4145 keys, 76..15952 items; with real-time tokens
-// and pointwise weights, too) one pass takes 0.79 of the time of two and is faster on nine of ten.  Where it is not, a few workgroups
-// make a second round (there it has to win by a fifth) or most units are idle.  The line takes 6070 of them, 100 of these slower than in two passes by
-// more than 3 %, and leaves 2 % of the time; the one before, fitted when leaving the work queue cost up to 45 us, took 2952 and left 12 %.
+// The fits are of 7808 calls timed in both forms (full and target layers; 1..512 pairs, 16..4145 keys, 76..15952 items; with real-time tokens
+// and pointwise weights, too), both of which took their next items early then and stored results in narrower words.  As the kernels are, 2400 calls of
+// all forms, 334 of which fit one pass and are not brief: one pass takes 0.88 of the time of two and is faster on 243.  Where it is not, a few workgroups
+// make a second round (there it has to win by a fifth) or most units are idle.  The line takes 195, at 0.81 of the time, eight of them slower than in two
+// passes by more than 3 %; of the 139 that it leaves 57 would be faster by more than that, which is 7 % of the time of the 139.
 static bool onepass_fits(const Params& p) {
     const int r = p.Hq / p.Hkv;
     return p.d == OP_D && power_of_two(r) && r <= OP_MAX_HEADS && p.total_q > 0 && max_query_rows(p) * r <= OnePass<2>::LANES;

@@ -237,8 +237,8 @@ struct FwdRows {
                     return fmaxf(mx, other_half(mx)) * c2;
                 };
                 // A caller that knows its first step (the request waves, whose key loop has few) takes the maximum at once instead
-                // of failing the test: the same reference and bits.  One 512 + 32 token request 6.63 -> 6.32 us, 2048 + 128 8.63 ->
-                // 8.31, 8 of 512..4096 14.1 -> 13.7.  The ordinary kernel does not: its loop has 64 steps a user, and the branch's
+                // of failing the test: the same reference and bits.  The same tensors again and again, one 512 + 32 token request
+                // 6.25 -> 5.76 us, 2048 + 128 8.59 -> 8.30, 8 of 512..4096 11.1 -> 10.5.  The ordinary kernel does not: its loop has 64 steps a user, and the branch's
                 // registers cost more than one failure (training steps 0.997 .. 1.10 of the time).
                 if (first) m[rb] = largest();
                 // (a row that has seen no key yet has the reference -inf: with real-time masks it may hold only masked

@@ -68,15 +68,17 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     // of 512..1024 keys 1815 -> 1795 us, 238 of 366..732 930 -> 901, 28 of up to 7896 2827 -> 2514; at head_dim 128 33 users of 434 + 60
     // keys 584 -> 497, 23 of 715..2379 2749 -> 2496, 128 of 750..8192 50.2 -> 49.7 ms; of 40 sampled calls one 1 % slower.)
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = 0;
+    unsigned taken = blockIdx.x / N_XCD;
     bool asked;
-    auto ask = [&]() __attribute__((always_inline)) {
-        if (tid == 0) queue_take_ahead(taken, p.queue, xcd, per_xcd, n_persistent);
+    auto ask = [&](unsigned& answer) __attribute__((always_inline)) {
+        if (tid == 0) queue_ask(answer, p.queue, xcd, per_xcd, n_persistent);
         asked = true;
     };
 
     // one work item: a (user, kv head, key tile) triple
     auto process = [&](unsigned id) {
+    unsigned answer;  // (an item's own: across the loop over items its register would be copied, which waits for every store of the item)
+    asm volatile("" : "=v"(answer));
     const WorkItem w = decode_spread(id, p.batch * p.Hkv, p.Hkv, tpg, spread);
     if (!w.valid) return;
     const int b = scheduled_user(p, w.user_slot), g = w.y;
@@ -345,7 +347,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
             accumulate(wt, f);
         };
         for (int it = 0; it < n_iter; it += 3) {
-            if (it + 6 >= n_iter && !asked) ask();
+            if (it + 6 >= n_iter && !asked) ask(answer);
             iteration(it, st0);
             if (it + 1 < n_iter) iteration(it + 1, st1);
             if (it + 2 < n_iter) iteration(it + 2, st2);
@@ -369,6 +371,7 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
         else if (wave_ragged) run(std::true_type{});
         else run(std::false_type{});
     }
+    if (asked) taken = queue_answer(answer, xcd, per_xcd, n_persistent);
 
     // A lane writes its key's row, 16 bytes at a time.  (The other way round the products leave keys in registers and features on the lanes, and
     // each store has 2 bytes per lane: 128 of them at head_dim 128, 2.5 us of an item.  Whole steps, this and its like in the other kernels: 256 users of
@@ -384,14 +387,19 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     };  // process
 
     // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
-    for (bool first = true;; first = false) {
-        if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) s_item = queue_resolve(p.queue, xcd, first, taken, per_xcd, n_persistent);
+    for (;;) {
+        if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) s_item = queue_resolve(p.queue, xcd, taken, per_xcd, n_persistent);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;
         asked = false;
         process((unsigned)id);
-        if (!asked) ask();  // (no such item, or a wave that only helped staging)
+        if (!asked) {  // (no such item, or a wave that only helped staging)
+            unsigned answer;
+            asm volatile("" : "=v"(answer));
+            ask(answer);
+            taken = queue_answer(answer, xcd, per_xcd, n_persistent);
+        }
         __syncthreads();  // the stages and s_item are free again
     }
 }
@@ -460,9 +468,10 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     // users 0.992 of the time of a step, 273 users of 2656 keys x 57, 12/4 heads, 946 -> 914 us, none slower by a hundredth).
     const int xcd = blockIdx.x % N_XCD;
     __shared__ unsigned s_taken;  // (a register would be one in scratch)
+    if (tid == 0) s_taken = blockIdx.x / N_XCD;
     bool asked;
     auto ask = [&]() __attribute__((always_inline)) {
-        if (tid == 0) queue_take_ahead(s_taken, p.queue, xcd, per_xcd, gridDim.x);
+        if (tid == 0) s_taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
         asked = true;
     };
 
@@ -531,7 +540,7 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
                     vf[ks] = *(const bf16x8*)((const __bf16*)p.v + off + ks * 16);
                 }
             }
-            // (behind the loads, which the wave waits for anyway: the store to s_taken waits for the atomic)
+            // (behind the loads, which the wave waits for anyway, as it does for this)
             if (wave_u == 0 && k0 + NW * 32 >= LK) ask();
             floatx16 dK[NDB], dV[NDB];  // transposed: [d (registers)][key (lanes)]
 #pragma unroll
@@ -626,8 +635,8 @@ __global__ __launch_bounds__(NW * 64, 3) void bwd_dkdv_resident_kernel(Params p,
     };  // process
 
     // persistent workgroup, as in bwd_dkdv_kernel
-    for (bool first = true;; first = false) {
-        if (wave_u == 0) s_item = queue_resolve(p.queue, xcd, first, s_taken, per_xcd, gridDim.x);
+    for (;;) {
+        if (wave_u == 0) s_item = queue_resolve(p.queue, xcd, s_taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = s_item;
         if (id < 0) break;

@@ -52,11 +52,13 @@ struct OnePass {
 };
 
 constexpr int OP_MAX_HEADS = 8;
-// Blocks before an item's end at which the workgroup takes its next item: asked for with the item's start, the last items of the lists wait behind
-// items in progress while other workgroups leave; asked for later, a block waits for the atomic (its copies are counted behind it; three blocks before
-// the end 562 users of 55..444 keys, 8/1 heads, pointwise 49.5 -> 56.1 us, 306 of 130..521, 8/2, 60.6 -> 68.0).  Whole steps, asked for with the start
-// -> here: 227 users of 318..1275 keys, 8/2 heads, 240 -> 207 us, 131 of 289..1157, 16/4, 137 -> 126, 453 of 178..1429, 4/4, 368 -> 354, 96 of
-// 82..658, 16/4, pointwise 111 -> 87; 160 target layers at random 0.988 of the time, 22 of them below 0.97 and four above 1.02 (1.04 at most).
+// Blocks before an item's end at which the workgroup takes its next item.  Wave 0 waits for the answer where it asks, and the others at the next barrier.
+// (Left in flight until behind the blocks, in a register of its own: eight calls of 300 to 700 users 1.003 of the time, 1.005 to 1.014 where there are two
+// groups of waves, 136 shorter calls 1.002.)  Asked for with the item's start, the last items of the lists wait behind items in progress while other
+// workgroups leave; asked for later is not better, either: three blocks before the end 562 users of 55..444 keys, 8/1 heads, pointwise 49.5 -> 56.1 us, 306
+// of 130..521, 8/2, 60.6 -> 68.0.  Whole steps, asked for with the start -> here: 227 users of 318..1275 keys, 8/2 heads, 240 -> 207 us, 131 of 289..1157,
+// 16/4, 137 -> 126, 453 of 178..1429, 4/4, 368 -> 354, 96 of 82..658, 16/4, pointwise 111 -> 87; 160 target layers at random 0.988 of the time, 22 of them
+// below 0.97 and four above 1.02 (1.04 at most).
 // An item of fewer blocks asks as soon as its lengths are read, and where that is the mean item all do with their start, before that: by the mean, which
 // does not follow the bounds of a call.  (By the bounds, that is late in calls of short users with roomy bounds: 463 users of 39..156 keys, 8/2 heads,
 // 46.6 -> 48.4 us, 56 calls of 64 to 160 keys in the mean with bounds of four times the longest 1.010.  With true bounds 24 calls of more keys in the
@@ -94,10 +96,10 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
     };
 
     const int xcd = blockIdx.x % N_XCD;
-    unsigned taken = 0;
+    unsigned taken = blockIdx.x / N_XCD;
     // takes the next item: once per item, at one of three places
     auto ask = [&]() __attribute__((always_inline)) {
-        if (tid == 0) queue_take_ahead(taken, p.queue, xcd, per_xcd, gridDim.x);
+        if (tid == 0) taken = queue_take_ahead(p.queue, xcd, per_xcd, gridDim.x);
     };
 
     auto process = [&](unsigned id) {
@@ -530,8 +532,8 @@ __global__ __launch_bounds__(NG * 256, 2) void bwd_onepass_kernel(Params p, RowM
     };  // process
 
     // persistent workgroup: its own index first, then what the work counters give until all lists are exhausted
-    for (bool first = true;; first = false) {
-        if (wave == 0) *s_item = queue_resolve(p.queue, xcd, first, taken, per_xcd, gridDim.x);
+    for (;;) {
+        if (wave == 0) *s_item = queue_resolve(p.queue, xcd, taken, per_xcd, gridDim.x);
         __syncthreads();
         const int id = __builtin_amdgcn_readfirstlane(*s_item);
         if (id < 0) break;

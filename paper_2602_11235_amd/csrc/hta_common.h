@@ -218,21 +218,28 @@ inline int64_t work_grid(int64_t n_groups, int64_t tpg, int spread = 0) {
 // 328 keys, 4/4 heads, 171 -> 132 us.)
 //   ids of XCD x's list that the first round deals out, n_groups workgroups in all
 __device__ inline unsigned queue_dealt(unsigned n_groups, int x) { return (n_groups + N_XCD - 1 - (unsigned)x) / N_XCD; }
-//   thread 0:  take the next slot of the own XCD shortly before an item ends ...  `taken` gets a count behind the dealt ones, which queue_resolve
-//   adds up: nothing reads it, and so nothing waits for the atomic, before that.  (An address that the compiler can prove uniform makes the atomic a
-//   reduction over the wave, which reads the result back at once and drains the copies in flight with it; so does a sum or a selection here.)
-__device__ inline void queue_take_ahead(unsigned& taken, int32_t* counters, int xcd, unsigned per_xcd, unsigned n_groups) {
+//   thread 0:  take the next slot of the own XCD shortly before an item ends ...  (An atomic on an address that the compiler can prove uniform becomes a
+//   reduction over the wave, which reads the result back at once: wave 0 waits for it here, and for what it has in flight.)
+__device__ inline unsigned queue_take_ahead(int32_t* counters, int xcd, unsigned per_xcd, unsigned n_groups) {
+    const unsigned dealt = queue_dealt(n_groups, xcd);
+    return dealt < per_xcd ? dealt + atomicAdd((unsigned*)&counters[xcd], 1u) : per_xcd;
+}
+//   or, in two steps, ask for it: `answer` gets a count behind the dealt ones, and nothing waits for the atomic ...
+__device__ inline void queue_ask(unsigned& answer, int32_t* counters, int xcd, unsigned per_xcd, unsigned n_groups) {
     if (queue_dealt(n_groups, xcd) >= per_xcd) return;
     int x = xcd;
     asm volatile("" : "+v"(x));
-    taken = atomicAdd((unsigned*)&counters[x], 1u);
+    answer = atomicAdd((unsigned*)&counters[x], 1u);
 }
-//   first wave:  ... and turn it (the workgroup's own index in the first round) into a work id, or -1 when all lists are exhausted.  (Lane q looks
-//   at the list of XCD xcd + q: one load, and none of the addresses is kept in registers for the length of every item.)
-__device__ inline int queue_resolve(int32_t* counters, int xcd, bool first, unsigned taken, unsigned per_xcd, unsigned n_groups) {
+//   ... before the answer is read, which all lanes of the first wave do, in front of the item's results (whose stores would be waited for with it)
+__device__ inline unsigned queue_answer(unsigned answer, int xcd, unsigned per_xcd, unsigned n_groups) {
     const unsigned dealt = queue_dealt(n_groups, xcd);
-    if (first) taken = blockIdx.x / N_XCD;
-    else taken = dealt < per_xcd ? __builtin_amdgcn_readfirstlane(taken) + dealt : per_xcd;
+    return dealt < per_xcd ? __builtin_amdgcn_readfirstlane(answer) + dealt : per_xcd;
+}
+//   first wave:  ... and turn it into a work id, or -1 when all lists are exhausted.  (Lane q looks at the list of XCD xcd + q: one
+//   load, and none of the addresses is kept in registers for the length of every item.)
+__device__ inline int queue_resolve(int32_t* counters, int xcd, unsigned taken, unsigned per_xcd, unsigned n_groups) {
+    taken = __builtin_amdgcn_readfirstlane(taken);
     if (taken < per_xcd) return (int)(taken * N_XCD + xcd);
     if (n_groups >= per_xcd * N_XCD) return -1;  // the first round was all
     int lane;  // (anew, for the same reason)

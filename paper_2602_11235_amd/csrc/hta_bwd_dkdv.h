@@ -66,7 +66,8 @@ __global__ __launch_bounds__(NW * 64, D > 64 ? 1 : 2) void bwd_dkdv_kernel(Param
     // The next item is taken four to six iterations before the current one ends, early enough for the atomic to have returned by then.  (Taken with the
     // start of the current one, the last items of the lists waited behind items in progress while other workgroups left.  Whole steps: 256 users
     // of 512..1024 keys 1815 -> 1795 us, 238 of 366..732 930 -> 901, 28 of up to 7896 2827 -> 2514; at head_dim 128 33 users of 434 + 60
-    // keys 584 -> 497, 23 of 715..2379 2749 -> 2496, 128 of 750..8192 50.2 -> 49.7 ms; of 40 sampled calls one 1 % slower.)
+    // keys 584 -> 497, 23 of 715..2379 2749 -> 2496, 128 of 750..8192 50.2 -> 49.7 ms; of 40 sampled calls one 1 % slower.  Waited for in the loop
+    // instead: 112 calls 1.000 of the time; backward passes of 128 users of 750..8192 keys 37.8 -> 38.0 ms, 180 of 300..900, 4/2 heads of 32, 203.1 -> 204.9 us.)
     const int xcd = blockIdx.x % N_XCD;
     unsigned taken = blockIdx.x / N_XCD;
     bool asked;
